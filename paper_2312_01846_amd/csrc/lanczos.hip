@@ -3,8 +3,8 @@
 //
 // Reductions come in two flavours:
 //   fast    -- fixed-grid tree (run-to-run reproducible, not sequential order);
-//   ordered -- one wavefront adds the products strictly in ascending-rank
-//              order, which reproduces a sequential CPU sum bit for bit.
+//   ordered -- the sum of the products strictly in ascending-rank order, which
+//              reproduces a sequential CPU sum bit for bit.
 #include <algorithm>
 #include <vector>
 
@@ -85,68 +85,234 @@ __global__ __launch_bounds__(RB) void k_dot_final(const double* __restrict__ par
     }
 }
 
-// Ordered sums: acc = ((0 + t_0) + t_1) + ... strictly in index order, t_i
-// the term of entry i (x_i; a_i * D[r_i]; a_i * Y_i; a_i * a_i).  One
-// wavefront streams the terms: while lane 0 adds a group of OS_DEPTH chunks of
-// 64 terms from LDS, the next group's loads are in flight, so the global
-// latency hides behind the add chain (wavefront-scope syncs only: a block
-// barrier would wait for those loads).
+// Ordered sums: s = ((0 + t_0) + t_1) + ... strictly in index order, t_i the
+// term of entry i (x_i; a_i * D[r_i]; a_i * Y_i; a_i * a_i), to the bit, but
+// not one add after another.  While s stays inside one binade, s = S u with u
+// its unit in the last place and 2^52 < |S| < 2^53, and adding t rounds to
+// (S + rint(t / u)) u unless t / u lies exactly half way between integers (a
+// tie, whose direction depends on S).  So a stretch without a tie whose every
+// prefix sum of the integers rint(t / u) stays strictly inside that range is
+// an integer sum, which may be taken in any order.  A workgroup takes OS_STEP
+// terms at a time: every wavefront reduces its chunk of OS_CHUNK terms to the
+// sum, the least and the greatest prefix, and the chunks are then applied in
+// order; a chunk that leaves the binade or holds a tie is added by its
+// wavefront in stretches that end at such a term, which is added by itself
+// (os_events), or term by term where such terms are frequent.
+// Bound by: added one by one, the latency of the chain (~17 cycles a term:
+// 7.34 ms for 1e6 squares); this way the loads and reductions of one compute
+// unit (0.69 ms; truncation of 4e6 entries to 1e6 with its norm 7.94 -> 1.00
+// ms).  Sums that wander about zero leave their binade every few dozen terms
+// and gain little.
 enum { OS_SUM = 0, OS_DOT = 1, OS_DOT_GATHERED = 2, OS_SUMSQ = 3 };
-constexpr int OS_DEPTH = 8;
+constexpr int OS_WAVES = 8;
+constexpr int OS_BLOCK = 64 * OS_WAVES;
+constexpr int OS_K = 8;                        // terms per lane
+constexpr int OS_CHUNK = 64 * OS_K;            // terms per wavefront
+constexpr int OS_STEP = OS_WAVES * OS_CHUNK;   // terms per step
+constexpr int OS_PAD = OS_CHUNK + OS_CHUNK / 8;  // a chunk in LDS, one slot of padding per 8
+constexpr int OS_EVENTS = 24;                  // singly added terms of a chunk before the rest is added one by one
 
-template <int MODE>
-__device__ __forceinline__ void os_load(const u64* __restrict__ r, const double* __restrict__ a,
-                                        const double* __restrict__ D, u64 i, u64 n, double& x, double& y) {
-    x = 0.0;
-    y = 0.0;
-    if (i < n) {
-        x = a[i];
-        if (MODE == OS_DOT) y = D[r[i]];
-        if (MODE == OS_DOT_GATHERED) y = D[i];
-    }
+__device__ __forceinline__ int os_slot(int i) { return i + (i >> 3); }
+
+// One step of a wavefront scan or reduction: the value CTRL selects from a
+// lower lane, `idle` where there is none (row_shr 1, 2, 4, 8 within rows of
+// 16 lanes, then the last lane of row 0 and 2 to the next, of row 1 to 2 and 3).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double os_dpp(double idle, double x) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(idle), __double2loint(x), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(idle), __double2hiint(x), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double os_scan_add(double x) {
+    x += os_dpp<0x111, 0xf>(0.0, x);
+    x += os_dpp<0x112, 0xf>(0.0, x);
+    x += os_dpp<0x114, 0xf>(0.0, x);
+    x += os_dpp<0x118, 0xf>(0.0, x);
+    x += os_dpp<0x142, 0xa>(0.0, x);
+    x += os_dpp<0x143, 0xc>(0.0, x);
+    return x;
+}
+// the wavefront's minimum (of finite values or infinities), in every lane
+__device__ __forceinline__ double os_last(double x) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                            __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+__device__ __forceinline__ double os_min(double x) {
+    x = fmin(x, os_dpp<0x111, 0xf>(x, x));
+    x = fmin(x, os_dpp<0x112, 0xf>(x, x));
+    x = fmin(x, os_dpp<0x114, 0xf>(x, x));
+    x = fmin(x, os_dpp<0x118, 0xf>(x, x));
+    x = fmin(x, os_dpp<0x142, 0xa>(x, x));
+    x = fmin(x, os_dpp<0x143, 0xc>(x, x));
+    return os_last(x);
 }
 
-template <int MODE>
-__device__ __forceinline__ double os_term(double x, double y) {
-    if (MODE == OS_SUM) return x;
-    if (MODE == OS_SUMSQ) return x * x;
-    return x * y;
+// s's biased exponent, and whether s is a normal number (then s = S 2^-sh)
+__device__ __forceinline__ bool os_normal(double s, int& sh) {
+    const int b = (__double2hiint(s) >> 20) & 0x7ff;
+    sh = 52 + 1023 - b;
+    return b >= 1 && b <= 2046;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(64) void k_ordered(const u64* __restrict__ r, const double* __restrict__ a,
-                                                const u64* __restrict__ nnz, const double* __restrict__ D,
-                                                double* out1, double* out2) {
-    constexpr int G = 64 * OS_DEPTH;
-    __shared__ double stage[G];
-    const u64 n = *nnz;
-    const int lane = threadIdx.x;
-    double x[OS_DEPTH], y[OS_DEPTH];
-#pragma unroll
-    for (int k = 0; k < OS_DEPTH; ++k) os_load<MODE>(r, a, D, (u64)k * 64 + lane, n, x[k], y[k]);
-    double acc = 0.0;
-    for (u64 base = 0; base < n; base += G) {
-#pragma unroll
-        for (int k = 0; k < OS_DEPTH; ++k) stage[k * 64 + lane] = os_term<MODE>(x[k], y[k]);
-#pragma unroll
-        for (int k = 0; k < OS_DEPTH; ++k) os_load<MODE>(r, a, D, base + G + (u64)k * 64 + lane, n, x[k], y[k]);
-        wave_sync();
-        if (lane == 0) {
-            if (n - base >= (u64)G) {
-                for (int q = 0; q < G; q += 64) {
-#pragma unroll
-                    for (int k = 0; k < 64; ++k) acc += stage[q + k];
-                }
-            } else {
-                const int cnt = (int)(n - base);
-                for (int q = 0; q < cnt; ++q) acc += stage[q];
+// Every prefix S + [lo, hi] strictly inside S's binade (the bounds themselves
+// are out: next to them the rounding unit may be another one).
+__device__ __forceinline__ bool os_inside(double S, double lo, double hi) {
+    constexpr double L = 4503599627370496.0, H = 9007199254740992.0;
+    return S > 0.0 ? (S + lo > L && S + hi < H) : (S + hi < -L && S + lo > -H);
+}
+
+// A chunk's terms (in LDS) added to s in order by one wavefront: 64 at a time
+// as an integer prefix sum up to the first one that cannot be, that one by
+// itself, and on from there.
+__device__ double os_events(const double* st, double s, int lane) {
+    int pos = 0, ev = 0;
+    while (pos < OS_CHUNK) {
+        if (ev > OS_EVENTS) {
+            for (; pos < OS_CHUNK && (pos & 7); ++pos) s += st[os_slot(pos)];
+            for (; pos < OS_CHUNK; pos += 8) {
+                const double* q = st + os_slot(pos);
+                const double x0 = q[0], x1 = q[1], x2 = q[2], x3 = q[3], x4 = q[4], x5 = q[5], x6 = q[6], x7 = q[7];
+                s += x0;
+                s += x1;
+                s += x2;
+                s += x3;
+                s += x4;
+                s += x5;
+                s += x6;
+                s += x7;
+            }
+            break;
+        }
+        const int m = min(64, OS_CHUNK - pos);
+        const double t = lane < m ? st[os_slot(pos + lane)] : 0.0;
+        int sh;
+        int first = 0;  // terms accepted together
+        if (s == 0.0) {
+            const u64 nz = __ballot(!(t == 0.0));
+            first = nz ? __builtin_ctzll(nz) : 64;
+        } else if (os_normal(s, sh)) {
+            const double x = ldexp(t, sh), r = rint(x);
+            const double S = ldexp(s, sh);
+            const double P = os_scan_add(r);
+            const u64 bad = __ballot(!(fabs(x - r) < 0.5 && os_inside(S, P, P)));
+            first = bad ? __builtin_ctzll(bad) : 64;
+            if (first > 0) {
+                const int l = first - 1;
+                const double Pl = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(P), l),
+                                                   __builtin_amdgcn_readlane(__double2loint(P), l));
+                s = ldexp(S + Pl, -sh);
             }
         }
-        wave_sync();
+        if (first >= m) {
+            pos += m;
+        } else {
+            pos += first;
+            s += st[os_slot(pos)];
+            ++pos;
+            ++ev;
+        }
     }
-    if (lane == 0) {
-        *out1 = acc;
-        if (out2) *out2 = acc;
+    return s;
+}
+
+struct OsChunk {
+    double d, lo, hi;  // the sum of the integers, their least and greatest prefix
+    int ok;            // 1: no tie; 2: every term is zero
+    int pad;
+};
+
+// The sum of the n terms term(i, x, y) of the values load(i, x, y) reads, the
+// same in every thread.
+template <class Load, class Term>
+__device__ __forceinline__ double os_block_sum(u64 n, const Load& load, const Term& term) {
+    __shared__ double stage[OS_WAVES][OS_PAD];
+    __shared__ OsChunk ch[2][OS_WAVES];
+    __shared__ double s_next;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double* const st = stage[wave];
+    double s = 0.0;
+    double x[OS_K], y[OS_K];
+    const u64 mine = (u64)wave * OS_CHUNK + lane;
+#pragma unroll
+    for (int k = 0; k < OS_K; ++k) load(mine + (u64)k * 64, x[k], y[k]);
+    int par = 0;
+    for (u64 base = 0; base < n; base += OS_STEP) {
+        // coalesced loads, then each lane's OS_K consecutive terms by way of LDS
+#pragma unroll
+        for (int k = 0; k < OS_K; ++k) st[os_slot(k * 64 + lane)] = term(x[k], y[k]);
+#pragma unroll
+        for (int k = 0; k < OS_K; ++k) load(base + OS_STEP + mine + (u64)k * 64, x[k], y[k]);
+        wave_sync();
+        double t[OS_K];
+#pragma unroll
+        for (int k = 0; k < OS_K; ++k) t[k] = st[lane * (OS_K + 1) + k];
+        int w0 = 0;
+        for (;;) {
+            int sh;
+            const bool normal = os_normal(s, sh);
+            if (wave >= w0) {
+                double d = 0.0, lo = INFINITY, hi = -INFINITY;
+                bool exact = true, zero = true;
+#pragma unroll
+                for (int k = 0; k < OS_K; ++k) {
+                    const double v = ldexp(t[k], sh), r = rint(v);
+                    exact = exact && fabs(v - r) < 0.5;
+                    zero = zero && t[k] == 0.0;
+                    d += r;
+                    lo = fmin(lo, d);
+                    hi = fmax(hi, d);
+                }
+                const double inc = os_scan_add(d);
+                const double before = inc - d;
+                const double wlo = os_min(before + lo), whi = -os_min(-(before + hi));
+                const bool all_exact = __ballot(!exact) == 0, all_zero = __ballot(!zero) == 0;
+                if (lane == 63) ch[par][wave] = OsChunk{inc, wlo, whi, all_zero ? 2 : (all_exact && normal ? 1 : 0), 0};
+            }
+            __syncthreads();
+            double S = normal ? ldexp(s, sh) : 0.0;
+            int f = w0;
+            for (; f < OS_WAVES; ++f) {
+                const OsChunk c = ch[par][f];
+                if (c.ok == 2) continue;  // adds nothing, whatever s is
+                if (c.ok == 0 || !os_inside(S, c.lo, c.hi)) break;
+                S += c.d;
+            }
+            if (normal) s = ldexp(S, -sh);
+            par ^= 1;  // (the next write to this half lies behind a barrier)
+            if (f == OS_WAVES) break;
+            if (wave == f) {
+                const double v = os_events(st, s, lane);
+                if (lane == 0) s_next = v;
+            }
+            __syncthreads();
+            s = s_next;
+            w0 = f + 1;
+            if (w0 == OS_WAVES) break;
+        }
+    }
+    return s;
+}
+
+template <int MODE>
+__global__ __launch_bounds__(OS_BLOCK) void k_ordered(const u64* __restrict__ r, const double* __restrict__ a,
+                                                      const u64* __restrict__ nnz, const double* __restrict__ D,
+                                                      double* out1, double* out2) {
+    const u64 n = *nnz;
+    const double s = os_block_sum(
+        n,
+        [&](u64 i, double& x, double& y) {
+            x = 0.0;
+            y = 0.0;
+            if (i < n) {
+                x = a[i];
+                if (MODE == OS_DOT) y = D[r[i]];
+                if (MODE == OS_DOT_GATHERED) y = D[i];
+            }
+        },
+        [](double x, double y) { return MODE == OS_SUM ? x : (MODE == OS_SUMSQ ? x * x : x * y); });
+    if (threadIdx.x == 0) {
+        *out1 = s;
+        if (out2) *out2 = s;
     }
 }
 
@@ -401,7 +567,7 @@ template <bool GATHERED>
 void dot_dense_impl(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
                     double* out1, double* out2, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<GATHERED ? OS_DOT_GATHERED : OS_DOT>, dim3(1), dim3(64), 0, P->stream, r, a, nnz,
+        hipLaunchKernelGGL(k_ordered<GATHERED ? OS_DOT_GATHERED : OS_DOT>, dim3(1), dim3(OS_BLOCK), 0, P->stream, r, a, nnz,
                            D, out1, out2);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
@@ -425,7 +591,7 @@ void launch_dot_gathered(sfci_problem* P, const double* a, const u64* nnz, u64 c
 
 void launch_sum(sfci_problem* P, const double* x, const u64* nnz, u64 cap, double* out, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_SUM>, dim3(1), dim3(64), 0, P->stream, (const u64*)nullptr, x, nnz,
+        hipLaunchKernelGGL(k_ordered<OS_SUM>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, x, nnz,
                            (const double*)nullptr, out, (double*)nullptr);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
@@ -438,7 +604,7 @@ void launch_sum(sfci_problem* P, const double* x, const u64* nnz, u64 cap, doubl
 
 void launch_sumsq(sfci_problem* P, const double* a, const u64* nnz, u64 cap, double* out, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(64), 0, P->stream, (const u64*)nullptr, a, nnz,
+        hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, a, nnz,
                            (const double*)nullptr, out, (double*)nullptr);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
@@ -454,7 +620,7 @@ void launch_dot_sparse(sfci_problem* P, const u64* xr, const double* xa, const u
     if (ordered) {
         double* prod = (double*)P->ws_prod.get(std::max<u64>(1, xcap) * sizeof(double));
         hipLaunchKernelGGL(k_sparse_products, dim3(gsz(xcap)), dim3(RB), 0, P->stream, xr, xa, xn, yr, ya, yn, prod);
-        hipLaunchKernelGGL(k_ordered<OS_SUM>, dim3(1), dim3(64), 0, P->stream, (const u64*)nullptr,
+        hipLaunchKernelGGL(k_ordered<OS_SUM>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr,
                            (const double*)prod, xn, (const double*)nullptr, out1, out2);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
@@ -485,7 +651,7 @@ void launch_normalise(sfci_problem* P, double* a, const u64* nnz, u64 cap, bool 
     double* part = part_ws ? part_ws : (double*)P->ws_red.get((RGRID + 8) * sizeof(double));
     double* ss = part + RGRID;
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(64), 0, P->stream, (const u64*)nullptr, a, nnz,
+        hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, a, nnz,
                            (const double*)nullptr, ss, (double*)nullptr);
     } else {
         unsigned g = std::min<unsigned>(RGRID, gsz(cap));
