@@ -585,11 +585,7 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
                 project_dense();
             }
             ++sigma_calls;
-            for (int l = 0; l <= j; ++l) {
-                DVec wl = W(l);
-                launch_dot_dense(P, wl.r, wl.a, wl.nnz, cap, P->d_D, T + l * nL + j, T + j * nL + l, det);
-                launch_dot_sparse(P, wl.r, wl.a, wl.nnz, cap, wj.r, wj.a, wj.nnz, S + l * nL + j, S + j * nL + l, det);
-            }
+            launch_step_dots(P, StepDots{Wr, Wa, sc, cap, j, nL, P->d_D, 0, T, S}, det);
             if (j + 1 < nL) {
                 launch_axpy_scatter(P, P->d_D, wj.r, wj.a, wj.nnz, cap, T + j * nL + j, -1.0);
                 if (j >= 1) {

@@ -500,12 +500,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             Inst& q = I[k];
             sfci_problem* P = q.P;
             DVec wj = q.W(j);
-            for (int l = 0; l <= j; ++l) {
-                DVec wl = q.W(l);
-                launch_dot_dense(P, wl.r, wl.a, wl.nnz, q.cap, P->d_D, q.T + l * nL + j, q.T + j * nL + l, det);
-                launch_dot_sparse(P, wl.r, wl.a, wl.nnz, q.cap, wj.r, wj.a, wj.nnz, q.S + l * nL + j,
-                                  q.S + j * nL + l, det);
-            }
+            launch_step_dots(P, StepDots{q.Wr, q.Wa, q.sc, q.cap, j, nL, P->d_D, 0, q.T, q.S}, det);
             if (j + 1 < nL) {
                 launch_axpy_scatter(P, P->d_D, wj.r, wj.a, wj.nnz, q.cap, q.T + j * nL + j, -1.0);
                 if (j >= 1) {

@@ -39,22 +39,14 @@ __device__ __forceinline__ double y_at(const u64* __restrict__ yr, const double*
     return (lo < yn && yr[lo] == key) ? ya[lo] : 0.0;
 }
 
-// y value paired with entry i of x: D[x_rank[i]] (dense) or Y[i] (already
-// gathered, GATHERED): the products and their order are the same either way.
-template <bool GATHERED>
-__device__ __forceinline__ double y_of(const u64* __restrict__ r, const double* __restrict__ D, u64 i) {
-    return GATHERED ? D[i] : D[r[i]];
-}
-
 // partial[b] = sum over a grid-stride slice of x_amp[i] * D[x_rank[i]]
-template <bool GATHERED>
 __global__ __launch_bounds__(RB) void k_dot_dense_part(const u64* __restrict__ r, const double* __restrict__ a,
                                                        const u64* __restrict__ nnz, const double* __restrict__ D,
                                                        double* __restrict__ part) {
     __shared__ double sh[RB];
     const u64 n = *nnz;
     double s = 0.0;
-    for (u64 i = (u64)blockIdx.x * RB + threadIdx.x; i < n; i += (u64)gridDim.x * RB) s += a[i] * y_of<GATHERED>(r, D, i);
+    for (u64 i = (u64)blockIdx.x * RB + threadIdx.x; i < n; i += (u64)gridDim.x * RB) s += a[i] * D[r[i]];
     double b = block_sum(s, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = b;
 }
@@ -86,7 +78,7 @@ __global__ __launch_bounds__(RB) void k_dot_final(const double* __restrict__ par
 }
 
 // Ordered sums: s = ((0 + t_0) + t_1) + ... strictly in index order, t_i the
-// term of entry i (x_i; a_i * D[r_i]; a_i * Y_i; a_i * a_i), to the bit, but
+// term of entry i (x_i; a_i * D[r_i]; a_i * a_i), to the bit, but
 // not one add after another.  While s stays inside one binade, s = S u with u
 // its unit in the last place and 2^52 < |S| < 2^53, and adding t rounds to
 // (S + rint(t / u)) u unless t / u lies exactly half way between integers (a
@@ -103,7 +95,7 @@ __global__ __launch_bounds__(RB) void k_dot_final(const double* __restrict__ par
 // unit (0.69 ms; truncation of 4e6 entries to 1e6 with its norm 7.94 -> 1.00
 // ms).  Sums that wander about zero leave their binade every few dozen terms
 // and gain little.
-enum { OS_SUM = 0, OS_DOT = 1, OS_DOT_GATHERED = 2, OS_SUMSQ = 3 };
+enum { OS_SUM = 0, OS_DOT = 1, OS_SUMSQ = 2 };
 constexpr int OS_WAVES = 8;
 constexpr int OS_BLOCK = 64 * OS_WAVES;
 constexpr int OS_K = 8;                        // terms per lane
@@ -306,7 +298,6 @@ __global__ __launch_bounds__(OS_BLOCK) void k_ordered(const u64* __restrict__ r,
             if (i < n) {
                 x = a[i];
                 if (MODE == OS_DOT) y = D[r[i]];
-                if (MODE == OS_DOT_GATHERED) y = D[i];
             }
         },
         [](double x, double y) { return MODE == OS_SUM ? x : (MODE == OS_SUMSQ ? x * x : x * y); });
@@ -329,6 +320,85 @@ __global__ __launch_bounds__(RB) void k_sparse_products(const u64* __restrict__ 
         const double yv = y_at(yr, ya, m, xr[i]);
         prod[i] = (yv != 0.0) ? xa[i] * yv : 0.0;
     }
+}
+
+// ---- all dots of one iteration step in one launch ----
+// T_lj = <w_l|y> and S_lj = <w_l|w_j> for every l <= j (blockIdx.y = 2 (l - l0)
+// for T, + 1 for S): 2 (j + 1) independent reductions over at most a few MB
+// each, which take a launch pair each only in launch gaps and in idle compute
+// units when issued one by one.  y is dense (indexed by rank) or gathered
+// per basis entry (ystride apart per l).
+__device__ __forceinline__ double step_y(const StepDots& d, int l, const u64* xr, u64 i) {
+    return d.ystride ? d.y[(u64)l * d.ystride + i] : d.y[xr[i]];
+}
+
+__device__ __forceinline__ void step_out(const StepDots& d, int l, int s_dot, double v) {
+    double* M = s_dot ? d.S : d.T;
+    M[l * d.nL + d.j] = v;
+    M[d.j * d.nL + l] = v;
+}
+
+// fast: the partial sums of the tree reduction, gridDim.x per dot
+__global__ __launch_bounds__(RB) void k_step_dots_part(StepDots d, double* __restrict__ part) {
+    __shared__ double sh[RB];
+    const int l = (int)(blockIdx.y >> 1);
+    const u64* xr = d.Wr + (u64)l * d.cap;
+    const double* xa = d.Wa + (u64)l * d.cap;
+    const u64 n = d.nnz[l];
+    double s = 0.0;
+    if ((blockIdx.y & 1u) == 0) {
+        for (u64 i = (u64)blockIdx.x * RB + threadIdx.x; i < n; i += (u64)gridDim.x * RB) s += xa[i] * step_y(d, l, xr, i);
+    } else {
+        const u64* yr = d.Wr + (u64)d.j * d.cap;
+        const double* ya = d.Wa + (u64)d.j * d.cap;
+        const u64 m = d.nnz[d.j];
+        for (u64 i = (u64)blockIdx.x * RB + threadIdx.x; i < n; i += (u64)gridDim.x * RB) {
+            const double yv = (l == d.j) ? ya[i] : y_at(yr, ya, m, xr[i]);
+            if (yv != 0.0) s += xa[i] * yv;
+        }
+    }
+    const double b = block_sum(s, sh);
+    if (threadIdx.x == 0) part[(u64)blockIdx.y * gridDim.x + blockIdx.x] = b;
+}
+
+__global__ __launch_bounds__(RB) void k_step_dots_final(StepDots d, const double* __restrict__ part, int np) {
+    __shared__ double sh[RB];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < np; i += RB) s += part[(u64)blockIdx.x * np + i];
+    const double b = block_sum(s, sh);
+    if (threadIdx.x == 0) step_out(d, (int)(blockIdx.x >> 1), (int)(blockIdx.x & 1u), b);
+}
+
+// deterministic: the products of the dots of w_l, l >= l0, in entry order
+// (cap apart; 0 where w_j has no entry), ...
+__global__ __launch_bounds__(RB) void k_step_products(StepDots d, int l0, double* __restrict__ prod) {
+    const int l = l0 + (int)(blockIdx.y >> 1);
+    const u64* xr = d.Wr + (u64)l * d.cap;
+    const double* xa = d.Wa + (u64)l * d.cap;
+    double* out = prod + (u64)blockIdx.y * d.cap;
+    const u64 n = d.nnz[l];
+    const u64 i0 = (u64)blockIdx.x * RB + threadIdx.x, step = (u64)gridDim.x * RB;
+    if ((blockIdx.y & 1u) == 0) {
+        for (u64 i = i0; i < n; i += step) out[i] = xa[i] * step_y(d, l, xr, i);
+    } else {
+        const u64* yr = d.Wr + (u64)d.j * d.cap;
+        const double* ya = d.Wa + (u64)d.j * d.cap;
+        const u64 m = d.nnz[d.j];
+        for (u64 i = i0; i < n; i += step) {
+            const double yv = (l == d.j) ? ya[i] : y_at(yr, ya, m, xr[i]);
+            out[i] = (yv != 0.0) ? xa[i] * yv : 0.0;
+        }
+    }
+}
+
+// ... and their in-order sums, a workgroup each
+__global__ __launch_bounds__(OS_BLOCK) void k_step_ordered(StepDots d, int l0, const double* __restrict__ prod) {
+    const int l = l0 + (int)(blockIdx.x >> 1);
+    const double* a = prod + (u64)blockIdx.x * d.cap;
+    const u64 n = d.nnz[l];
+    const double s = os_block_sum(
+        n, [&](u64 i, double& x, double& y) { x = (i < n) ? a[i] : 0.0, y = 0.0; }, [](double x, double) { return x; });
+    if (threadIdx.x == 0) step_out(d, l, (int)(blockIdx.x & 1u), s);
 }
 
 // D[r_i] = D[r_i] - coef * a_i  (SUB)   or   D[r_i] = D[r_i] + coef * a_i  (ADD)
@@ -562,31 +632,17 @@ unsigned gsz(u64 cap) {
 
 }  // namespace
 
-namespace {
-template <bool GATHERED>
-void dot_dense_impl(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
-                    double* out1, double* out2, bool ordered) {
+void launch_dot_dense(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
+                      double* out1, double* out2, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<GATHERED ? OS_DOT_GATHERED : OS_DOT>, dim3(1), dim3(OS_BLOCK), 0, P->stream, r, a, nnz,
-                           D, out1, out2);
+        hipLaunchKernelGGL(k_ordered<OS_DOT>, dim3(1), dim3(OS_BLOCK), 0, P->stream, r, a, nnz, D, out1, out2);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
         unsigned g = std::min<unsigned>(RGRID, gsz(cap));
-        hipLaunchKernelGGL(k_dot_dense_part<GATHERED>, dim3(g), dim3(RB), 0, P->stream, r, a, nnz, D, part);
+        hipLaunchKernelGGL(k_dot_dense_part, dim3(g), dim3(RB), 0, P->stream, r, a, nnz, D, part);
         hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(RB), 0, P->stream, part, (int)g, out1, out2);
     }
     SFCI_CHECK_HIP(hipGetLastError());
-}
-}  // namespace
-
-void launch_dot_dense(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
-                      double* out1, double* out2, bool ordered) {
-    dot_dense_impl<false>(P, r, a, nnz, cap, D, out1, out2, ordered);
-}
-
-void launch_dot_gathered(sfci_problem* P, const double* a, const u64* nnz, u64 cap, const double* Y, double* out1,
-                         double* out2, bool ordered) {
-    dot_dense_impl<true>(P, nullptr, a, nnz, cap, Y, out1, out2, ordered);
 }
 
 void launch_sum(sfci_problem* P, const double* x, const u64* nnz, u64 cap, double* out, bool ordered) {
@@ -627,6 +683,26 @@ void launch_dot_sparse(sfci_problem* P, const u64* xr, const double* xa, const u
         unsigned g = std::min<unsigned>(RGRID, gsz(xcap));
         hipLaunchKernelGGL(k_dot_sparse_part, dim3(g), dim3(RB), 0, P->stream, xr, xa, xn, yr, ya, yn, part);
         hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(RB), 0, P->stream, part, (int)g, out1, out2);
+    }
+    SFCI_CHECK_HIP(hipGetLastError());
+}
+
+void launch_step_dots(sfci_problem* P, const StepDots& d, bool ordered) {
+    const unsigned g = std::min<unsigned>(RGRID, gsz(d.cap));
+    if (!ordered) {
+        double* part = (double*)P->ws_red.get((size_t)2 * d.nL * RGRID * sizeof(double));
+        hipLaunchKernelGGL(k_step_dots_part, dim3(g, 2 * (d.j + 1)), dim3(RB), 0, P->stream, d, part);
+        hipLaunchKernelGGL(k_step_dots_final, dim3(2 * (d.j + 1)), dim3(RB), 0, P->stream, d, part, (int)g);
+    } else {
+        // as many w_l at a time as their products fit in 256 MiB (at least one)
+        const u64 fit = (256ull << 20) / (2 * std::max<u64>(1, d.cap) * sizeof(double));
+        const int group = (int)std::max<u64>(1, std::min<u64>(fit, (u64)d.nL));
+        double* prod = (double*)P->ws_prod.get((size_t)2 * group * std::max<u64>(1, d.cap) * sizeof(double));
+        for (int l0 = 0; l0 <= d.j; l0 += group) {
+            const unsigned dots = 2u * (unsigned)std::min(group, d.j + 1 - l0);
+            hipLaunchKernelGGL(k_step_products, dim3(g, dots), dim3(RB), 0, P->stream, d, l0, prod);
+            hipLaunchKernelGGL(k_step_ordered, dim3(dots), dim3(OS_BLOCK), 0, P->stream, d, l0, prod);
+        }
     }
     SFCI_CHECK_HIP(hipGetLastError());
 }

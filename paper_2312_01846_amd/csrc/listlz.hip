@@ -674,11 +674,7 @@ void lanczos_list(sfci_problem* P, const sfci_lanczos_opts* o, const ListBasis& 
                 sigma_sorted_passes(P, sl, sink, sc + 32, tup_cap, o->screen_eps);
             tsig.end(P->stream);
             ++*sigma_calls;
-            for (int l = 0; l <= j; ++l) {
-                launch_dot_gathered(P, Waj(l), Wn(l), cap, Y + (size_t)l * cap, T + l * nL + j, T + j * nL + l, det);
-                launch_dot_sparse(P, Wrj(l), Waj(l), Wn(l), cap, Wrj(j), Waj(j), Wn(j), S + l * nL + j,
-                                  S + j * nL + l, det);
-            }
+            launch_step_dots(P, StepDots{Wr, Wa, sc, cap, j, nL, Y, cap, T, S}, det);
             if (j + 1 < nL) {
                 // Eq. 10 on supp(w_j) U supp(w_{j-1}), then the top-M of all candidates
                 C.ensure(0);

@@ -420,9 +420,19 @@ void segmented_sum_append(sfci_problem* P, const K* keys, const double* vals, u6
 // ---- Lanczos vector ops (lanczos.hip) ----
 void launch_dot_dense(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
                       double* out1, double* out2, bool ordered);
-// The same sum with Y[i] (the y value already gathered for entry i) in place of D[r[i]].
-void launch_dot_gathered(sfci_problem* P, const double* a, const u64* nnz, u64 cap, const double* Y, double* out1,
-                         double* out2, bool ordered);
+// The dots of iteration step j: T_lj = <w_l|y> and S_lj = <w_l|w_j>, l = 0..j,
+// written to both triangles of the n_L x n_L matrices.
+struct StepDots {
+    const u64* Wr;  // basis vector w_l at Wr + l cap, Wa + l cap, nnz[l] entries
+    const double* Wa;
+    const u64* nnz;
+    u64 cap;
+    int j, nL;
+    const double* y;  // ystride = 0: dense, y[rank]; else y at entry i of w_l is y[l ystride + i]
+    u64 ystride;
+    double *T, *S;
+};
+void launch_step_dots(sfci_problem* P, const StepDots& d, bool ordered);
 // sum of x[0..*nnz) (ordered: strictly in index order) and sum of squares
 void launch_sum(sfci_problem* P, const double* x, const u64* nnz, u64 cap, double* out, bool ordered);
 void launch_sumsq(sfci_problem* P, const double* a, const u64* nnz, u64 cap, double* out, bool ordered);
