@@ -2,6 +2,7 @@
 // iteration driver (Sec. 2.1).  All device work goes to the problem's stream.
 #include <algorithm>
 #include <atomic>
+#include <cstddef>
 #include <cstdlib>
 #include <cstring>
 #include <limits>
@@ -255,7 +256,7 @@ sfci_status sfci_problem_destroy(sfci_problem* P) {
     DevBuf* bufs[] = {&P->ws_sel,   &P->ws_cnt,   &P->ws_scan,  &P->ws_scan2,  &P->ws_scalar, &P->ws_red,
                       &P->ws_tup_k, &P->ws_tup_v, &P->ws_tup_k2, &P->ws_tup_v2, &P->ws_seg_v, &P->ws_seg_f,
                       &P->ws_src_cnt, &P->ws_src_off, &P->ws_hist, &P->ws_list_r, &P->ws_list_a, &P->ws_prod,
-                      &P->ws_sel2,    &P->ws_cand_r, &P->ws_cand_a};
+                      &P->ws_cand_r, &P->ws_cand_a};
     for (DevBuf* b : bufs) b->release();
     for (auto& b : P->ws_lz) b.release();
     P->ws_rt_rows.release();
@@ -363,31 +364,37 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     CandSrc src{};
     dense_sigma(P, sl, opts->dedup, (unsigned long long*)&scal[1], opts->screen_eps);
     src.dense = P->d_D;
-    select_prepare(P, src, opts->M, &scal[2]);
+    // an output that holds whatever may be kept is written without waiting for the count
+    const u64 most = opts->M >= P->Ndet ? P->Ndet : std::min<u64>(P->Ndet, opts->M + tie_extra(P));
+    const bool direct = out->capacity >= most && out->rank && out->amp && select_one_step(P, opts->M);
+    if (direct) select_topm(P, src, opts->M, out->rank, out->amp, &scal[2], true);
+    else select_prepare(P, src, opts->M, &scal[2]);
     u64 hs[4];
+    SelState sst;
     SFCI_CHECK_HIP(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, P->stream));
+    SFCI_CHECK_HIP(hipMemcpyAsync(&sst, P->ws_sel.p, offsetof(SelState, ticket), hipMemcpyDeviceToHost, P->stream));
+    if (direct) SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
     sync(P);
     const u64 need = hs[2];
     sfci_status rc = SFCI_OK;
-    if (need > out->capacity || (need && (!out->rank || !out->amp))) {
-        launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
-        out->nnz = need;
-        rc = (sfci_status)sfci_set_error(SFCI_E_CAPACITY, "output capacity " + std::to_string(out->capacity) +
-                                                               " < " + std::to_string(need));
-    } else {
-        select_write(P, src, out->rank, out->amp, true);
-        out->nnz = need;
+    out->nnz = need;
+    if (!direct) {
+        if (need > out->capacity || (need && (!out->rank || !out->amp))) {
+            launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
+            rc = (sfci_status)sfci_set_error(SFCI_E_CAPACITY, "output capacity " + std::to_string(out->capacity) +
+                                                                   " < " + std::to_string(need));
+        } else {
+            select_write(P, src, out->rank, out->amp, true);
+        }
+        SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
+        sync(P);
     }
-    SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
-    sync(P);
     if (stats) {
         float ms = 0.f;
         SFCI_CHECK_HIP(hipEventElapsedTime(&ms, e0, e1));
         stats->ms = ms;
         stats->terms_enumerated = v->nnz * tps;
         stats->terms_emitted = hs[1];
-        SelState sst;
-        SFCI_CHECK_HIP(hipMemcpy(&sst, P->ws_sel.p, sizeof(SelState) - sizeof(sst.hist), hipMemcpyDeviceToHost));
         stats->candidates = sst.take_all ? sst.count_out : sst.total;
     }
     (void)hipEventDestroy(e0);
@@ -410,13 +417,21 @@ sfci_status sfci_topm(sfci_problem* P, const sfci_svec* v, uint64_t M, int32_t n
     src.lval = v->amp;
     src.lcount = scal;
     src.lcap = v->nnz;
-    select_prepare(P, src, M, &scal[1]);
-    u64 need = read_u64(P, &scal[1]);
+    // an output that holds whatever may be kept is written without waiting for the count
+    const u64 most = M >= v->nnz ? v->nnz : std::min<u64>(v->nnz, M + tie_extra(P));
+    const bool direct = out->capacity >= most && (most == 0 || (out->rank && out->amp));
+    if (direct) select_topm(P, src, M, out->rank, out->amp, &scal[1], false);
+    else select_prepare(P, src, M, &scal[1]);
+    if (direct && !normalise) {
+        out->nnz = read_u64(P, &scal[1]);
+        return SFCI_OK;
+    }
+    const u64 need = read_u64(P, &scal[1]);
     if (need > out->capacity) {
         out->nnz = need;
         return (sfci_status)sfci_set_error(SFCI_E_CAPACITY, "output capacity too small");
     }
-    if (need) select_write(P, src, out->rank, out->amp, false);
+    if (need && !direct) select_write(P, src, out->rank, out->amp, false);
     if (normalise && need) launch_normalise(P, out->amp, &scal[1], need, true);
     out->nnz = need;
     sync(P);

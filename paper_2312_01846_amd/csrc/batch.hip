@@ -25,7 +25,7 @@ struct sfci_batch {
     hipStream_t own = nullptr;         // capture-capable stream used during a batched run
     std::vector<DevBuf> descs;  // per iteration step j: the n instance descriptions
     DevBuf prefix, counter, scratch;
-    DevBuf binst, bscan;        // batched vector steps: the instances (BInst), the two scans' jobs
+    DevBuf binst;               // batched vector steps: the instances (BInst)
     RowTileGradWs grad_ws;
     // per-instance chains run on these streams (forked from and joined to `own`)
     std::vector<hipStream_t> aux;
@@ -133,7 +133,6 @@ sfci_status sfci_batch_destroy(sfci_batch* B) {
     for (auto& d : B->descs) d.release();
     B->prefix.release();
     B->binst.release();
-    B->bscan.release();
     B->counter.release();
     B->scratch.release();
     B->grad_ws.release();
@@ -252,13 +251,10 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
     bool batched_rest = batched_sigma;
     if (const char* env = getenv("SFCI_BATCH_REST")) batched_rest = batched_rest && env[0] != '0';
     const BInst* d_bi = nullptr;
-    const BScanJob* d_scan_dense = nullptr;
-    const BScanJob* d_scan_list = nullptr;
     u64 max_cap = 1, max_ndet = 1;
     int max_ndig = 1;
     if (batched_rest) {
         std::vector<BInst> hb(n);
-        std::vector<BScanJob> hs(2 * (size_t)n);
         for (int k = 0; k < n; ++k) {
             Inst& q = I[k];
             sfci_problem* P = q.P;
@@ -281,11 +277,10 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             // also the gradient pass's raw sums and the per-instance reductions
             b.red = (double*)P->ws_red.get(std::max<u64>(bstep_red_doubles(nL), 2048 + n2 + n2 * n2) * sizeof(double));
             b.st = (SelState*)P->ws_sel.get(sizeof(SelState));
-            b.st2 = (SelState*)P->ws_sel2.get(sizeof(SelState));
             b.cr = (u64*)P->ws_cand_r.get(P->Ndet * sizeof(u64));
             b.ca = (double*)P->ws_cand_a.get(P->Ndet * sizeof(double));
-            b.cnt = (u64*)P->ws_cnt.get(nch * sizeof(u64));
-            b.bsum = (u64*)P->ws_scan.get(scan_block_sums(nch) * sizeof(u64));
+            b.cnt = (u64*)P->ws_cnt.get(nch * (sizeof(u64) + sizeof(u32)));
+            b.ccnt = (u32*)(b.cnt + nch);
             b.psi_r = q.psi_r;
             b.psi_a = q.psi_a;
             b.psi_n = q.sc + 34;
@@ -293,20 +288,14 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             b.ndet_m1 = P->kg.ndet_m1;
             b.rank_bits = P->kg.rank_bits;
             b.nL = nL;
-            hs[k] = BScanJob{b.cnt, b.cnt, nch, b.bsum, &b.st->count_cand};
-            hs[n + k] = BScanJob{b.cnt, b.cnt, nch, b.bsum, &b.st2->count_out};
             max_cap = std::max(max_cap, q.cap);
             max_ndet = std::max(max_ndet, P->Ndet);
             max_ndig = std::max(max_ndig, (63 + P->kg.rank_bits + 10) / 11);
         }
         BInst* dbi = (BInst*)B->binst.get((size_t)n * sizeof(BInst));
-        BScanJob* dsj = (BScanJob*)B->bscan.get(2 * (size_t)n * sizeof(BScanJob));
         SFCI_CHECK_HIP(hipMemcpyAsync(dbi, hb.data(), hb.size() * sizeof(BInst), hipMemcpyHostToDevice, st));
-        SFCI_CHECK_HIP(hipMemcpyAsync(dsj, hs.data(), hs.size() * sizeof(BScanJob), hipMemcpyHostToDevice, st));
-        SFCI_CHECK_HIP(hipStreamSynchronize(st));  // the host arrays go out of scope
+        SFCI_CHECK_HIP(hipStreamSynchronize(st));  // the host array goes out of scope
         d_bi = dbi;
-        d_scan_dense = dsj;
-        d_scan_list = dsj + n;
     }
     // The gradient pass's buffers at their full size before any graph is
     // captured: growing one later would free memory the graphs use.
@@ -488,8 +477,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
                 bstep_axpy(st, d_bi, n, j, j, 0, max_cap);
                 if (j >= 1) bstep_axpy(st, d_bi, n, j - 1, j, 0, max_cap);
                 // D is left as it is: the next sigma launch writes every row (full_rows)
-                bstep_select(st, d_bi, n, BOUT_NEXT, j, max_ndet, B->P[0]->num_cu, band, max_ndig, d_scan_dense,
-                             d_scan_list, 0, false);
+                bstep_select(st, d_bi, n, BOUT_NEXT, j, max_ndet, B->P[0]->num_cu, band, max_ndig, 0, false);
                 bstep_normalise(st, d_bi, n, BOUT_NEXT, j, max_cap);
             } else {
                 bstep_fill_zero(st, d_bi, n, max_ndet);
@@ -522,13 +510,11 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             bstep_geneig(st, d_bi, n, nL);
             for (int j = 0; j < nL; ++j) bstep_axpy(st, d_bi, n, j, 0, 1, max_cap);
             if (!last) {
-                bstep_select(st, d_bi, n, BOUT_W0, 0, max_ndet, B->P[0]->num_cu, band, max_ndig, d_scan_dense,
-                             d_scan_list, 0);
+                bstep_select(st, d_bi, n, BOUT_W0, 0, max_ndet, B->P[0]->num_cu, band, max_ndig, 0);
                 bstep_normalise(st, d_bi, n, BOUT_W0, 0, max_cap);
             } else {
                 // every nonzero entry of Psi (capacity n_L * cap suffices)
-                bstep_select(st, d_bi, n, BOUT_PSI, 0, max_ndet, B->P[0]->num_cu, band, max_ndig, d_scan_dense,
-                             d_scan_list, 1);
+                bstep_select(st, d_bi, n, BOUT_PSI, 0, max_ndet, B->P[0]->num_cu, band, max_ndig, 1);
             }
             bstep_inc_blk(st, d_bi, n);
             return;

@@ -1,6 +1,6 @@
 // sfci_topm_noalloc: the truncation of sfci_topm for callers that cannot
 // allocate device memory.  Every piece of working memory -- the radix-select
-// state, the per-chunk counts and their scan sums, the norm's partial sums,
+// state, the per-segment counts, the norm's partial sums,
 // the validation flags and the device-side counts -- lives in one file-scope
 // device array.  Host code never passes that array's name to a kernel (in
 // host code it is a stand-in, not a device address): its device address is
@@ -14,15 +14,12 @@
 namespace {
 
 constexpr u64 kMaxNnz = SFCI_TOPM_NOALLOC_MAX_NNZ;
-constexpr u64 kChunk = 4096;  // candidates per selection chunk (select_chunks)
-constexpr u64 kMaxChunks = kMaxNnz / kChunk;
-constexpr u64 kMaxBsum = 64;  // >= scan_block_sums(kMaxChunks)
+constexpr u64 kMaxSegs = kMaxNnz / 4096;  // >= select_segments(n) for every n up to the limit
 
 constexpr size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t kOffSt = 0;
 constexpr size_t kOffCnt = kOffSt + up256(sizeof(SelState));
-constexpr size_t kOffBsum = kOffCnt + up256(kMaxChunks * sizeof(u64));
-constexpr size_t kOffRed = kOffBsum + up256(kMaxBsum * sizeof(u64));
+constexpr size_t kOffRed = kOffCnt + up256(kMaxSegs * sizeof(u64));
 constexpr size_t kRedDoubles = 1024 + 8;  // >= normalise_ws_doubles()
 constexpr size_t kOffScal = kOffRed + up256(kRedDoubles * sizeof(double));
 constexpr size_t kScalWords = 8;  // [0] nnz(v) [1] kept count [2] bad rank flag [3] order flag
@@ -83,12 +80,11 @@ extern "C" sfci_status sfci_topm_noalloc(sfci_problem* P, const sfci_svec* v, ui
         if (v->nnz && (!v->rank || !v->amp)) return (sfci_status)sfci_set_error(SFCI_E_ARG, "NULL input arrays");
         DeviceGuard dg(P->device);
         unsigned char* base = (unsigned char*)scratch_on(P->device);
-        SelWs ws{(SelState*)(base + kOffSt), (u64*)(base + kOffCnt), (u64*)(base + kOffBsum)};
+        SelWs ws{(SelState*)(base + kOffSt), (u64*)(base + kOffCnt)};
         double* red = (double*)(base + kOffRed);
         u64* scal = (u64*)(base + kOffScal);
         const u64 n = v->nnz;
-        if (select_chunks(n) > kMaxChunks || scan_block_sums(select_chunks(n)) > kMaxBsum ||
-            normalise_ws_doubles() > kRedDoubles)
+        if (select_segments(n) > kMaxSegs || normalise_ws_doubles() > kRedDoubles)
             throw sfci_error(SFCI_E_DEVICE, "scratch layout too small");
         // the previous call's contents are still there: clear what must start at zero
         launch_fill_u64(scal, kScalWords, 0, P->stream);

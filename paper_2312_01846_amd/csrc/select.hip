@@ -1,13 +1,27 @@
 // Truncation to the M largest amplitudes (Sec. 2.1, Eqs. 10-11; the paper
-// sorts the whole intermediate vector, Sec. 3).  Here: an MSD radix select
-// over the 128-bit key K = bits(|c|) ++ (N_det - 1 - rank), which orders
-// entries by |c| descending and breaks exact ties by rank ascending, followed
-// by an order-preserving compaction that writes the kept entries by rank.
-// Every pass is a streaming read of the candidates (dense N_det array or a
-// rank-sorted list); no sort of the candidates is needed.  Exactly min(M,
-// nonzero) entries are kept, unless the problem's tie_band extension is on
-// (then entries within a relative 2^-36 of the M-th |c| stay too, at most
+// sorts the whole intermediate vector, Sec. 3).  Here: a radix select over
+// the 128-bit key K = bits(|c|) ++ (N_det - 1 - rank), which orders entries by
+// |c| descending and breaks exact ties by rank ascending, followed by an
+// order-preserving compaction that writes the kept entries by rank.  Exactly
+// min(M, nonzero) entries are kept, unless the problem's tie_band extension is
+// on (then entries within a relative 2^-36 of the M-th |c| stay too, at most
 // SFCI_TIE_SLACK of them).
+//
+// Steps (every pass a streaming read; launches end in a "last workgroup" that
+// does the single-workgroup part, so that none is launched for it):
+//   1. histogram of the top digit (the exponent), pick the M-th entry's;
+//   2. dense sources: the entries at or above that binade go to fixed
+//      segments (a segment per chunk of slots, no scan needed), the
+//      accumulator is zeroed on the way;
+//   3. histogram of the next 11 bits over the segments, pick;
+//   4. the few entries that share those 22 bits are gathered and the M-th key
+//      is found among them by counting; where they are many (ties in masses)
+//      the remaining digits are picked one histogram at a time instead;
+//   5. kept entries per segment, their scan; 6. the compaction.
+// Sources of at most SEL_ONE entries are done by one workgroup in one launch.
+// Measured (a histogram of every digit over the whole source, before -> now):
+// 2.35e7 slots, M = 9e5: 450 -> 240 us; 4.33e9 slots, M = 1e6: 41 -> 20.5 ms;
+// a list of 4e6, M = 1e6: 215 -> 110 us.
 #include <algorithm>
 
 #include "../../include/sfci.h"
@@ -22,6 +36,10 @@ constexpr int NBIN = 1 << DIG;
 constexpr int CBLOCK = 256;
 constexpr int CITEMS = 16;
 constexpr u64 CCHUNK = (u64)CBLOCK * CITEMS;
+constexpr int SEG_UNROLL = 4;  // groups of 64 entries whose loads are in flight together
+constexpr int ONE_BLOCK = 1024;
+constexpr int ONE_ITEMS = SEL_ONE / ONE_BLOCK;
+constexpr int SEG_BLOCK = 1024;  // threads of the segment passes that end in histograms or gathers
 
 struct Geo {
     int tb;    // total key bits = 63 + rank_bits
@@ -30,10 +48,19 @@ struct Geo {
     int rank_bits;
 };
 
+__host__ __device__ __forceinline__ Geo geo_of(int rank_bits, u64 ndet_m1) {
+    Geo g;
+    g.rank_bits = rank_bits;
+    g.tb = 63 + rank_bits;
+    g.ndig = (g.tb + DIG - 1) / DIG;
+    g.ndet_m1 = ndet_m1;
+    return g;
+}
+
+__device__ __forceinline__ u64 abs_bits(double c) { return (u64)__double_as_longlong(c) & 0x7FFFFFFFFFFFFFFFull; }
+
 __device__ __forceinline__ u128 sel_key(u64 rank, double c, const Geo& g) {
-    u64 P = (u64)__double_as_longlong(c) & 0x7FFFFFFFFFFFFFFFull;
-    u64 Q = g.ndet_m1 - rank;
-    return ((u128)P << g.rank_bits) | (u128)Q;
+    return ((u128)abs_bits(c) << g.rank_bits) | (u128)(g.ndet_m1 - rank);
 }
 
 __device__ __forceinline__ int dig_lo(const Geo& g, int L) {
@@ -41,620 +68,1092 @@ __device__ __forceinline__ int dig_lo(const Geo& g, int L) {
     return lo < 0 ? 0 : lo;
 }
 
-struct DenseSrc {
-    const double* D;
-    u64 n;
-    __device__ __forceinline__ u64 size() const { return n; }
-    __device__ __forceinline__ void get(u64 i, u64& r, double& c) const { r = i; c = D[i]; }
-};
-
-struct ListSrc {
+// One selection.  Candidates lie in segments: segment s holds count(s) entries
+// from (s << shift) on, cnt[s] of them (dense source), or a list's own
+// stretch of *n entries in all (cnt == nullptr).
+struct SelJob {
+    const double* D;  // dense source (rank = index) of Dn slots, nullptr: the list itself
+    u64 Dn;
     const u64* r;
-    const double* v;
-    const u64* cnt;
-    __device__ __forceinline__ u64 size() const { return *cnt; }
-    __device__ __forceinline__ void get(u64 i, u64& rr, double& c) const { rr = r[i]; c = v[i]; }
+    const double* a;
+    u32* cnt;
+    const u64* n;
+    u64 cap;   // slots (dense) or the list's capacity: nseg() segments
+    int shift;
+    u64* off;  // per segment: kept entries, then their exclusive scan
+    SelState* st;
+    u64 M;
+    int band;
+    Geo g;
+    u64* out_r;
+    double* out_a;
+    u64* out_n;  // may be nullptr
+    double* Dz;  // the accumulator to zero on the way, or nullptr
+    __device__ __forceinline__ u64 nseg() const { return (cap + (1ull << shift) - 1) >> shift; }
+    __device__ __forceinline__ u32 count(u64 s) const {
+        if (cnt) return cnt[s];
+        const u64 m = *n, b = s << shift;
+        return b >= m ? 0u : (u32)min((u64)1 << shift, m - b);
+    }
+    __device__ __forceinline__ bool all() const { return M == UINT64_MAX; }
 };
 
-__device__ __forceinline__ u64 abs_bits(double c) { return (u64)__double_as_longlong(c) & 0x7FFFFFFFFFFFFFFFull; }
+// Where a launch's jobs come from: one by value, or a batch's instances
+// (blockIdx.y).
+struct OneJob {
+    SelJob j;
+    __device__ __forceinline__ SelJob operator()(unsigned) const { return j; }
+};
 
-__device__ __forceinline__ bool sel_pred(const SelState& st, const Geo& g, u64 r, double c) {
-    if (c == 0.0) return false;
-    if (st.cand) return abs_bits(c) >= st.cand_bits;
-    if (st.take_all) return true;
-    if (!st.done || st.level == 0) return false;  // M = 0: nothing is kept
-    if (st.use_thr) return abs_bits(c) >= st.thr_bits;
-    u128 K = sel_key(r, c, g);
-    u128 pre = ((u128)st.pre_hi << 64) | st.pre_lo;
-    int sh = dig_lo(g, st.level - 1);
-    return (K >> sh) >= pre;
+struct BatchJobs {
+    const BInst* B;
+    int kind, j, band, all, zero;
+    __device__ __forceinline__ SelJob operator()(unsigned y) const {
+        const BInst& b = B[y];
+        SelJob s;
+        s.D = b.D;
+        s.Dn = b.Ndet;
+        s.r = b.cr;
+        s.a = b.ca;
+        s.cnt = b.ccnt;
+        s.n = nullptr;
+        s.cap = b.Ndet;
+        s.shift = SEL_DENSE_SHIFT;
+        s.off = b.cnt;
+        s.st = b.st;
+        s.M = all ? UINT64_MAX : b.M;
+        s.band = band;
+        s.g = geo_of(b.rank_bits, b.ndet_m1);
+        if (kind == BOUT_PSI) {
+            s.out_r = b.psi_r;
+            s.out_a = b.psi_a;
+            s.out_n = b.psi_n;
+        } else {
+            const u64 l = kind == BOUT_W0 ? 0 : (u64)j + 1;
+            s.out_r = b.Wr + l * b.cap;
+            s.out_a = b.Wa + l * b.cap;
+            s.out_n = b.sc + l;
+        }
+        s.Dz = zero ? b.D : nullptr;
+        return s;
+    }
+};
+
+// Words that one workgroup leaves for the last one of the same launch go
+// through agent-scope atomics on both sides (they bypass the caches that are
+// not shared): a __threadfence() per workgroup instead writes back and drops a
+// whole L2 each time (0.1 us per workgroup, 0.5 ms in a launch of 5 740).
+__device__ __forceinline__ u64 shared_load(const u64* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void shared_store(u64* p, u64 v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void sel_init_body(SelState* st, u64 M, int take_all, int take_none) {
+// True in every thread of the workgroup that is the last of `total` to get
+// here.  The atomics every wavefront issued before are complete by then.
+__device__ __forceinline__ bool last_workgroup(unsigned* ticket, unsigned total) {
+    __shared__ unsigned s_t;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) s_t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const bool last = s_t == total - 1;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    return last;
+}
+
+template <class JP>
+__global__ __launch_bounds__(256) void k_sel_init(JP jp) {
+    const SelJob J = jp(blockIdx.y);
+    SelState* st = J.st;
     for (int t = threadIdx.x; t < NBIN; t += blockDim.x) st->hist[t] = 0;
     if (threadIdx.x == 0) {
-        st->need = M;
+        st->need = J.M;
         st->pre_hi = 0;
         st->pre_lo = 0;
         st->level = 0;
-        st->done = (take_all || take_none) ? 1 : 0;
-        st->take_all = take_all;
+        st->done = (J.all() || J.M == 0) ? 1 : 0;
+        st->take_all = J.all() ? 1 : 0;
         st->total = 0;
         st->count_out = 0;
-        st->cmin = ~0ull;
-        st->thr_bits = 0;
         st->count_thr = 0;
+        st->cmin = ~0ull;
+        st->key_hi = ~0ull;  // above every key: nothing is kept
+        st->key_lo = ~0ull;
+        st->thr_bits = ~0ull;
         st->use_thr = 0;
-        st->cand = 0;
-        st->cand_bits = 0;
-        st->count_cand = 0;
+        st->cand_bits = J.all() ? 1ull : ~0ull;
+        st->bin = 0;
+        st->small_n = 0;
+        for (int k = 0; k < SEL_TICKETS; ++k) st->ticket[k] = 0;
     }
 }
 
-__global__ void k_sel_init(SelState* st, u64 M, int take_all, int take_none) { sel_init_body(st, M, take_all, take_none); }
+// A workgroup's counts of a digit, flushed to the state's histogram.
+__device__ __forceinline__ void hist_flush(SelState* st, unsigned bin, u32 c) {
+    if (c) atomicAdd((unsigned long long*)&st->hist[bin], (unsigned long long)c);
+}
 
-// Dense sources: after the level-0 pick (the top key digit is the exponent
-// field of |c|), every entry that can still be kept has |c| >= 2^e, e the
-// binade of the M-th |c| (with the tie band: >= 2^e (1 - 2^-36)).  Those
-// candidates are compacted into a list and the rest of the selection runs on
-// the list.
-__device__ __forceinline__ void sel_cand_bound_body(SelState* st, int band) {
-    if (threadIdx.x != 0) return;
-    u64 b;
-    if (st->take_all) {
-        b = 1;  // every nonzero entry
-    } else if (st->level == 0) {
-        b = ~0ull;  // M = 0: nothing
-    } else {
-        const u64 d0 = st->pre_lo & (u64)(NBIN - 1);
-        if (d0 == 0) b = 1;
-        else if (band) b = abs_bits(__longlong_as_double((long long)(d0 << 52)) * (1.0 - 1.0 / 68719476736.0));
-        else b = d0 << 52;
+// Counts of exponents: neighbouring entries share a few of them, so the 256
+// around 1 have 16 copies each side by side (16 lanes hitting one word cost
+// 16 turns); the others one.
+struct ExpHist {
+    static constexpr int LO = 1023 - 200, WIN = 256, R = 16;
+    u32* h;  // WIN * R, then NBIN
+    __device__ __forceinline__ void clear() {
+        for (int t = threadIdx.x; t < WIN * R + NBIN; t += blockDim.x) h[t] = 0;
     }
-    st->cand_bits = b;
-    st->cand = 1;
-}
-
-__global__ void k_sel_cand_bound(SelState* st, int band) { sel_cand_bound_body(st, band); }
-
-// Ties at the cut: the smallest |c| among the M selected (exact rule) ...
-template <class Src>
-__device__ __forceinline__ void sel_min_body(const Src& src, SelState* __restrict__ st, const Geo& g, unsigned bx, unsigned gx) {
-    const SelState s = *st;
-    if (s.take_all || !s.done || s.level == 0) return;
-    const u64 n = src.size();
-    u64 m = ~0ull;
-    for (u64 i = (u64)bx * blockDim.x + threadIdx.x; i < n; i += (u64)gx * blockDim.x) {
-        u64 r;
-        double c;
-        src.get(i, r, c);
-        if (sel_pred(s, g, r, c)) m = min(m, abs_bits(c));
+    __device__ __forceinline__ void add(double c) {
+        const unsigned e = (unsigned)(abs_bits(c) >> 52), w = e - (unsigned)LO;
+        atomicAdd(w < (unsigned)WIN ? &h[w * R + (threadIdx.x & (R - 1))] : &h[WIN * R + e], 1u);
     }
-    // one atomic per workgroup: wavefront minima, then the workgroup's
-    __shared__ u64 wmin[4];
-    for (int off = 32; off >= 1; off >>= 1) m = min(m, (u64)__shfl_xor((long long)m, off));
-    if ((threadIdx.x & 63) == 0) wmin[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = min(m, wmin[w]);
-        if (m != ~0ull) atomicMin((unsigned long long*)&st->cmin, (unsigned long long)m);
+    __device__ __forceinline__ void flush(SelState* st) {
+        for (int t = threadIdx.x; t < NBIN; t += blockDim.x) {
+            u32 c = h[WIN * R + t];
+            const unsigned w = (unsigned)t - (unsigned)LO;
+            if (w < (unsigned)WIN)
+                for (int k = 0; k < R; ++k) c += h[w * R + k];
+            hist_flush(st, (unsigned)t, c);
+        }
     }
+};
+
+// The M-th key is known: what is kept, and the tie band's threshold.
+__device__ __forceinline__ void sel_decide(SelState* st, u128 K, const Geo& g) {
+    st->key_hi = (u64)(K >> 64);
+    st->key_lo = (u64)K;
+    st->cmin = (u64)(K >> g.rank_bits);
+    st->thr_bits = abs_bits(__longlong_as_double((long long)st->cmin) * (1.0 - 1.0 / 68719476736.0));
+    st->done = 1;
 }
 
-template <class Src>
-__global__ __launch_bounds__(256) void k_sel_min(Src src, SelState* __restrict__ st, Geo g) {
-    sel_min_body(src, st, g, blockIdx.x, gridDim.x);
-}
-
-// ... the threshold cmin * (1 - 2^-36) ...
-__device__ __forceinline__ void sel_thr_body(SelState* st) {
-    if (threadIdx.x != 0 || st->take_all || !st->done || st->level == 0 || st->cmin == ~0ull) return;
-    const double thr = __longlong_as_double((long long)st->cmin) * (1.0 - 1.0 / 68719476736.0);
-    st->thr_bits = abs_bits(thr);
-}
-
-__global__ void k_sel_thr(SelState* st) { sel_thr_body(st); }
-
-// ... how many nonzero candidates reach it ...
-template <class Src>
-__device__ __forceinline__ void sel_count_thr_body(const Src& src, SelState* __restrict__ st, unsigned bx, unsigned gx) {
-    if (st->take_all || !st->done || st->level == 0 || st->cmin == ~0ull) return;
-    const u64 thr = st->thr_bits;
-    const u64 n = src.size();
-    unsigned long long c_ = 0;
-    for (u64 i = (u64)bx * blockDim.x + threadIdx.x; i < n; i += (u64)gx * blockDim.x) {
-        u64 r;
-        double c;
-        src.get(i, r, c);
-        c_ += (c != 0.0 && abs_bits(c) >= thr) ? 1ull : 0ull;
-    }
-    __shared__ unsigned long long wsum[4];
-    for (int off = 32; off >= 1; off >>= 1) c_ += (unsigned long long)__shfl_xor((long long)c_, off);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = c_;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) c_ += wsum[w];
-        if (c_) atomicAdd((unsigned long long*)&st->count_thr, c_);
-    }
-}
-
-template <class Src>
-__global__ __launch_bounds__(256) void k_sel_count_thr(Src src, SelState* __restrict__ st) {
-    sel_count_thr_body(src, st, blockIdx.x, gridDim.x);
-}
-
-// ... and whether they are kept (at most SFCI_TIE_SLACK beyond M).
-__device__ __forceinline__ void sel_mode_body(SelState* st, u64 M) {
-    if (threadIdx.x != 0 || st->take_all || !st->done || st->level == 0 || st->cmin == ~0ull) return;
-    st->use_thr = (st->count_thr <= M + (u64)SFCI_TIE_SLACK) ? 1 : 0;
-}
-
-__global__ void k_sel_mode(SelState* st, u64 M) { sel_mode_body(st, M); }
-
-template <class Src>
-__device__ __forceinline__ void sel_hist_body(const Src& src, SelState* __restrict__ st, const Geo& g, int L, unsigned bx, unsigned gx) {
-    if (st->done) return;
-    __shared__ unsigned int h[NBIN];
-    __shared__ unsigned long long blk_total;
-    for (int t = threadIdx.x; t < NBIN; t += blockDim.x) h[t] = 0;
-    if (threadIdx.x == 0) blk_total = 0;
-    __syncthreads();
-    const u128 pre = ((u128)st->pre_hi << 64) | st->pre_lo;
-    const int lo = dig_lo(g, L);
-    const int hi_sh = g.tb - DIG * L;  // bits above the current digit
-    const u64 n = src.size();
-    u64 my_total = 0;
-    for (u64 i = (u64)bx * blockDim.x + threadIdx.x; i < n; i += (u64)gx * blockDim.x) {
-        u64 r;
-        double c;
-        src.get(i, r, c);
-        if (c == 0.0) continue;
-        ++my_total;
-        u128 K = sel_key(r, c, g);
-        if (L > 0 && (K >> hi_sh) != pre) continue;
-        unsigned d = (unsigned)((K >> lo) & (u128)(NBIN - 1));
-        atomicAdd(&h[d], 1u);
-    }
-    if (L == 0 && my_total) atomicAdd(&blk_total, (unsigned long long)my_total);
-    __syncthreads();
-    for (int t = threadIdx.x; t < NBIN; t += blockDim.x)
-        if (h[t]) atomicAdd((unsigned long long*)&st->hist[t], (unsigned long long)h[t]);
-    if (L == 0 && threadIdx.x == 0 && blk_total) atomicAdd((unsigned long long*)&st->total, blk_total);
-}
-
-template <class Src>
-__global__ __launch_bounds__(256) void k_sel_hist(Src src, SelState* __restrict__ st, Geo g, int L) {
-    sel_hist_body(src, st, g, L, blockIdx.x, gridDim.x);
-}
-
-// Pick the digit of level L: the largest d >= 1 whose bins d.. hold at least
-// `need` entries (else 0), as a block-wide suffix scan over the histogram.
+// Digit of level L: the largest d >= 1 whose bins d.. hold at least `need`
+// entries (else 0), a suffix scan over the histogram by one workgroup of at
+// least 256 threads (the first 256 work); the histogram is cleared.  At level
+// 0 also the total, and the bound of a dense source's candidates.
 constexpr int PICK_T = 256;
 constexpr int PICK_PER = NBIN / PICK_T;
-__device__ __forceinline__ void sel_pick_body(SelState* st, const Geo& g, int L, u64 M) {
+__device__ __forceinline__ void sel_pick(SelState* st, const SelJob& J, int L) {
+    __shared__ u64 wtot[PICK_T / 64];
     __shared__ int s_d;
-    __shared__ u64 s_acc;
-    const int t = threadIdx.x;
-    if (st->done) return;  // uniform: nobody writes it before every thread has read it
-    const u64 need = st->need;
-    if (L == 0 && st->total <= M) {
-        __syncthreads();
-        for (int b = t; b < NBIN; b += PICK_T) st->hist[b] = 0;
-        if (t == 0) {
-            st->take_all = 1;
-            st->done = 1;
-        }
-        return;
-    }
+    __shared__ u64 s_acc, s_hd;
+    const Geo g = J.g;
+    const int t = threadIdx.x, lane = t & 63;
+    const bool on = t < PICK_T;
     u64 h[PICK_PER];
     u64 mine = 0;
-    for (int k = 0; k < PICK_PER; ++k) {
-        h[k] = st->hist[t * PICK_PER + k];
-        mine += h[k];
+    if (on)
+        for (int k = 0; k < PICK_PER; ++k) {
+            h[k] = shared_load(&st->hist[t * PICK_PER + k]);
+            mine += h[k];
+        }
+    u64 suf = mine;  // suffix sum within the wavefront, then over the wavefronts
+    if (on) {
+        for (int off = 1; off < 64; off <<= 1) {
+            const u64 y = (u64)__shfl_down((long long)suf, off);
+            if (lane + off < 64) suf += y;
+        }
+        if (lane == 0) wtot[t >> 6] = suf;
     }
     if (t == 0) {
         s_d = 0;
         s_acc = 0;
+        s_hd = 0;
     }
-    // exclusive suffix sum over threads (bins above this thread's block):
-    // suffix scan within the wavefront, then the totals of later wavefronts
-    __shared__ u64 wtot[PICK_T / 64];
-    const int lane = t & 63;
-    u64 suf = mine;
-    for (int off = 1; off < 64; off <<= 1) {
-        const u64 y = (u64)__shfl_down((long long)suf, off);
-        if (lane + off < 64) suf += y;
-    }
-    if (lane == 0) wtot[t >> 6] = suf;
     __syncthreads();
-    u64 above = suf - mine;
-    for (int w = (t >> 6) + 1; w < PICK_T / 64; ++w) above += wtot[w];
-    u64 incl = above;  // entries in bins > current bin
-    for (int k = PICK_PER - 1; k >= 0; --k) {
-        const int b = t * PICK_PER + k;
-        const u64 hi = incl;  // bins > b
-        incl += h[k];         // bins >= b
-        if (b >= 1 && incl >= need && hi < need) {
-            s_d = b;
-            s_acc = hi;
+    u64 total = 0;
+    for (int w = 0; w < PICK_T / 64; ++w) total += wtot[w];
+    const u64 need = st->need;
+    if (on) {
+        u64 above = suf - mine;
+        for (int w = (t >> 6) + 1; w < PICK_T / 64; ++w) above += wtot[w];
+        u64 incl = above;  // entries in bins > the current one
+        for (int k = PICK_PER - 1; k >= 0; --k) {
+            const int b = t * PICK_PER + k;
+            const u64 hi = incl;
+            incl += h[k];
+            if ((b >= 1 && incl >= need && hi < need) || (b == 0 && hi < need)) {
+                s_d = b;
+                s_acc = hi;
+                s_hd = h[k];
+            }
+        }
+        for (int k = 0; k < PICK_PER; ++k) st->hist[t * PICK_PER + k] = 0;
+    }
+    __syncthreads();
+    if (t != 0) return;
+    if (L == 0) {
+        st->total = total;
+        if (total <= J.M) {
+            st->take_all = 1;
+            st->done = 1;
+            st->cand_bits = 1;
+            return;
         }
     }
-    __syncthreads();
-    int d = s_d;
-    u64 acc = s_acc;
-    if (d == 0) {
-        // no bin >= 1 reaches `need`: the digit is 0, with everything above it taken
-        acc = 0;
-        for (int w = 0; w < PICK_T / 64; ++w) acc += wtot[w];
-        acc -= st->hist[0];
+    const int d = s_d;
+    st->need = need - s_acc;
+    st->bin = s_hd;
+    const int width = (g.tb - DIG * L) - dig_lo(g, L);
+    const u128 pre = ((((u128)st->pre_hi) << 64 | st->pre_lo) << width) | (u128)(unsigned)d;
+    st->pre_hi = (u64)(pre >> 64);
+    st->pre_lo = (u64)pre;
+    st->level = L + 1;
+    if (L == 0) {
+        // every entry that can still be kept has |c| >= 2^e, e the binade of
+        // the M-th |c| (with the tie band: >= 2^e (1 - 2^-36))
+        const u64 lo = (u64)d << 52;
+        st->cand_bits = d == 0 ? 1ull
+                        : J.band ? abs_bits(__longlong_as_double((long long)lo) * (1.0 - 1.0 / 68719476736.0))
+                                 : lo;
     }
-    const u64 hd = st->hist[d];
-    __syncthreads();
-    for (int b = t; b < NBIN; b += PICK_T) st->hist[b] = 0;
-    if (t == 0) {
-        st->need = need - acc;
-        const int lo = dig_lo(g, L);
-        const int width = (g.tb - DIG * L) - lo;
-        u128 pre = ((u128)st->pre_hi << 64) | st->pre_lo;
-        pre = (pre << width) | (u128)(unsigned)d;
-        st->pre_hi = (u64)(pre >> 64);
-        st->pre_lo = (u64)pre;
-        st->level = L + 1;
-        if (hd == st->need || L == g.ndig - 1) st->done = 1;
-    }
+    if (L == g.ndig - 1) sel_decide(st, pre, g);  // every digit fixed
 }
 
-__global__ __launch_bounds__(PICK_T) void k_sel_pick(SelState* st, Geo g, int L, u64 M) { sel_pick_body(st, g, L, M); }
-
-template <class Src>
-__device__ __forceinline__ void compact_count_body(const Src& src, const SelState* __restrict__ st, const Geo& g,
-                                                   u64* __restrict__ cnt, unsigned bx) {
-    const u64 n = src.size();
-    const u64 base = (u64)bx * CCHUNK;
-    if (base >= n) {  // grid sized for capacity; chunk beyond the live size
-        if (threadIdx.x == 0) cnt[bx] = 0;
-        return;
-    }
-    const SelState s = *st;
-    unsigned c = 0;
-    for (int k = 0; k < CITEMS; ++k) {
-        u64 i = base + (u64)k * CBLOCK + threadIdx.x;
-        if (i < n) {
-            u64 r;
-            double v;
-            src.get(i, r, v);
-            c += sel_pred(s, g, r, v) ? 1u : 0u;
-        }
-    }
-    __shared__ unsigned sh[CBLOCK / 64];
-    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
+// Step 1 on a dense source.  Bound by the read of the accumulator (188 MB per
+// 20-orbital instance).
+template <class JP>
+__global__ __launch_bounds__(512) void k_sel_hist0_dense(JP jp) {
+    __shared__ u32 hb[ExpHist::WIN * ExpHist::R + NBIN];
+    const SelJob J = jp(blockIdx.y);
+    if (J.st->done) return;
+    ExpHist H{hb};
+    H.clear();
     __syncthreads();
-    if (threadIdx.x == 0) {
-        u64 t = 0;
-        for (int w = 0; w < CBLOCK / 64; ++w) t += sh[w];
-        cnt[bx] = t;
+    const u64 n = J.Dn, step = (u64)gridDim.x * blockDim.x;
+    u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    for (; i + 7 * step < n; i += 8 * step) {
+        double c[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = J.D[i + (u64)k * step];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (c[k] != 0.0) H.add(c[k]);
     }
+    for (; i < n; i += step) {
+        const double c = J.D[i];
+        if (c != 0.0) H.add(c);
+    }
+    __syncthreads();
+    H.flush(J.st);
+    if (last_workgroup(&J.st->ticket[0], gridDim.x)) sel_pick(J.st, J, 0);
 }
 
-template <class Src>
-__global__ __launch_bounds__(CBLOCK) void k_compact_count(Src src, const SelState* __restrict__ st, Geo g,
-                                                          u64* __restrict__ cnt) {
-    compact_count_body(src, st, g, cnt, blockIdx.x);
-}
-
-template <class Src, bool ZERO>
-__device__ __forceinline__ void compact_write_body(const Src& src, const SelState* __restrict__ st, const Geo& g,
-                                                   const u64* __restrict__ off, u64* __restrict__ out_r,
-                                                   double* __restrict__ out_a, double* __restrict__ Dz, unsigned bx) {
-    const u64 n = src.size();
-    const u64 base = (u64)bx * CCHUNK;
-    if (base >= n) return;
-    const SelState s = *st;
-    __shared__ unsigned wtot[CBLOCK / 64];
-    u64 run = off[bx];
+// Step 2: a workgroup per chunk of slots.  Chunk order and slot order are rank
+// order, so the segments are rank-ordered without a scan over the chunks.
+template <class JP>
+__global__ __launch_bounds__(CBLOCK) void k_sel_collect(JP jp) {
+    const SelJob J = jp(blockIdx.y);
+    const u64 base = (u64)blockIdx.x * CCHUNK;
+    if (base >= J.Dn) return;
+    __shared__ unsigned c64[64];  // entries of (item k, wavefront w) at 4 k + w, then their exclusive scan
+    const u64 bound = J.st->cand_bits;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[CITEMS];
+#pragma unroll
     for (int k = 0; k < CITEMS; ++k) {
-        u64 i = base + (u64)k * CBLOCK + threadIdx.x;
-        u64 r = 0;
-        double v = 0.0;
-        bool p = false;
-        if (i < n) {
-            src.get(i, r, v);
-            p = sel_pred(s, g, r, v);
-            if (ZERO && v != 0.0) Dz[i] = 0.0;
+        const u64 i = base + (u64)k * CBLOCK + threadIdx.x;
+        v[k] = i < J.Dn ? J.D[i] : 0.0;
+    }
+    u64 m[CITEMS];
+#pragma unroll
+    for (int k = 0; k < CITEMS; ++k) {
+        m[k] = __ballot(v[k] != 0.0 && abs_bits(v[k]) >= bound);
+        if (lane == 0) c64[k * (CBLOCK / 64) + wave] = (unsigned)__popcll(m[k]);
+        if (J.Dz && v[k] != 0.0) J.Dz[base + (u64)k * CBLOCK + threadIdx.x] = 0.0;
+    }
+    static_assert(CITEMS * (CBLOCK / 64) == 64, "one count per lane");
+    __syncthreads();
+    if (wave == 0) {
+        const unsigned c = c64[lane];
+        unsigned inc = c;
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned y = __shfl_up(inc, off);
+            if (lane >= off) inc += y;
         }
-        u64 m = __ballot(p);
-        unsigned below = (unsigned)__popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) wtot[wave] = (unsigned)__popcll(m);
+        c64[lane] = inc - c;
+        if (lane == 63) J.cnt[blockIdx.x] = inc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CITEMS; ++k) {
+        if ((m[k] >> lane) & 1u) {
+            const u64 at = base + c64[k * (CBLOCK / 64) + wave] + __popcll(m[k] & ((1ull << lane) - 1ull));
+            const_cast<u64*>(J.r)[at] = base + (u64)k * CBLOCK + threadIdx.x;
+            const_cast<double*>(J.a)[at] = v[k];
+        }
+    }
+}
+
+// fn(rank, value) for every entry, wavefronts over the segments.
+template <class F>
+__device__ __forceinline__ void for_segments(const SelJob& J, F&& fn) {
+    const u64 ns = J.nseg();
+    const u64 nw = (u64)gridDim.x * (blockDim.x >> 6);
+    const int lane = threadIdx.x & 63;
+    for (u64 s = (u64)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); s < ns; s += nw) {
+        const u32 m = J.count(s);
+        const u64 b = s << J.shift;
+        for (u32 i0 = 0; i0 < m; i0 += 64 * SEG_UNROLL) {
+            u64 r[SEG_UNROLL];
+            double c[SEG_UNROLL];
+#pragma unroll
+            for (int u = 0; u < SEG_UNROLL; ++u) {
+                const u32 i = i0 + (u32)u * 64 + lane;
+                r[u] = 0;
+                c[u] = 0.0;
+                if (i < m) {
+                    r[u] = J.r[b + i];
+                    c[u] = J.a[b + i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < SEG_UNROLL; ++u)
+                if (c[u] != 0.0) fn(r[u], c[u]);
+        }
+    }
+}
+
+// Step 1 on a list.
+template <class JP>
+__global__ __launch_bounds__(SEG_BLOCK) void k_sel_hist0(JP jp) {
+    __shared__ u32 hb[ExpHist::WIN * ExpHist::R + NBIN];
+    const SelJob J = jp(blockIdx.y);
+    if (J.st->done) return;
+    ExpHist H{hb};
+    H.clear();
+    __syncthreads();
+    for_segments(J, [&](u64, double c) { H.add(c); });
+    __syncthreads();
+    H.flush(J.st);
+    if (last_workgroup(&J.st->ticket[0], gridDim.x)) sel_pick(J.st, J, 0);
+}
+
+// Step 3 and the remaining digits: histogram of digit L among the entries that
+// share the digits above, pick (nothing once the key is known).  Large
+// workgroups: every one flushes up to 2 048 bins with global atomics.
+template <class JP>
+__global__ __launch_bounds__(SEG_BLOCK) void k_sel_hist(JP jp, int L) {
+    __shared__ u32 hb[NBIN];
+    const SelJob J = jp(blockIdx.y);
+    SelState* st = J.st;
+    if (st->done || L >= J.g.ndig) return;
+    for (int t = threadIdx.x; t < NBIN; t += blockDim.x) hb[t] = 0;
+    __syncthreads();
+    const u128 pre = ((u128)st->pre_hi << 64) | st->pre_lo;
+    const int lo = dig_lo(J.g, L), hi_sh = J.g.tb - DIG * L;
+    for_segments(J, [&](u64 r, double c) {
+        const u128 K = sel_key(r, c, J.g);
+        if ((K >> hi_sh) == pre) atomicAdd(&hb[(unsigned)((K >> lo) & (u128)(NBIN - 1))], 1u);
+    });
+    __syncthreads();
+    for (int t = threadIdx.x; t < NBIN; t += blockDim.x) hist_flush(st, (unsigned)t, hb[t]);
+    if (last_workgroup(&st->ticket[L], gridDim.x)) sel_pick(st, J, L);
+}
+
+// LDS of block_kth.
+struct KthLds {
+    u32 hist[NBIN];
+    u64 hi[64], lo[64];
+    u64 wsum[ONE_BLOCK / 64];
+    u64 need, pre_hi, pre_lo, khi, klo;
+    u32 bin, n;
+};
+
+// The need-th largest key of a workgroup's keys (each(f) calls f for the keys
+// of the calling thread; those that do not start with the digits pre above
+// level L are skipped): digit by digit until at most 64 share them, then by
+// counting.  Every thread gets it.  A workgroup of ONE_BLOCK threads.
+template <class Each>
+__device__ __forceinline__ u128 block_kth(KthLds& S, const Each& each, u64 need0, int L, u128 pre0, const Geo& g) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int NW = ONE_BLOCK / 64;
+    if (t == 0) {
+        S.need = need0;
+        S.pre_hi = (u64)(pre0 >> 64);
+        S.pre_lo = (u64)pre0;
+        S.n = 0;
+    }
+    for (;; ++L) {
+        S.hist[t] = 0;
+        S.hist[t + ONE_BLOCK] = 0;
         __syncthreads();
-        unsigned wbase = 0, all = 0;
-        for (int w = 0; w < CBLOCK / 64; ++w) {
-            if (w < wave) wbase += wtot[w];
-            all += wtot[w];
+        const u128 pre = ((u128)S.pre_hi << 64) | S.pre_lo;
+        const u64 need = S.need;
+        const int lo = dig_lo(g, L), hi_sh = g.tb - DIG * L;
+        each([&](u128 K) {
+            if (L == 0 || (K >> hi_sh) == pre) atomicAdd(&S.hist[(unsigned)((K >> lo) & (u128)(NBIN - 1))], 1u);
+        });
+        __syncthreads();
+        // two bins per thread: the entries above each, by a suffix scan
+        const u32 h0 = S.hist[2 * t], h1 = S.hist[2 * t + 1];
+        u64 suf = (u64)h0 + h1;
+        for (int off = 1; off < 64; off <<= 1) {
+            const u64 y = (u64)__shfl_down((long long)suf, off);
+            if (lane + off < 64) suf += y;
         }
-        if (p) {
-            u64 at = run + wbase + below;
-            out_r[at] = r;
-            out_a[at] = v;
+        if (lane == 0) S.wsum[wave] = suf;
+        __syncthreads();
+        u64 above = suf - h0 - h1;
+        for (int w = wave + 1; w < NW; ++w) above += S.wsum[w];
+        const int width = hi_sh - lo;
+        auto picked = [&](int b, u64 hi, u32 h) {
+            const u128 p = (pre << width) | (u128)(unsigned)b;
+            S.pre_hi = (u64)(p >> 64);
+            S.pre_lo = (u64)p;
+            S.need = need - hi;
+            S.bin = h;
+        };
+        if (above < need && above + h1 >= need) picked(2 * t + 1, above, h1);
+        else if (above + h1 < need && above + h1 + h0 >= need) picked(2 * t, above + h1, h0);
+        __syncthreads();
+        const u128 pre2 = ((u128)S.pre_hi << 64) | S.pre_lo;
+        if (L == g.ndig - 1) return pre2;  // every digit fixed
+        if (S.bin > 64) continue;
+        each([&](u128 K) {
+            if ((K >> lo) == pre2) {
+                const unsigned at = atomicAdd(&S.n, 1u);
+                S.hi[at] = (u64)(K >> 64);
+                S.lo[at] = (u64)K;
+            }
+        });
+        __syncthreads();
+        const unsigned c = S.bin;
+        if ((unsigned)t < c) {
+            const u64 need2 = S.need;
+            const u128 K = ((u128)S.hi[t] << 64) | S.lo[t];
+            unsigned more = 0, same = 0;
+            for (unsigned q = 0; q < c; ++q) {
+                const u128 Q = ((u128)S.hi[q] << 64) | S.lo[q];
+                more += Q > K ? 1u : 0u;
+                same += Q == K ? 1u : 0u;
+            }
+            if (more < need2 && more + same >= need2) {  // (equal keys write the same)
+                S.khi = (u64)(K >> 64);
+                S.klo = (u64)K;
+            }
         }
-        run += all;
+        __syncthreads();
+        return ((u128)S.khi << 64) | S.klo;
+    }
+}
+
+// Step 4: the entries of the picked bin, when they are few, and the M-th key
+// among them.
+template <class JP>
+__global__ __launch_bounds__(ONE_BLOCK) void k_sel_small(JP jp) {
+    __shared__ KthLds S;
+    __shared__ u64 hi[SEL_SMALL], lo[SEL_SMALL];
+    const SelJob J = jp(blockIdx.y);
+    SelState* st = J.st;
+    if (st->done || st->bin > SEL_SMALL) return;
+    const u128 pre = ((u128)st->pre_hi << 64) | st->pre_lo;
+    const int sh = dig_lo(J.g, st->level - 1);
+    for_segments(J, [&](u64 r, double c) {
+        const u128 K = sel_key(r, c, J.g);
+        if ((K >> sh) == pre) {
+            const unsigned at = atomicAdd(&st->small_n, 1u);
+            shared_store(&st->small_hi[at], (u64)(K >> 64));
+            shared_store(&st->small_lo[at], (u64)K);
+        }
+    });
+    if (!last_workgroup(&st->ticket[SEL_TICKETS - 2], gridDim.x)) return;
+    const unsigned n = (unsigned)st->bin;
+    for (unsigned t = threadIdx.x; t < n; t += blockDim.x) {
+        hi[t] = shared_load(&st->small_hi[t]);
+        lo[t] = shared_load(&st->small_lo[t]);
+    }
+    __syncthreads();
+    const u128 K = block_kth(
+        S,
+        [&](auto&& f) {
+            for (unsigned t = threadIdx.x; t < n; t += ONE_BLOCK) f(((u128)hi[t] << 64) | lo[t]);
+        },
+        st->need, st->level, pre, J.g);
+    if (threadIdx.x == 0) sel_decide(st, K, J.g);
+}
+
+struct SelPred {
+    bool all, thr;
+    u64 thr_bits;
+    u128 K;
+    __device__ __forceinline__ explicit SelPred(const SelState& s)
+        : all(s.take_all != 0), thr(s.use_thr != 0), thr_bits(s.thr_bits), K(((u128)s.key_hi << 64) | s.key_lo) {}
+    // c != 0
+    __device__ __forceinline__ bool operator()(u64 r, double c, const Geo& g) const {
+        return all || (thr ? abs_bits(c) >= thr_bits : sel_key(r, c, g) >= K);
+    }
+};
+
+// Exclusive scan of n counts in place by one workgroup, each taken as
+// (x >> sh) & mask; returns the total.
+__device__ __forceinline__ u64 scan_in_place(u64* x, u64 n, int sh, u64 mask) {
+    __shared__ u64 w_tot[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+    constexpr int PER = 8;
+    u64 carry = 0;
+    for (u64 base = 0; base < n; base += (u64)blockDim.x * PER) {
+        const u64 i0 = base + (u64)threadIdx.x * PER;
+        u64 v[PER], sum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            v[k] = i0 + k < n ? (shared_load(&x[i0 + k]) >> sh) & mask : 0;
+            sum += v[k];
+        }
+        u64 inc = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const u64 y = (u64)__shfl_up((long long)inc, off);
+            if (lane >= off) inc += y;
+        }
+        if (lane == 63) w_tot[wave] = inc;
+        __syncthreads();
+        u64 run = carry + inc - sum, tot = 0;
+        for (int w = 0; w < nw; ++w) {
+            if (w < wave) run += w_tot[w];
+            tot += w_tot[w];
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (i0 + k < n) x[i0 + k] = run;
+            run += v[k];
+        }
+        carry += tot;
         __syncthreads();
     }
+    return carry;
 }
 
-template <class Src, bool ZERO>
-__global__ __launch_bounds__(CBLOCK) void k_compact_write(Src src, const SelState* __restrict__ st, Geo g,
-                                                          const u64* __restrict__ off, u64* __restrict__ out_r,
-                                                          double* __restrict__ out_a, double* __restrict__ Dz) {
-    compact_write_body<Src, ZERO>(src, st, g, off, out_r, out_a, Dz, blockIdx.x);
-}
-
-__global__ void k_copy_count(const u64* src, u64* dst) {
-    if (threadIdx.x == 0) *dst = *src;
-}
-
-// ---- batched selection: each launch serves every instance of a batch
-// (blockIdx.y), the same steps as select_topm on a dense source ----
-__device__ __forceinline__ Geo bgeo(const BInst& b) {
-    Geo g;
-    g.rank_bits = b.rank_bits;
-    g.tb = 63 + b.rank_bits;
-    g.ndig = (g.tb + DIG - 1) / DIG;
-    g.ndet_m1 = b.ndet_m1;
-    return g;
-}
-__device__ __forceinline__ u64 bchunks(const BInst& b) { return b.Ndet ? (b.Ndet + CCHUNK - 1) / CCHUNK : 1; }
-__device__ __forceinline__ ListSrc blist(const BInst& b) { return ListSrc{b.cr, b.ca, &b.st->count_cand}; }
-__device__ __forceinline__ void bout_vec(const BInst& b, int kind, int j, u64*& r, double*& a, u64*& n) {
-    if (kind == BOUT_PSI) {
-        r = b.psi_r;
-        a = b.psi_a;
-        n = b.psi_n;
-    } else {
-        const u64 l = kind == BOUT_W0 ? 0 : (u64)j + 1;
-        r = b.Wr + l * b.cap;
-        a = b.Wa + l * b.cap;
-        n = b.sc + l;
+// Step 5: per segment the entries kept by the M-th key (low 32 bits) and by
+// the tie band's threshold (high 32 bits); the last workgroup settles which
+// of the two rules holds and scans.
+template <class JP>
+__global__ __launch_bounds__(256) void k_sel_count(JP jp) {
+    const SelJob J = jp(blockIdx.y);
+    SelState* st = J.st;
+    const SelPred keep(*st);
+    const u64 thr = st->thr_bits;
+    const bool band = J.band && st->cmin != ~0ull;
+    const u64 ns = J.nseg();
+    const u64 nw = (u64)gridDim.x * (blockDim.x >> 6);
+    const int lane = threadIdx.x & 63;
+    u64 by_thr = 0;
+    for (u64 s = (u64)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); s < ns; s += nw) {
+        const u32 m = J.count(s);
+        const u64 b = s << J.shift;
+        u32 kc = 0, kt = 0;
+        for (u32 i0 = 0; i0 < m; i0 += 64 * SEG_UNROLL) {
+            u64 r[SEG_UNROLL];
+            double c[SEG_UNROLL];
+#pragma unroll
+            for (int u = 0; u < SEG_UNROLL; ++u) {
+                const u32 i = i0 + (u32)u * 64 + lane;
+                r[u] = 0;
+                c[u] = 0.0;
+                if (i < m) {
+                    r[u] = J.r[b + i];
+                    c[u] = J.a[b + i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < SEG_UNROLL; ++u) {
+                kc += (u32)__popcll(__ballot(c[u] != 0.0 && keep(r[u], c[u], J.g)));
+                if (band) kt += (u32)__popcll(__ballot(c[u] != 0.0 && abs_bits(c[u]) >= thr));
+            }
+        }
+        if (lane == 0) shared_store(&J.off[s], ((u64)kt << 32) | kc);
+        by_thr += kt;
+    }
+    if (band && lane == 0 && by_thr) atomicAdd((unsigned long long*)&st->count_thr, (unsigned long long)by_thr);
+    if (!last_workgroup(&st->ticket[SEL_TICKETS - 1], gridDim.x)) return;
+    const u64 ct = shared_load(&st->count_thr);
+    const bool use_thr = band && ct <= J.M + (u64)SFCI_TIE_SLACK;
+    const u64 total = scan_in_place(J.off, ns, use_thr ? 32 : 0, 0xFFFFFFFFull);
+    if (threadIdx.x == 0) {
+        st->use_thr = use_thr ? 1 : 0;
+        st->count_out = total;
+        st->count_thr = 0;
+        if (J.out_n) *J.out_n = total;
     }
 }
 
-// list = 0: the dense pass's state, 1: the candidate list's; M = UINT64_MAX
-// keeps every nonzero entry, M = 0 none (the dense pass then lists all, or no,
-// nonzero entries as candidates)
-__global__ void k_bsel_init(const BInst* __restrict__ B, int list, int all) {
-    const BInst& b = B[blockIdx.y];
-    const u64 M = all ? UINT64_MAX : b.M;
-    sel_init_body(list ? b.st2 : b.st, M, M == UINT64_MAX ? 1 : 0, M == 0 ? 1 : 0);
-}
-
-__global__ __launch_bounds__(256) void k_bsel_hist_dense(const BInst* __restrict__ B, int L) {
-    const BInst& b = B[blockIdx.y];
-    sel_hist_body(DenseSrc{b.D, b.Ndet}, b.st, bgeo(b), L, blockIdx.x, gridDim.x);
-}
-
-__global__ __launch_bounds__(256) void k_bsel_hist_list(const BInst* __restrict__ B, int L) {
-    const BInst& b = B[blockIdx.y];
-    sel_hist_body(blist(b), b.st2, bgeo(b), L, blockIdx.x, gridDim.x);
-}
-
-__global__ __launch_bounds__(PICK_T) void k_bsel_pick(const BInst* __restrict__ B, int list, int L) {
-    const BInst& b = B[blockIdx.y];
-    sel_pick_body(list ? b.st2 : b.st, bgeo(b), L, b.M);
-}
-
-__global__ void k_bsel_cand_bound(const BInst* __restrict__ B, int band) { sel_cand_bound_body(B[blockIdx.y].st, band); }
-
-__global__ __launch_bounds__(CBLOCK) void k_bcompact_count_dense(const BInst* __restrict__ B) {
-    const BInst& b = B[blockIdx.y];
-    if (blockIdx.x >= bchunks(b)) return;  // past this instance's chunks (and its count array)
-    compact_count_body(DenseSrc{b.D, b.Ndet}, b.st, bgeo(b), b.cnt, blockIdx.x);
-}
-
-template <bool ZERO>
-__global__ __launch_bounds__(CBLOCK) void k_bcompact_write_dense(const BInst* __restrict__ B) {
-    const BInst& b = B[blockIdx.y];
-    if (blockIdx.x >= bchunks(b)) return;
-    compact_write_body<DenseSrc, ZERO>(DenseSrc{b.D, b.Ndet}, b.st, bgeo(b), b.cnt, b.cr, b.ca, b.D, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_bsel_min_list(const BInst* __restrict__ B) {
-    const BInst& b = B[blockIdx.y];
-    sel_min_body(blist(b), b.st2, bgeo(b), blockIdx.x, gridDim.x);
-}
-
-__global__ void k_bsel_thr(const BInst* __restrict__ B) { sel_thr_body(B[blockIdx.y].st2); }
-
-__global__ __launch_bounds__(256) void k_bsel_count_thr_list(const BInst* __restrict__ B) {
-    const BInst& b = B[blockIdx.y];
-    sel_count_thr_body(blist(b), b.st2, blockIdx.x, gridDim.x);
-}
-
-__global__ void k_bsel_mode(const BInst* __restrict__ B) { sel_mode_body(B[blockIdx.y].st2, B[blockIdx.y].M); }
-
-__global__ __launch_bounds__(CBLOCK) void k_bcompact_count_list(const BInst* __restrict__ B) {
-    const BInst& b = B[blockIdx.y];
-    if (blockIdx.x >= bchunks(b)) return;
-    compact_count_body(blist(b), b.st2, bgeo(b), b.cnt, blockIdx.x);
-}
-
-__global__ void k_bcopy_count(const BInst* __restrict__ B, int kind, int j) {
-    const BInst& b = B[blockIdx.y];
-    u64* r;
-    double* a;
-    u64* n;
-    bout_vec(b, kind, j, r, a, n);
-    if (threadIdx.x == 0) *n = b.st2->count_out;
-}
-
-__global__ __launch_bounds__(CBLOCK) void k_bcompact_write_list(const BInst* __restrict__ B, int kind, int j) {
-    const BInst& b = B[blockIdx.y];
-    if (blockIdx.x >= bchunks(b)) return;
-    u64* r;
-    double* a;
-    u64* n;
-    bout_vec(b, kind, j, r, a, n);
-    compact_write_body<ListSrc, false>(blist(b), b.st2, bgeo(b), b.cnt, r, a, nullptr, blockIdx.x);
-}
-
-Geo make_geo(sfci_problem* P) {
-    Geo g;
-    g.rank_bits = P->kg.rank_bits;
-    g.tb = 63 + g.rank_bits;
-    g.ndig = (g.tb + DIG - 1) / DIG;
-    g.ndet_m1 = P->kg.ndet_m1;
-    return g;
-}
-
-template <class Src>
-void run_prepare(sfci_problem* P, const Src& src, u64 n_upper, u64 M, u64* out_count_dev, SelState* st = nullptr,
-                 u64* cnt_ws = nullptr, u64* bsum_ws = nullptr) {
-    // k_sel_min always runs: its cmin (the smallest kept |c|) bounds the list
-    // iteration's running candidate list.  The band's three steps only with
-    // the extension on.
-    Geo g = make_geo(P);
-    if (!st) st = (SelState*)P->ws_sel.get(sizeof(SelState));
-    int take_all = (M == UINT64_MAX) ? 1 : 0;
-    int take_none = (M == 0) ? 1 : 0;
-    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, P->stream, st, M, take_all, take_none);
-    unsigned hgrid = (unsigned)std::min<u64>((n_upper + 255) / 256, (u64)P->num_cu * 8);
-    if (hgrid < 1) hgrid = 1;
-    if (!take_all && !take_none) {
-        for (int L = 0; L < g.ndig; ++L) {
-            hipLaunchKernelGGL(k_sel_hist<Src>, dim3(hgrid), dim3(256), 0, P->stream, src, st, g, L);
-            hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(PICK_T), 0, P->stream, st, g, L, M);
-        }
-        hipLaunchKernelGGL(k_sel_min<Src>, dim3(hgrid), dim3(256), 0, P->stream, src, st, g);
-        if (P->tie_band) {
-            hipLaunchKernelGGL(k_sel_thr, dim3(1), dim3(64), 0, P->stream, st);
-            hipLaunchKernelGGL(k_sel_count_thr<Src>, dim3(hgrid), dim3(256), 0, P->stream, src, st);
-            hipLaunchKernelGGL(k_sel_mode, dim3(1), dim3(64), 0, P->stream, st, M);
+// Step 6: a wavefront per segment writes its kept entries at the segment's offset.
+template <class JP>
+__global__ __launch_bounds__(256) void k_sel_write(JP jp) {
+    const SelJob J = jp(blockIdx.y);
+    const SelPred keep(*J.st);
+    const u64 ns = J.nseg();
+    const u64 nw = (u64)gridDim.x * (blockDim.x >> 6);
+    const int lane = threadIdx.x & 63;
+    for (u64 s = (u64)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); s < ns; s += nw) {
+        const u32 m = J.count(s);
+        const u64 b = s << J.shift;
+        u64 at = J.off[s];
+        for (u32 i0 = 0; i0 < m; i0 += 64 * SEG_UNROLL) {
+            u64 r[SEG_UNROLL];
+            double c[SEG_UNROLL];
+#pragma unroll
+            for (int u = 0; u < SEG_UNROLL; ++u) {
+                const u32 i = i0 + (u32)u * 64 + lane;
+                r[u] = 0;
+                c[u] = 0.0;
+                if (i < m) {
+                    r[u] = J.r[b + i];
+                    c[u] = J.a[b + i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < SEG_UNROLL; ++u) {
+                const bool p = c[u] != 0.0 && keep(r[u], c[u], J.g);
+                const u64 pm = __ballot(p);
+                if (p) {
+                    const u64 o = at + (u64)__popcll(pm & ((1ull << lane) - 1ull));
+                    J.out_r[o] = r[u];
+                    J.out_a[o] = c[u];
+                }
+                at += (u64)__popcll(pm);
+            }
         }
     }
-    u64 nblk = (n_upper + CCHUNK - 1) / CCHUNK;
-    if (nblk < 1) nblk = 1;
-    u64* cnt = cnt_ws ? cnt_ws : (u64*)P->ws_cnt.get(nblk * sizeof(u64));
-    hipLaunchKernelGGL(k_compact_count<Src>, dim3((unsigned)nblk), dim3(CBLOCK), 0, P->stream, src, st, g, cnt);
-    exclusive_scan_u64(P, cnt, cnt, nblk, &st->count_out, bsum_ws);
-    if (out_count_dev) hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(64), 0, P->stream, &st->count_out, out_count_dev);
+}
+
+// Every nonzero slot of a dense source, in rank order, without a candidate
+// stage (M = all; also the candidates of a space too large for segments:
+// |c| >= cand_bits): counts per chunk and their scan, then the compaction.
+template <class JP>
+__global__ __launch_bounds__(CBLOCK) void k_dense_count(JP jp, u64 nchunk) {
+    const SelJob J = jp(blockIdx.y);
+    const u64 bound = J.st->cand_bits;
+    __shared__ unsigned sh[CBLOCK / 64];
+    for (u64 ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
+        const u64 base = ch * CCHUNK;
+        unsigned c = 0;
+#pragma unroll
+        for (int k = 0; k < CITEMS; ++k) {
+            const u64 i = base + (u64)k * CBLOCK + threadIdx.x;
+            const double v = i < J.Dn ? J.D[i] : 0.0;
+            c += (v != 0.0 && abs_bits(v) >= bound) ? 1u : 0u;
+        }
+        for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            u64 t = 0;
+            for (int w = 0; w < CBLOCK / 64; ++w) t += sh[w];
+            shared_store(&J.off[ch], t);
+        }
+        __syncthreads();
+    }
+    if (!last_workgroup(&J.st->ticket[SEL_TICKETS - 1], gridDim.x)) return;
+    const u64 total = scan_in_place(J.off, nchunk, 0, ~0ull);
+    if (threadIdx.x == 0) {
+        J.st->count_out = total;
+        J.st->ticket[SEL_TICKETS - 1] = 0;
+        if (J.out_n) *J.out_n = total;
+    }
+}
+
+template <class JP>
+__global__ __launch_bounds__(CBLOCK) void k_dense_write(JP jp) {
+    const SelJob J = jp(blockIdx.y);
+    const u64 base = (u64)blockIdx.x * CCHUNK;
+    if (base >= J.Dn) return;
+    __shared__ unsigned c64[64];
+    const u64 bound = J.st->cand_bits;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[CITEMS];
+#pragma unroll
+    for (int k = 0; k < CITEMS; ++k) {
+        const u64 i = base + (u64)k * CBLOCK + threadIdx.x;
+        v[k] = i < J.Dn ? J.D[i] : 0.0;
+    }
+    u64 m[CITEMS];
+#pragma unroll
+    for (int k = 0; k < CITEMS; ++k) {
+        m[k] = __ballot(v[k] != 0.0 && abs_bits(v[k]) >= bound);
+        if (lane == 0) c64[k * (CBLOCK / 64) + wave] = (unsigned)__popcll(m[k]);
+        if (J.Dz && v[k] != 0.0) J.Dz[base + (u64)k * CBLOCK + threadIdx.x] = 0.0;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const unsigned c = c64[lane];
+        unsigned inc = c;
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned y = __shfl_up(inc, off);
+            if (lane >= off) inc += y;
+        }
+        c64[lane] = inc - c;
+    }
+    __syncthreads();
+    const u64 at0 = J.off[blockIdx.x];
+#pragma unroll
+    for (int k = 0; k < CITEMS; ++k) {
+        if ((m[k] >> lane) & 1u) {
+            const u64 at = at0 + c64[k * (CBLOCK / 64) + wave] + __popcll(m[k] & ((1ull << lane) - 1ull));
+            J.out_r[at] = base + (u64)k * CBLOCK + threadIdx.x;
+            J.out_a[at] = v[k];
+        }
+    }
+}
+
+// The whole selection of a source of at most SEL_ONE entries by one
+// workgroup, the values in registers: one launch (30 us at 3 136 slots) where
+// the steps above are 7 and the histogram per digit took 24.
+template <class JP>
+__global__ __launch_bounds__(ONE_BLOCK) void k_sel_one(JP jp) {
+    __shared__ KthLds S;
+    __shared__ u64 wsum[ONE_BLOCK / 64];
+    __shared__ unsigned cpos[ONE_ITEMS * (ONE_BLOCK / 64)];
+    __shared__ u64 s_count;
+    const SelJob J = jp(blockIdx.y);
+    const Geo g = J.g;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int NW = ONE_BLOCK / 64;
+    const u64 n = J.D ? J.Dn : min(*J.n, J.cap);
+    const int nk = (int)((n + ONE_BLOCK - 1) / ONE_BLOCK);
+    auto rank_of = [&](int k) -> u64 {
+        const u64 i = (u64)k * ONE_BLOCK + t;
+        return J.D ? i : J.r[i];
+    };
+    auto block_sum = [&](u64 x) -> u64 {
+        for (int off = 32; off >= 1; off >>= 1) x += (u64)__shfl_xor((long long)x, off);
+        __syncthreads();
+        if (lane == 0) wsum[wave] = x;
+        __syncthreads();
+        u64 s = 0;
+        for (int w = 0; w < NW; ++w) s += wsum[w];
+        return s;
+    };
+    double v[ONE_ITEMS];
+    u64 nz = 0;
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        const u64 i = (u64)k * ONE_BLOCK + t;
+        v[k] = 0.0;
+        if (k < nk && i < n) v[k] = J.D ? J.D[i] : J.a[i];
+        nz += v[k] != 0.0 ? 1 : 0;
+        if (J.Dz && v[k] != 0.0) J.Dz[i] = 0.0;
+    }
+    const u64 total = block_sum(nz);
+    bool all = J.all() || total <= J.M;
+    const bool none = J.M == 0;
+    bool use_thr = false;
+    u128 KM = ~(u128)0;
+    u64 cmin = ~0ull, thr = ~0ull;
+    if (!all && !none) {
+        KM = block_kth(
+            S,
+            [&](auto&& f) {
+#pragma unroll
+                for (int k = 0; k < ONE_ITEMS; ++k)
+                    if (k < nk && v[k] != 0.0) f(sel_key(rank_of(k), v[k], g));
+            },
+            J.M, 0, (u128)0, g);
+        cmin = (u64)(KM >> g.rank_bits);
+        thr = abs_bits(__longlong_as_double((long long)cmin) * (1.0 - 1.0 / 68719476736.0));
+        if (J.band) {
+            u64 c = 0;
+#pragma unroll
+            for (int k = 0; k < ONE_ITEMS; ++k) c += (v[k] != 0.0 && abs_bits(v[k]) >= thr) ? 1 : 0;
+            use_thr = block_sum(c) <= J.M + (u64)SFCI_TIE_SLACK;
+        }
+    }
+    u64 m[ONE_ITEMS];
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        bool p = k < nk && v[k] != 0.0 && !none;
+        if (p && !all) p = use_thr ? abs_bits(v[k]) >= thr : sel_key(rank_of(k), v[k], g) >= KM;
+        m[k] = __ballot(p);
+        if (lane == 0) cpos[k * NW + wave] = (unsigned)__popcll(m[k]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        unsigned carry = 0;
+        for (int b = 0; b < ONE_ITEMS * NW; b += 64) {
+            const unsigned c = cpos[b + lane];
+            unsigned inc = c;
+            for (int off = 1; off < 64; off <<= 1) {
+                const unsigned y = __shfl_up(inc, off);
+                if (lane >= off) inc += y;
+            }
+            cpos[b + lane] = carry + inc - c;
+            carry += (unsigned)__shfl((int)inc, 63);
+        }
+        if (lane == 0) s_count = carry;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        if ((m[k] >> lane) & 1u) {
+            const u64 at = cpos[k * NW + wave] + (u64)__popcll(m[k] & ((1ull << lane) - 1ull));
+            J.out_r[at] = rank_of(k);
+            J.out_a[at] = v[k];
+        }
+    }
+    if (t == 0) {
+        if (J.out_n) *J.out_n = s_count;
+        J.st->total = total;
+        J.st->take_all = all ? 1 : 0;
+        J.st->count_out = s_count;
+        J.st->cmin = cmin;
+    }
+}
+
+unsigned seg_grid(int num_cu, u64 nseg) {
+    return (unsigned)std::max<u64>(1, std::min<u64>((nseg + 3) / 4, (u64)num_cu * 8));
+}
+
+unsigned hist0_grid(int num_cu, u64 n) {
+    return (unsigned)std::max<u64>(1, std::min<u64>((n + 4095) / 4096, (u64)num_cu * 3));
+}
+
+// Steps 3 and 4 for candidates whose top digit is picked (from = 1), or all
+// digits of a list (from = 0).
+template <class JP>
+void run_digits(hipStream_t st, const JP& jp, unsigned n, int num_cu, u64 nseg, int from, int max_ndig) {
+    const unsigned grid = (unsigned)std::max<u64>(1, std::min<u64>((nseg + 15) / 16, (u64)num_cu));
+    if (from == 0) hipLaunchKernelGGL(k_sel_hist0<JP>, dim3(grid, n), dim3(SEG_BLOCK), 0, st, jp);
+    hipLaunchKernelGGL(k_sel_hist<JP>, dim3(grid, n), dim3(SEG_BLOCK), 0, st, jp, 1);
+    hipLaunchKernelGGL(k_sel_small<JP>, dim3(grid, n), dim3(ONE_BLOCK), 0, st, jp);
+    // the remaining digits one by one, for bins that hold more than SEL_SMALL
+    // entries (their kernels return at once otherwise)
+    for (int L = 2; L < max_ndig; ++L)
+        hipLaunchKernelGGL(k_sel_hist<JP>, dim3(grid, n), dim3(SEG_BLOCK), 0, st, jp, L);
+}
+
+SelJob make_job(sfci_problem* P, u64 M, SelState* st) {
+    SelJob J{};
+    J.st = st;
+    J.M = M;
+    J.band = P->tie_band ? 1 : 0;
+    J.g = geo_of(P->kg.rank_bits, P->kg.ndet_m1);
+    return J;
+}
+
+SelJob dense_job(sfci_problem* P, const CandSrc& src, u64 M, bool zero) {
+    SelJob J = make_job(P, M, (SelState*)P->ws_sel.get(sizeof(SelState)));
+    J.D = src.dense;
+    J.Dn = P->Ndet;
+    J.cap = P->Ndet;
+    J.shift = SEL_DENSE_SHIFT;
+    J.Dz = zero ? (double*)src.dense : nullptr;
+    return J;
+}
+
+SelJob list_job(sfci_problem* P, const CandSrc& src, u64 M, SelState* st, u64* off) {
+    SelJob J = make_job(P, M, st);
+    J.r = src.lrank;
+    J.a = src.lval;
+    J.n = src.lcount;
+    J.cap = src.lcap;
+    J.shift = select_shift(src.lcap);
+    J.off = off;
+    return J;
+}
+
+// Steps 1 to 5 on a list.
+void list_prepare(sfci_problem* P, const SelJob& J) {
+    const u64 ns = select_segments(J.cap);
+    const unsigned grid = seg_grid(P->num_cu, ns);
+    const OneJob jp{J};
+    hipLaunchKernelGGL(k_sel_init<OneJob>, dim3(1), dim3(256), 0, P->stream, jp);
+    if (J.M != UINT64_MAX && J.M != 0) run_digits(P->stream, jp, 1, P->num_cu, ns, 0, J.g.ndig);
+    hipLaunchKernelGGL(k_sel_count<OneJob>, dim3(grid), dim3(256), 0, P->stream, jp);
     SFCI_CHECK_HIP(hipGetLastError());
 }
 
-template <class Src>
-void run_write(sfci_problem* P, const Src& src, u64 n_upper, u64* out_rank, double* out_amp, bool zero_dense,
-               double* Dz, SelState* st = nullptr, u64* cnt_ws = nullptr) {
-    Geo g = make_geo(P);
-    if (!st) st = (SelState*)P->ws_sel.p;
-    u64 nblk = (n_upper + CCHUNK - 1) / CCHUNK;
-    if (nblk < 1) nblk = 1;
-    u64* cnt = cnt_ws ? cnt_ws : (u64*)P->ws_cnt.p;
-    if (zero_dense)
-        hipLaunchKernelGGL((k_compact_write<Src, true>), dim3((unsigned)nblk), dim3(CBLOCK), 0, P->stream, src, st, g,
-                           cnt, out_rank, out_amp, Dz);
-    else
-        hipLaunchKernelGGL((k_compact_write<Src, false>), dim3((unsigned)nblk), dim3(CBLOCK), 0, P->stream, src, st,
-                           g, cnt, out_rank, out_amp, Dz);
+void list_write(sfci_problem* P, const SelJob& J) {
+    hipLaunchKernelGGL(k_sel_write<OneJob>, dim3(seg_grid(P->num_cu, select_segments(J.cap))), dim3(256), 0,
+                       P->stream, OneJob{J});
     SFCI_CHECK_HIP(hipGetLastError());
 }
+
+// Dense source, candidates in segments: the buffers (N_det entries: a chunk's
+// segment has a slot for each of its entries).
+void dense_segments(sfci_problem* P, SelJob& J) {
+    const u64 nch = select_chunks(P->Ndet);
+    J.r = (u64*)P->ws_cand_r.get(P->Ndet * sizeof(u64));
+    J.a = (double*)P->ws_cand_a.get(P->Ndet * sizeof(double));
+    J.off = (u64*)P->ws_cnt.get(nch * (sizeof(u64) + sizeof(u32)));
+    J.cnt = (u32*)(J.off + nch);
+}
+
+template <class JP>
+void dense_seg_prepare(hipStream_t st, const JP& jp, unsigned n, int num_cu, u64 max_n, int max_ndig, bool trunc) {
+    const u64 nch = select_chunks(max_n);
+    const unsigned grid = seg_grid(num_cu, nch);
+    hipLaunchKernelGGL(k_sel_init<JP>, dim3(1, n), dim3(256), 0, st, jp);
+    if (trunc) hipLaunchKernelGGL(k_sel_hist0_dense<JP>, dim3(hist0_grid(num_cu, max_n), n), dim3(512), 0, st, jp);
+    hipLaunchKernelGGL(k_sel_collect<JP>, dim3((unsigned)nch, n), dim3(CBLOCK), 0, st, jp);
+    if (trunc) run_digits(st, jp, n, num_cu, nch, 1, max_ndig);
+    hipLaunchKernelGGL(k_sel_count<JP>, dim3(grid, n), dim3(256), 0, st, jp);
+}
+
+// Dense source in place: every slot with |c| >= cand_bits.
+template <class JP>
+void dense_count(hipStream_t st, const JP& jp, unsigned n, int num_cu, u64 max_n) {
+    const u64 nch = select_chunks(max_n);
+    hipLaunchKernelGGL(k_dense_count<JP>, dim3((unsigned)std::min<u64>(nch, (u64)num_cu * 8), n), dim3(CBLOCK), 0,
+                       st, jp, nch);
+}
+
+u64 read_u64(sfci_problem* P, const u64* d) {
+    u64 h = 0;
+    SFCI_CHECK_HIP(hipMemcpyAsync(&h, d, sizeof(u64), hipMemcpyDeviceToHost, P->stream));
+    SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+    return h;
+}
+
+// A source one workgroup takes in one launch.
+bool one_block(sfci_problem* P, const CandSrc& src) { return (src.dense ? P->Ndet : src.lcap) <= (u64)SEL_ONE; }
 
 }  // namespace
 
-void select_prepare(sfci_problem* P, const CandSrc& src, u64 M, u64* count_dev) {
-    if (src.dense) {
-        DenseSrc s{src.dense, P->Ndet};
-        run_prepare(P, s, P->Ndet, M, count_dev);
-    } else {
-        ListSrc s{src.lrank, src.lval, src.lcount};
-        run_prepare(P, s, src.lcap, M, count_dev);
-    }
-}
-
-void select_write(sfci_problem* P, const CandSrc& src, u64* out_rank, double* out_amp, bool zero_dense) {
-    if (src.dense) {
-        DenseSrc s{src.dense, P->Ndet};
-        run_write(P, s, P->Ndet, out_rank, out_amp, zero_dense, (double*)src.dense);
-    } else {
-        ListSrc s{src.lrank, src.lval, src.lcount};
-        run_write(P, s, src.lcap, out_rank, out_amp, false, nullptr);
-    }
+bool select_one_step(const sfci_problem* P, u64 M) {
+    return M == UINT64_MAX || M == 0 || P->Ndet <= (u64)SEL_ONE || P->Ndet * 16 <= SEL_SEG_BYTES;
 }
 
 u64 select_chunks(u64 n_upper) { return std::max<u64>(1, (n_upper + CCHUNK - 1) / CCHUNK); }
+// Lists of up to 4 Mi entries in segments of 1 024 (a wavefront each: more of
+// them in flight), longer ones of 4 096.
+int select_shift(u64 lcap) { return lcap <= (4ull << 20) ? 10 : SEL_DENSE_SHIFT; }
+u64 select_segments(u64 lcap) {
+    const int sh = select_shift(lcap);
+    return std::max<u64>(1, (lcap + (1ull << sh) - 1) >> sh);
+}
+
+// Two steps, for callers that must know the count before the entries are
+// written.  What the second one needs is kept in P->sel_mode: 1 segments of
+// the dense source, 2 a list, 3 the dense source in place.
+void select_prepare(sfci_problem* P, const CandSrc& src, u64 M, u64* count_dev) {
+    if (!src.dense) {
+        SelJob J = list_job(P, src, M, (SelState*)P->ws_sel.get(sizeof(SelState)),
+                            (u64*)P->ws_cnt.get(select_segments(src.lcap) * sizeof(u64)));
+        J.out_n = count_dev;
+        list_prepare(P, J);
+        P->sel_mode = 2;
+        return;
+    }
+    SelJob J = dense_job(P, src, M, false);
+    J.out_n = count_dev;
+    const bool trunc = M != UINT64_MAX && M != 0;
+    if (trunc && P->Ndet * 16 <= SEL_SEG_BYTES) {
+        // (the accumulator is zeroed when the candidates are taken: the caller zeroes it anyway)
+        J.Dz = (double*)src.dense;
+        dense_segments(P, J);
+        dense_seg_prepare(P->stream, OneJob{J}, 1, P->num_cu, P->Ndet, J.g.ndig, true);
+        P->sel_mode = 1;
+    } else {
+        const u64 nch = select_chunks(P->Ndet);
+        J.off = (u64*)P->ws_cnt.get(nch * sizeof(u64));
+        hipLaunchKernelGGL(k_sel_init<OneJob>, dim3(1), dim3(256), 0, P->stream, OneJob{J});
+        if (trunc) {
+            // a space too large for segments: the candidates' number decides their buffers
+            hipLaunchKernelGGL(k_sel_hist0_dense<OneJob>, dim3(hist0_grid(P->num_cu, P->Ndet)), dim3(512), 0,
+                               P->stream, OneJob{J});
+        }
+        dense_count(P->stream, OneJob{J}, 1, P->num_cu, P->Ndet);
+        P->sel_mode = 3;
+        if (trunc) {
+            const u64 nc = read_u64(P, &J.st->count_out);
+            J.out_r = (u64*)P->ws_cand_r.get(std::max<u64>(1, nc) * sizeof(u64));
+            J.out_a = (double*)P->ws_cand_a.get(std::max<u64>(1, nc) * sizeof(double));
+            J.Dz = (double*)src.dense;
+            hipLaunchKernelGGL(k_dense_write<OneJob>, dim3((unsigned)nch), dim3(CBLOCK), 0, P->stream, OneJob{J});
+            CandSrc ls{};
+            ls.lrank = J.out_r;
+            ls.lval = J.out_a;
+            ls.lcount = &J.st->count_cand;
+            ls.lcap = std::max<u64>(1, nc);
+            launch_set_u64(P, &J.st->count_cand, nc);
+            SelJob K = list_job(P, ls, M, J.st, (u64*)P->ws_cnt.get(select_segments(ls.lcap) * sizeof(u64)));
+            K.out_n = count_dev;
+            const unsigned grid = seg_grid(P->num_cu, select_segments(ls.lcap));
+            run_digits(P->stream, OneJob{K}, 1, P->num_cu, select_segments(ls.lcap), 1, K.g.ndig);
+            hipLaunchKernelGGL(k_sel_count<OneJob>, dim3(grid), dim3(256), 0, P->stream, OneJob{K});
+            P->sel_mode = 2;
+            P->sel_src = ls;
+        }
+    }
+    SFCI_CHECK_HIP(hipGetLastError());
+}
+
+void select_write(sfci_problem* P, const CandSrc& src, u64* out_rank, double* out_amp, bool zero_dense) {
+    SelState* st = (SelState*)P->ws_sel.p;
+    u64* off = (u64*)P->ws_cnt.p;
+    if (P->sel_mode == 3) {
+        SelJob J = dense_job(P, src, UINT64_MAX, zero_dense);
+        J.off = off;
+        J.out_r = out_rank;
+        J.out_a = out_amp;
+        hipLaunchKernelGGL(k_dense_write<OneJob>, dim3((unsigned)select_chunks(P->Ndet)), dim3(CBLOCK), 0, P->stream,
+                           OneJob{J});
+        SFCI_CHECK_HIP(hipGetLastError());
+        return;
+    }
+    SelJob J;
+    if (P->sel_mode == 1) {
+        J = dense_job(P, src, 0, false);
+        dense_segments(P, J);
+    } else {
+        J = list_job(P, src.dense ? P->sel_src : src, 0, st, off);
+    }
+    J.out_r = out_rank;
+    J.out_a = out_amp;
+    list_write(P, J);
+}
 
 void select_prepare_ws(sfci_problem* P, const CandSrc& src, u64 M, u64* count_dev, const SelWs& ws) {
-    ListSrc s{src.lrank, src.lval, src.lcount};
-    run_prepare(P, s, src.lcap, M, count_dev, ws.st, ws.cnt, ws.bsum);
+    SelJob J = list_job(P, src, M, ws.st, ws.off);
+    J.out_n = count_dev;
+    list_prepare(P, J);
 }
 
 void select_write_ws(sfci_problem* P, const CandSrc& src, u64* out_rank, double* out_amp, const SelWs& ws) {
-    ListSrc s{src.lrank, src.lval, src.lcount};
-    run_write(P, s, src.lcap, out_rank, out_amp, false, nullptr, ws.st, ws.cnt);
+    SelJob J = list_job(P, src, 0, ws.st, ws.off);
+    J.out_r = out_rank;
+    J.out_a = out_amp;
+    list_write(P, J);
 }
 
+// One step, for outputs that hold whatever may be kept.
 void select_topm(sfci_problem* P, const CandSrc& src, u64 M, u64* out_rank, double* out_amp, u64* out_count_dev,
                  bool zero_dense) {
-    if (!src.dense || !zero_dense || M == UINT64_MAX || M == 0) {
+    if (one_block(P, src)) {
+        SelState* st = (SelState*)P->ws_sel.get(sizeof(SelState));
+        SelJob J = src.dense ? dense_job(P, src, M, zero_dense) : list_job(P, src, M, st, nullptr);
+        J.out_r = out_rank;
+        J.out_a = out_amp;
+        J.out_n = out_count_dev;
+        hipLaunchKernelGGL(k_sel_one<OneJob>, dim3(1), dim3(ONE_BLOCK), 0, P->stream, OneJob{J});
+        SFCI_CHECK_HIP(hipGetLastError());
+        return;
+    }
+    if (!src.dense || M == UINT64_MAX || M == 0) {
         select_prepare(P, src, M, out_count_dev);
         select_write(P, src, out_rank, out_amp, zero_dense);
         return;
     }
-    // Dense source, truncation to M: one histogram pass for the binade of the
-    // M-th |c|, one pass to count and one to compact the candidates into a
-    // rank-ordered list (zeroing the dense array), then the full selection on
-    // the list.
-    Geo g = make_geo(P);
-    SelState* st = (SelState*)P->ws_sel.get(sizeof(SelState));
-    SelState* st2 = (SelState*)P->ws_sel2.get(sizeof(SelState));
-    u64* cr = (u64*)P->ws_cand_r.get(P->Ndet * sizeof(u64));
-    double* ca = (double*)P->ws_cand_a.get(P->Ndet * sizeof(double));
-    DenseSrc ds{src.dense, P->Ndet};
-    const unsigned hgrid = (unsigned)std::max<u64>(1, std::min<u64>((P->Ndet + 255) / 256, (u64)P->num_cu * 8));
-    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, P->stream, st, M, 0, 0);
-    hipLaunchKernelGGL(k_sel_hist<DenseSrc>, dim3(hgrid), dim3(256), 0, P->stream, ds, st, g, 0);
-    hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(PICK_T), 0, P->stream, st, g, 0, M);
-    hipLaunchKernelGGL(k_sel_cand_bound, dim3(1), dim3(64), 0, P->stream, st, P->tie_band ? 1 : 0);
-    const u64 nblk = std::max<u64>(1, (P->Ndet + CCHUNK - 1) / CCHUNK);
-    u64* cnt = (u64*)P->ws_cnt.get(nblk * sizeof(u64));
-    hipLaunchKernelGGL(k_compact_count<DenseSrc>, dim3((unsigned)nblk), dim3(CBLOCK), 0, P->stream, ds, st, g, cnt);
-    exclusive_scan_u64(P, cnt, cnt, nblk, &st->count_cand);
-    hipLaunchKernelGGL((k_compact_write<DenseSrc, true>), dim3((unsigned)nblk), dim3(CBLOCK), 0, P->stream, ds, st, g,
-                       cnt, cr, ca, (double*)src.dense);
-    SFCI_CHECK_HIP(hipGetLastError());
-    ListSrc ls{cr, ca, &st->count_cand};
-    run_prepare(P, ls, P->Ndet, M, out_count_dev, st2);
-    run_write(P, ls, P->Ndet, out_rank, out_amp, false, nullptr, st2);
+    SelJob J = dense_job(P, src, M, zero_dense);
+    dense_segments(P, J);
+    J.out_r = out_rank;
+    J.out_a = out_amp;
+    J.out_n = out_count_dev;
+    dense_seg_prepare(P->stream, OneJob{J}, 1, P->num_cu, P->Ndet, J.g.ndig, true);
+    list_write(P, J);
 }
 
 void bstep_select(hipStream_t st, const BInst* d, int n, int out_kind, int j, u64 max_ndet, int num_cu, int band,
-                  int max_ndig, const BScanJob* d_scan_dense, const BScanJob* d_scan_list, int all, bool zero) {
+                  int max_ndig, int all, bool zero) {
+    const BatchJobs jp{d, out_kind, j, band, all, zero ? 1 : 0};
     const unsigned N = (unsigned)n;
-    const unsigned hgrid = (unsigned)std::max<u64>(1, std::min<u64>((max_ndet + 255) / 256, (u64)num_cu * 8));
-    const u64 nch = select_chunks(max_ndet);
-    // the dense pass: the binade of the M-th |c|, then every entry at or above
-    // it compacted into the candidate list by rank (the accumulator zeroed)
-    hipLaunchKernelGGL(k_bsel_init, dim3(1, N), dim3(256), 0, st, d, 0, all);
-    hipLaunchKernelGGL(k_bsel_hist_dense, dim3(hgrid, N), dim3(256), 0, st, d, 0);
-    hipLaunchKernelGGL(k_bsel_pick, dim3(1, N), dim3(PICK_T), 0, st, d, 0, 0);
-    hipLaunchKernelGGL(k_bsel_cand_bound, dim3(1, N), dim3(64), 0, st, d, band);
-    hipLaunchKernelGGL(k_bcompact_count_dense, dim3((unsigned)nch, N), dim3(CBLOCK), 0, st, d);
-    bscan_u64(st, d_scan_dense, n, nch);
-    if (zero) hipLaunchKernelGGL(k_bcompact_write_dense<true>, dim3((unsigned)nch, N), dim3(CBLOCK), 0, st, d);
-    else hipLaunchKernelGGL(k_bcompact_write_dense<false>, dim3((unsigned)nch, N), dim3(CBLOCK), 0, st, d);
-    // the full selection on the candidate list
-    hipLaunchKernelGGL(k_bsel_init, dim3(1, N), dim3(256), 0, st, d, 1, all);
-    for (int L = 0; L < max_ndig; ++L) {
-        hipLaunchKernelGGL(k_bsel_hist_list, dim3(hgrid, N), dim3(256), 0, st, d, L);
-        hipLaunchKernelGGL(k_bsel_pick, dim3(1, N), dim3(PICK_T), 0, st, d, 1, L);
+    if (max_ndet <= (u64)SEL_ONE) {
+        hipLaunchKernelGGL(k_sel_one<BatchJobs>, dim3(1, N), dim3(ONE_BLOCK), 0, st, jp);
+    } else {
+        dense_seg_prepare(st, jp, N, num_cu, max_ndet, max_ndig, all == 0);
+        hipLaunchKernelGGL(k_sel_write<BatchJobs>, dim3(seg_grid(num_cu, select_chunks(max_ndet)), N), dim3(256), 0,
+                           st, jp);
     }
-    hipLaunchKernelGGL(k_bsel_min_list, dim3(hgrid, N), dim3(256), 0, st, d);
-    if (band) {
-        hipLaunchKernelGGL(k_bsel_thr, dim3(1, N), dim3(64), 0, st, d);
-        hipLaunchKernelGGL(k_bsel_count_thr_list, dim3(hgrid, N), dim3(256), 0, st, d);
-        hipLaunchKernelGGL(k_bsel_mode, dim3(1, N), dim3(64), 0, st, d);
-    }
-    hipLaunchKernelGGL(k_bcompact_count_list, dim3((unsigned)nch, N), dim3(CBLOCK), 0, st, d);
-    bscan_u64(st, d_scan_list, n, nch);
-    hipLaunchKernelGGL(k_bcopy_count, dim3(1, N), dim3(64), 0, st, d, out_kind, j);
-    hipLaunchKernelGGL(k_bcompact_write_list, dim3((unsigned)nch, N), dim3(CBLOCK), 0, st, d, out_kind, j);
     SFCI_CHECK_HIP(hipGetLastError());
 }

@@ -43,26 +43,45 @@ struct RowTileGradWs {
     void release() { desc.release(); prefix.release(); counter.release(); scratch.release(); }
 };
 
-// Top-M selection state (device resident): a radix select over the 128-bit
-// key K = (bits(|c|) << rank_bits) | (N_det - 1 - rank), 11-bit digits from
-// the top, so that larger K = larger |c|, then lower rank.
+// Top-M selection (select.hip).
+constexpr int SEL_ONE = 16384;             // sources of at most this many entries: one workgroup, one launch
+constexpr unsigned SEL_SMALL = 2048;       // entries of the picked bin among which the M-th key is found by counting
+constexpr int SEL_TICKETS = 16;            // a ticket per kernel of a selection that ends in a last workgroup
+constexpr int SEL_DENSE_SHIFT = 12;        // slots per segment of a dense source (log2)
+constexpr u64 SEL_SEG_BYTES = 1ull << 30;  // a single sigma's candidate segments may take this much
+
+// Selection state (device resident): a radix select over the 128-bit key
+// K = (bits(|c|) << rank_bits) | (N_det - 1 - rank), 11-bit digits from the
+// top, so that larger K = larger |c|, then lower rank.
 struct SelState {
     u64 need;       // entries still to take inside the current prefix
     u64 pre_hi, pre_lo;
     int level;      // digits fixed so far
-    int done;       // selection decided
+    int done;       // the M-th key is known, or not needed
     int take_all;   // keep every nonzero entry
-    int pad;
-    u64 total;      // nonzero candidates (filled at level 0)
-    u64 count_out;  // entries written by the compaction
+    int use_thr;    // keep every |c| >= thr (they are at most M + SFCI_TIE_SLACK)
+    u64 total;      // nonzero entries of the source
+    u64 count_out;  // entries kept
     u64 cmin;       // bits of the smallest |c| among the M selected
+    u64 key_hi, key_lo;  // the M-th key
     u64 thr_bits;   // bits of cmin * (1 - 2^-36)
-    u64 count_thr;  // nonzero candidates with |c| >= that
-    int use_thr;    // keep every |c| >= thr (count_thr <= M + SFCI_TIE_SLACK)
-    int cand;       // compaction predicate: |c| >= cand_bits instead of the selection
-    u64 cand_bits;  // dense sources: bits of the candidate bound (binade of the M-th |c|, less 2^-36)
-    u64 count_cand; // candidates compacted into the list
+    u64 count_thr;  // entries with |c| >= that
+    u64 cand_bits;  // bits of the bound on a dense source's candidates (binade of the M-th |c|, less 2^-36)
+    u64 count_cand; // number of candidates where they form one list
+    u64 bin;        // entries that share the current prefix
+    unsigned small_n, pad;
+    unsigned ticket[SEL_TICKETS];
     u64 hist[2048];
+    u64 small_hi[SEL_SMALL], small_lo[SEL_SMALL];  // the picked bin's keys
+};
+
+// What a selection reads: the dense accumulator or a list.
+struct CandSrc {
+    const double* dense;  // if non-null: D[0..Ndet)
+    const u64* lrank;     // else list
+    const double* lval;
+    const u64* lcount;    // device scalar
+    u64 lcap;
 };
 
 struct KeyGeom {
@@ -106,7 +125,9 @@ struct sfci_problem {
     DevBuf ws_sel, ws_cnt, ws_scan, ws_scan2, ws_scalar, ws_red;
     DevBuf ws_tup_k, ws_tup_v, ws_tup_k2, ws_tup_v2, ws_seg_v, ws_seg_f, ws_src_cnt, ws_src_off, ws_hist;
     DevBuf ws_list_r, ws_list_a, ws_prod;
-    DevBuf ws_sel2, ws_cand_r, ws_cand_a;  // top-M of a dense source: candidate list and its selection state
+    DevBuf ws_cand_r, ws_cand_a;  // top-M of a dense source: its candidates
+    int sel_mode = 0;             // what select_prepare left for select_write (select.hip)
+    CandSrc sel_src{};
     DevBuf ws_lz[8];
     DevBuf ws_rt_rows, ws_rt_beta, ws_rt_nbr, ws_rt_desc;
     DevBuf ws_ab_rc, ws_ab_cr, ws_ab_off, ws_ab_it;  // alpha-beta item lists (rows of several tiles)
@@ -270,19 +291,9 @@ void launch_symmetrise(sfci_problem* P, const double* Rh, const double* Rg, doub
 void launch_fill_f64(double* p, u64 n, double val, hipStream_t s);
 void launch_fill_u64(u64* p, u64 n, u64 val, hipStream_t s);
 // exclusive scan of n u64 counts into out (may alias); total -> *total_dev (device scalar).
-// bsum_ws (may be NULL: the problem's buffer) holds scan_block_sums(n) u64.
-void exclusive_scan_u64(sfci_problem* P, const u64* in, u64* out, u64 n, u64* total_dev, u64* bsum_ws = nullptr);
-u64 scan_block_sums(u64 n);
+void exclusive_scan_u64(sfci_problem* P, const u64* in, u64* out, u64 n, u64* total_dev);
 
 // ---- selection (select.hip) ----
-// Source of candidates: either a dense array (index = rank) or a list.
-struct CandSrc {
-    const double* dense;  // if non-null: D[0..Ndet)
-    const u64* lrank;     // else list
-    const double* lval;
-    const u64* lcount;    // device scalar
-    u64 lcap;
-};
 // ---- batched iteration steps: one launch serves every instance ----
 // One instance of a batch, in a device array indexed by blockIdx.y: its basis
 // vectors, dense accumulator, block matrices, and selection workspaces.
@@ -301,12 +312,11 @@ struct BInst {
     int* blk;
     int* status;
     double* red;              // reduction partials, bstep_red_doubles(n_L)
-    SelState* st;             // selection on the dense accumulator, then on the candidate list
-    SelState* st2;
-    u64* cr;                  // candidate list (N_det capacity)
+    SelState* st;             // selection
+    u64* cr;                  // candidate segments (N_det capacity)
     double* ca;
-    u64* cnt;                 // per-chunk counts (select chunks of N_det) and their scan's block sums
-    u64* bsum;
+    u64* cnt;                 // per segment (select chunks of N_det): kept entries and their scan,
+    u32* ccnt;                // and candidates
     u64* psi_r;               // the final Psi of the last block
     double* psi_a;
     u64* psi_n;
@@ -327,21 +337,10 @@ void bstep_normalise(hipStream_t st, const BInst* d, int n, int out_kind, int j,
 void bstep_fill_zero(hipStream_t st, const BInst* d, int n, u64 max_ndet);
 void bstep_geneig(hipStream_t st, const BInst* d, int n, int nL);
 void bstep_inc_blk(hipStream_t st, const BInst* d, int n);
-// Exclusive scans of u64 counts, one per job: out[i] = sum in[0..i), *total = sum (may be null).
-struct BScanJob {
-    const u64* in;
-    u64* out;
-    u64 n;
-    u64* bsum;  // scan_block_sums(n) words
-    u64* total;
-};
-void bscan_u64(hipStream_t st, const BScanJob* d_jobs, int n_jobs, u64 max_n);
 // select_topm of every instance's dense accumulator (zeroed on the way unless
-// !zero) into the out_kind vector, keeping M entries (all != 0: every nonzero entry);
-// scan jobs: the accumulator's chunk counts (total to st->count_cand) and the
-// candidate list's (total to st2->count_out).
+// !zero) into the out_kind vector, keeping M entries (all != 0: every nonzero entry).
 void bstep_select(hipStream_t st, const BInst* d, int n, int out_kind, int j, u64 max_ndet, int num_cu, int band,
-                  int max_ndig, const BScanJob* d_scan_dense, const BScanJob* d_scan_list, int all, bool zero = true);
+                  int max_ndig, int all, bool zero = true);
 
 // Select the M largest (|c|, then lower rank) nonzero candidates and write them
 // by ascending rank to (out_rank, out_amp); *out_count_dev receives the count.
@@ -351,18 +350,21 @@ void select_topm(sfci_problem* P, const CandSrc& src, u64 M, u64* out_rank, doub
                  bool zero_dense);
 // Two-phase form: prepare (selection levels + counts; the count goes to
 // *count_dev), then write.  The state lives in the problem's workspace, so no
-// other selection may run in between.
+// other selection may run in between.  Truncating a dense source (M neither 0
+// nor UINT64_MAX) clears it in the first phase already.
 void select_prepare(sfci_problem* P, const CandSrc& src, u64 M, u64* count_dev);
 void select_write(sfci_problem* P, const CandSrc& src, u64* out_rank, double* out_amp, bool zero_dense);
 // The same two phases on a candidate list with caller-given working memory
-// (no allocation): the state, select_chunks(lcap) per-chunk counts and
-// scan_block_sums(select_chunks(lcap)) scan sums.
+// (no allocation): the state and select_segments(lcap) offsets.
 struct SelWs {
     SelState* st;
-    u64* cnt;
-    u64* bsum;
+    u64* off;
 };
-u64 select_chunks(u64 n_upper);
+// Whether select_topm of the dense accumulator takes no more memory than the two-phase form.
+bool select_one_step(const sfci_problem* P, u64 M);
+u64 select_chunks(u64 n_upper);  // of a dense source of n_upper slots
+int select_shift(u64 lcap);      // log2 of a list's entries per segment
+u64 select_segments(u64 lcap);
 void select_prepare_ws(sfci_problem* P, const CandSrc& src, u64 M, u64* count_dev, const SelWs& ws);
 void select_write_ws(sfci_problem* P, const CandSrc& src, u64* out_rank, double* out_amp, const SelWs& ws);
 

@@ -126,24 +126,6 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_down(const u64* in, u64 n, 
     scan_down_body(in, n, boff, out, blockIdx.x);
 }
 
-// One scan per job (blockIdx.y); blocks past a job's own size return at once.
-__global__ __launch_bounds__(SCAN_BLOCK) void k_bscan_reduce(const BScanJob* __restrict__ jobs) {
-    const BScanJob J = jobs[blockIdx.y];
-    if ((u64)blockIdx.x * SCAN_TILE >= (J.n ? J.n : 1)) return;  // n = 0: block 0 writes a zero sum
-    scan_reduce_body(J.in, J.n, J.bsum, blockIdx.x);
-}
-
-__global__ __launch_bounds__(TOP_BLOCK) void k_bscan_top(const BScanJob* __restrict__ jobs) {
-    const BScanJob J = jobs[blockIdx.y];
-    scan_top_body(J.bsum, (J.n + SCAN_TILE - 1) / SCAN_TILE, J.total);
-}
-
-__global__ __launch_bounds__(SCAN_BLOCK) void k_bscan_down(const BScanJob* __restrict__ jobs) {
-    const BScanJob J = jobs[blockIdx.y];
-    if ((u64)blockIdx.x * SCAN_TILE >= J.n) return;
-    scan_down_body(J.in, J.n, J.bsum, J.out, blockIdx.x);
-}
-
 unsigned grid1d(u64 n, u64 per, u64 cap = 65536) {
     u64 g = (n + per - 1) / per;
     if (g < 1) g = 1;
@@ -165,21 +147,11 @@ void launch_fill_u64(u64* p, u64 n, u64 val, hipStream_t s) {
     SFCI_CHECK_HIP(hipGetLastError());
 }
 
-u64 scan_block_sums(u64 n) { return std::max<u64>(1, (n + SCAN_TILE - 1) / SCAN_TILE); }
-
-void exclusive_scan_u64(sfci_problem* P, const u64* in, u64* out, u64 n, u64* total_dev, u64* bsum_ws) {
-    const u64 nb = scan_block_sums(n);
-    u64* bsum = bsum_ws ? bsum_ws : (u64*)P->ws_scan.get(nb * sizeof(u64));
+void exclusive_scan_u64(sfci_problem* P, const u64* in, u64* out, u64 n, u64* total_dev) {
+    const u64 nb = std::max<u64>(1, (n + SCAN_TILE - 1) / SCAN_TILE);
+    u64* bsum = (u64*)P->ws_scan.get(nb * sizeof(u64));
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, P->stream, in, n, bsum);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(TOP_BLOCK), 0, P->stream, bsum, nb, total_dev);
     hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, P->stream, in, n, bsum, out);
-    SFCI_CHECK_HIP(hipGetLastError());
-}
-
-void bscan_u64(hipStream_t st, const BScanJob* d_jobs, int n_jobs, u64 max_n) {
-    const u64 nb = scan_block_sums(max_n);
-    hipLaunchKernelGGL(k_bscan_reduce, dim3((unsigned)nb, (unsigned)n_jobs), dim3(SCAN_BLOCK), 0, st, d_jobs);
-    hipLaunchKernelGGL(k_bscan_top, dim3(1, (unsigned)n_jobs), dim3(TOP_BLOCK), 0, st, d_jobs);
-    hipLaunchKernelGGL(k_bscan_down, dim3((unsigned)nb, (unsigned)n_jobs), dim3(SCAN_BLOCK), 0, st, d_jobs);
     SFCI_CHECK_HIP(hipGetLastError());
 }
