@@ -4,13 +4,16 @@
 // Standard partitioning with the diagonal of H as the zeroth-order operator:
 //   E0 = <Psi|H|Psi> / <Psi|Psi>,
 //   E2 = [ sum over k outside supp(Psi) of (H Psi)_k^2 / (E0 - H_kk) ] / <Psi|Psi>.
-// The same sigma machinery produces H Psi as a rank-sorted list; one pass
-// forms E0's products over supp(Psi) (each Psi rank searched in H Psi), one
-// the external terms (each H Psi rank searched in Psi) with H_kk in the
-// diagonal element's fixed addition order.  The
-// deterministic option (sort-path sigma, every sum strictly in rank order)
-// gives the bits of a sequential evaluation; otherwise the dense tile kernel
-// and tree reductions.
+// Two forms:
+//   * deterministic, or no room for the N_det array: the sort path gives H Psi
+//     as a rank-sorted list; one pass forms E0's products over supp(Psi) (each
+//     Psi rank searched in H Psi), one the external terms (each H Psi rank
+//     searched in Psi) with H_kk in the diagonal element's fixed addition
+//     order; deterministic sums run strictly in rank order (the bits of a
+//     sequential evaluation);
+//   * otherwise H Psi stays in the dense accumulator: E0 is a gather at
+//     supp(Psi), those slots are cleared, and every slot still nonzero is an
+//     external determinant, taken a target row at a time (k_pt2_rows).
 #include <algorithm>
 
 #include "sfci_internal.h"
@@ -75,6 +78,118 @@ __global__ __launch_bounds__(PB) void k_pt2_outer(SpaceDev sp, Ints I, const u64
     }
     for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off);
     if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(n_ext, cnt);
+}
+
+// The beta strings, by rank.
+__global__ __launch_bounds__(PB) void k_pt2_beta(SpaceDev sp, const u64* __restrict__ binom, u32* __restrict__ bits) {
+    __shared__ BinomLds B;
+    load_binom(B, binom);
+    __syncthreads();
+    for (u64 r = (u64)blockIdx.x * PB + threadIdx.x; r < sp.Nb; r += (u64)gridDim.x * PB)
+        bits[r] = str_unrank(r, sp.nb, sp.n, B);
+}
+
+// The external terms straight from the accumulator, a workgroup per target
+// alpha row, which clears the slots it reads.  H_kk is summed in
+// diag_element's order, so its bits (and E0 - H_kk where the two nearly meet)
+// are the list form's: the alpha parts are formed once per row, the pair terms
+// come from LDS.  Bound by the adds and LDS reads of H_kk; the list form
+// (compaction, a binary search in Psi, two unranks and ~28 gathers of
+// integrals per entry) took 1040 us where this takes 248 us (20 orbitals,
+// 2.0e7 external determinants).
+__global__ __launch_bounds__(PB) void k_pt2_rows(SpaceDev sp, Ints I, const u64* __restrict__ binom,
+                                                 double* __restrict__ D, const u32* __restrict__ bits,
+                                                 const double* __restrict__ e0p, double* __restrict__ part,
+                                                 unsigned long long* __restrict__ n_ext) {
+    __shared__ BinomLds B;
+    __shared__ double K2[32 * 32], J[32 * 32], hd[32], ka[32 * 31 / 2], ea, wsum[PB / 64];
+    __shared__ uint8_t occ[32];
+    load_binom(B, binom);
+    const int n = sp.n, na = sp.na;
+    for (int t = threadIdx.x; t < n * n; t += PB) {
+        const int p = t / n, q = t - p * n;
+        J[t] = I.G(p, p, q, q);
+        K2[t] = (I.G(p, p, q, q) - I.G(p, q, q, p));
+    }
+    if (threadIdx.x < (unsigned)n) hd[threadIdx.x] = I.H(threadIdx.x, threadIdx.x);
+    __syncthreads();
+    const double E0 = *e0p;
+    const int lane = threadIdx.x & 63, npair = na * (na - 1) / 2;
+    unsigned long long cnt = 0;
+    double sum = 0.0;
+    for (u64 row = blockIdx.x; row < sp.Na; row += gridDim.x) {
+        const u32 A = str_unrank_wave(row, na, n, B);
+        __syncthreads();  // the previous row's tables are no longer read
+        if (threadIdx.x < (unsigned)n && ((A >> threadIdx.x) & 1u))
+            occ[__popc(A & ((1u << threadIdx.x) - 1u))] = (uint8_t)threadIdx.x;
+        if (threadIdx.x == PB - 1) {
+            double e = 0.0;
+            for (u32 m = A; m; m &= m - 1u) e += hd[__builtin_ctz(m)];
+            ea = e;
+        }
+        __syncthreads();
+        for (int t = threadIdx.x; t < npair; t += PB) {
+            const uint16_t pr = decode_pair(t, na);  // lexicographic: diag_element's order
+            ka[t] = K2[occ[pr & 255] * n + occ[pr >> 8]];
+        }
+        __syncthreads();
+        double* const Dr = D + row * sp.Nb;
+        constexpr int U = 4;
+        for (u64 x0 = threadIdx.x; x0 < sp.Nb; x0 += (u64)PB * U) {
+            double y[U];
+            u32 bt[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const u64 x = x0 + (u64)u * PB;
+                y[u] = x < sp.Nb ? Dr[x] : 0.0;
+                bt[u] = x < sp.Nb ? bits[x] : 0u;
+            }
+            double e[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                e[u] = ea;
+                for (u32 m = bt[u]; m; m &= m - 1u) e[u] += hd[__builtin_ctz(m)];
+            }
+            for (int t = 0; t < npair; ++t) {
+                const double k = ka[t];
+#pragma unroll
+                for (int u = 0; u < U; ++u) e[u] += k;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                for (u32 m = bt[u]; m; m &= m - 1u) {
+                    const double* Kp = K2 + __builtin_ctz(m) * n;
+                    for (u32 m2 = m & (m - 1u); m2; m2 &= m2 - 1u) e[u] += Kp[__builtin_ctz(m2)];
+                }
+            for (int t = 0; t < na; ++t) {
+                const double* Jp = J + occ[t] * n;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    for (u32 m = bt[u]; m; m &= m - 1u) e[u] += Jp[__builtin_ctz(m)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (y[u] == 0.0) continue;
+                Dr[x0 + (u64)u * PB] = 0.0;
+                sum += (y[u] * y[u]) / (E0 - e[u]);
+                ++cnt;
+            }
+        }
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+        cnt += __shfl_xor(cnt, off);
+        sum += __shfl_xor(sum, off);
+    }
+    if (lane == 0) {
+        if (cnt) atomicAdd(n_ext, cnt);
+        wsum[threadIdx.x >> 6] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < PB / 64; ++w) s += wsum[w];
+        part[blockIdx.x] = s;
+    }
 }
 
 unsigned grid_of(u64 n) {
@@ -156,13 +271,20 @@ extern "C" sfci_status sfci_energy_gradients(sfci_problem* P, const sfci_svec* p
         launch_fill_u64(sc, 16, 0, P->stream);
         launch_set_u64(P, sc, psi->nnz);
         const SigmaLaunch sl{psi->rank, psi->amp, sc, psi->nnz};
-        u64* yr;
-        double* ya;
-        sigma_full_list(P, sl, det, sc + 1, &yr, &ya, sc + 2);
-        double* prod = (double*)P->ws_prod.get(std::max<u64>(1, psi->nnz) * sizeof(double));
-        hipLaunchKernelGGL(k_pt2_inner, dim3(grid_of(psi->nnz)), dim3(PB), 0, P->stream, yr, ya, sc + 2, psi->rank,
-                           psi->amp, (u64)psi->nnz, prod);
-        launch_sum(P, prod, sc, psi->nnz, sd + 0, det);
+        if (!det && ensure_dense(P)) {
+            // H Psi in the accumulator, gathered at supp(Psi)
+            dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)(sc + 1));
+            launch_dot_dense(P, psi->rank, psi->amp, sc, psi->nnz, P->d_D, sd + 0, nullptr, false);
+            launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
+        } else {
+            u64* yr;
+            double* ya;
+            sigma_full_list(P, sl, det, sc + 1, &yr, &ya, sc + 2);
+            double* prod = (double*)P->ws_prod.get(std::max<u64>(1, psi->nnz) * sizeof(double));
+            hipLaunchKernelGGL(k_pt2_inner, dim3(grid_of(psi->nnz)), dim3(PB), 0, P->stream, yr, ya, sc + 2,
+                               psi->rank, psi->amp, (u64)psi->nnz, prod);
+            launch_sum(P, prod, sc, psi->nnz, sd + 0, det);
+        }
         launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, det);
         hipLaunchKernelGGL(k_pt2_e0, dim3(1), dim3(64), 0, P->stream, sd + 0, sd + 1, sd + 2);
         SFCI_CHECK_HIP(hipGetLastError());
@@ -192,19 +314,37 @@ extern "C" sfci_status sfci_pt2(sfci_problem* P, const sfci_svec* psi, int32_t d
         launch_fill_u64(sc, 16, 0, P->stream);
         launch_set_u64(P, sc, psi->nnz);
         const SigmaLaunch sl{psi->rank, psi->amp, sc, psi->nnz};
-        u64* yr;
-        double* ya;
-        const u64 ny = sigma_full_list(P, sl, det, sc + 1, &yr, &ya, sc + 2);
-        double* prod = (double*)P->ws_prod.get(std::max<u64>(std::max<u64>(1, ny), psi->nnz) * sizeof(double));
-        hipLaunchKernelGGL(k_pt2_inner, dim3(grid_of(psi->nnz)), dim3(PB), 0, P->stream, yr, ya, sc + 2, psi->rank,
-                           psi->amp, (u64)psi->nnz, prod);
-        launch_sum(P, prod, sc, psi->nnz, sd + 0, det);
-        launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, det);
-        hipLaunchKernelGGL(k_pt2_e0, dim3(1), dim3(64), 0, P->stream, sd + 0, sd + 1, sd + 2);
-        hipLaunchKernelGGL(k_pt2_outer, dim3(grid_of(ny)), dim3(PB), 0, P->stream,
-                           SpaceDev{P->n, P->na, P->nb, P->Na, P->Nb}, Ints{P->d_h, P->d_g, P->n}, P->d_binom, yr,
-                           ya, sc + 2, psi->rank, (u64)psi->nnz, sd + 2, prod, (unsigned long long*)(sc + 3));
-        launch_sum(P, prod, sc + 2, std::max<u64>(1, ny), sd + 3, det);
+        const SpaceDev sp{P->n, P->na, P->nb, P->Na, P->Nb};
+        const Ints I{P->d_h, P->d_g, P->n};
+        if (!det && ensure_dense(P)) {
+            dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)(sc + 1));
+            launch_dot_dense(P, psi->rank, psi->amp, sc, psi->nnz, P->d_D, sd + 0, nullptr, false);
+            launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, false);
+            hipLaunchKernelGGL(k_pt2_e0, dim3(1), dim3(64), 0, P->stream, sd + 0, sd + 1, sd + 2);
+            launch_scatter_zero(P, P->d_D, psi->rank, sc, psi->nnz);
+            // a partial sum per workgroup, then the N_beta strings
+            const unsigned g = (unsigned)std::min<u64>(P->Na, (u64)P->num_cu * 8);
+            double* part = (double*)P->ws_prod.get(g * sizeof(double) + P->Nb * sizeof(u32));
+            u32* bits = (u32*)(part + g);
+            hipLaunchKernelGGL(k_pt2_beta, dim3(grid_of(P->Nb)), dim3(PB), 0, P->stream, sp, P->d_binom, bits);
+            hipLaunchKernelGGL(k_pt2_rows, dim3(g), dim3(PB), 0, P->stream, sp, I, P->d_binom, P->d_D, bits, sd + 2,
+                               part, (unsigned long long*)(sc + 3));
+            launch_set_u64(P, sc + 2, g);
+            launch_sum(P, part, sc + 2, g, sd + 3, false);
+        } else {
+            u64* yr;
+            double* ya;
+            const u64 ny = sigma_full_list(P, sl, det, sc + 1, &yr, &ya, sc + 2);
+            double* prod = (double*)P->ws_prod.get(std::max<u64>(std::max<u64>(1, ny), psi->nnz) * sizeof(double));
+            hipLaunchKernelGGL(k_pt2_inner, dim3(grid_of(psi->nnz)), dim3(PB), 0, P->stream, yr, ya, sc + 2,
+                               psi->rank, psi->amp, (u64)psi->nnz, prod);
+            launch_sum(P, prod, sc, psi->nnz, sd + 0, det);
+            launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, det);
+            hipLaunchKernelGGL(k_pt2_e0, dim3(1), dim3(64), 0, P->stream, sd + 0, sd + 1, sd + 2);
+            hipLaunchKernelGGL(k_pt2_outer, dim3(grid_of(ny)), dim3(PB), 0, P->stream, sp, I, P->d_binom, yr, ya,
+                               sc + 2, psi->rank, (u64)psi->nnz, sd + 2, prod, (unsigned long long*)(sc + 3));
+            launch_sum(P, prod, sc + 2, std::max<u64>(1, ny), sd + 3, det);
+        }
         SFCI_CHECK_HIP(hipGetLastError());
         double hd[4];
         u64 hc[4];
