@@ -86,6 +86,10 @@ __global__ void k_validate(const u64* __restrict__ r, u64 n, u64 ndet, int* __re
 // The fast-mode reductions keep their partial sums at the front of ws_red.
 constexpr u64 RAW_PAD = 2048;
 
+__global__ void k_checked_len(u64* nnz, u64 n, const int* flags) {
+    if (threadIdx.x == 0) *nnz = (flags[0] || flags[1]) ? 0 : n;
+}
+
 __global__ void k_set_u64(u64* p, u64 v) {
     if (threadIdx.x == 0) *p = v;
 }
@@ -118,6 +122,20 @@ u64 read_u64(sfci_problem* P, const u64* d) {
 
 }  // namespace
 
+// flags[0]: a rank >= N_det, flags[1]: ranks not strictly ascending.
+static void throw_bad_vec(const int* flags) {
+    if (flags[0]) throw sfci_error(SFCI_E_RANGE, "input rank >= N_det");
+    if (flags[1]) throw sfci_error(SFCI_E_DUP, "input ranks not strictly ascending");
+}
+
+// The check on the device alone: flags (zero before) and the length *nnz, 0
+// for a bad vector, so that what follows on the stream never reads its ranks.
+static void launch_check_vec(sfci_problem* P, const u64* r, u64 n, u64* nnz, int* flags) {
+    if (n) hipLaunchKernelGGL(k_validate, dim3(g1(n)), dim3(256), 0, P->stream, r, n, P->Ndet, flags);
+    hipLaunchKernelGGL(k_checked_len, dim3(1), dim3(64), 0, P->stream, nnz, n, (const int*)flags);
+    SFCI_CHECK_HIP(hipGetLastError());
+}
+
 void validate_vec(sfci_problem* P, const u64* r, u64 n) {
     if (n == 0) return;
     int* flags = (int*)P->ws_scalar.get(64);
@@ -126,9 +144,18 @@ void validate_vec(sfci_problem* P, const u64* r, u64 n) {
     int hf[2] = {0, 0};
     SFCI_CHECK_HIP(hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, P->stream));
     sync(P);
-    if (hf[0]) throw sfci_error(SFCI_E_RANGE, "input rank >= N_det");
-    if (hf[1]) throw sfci_error(SFCI_E_DUP, "input ranks not strictly ascending");
+    throw_bad_vec(hf);
 }
+
+namespace {
+// The two events around a call, kept by the problem.
+struct CallEvents {
+    explicit CallEvents(sfci_problem* P) {
+        for (hipEvent_t& e : P->ev)
+            if (!e) SFCI_CHECK_HIP(hipEventCreate(&e));
+    }
+};
+}  // namespace
 
 bool ensure_dense(sfci_problem* P) {
     if (P->dense_state == 0) {
@@ -153,9 +180,13 @@ bool ensure_dense(sfci_problem* P) {
 }
 
 // Dense-mode sigma into P->d_D: the target-owned tile kernel unless the
-// caller asks for the one-atomic-per-term kernel (or the tiles do not fit).
+// caller asks for the one-atomic-per-term kernel (or the tiles do not fit), or
+// leaves the choice open and the space is small enough for H as a table.
 void dense_sigma(sfci_problem* P, const SigmaLaunch& sl, int dedup, unsigned long long* emitted, double eps) {
-    if (dedup != SFCI_DEDUP_DENSE_ATOMIC && rowtile_available(P)) {
+    if (dedup == SFCI_DEDUP_AUTO && P->excite_eps == 0.0 && small_h_ready(P)) {
+        launch_small_load(P, sl.v_rank, sl.v_amp, sl.v_nnz, 0, false, nullptr, nullptr, (u64*)emitted, nullptr);
+        launch_small_sigma(P, eps);
+    } else if (dedup != SFCI_DEDUP_DENSE_ATOMIC && rowtile_available(P)) {
         launch_sigma_rowtile(P, sl, P->d_D, emitted, eps);
     } else {
         launch_sigma_dense(P, sl, P->d_D, emitted);
@@ -252,7 +283,10 @@ sfci_status sfci_problem_destroy(sfci_problem* P) {
         if (P->d_binom) (void)hipFree(P->d_binom);
         if (P->d_D) (void)hipFree(P->d_D);
     }
+    for (hipEvent_t e : P->ev)
+        if (e) (void)hipEventDestroy(e);
     rowtile_release(P);
+    for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd}) b->release();
     DevBuf* bufs[] = {&P->ws_sel,   &P->ws_cnt,   &P->ws_scan,  &P->ws_scan2,  &P->ws_scalar, &P->ws_red,
                       &P->ws_tup_k, &P->ws_tup_v, &P->ws_tup_k2, &P->ws_tup_v2, &P->ws_seg_v, &P->ws_seg_f,
                       &P->ws_src_cnt, &P->ws_src_off, &P->ws_hist, &P->ws_list_r, &P->ws_list_a, &P->ws_prod,
@@ -314,27 +348,30 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     if (opts->dedup < 0 || opts->dedup > 3) return (sfci_status)sfci_set_error(SFCI_E_ARG, "bad dedup mode");
     if (!(opts->screen_eps >= 0.0) || !(opts->excite_eps >= 0.0))
         return (sfci_status)sfci_set_error(SFCI_E_ARG, "screen_eps and excite_eps must be >= 0");
-    validate_vec(P, v->rank, v->nnz);
-    P->tie_band = opts->tie_band ? 1 : 0;
-    P->excite_eps = opts->excite_eps;
-    hipEvent_t e0, e1;
-    SFCI_CHECK_HIP(hipEventCreate(&e0));
-    SFCI_CHECK_HIP(hipEventCreate(&e1));
-    SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
-    u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));  // [0] nnz(v) [1] emitted [2] count [3] list count
-    launch_fill_u64(scal, 8, 0, P->stream);
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, P->stream, scal, (u64)v->nnz);
-    SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
     const u64 tps = terms_per_source(P->n, P->na, P->nb);
     bool use_sort = opts->deterministic || opts->dedup == SFCI_DEDUP_SORT;
     bool list_tiles = false;  // no N_det array, fast: the tile kernel's slices may serve
     if (!use_sort && !ensure_dense(P)) {
-        if (opts->dedup == SFCI_DEDUP_DENSE || opts->dedup == SFCI_DEDUP_DENSE_ATOMIC)
+        if (opts->dedup == SFCI_DEDUP_DENSE || opts->dedup == SFCI_DEDUP_DENSE_ATOMIC) {
+            validate_vec(P, v->rank, v->nnz);
             return (sfci_status)sfci_set_error(SFCI_E_UNSUPPORTED, "dense accumulator does not fit on the device");
+        }
         use_sort = true;
         list_tiles = true;
     }
+    if (use_sort) validate_vec(P, v->rank, v->nnz);
+    P->tie_band = opts->tie_band ? 1 : 0;
+    P->excite_eps = opts->excite_eps;
+    CallEvents ev(P);
+    const hipEvent_t e0 = P->ev[0], e1 = P->ev[1];
+    SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
+    // [0] nnz(v) [1] emitted [2] count [3] list count [4] validation flags
+    u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));
+    const bool small = !use_sort && opts->dedup == SFCI_DEDUP_AUTO && opts->excite_eps == 0.0 && small_h_ready(P);
+    launch_fill_u64(scal, 8, 0, P->stream);
+    SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
     if (use_sort) {
+        launch_set_u64(P, scal, v->nnz);
         // alpha-range passes (sort path, or tile-kernel slices in fast mode)
         // into a running top-M candidate list, no N_det array and no
         // full-length sigma list
@@ -357,24 +394,31 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
             stats->terms_emitted = emitted;
             stats->candidates = distinct;
         }
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
         return rc;
     }
+    // the input is checked on the device, a bad vector counts as empty there, and the flags come back with
+    // the results
     CandSrc src{};
-    dense_sigma(P, sl, opts->dedup, (unsigned long long*)&scal[1], opts->screen_eps);
+    if (small) {
+        launch_small_load(P, v->rank, v->amp, nullptr, v->nnz, true, scal, nullptr, &scal[1], (int*)&scal[4]);
+        launch_small_sigma(P, opts->screen_eps);
+    } else {
+        launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
+        dense_sigma(P, sl, opts->dedup, (unsigned long long*)&scal[1], opts->screen_eps);
+    }
     src.dense = P->d_D;
     // an output that holds whatever may be kept is written without waiting for the count
     const u64 most = opts->M >= P->Ndet ? P->Ndet : std::min<u64>(P->Ndet, opts->M + tie_extra(P));
     const bool direct = out->capacity >= most && out->rank && out->amp && select_one_step(P, opts->M);
     if (direct) select_topm(P, src, opts->M, out->rank, out->amp, &scal[2], true);
     else select_prepare(P, src, opts->M, &scal[2]);
-    u64 hs[4];
+    u64 hs[5];
     SelState sst;
     SFCI_CHECK_HIP(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, P->stream));
     SFCI_CHECK_HIP(hipMemcpyAsync(&sst, P->ws_sel.p, offsetof(SelState, ticket), hipMemcpyDeviceToHost, P->stream));
     if (direct) SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
     sync(P);
+    throw_bad_vec((const int*)&hs[4]);
     const u64 need = hs[2];
     sfci_status rc = SFCI_OK;
     out->nnz = need;
@@ -397,8 +441,6 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
         stats->terms_emitted = hs[1];
         stats->candidates = sst.take_all ? sst.count_out : sst.total;
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     return rc;
     SFCI_GUARD_END
 }
@@ -507,9 +549,8 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
     auto W = [&](int j) { return DVec{Wr + (size_t)j * cap, Wa + (size_t)j * cap, sc + j, cap}; };
     EventTimer tsig;
     tsig.on = (stats != nullptr);
-    hipEvent_t e0, e1;
-    SFCI_CHECK_HIP(hipEventCreate(&e0));
-    SFCI_CHECK_HIP(hipEventCreate(&e1));
+    CallEvents ev(P);
+    const hipEvent_t e0 = P->ev[0], e1 = P->ev[1];
     SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
     // Projected roots (excited states, Sec. 4): <Psi_i|Psi_i> and H Psi_i once;
     // per root scalars: [0] q, [1] c or d numerator, [2] c or d.
@@ -569,7 +610,36 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
         ListBasis LB{cap, Wr, Wa, sc, Td, Sd, xd, lam, energies_d, status, nnz_hist};
         lanczos_list(P, o, LB, psi_out, &psi_n, &sigma_calls, tsig, &blocks_run);
     }
-    for (int b = 0; b < (list_mode ? 0 : nblk); ++b) {
+    // a small space in fast mode: H as a table, the rest of a step in one launch
+    const bool small = !list_mode && !det && n_roots == 0 && o->dedup == SFCI_DEDUP_AUTO && o->excite_eps == 0.0 &&
+                       small_h_ready(P);
+    for (int b = 0; b < (small ? nblk : 0); ++b) {
+        double* T = Td + (size_t)b * nL * nL;
+        double* S = Sd + (size_t)b * nL * nL;
+        SmallStep s{Wr, Wa, sc, cap, P->d_D, P->Ndet, (double*)P->sh_vd.p, (const u32*)P->sh_nz.p, T, S, nL,
+                    P->tie_band, o->M, sc + 32, nnz_hist + (size_t)b * nL, P->kg.rank_bits,
+                    2 * P->Ndet <= (u64)SEL_ONE ? 1 : 0};
+        if (b == 0) launch_small_load(P, Wr, Wa, sc, 0, false, nullptr, nnz_hist, sc + 32, nullptr);
+        for (int j = 0; j < nL; ++j) {
+            tsig.begin(P->stream);
+            launch_small_sigma(P, o->screen_eps);
+            tsig.end(P->stream);
+            ++sigma_calls;
+            launch_small_step(P, s, j);
+        }
+        launch_geneig_full(P, nL, T, S, lam, xd, energies_d + b, status);
+        blocks_run = b + 1;
+        const bool last = b + 1 == nblk || halt_after_block(P, o, energies_d, b);
+        s.hist = nnz_hist + (size_t)(b + 1) * nL;  // w_0 of the next block
+        launch_small_psi(P, s, xd, last);
+        if (last) {
+            CandSrc src{};
+            src.dense = P->d_D;
+            select_prepare(P, src, UINT64_MAX, sc + 34);
+            break;
+        }
+    }
+    for (int b = 0; b < (list_mode || small ? 0 : nblk); ++b) {
         double* T = Td + (size_t)b * nL * nL;
         double* S = Sd + (size_t)b * nL * nL;
         for (int j = 0; j < nL; ++j) {
@@ -685,8 +755,6 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
         stats->terms_emitted = emitted;
         stats->blocks_run = blocks_run;
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     if (hstat) return (sfci_status)sfci_set_error(SFCI_E_DEVICE, "generalized eigenproblem: S has no positive direction");
     return rc;
     SFCI_GUARD_END

@@ -273,7 +273,7 @@ extern "C" sfci_status sfci_energy_gradients(sfci_problem* P, const sfci_svec* p
         const SigmaLaunch sl{psi->rank, psi->amp, sc, psi->nnz};
         if (!det && ensure_dense(P)) {
             // H Psi in the accumulator, gathered at supp(Psi)
-            dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)(sc + 1));
+            dense_sigma(P, sl, SFCI_DEDUP_AUTO, (unsigned long long*)(sc + 1));
             launch_dot_dense(P, psi->rank, psi->amp, sc, psi->nnz, P->d_D, sd + 0, nullptr, false);
             launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
         } else {
@@ -317,7 +317,7 @@ extern "C" sfci_status sfci_pt2(sfci_problem* P, const sfci_svec* psi, int32_t d
         const SpaceDev sp{P->n, P->na, P->nb, P->Na, P->Nb};
         const Ints I{P->d_h, P->d_g, P->n};
         if (!det && ensure_dense(P)) {
-            dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)(sc + 1));
+            dense_sigma(P, sl, SFCI_DEDUP_AUTO, (unsigned long long*)(sc + 1));
             launch_dot_dense(P, psi->rank, psi->amp, sc, psi->nnz, P->d_D, sd + 0, nullptr, false);
             launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, false);
             hipLaunchKernelGGL(k_pt2_e0, dim3(1), dim3(64), 0, P->stream, sd + 0, sd + 1, sd + 2);

@@ -800,104 +800,285 @@ __global__ __launch_bounds__(CBLOCK) void k_dense_write(JP jp) {
 // The whole selection of a source of at most SEL_ONE entries by one
 // workgroup, the values in registers: one launch (30 us at 3 136 slots) where
 // the steps above are 7 and the histogram per digit took 24.
-template <class JP>
-__global__ __launch_bounds__(ONE_BLOCK) void k_sel_one(JP jp) {
-    __shared__ KthLds S;
-    __shared__ u64 wsum[ONE_BLOCK / 64];
-    __shared__ unsigned cpos[ONE_ITEMS * (ONE_BLOCK / 64)];
-    __shared__ u64 s_count;
-    const SelJob J = jp(blockIdx.y);
-    const Geo g = J.g;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+struct OneLds {
+    KthLds S;
+    u64 wsum[ONE_BLOCK / 64];
+    double dsum[ONE_BLOCK / 64];
+    unsigned cpos[ONE_ITEMS * (ONE_BLOCK / 64)];
+    u64 count;
+};
+
+__device__ __forceinline__ u64 one_sum(OneLds& S, u64 x) {
+    for (int off = 32; off >= 1; off >>= 1) x += (u64)__shfl_xor((long long)x, off);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) S.wsum[threadIdx.x >> 6] = x;
+    __syncthreads();
+    u64 s = 0;
+    for (int w = 0; w < ONE_BLOCK / 64; ++w) s += S.wsum[w];
+    return s;
+}
+
+struct OneResult {
+    u64 total, count, cmin;
+    bool all;
+};
+
+// v[k]: the value of entry k ONE_BLOCK + threadIdx.x (0 beyond n); on return
+// keep's bit k tells whether it is kept and at[k] where it goes (by entry order).
+template <class Rank>
+__device__ __forceinline__ OneResult one_select(OneLds& L, const double (&v)[ONE_ITEMS], int nk, const Rank& rank_of,
+                                                u64 M, bool band, const Geo& g, unsigned& keep,
+                                                unsigned (&at)[ONE_ITEMS]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int NW = ONE_BLOCK / 64;
-    const u64 n = J.D ? J.Dn : min(*J.n, J.cap);
-    const int nk = (int)((n + ONE_BLOCK - 1) / ONE_BLOCK);
-    auto rank_of = [&](int k) -> u64 {
-        const u64 i = (u64)k * ONE_BLOCK + t;
-        return J.D ? i : J.r[i];
-    };
-    auto block_sum = [&](u64 x) -> u64 {
-        for (int off = 32; off >= 1; off >>= 1) x += (u64)__shfl_xor((long long)x, off);
-        __syncthreads();
-        if (lane == 0) wsum[wave] = x;
-        __syncthreads();
-        u64 s = 0;
-        for (int w = 0; w < NW; ++w) s += wsum[w];
-        return s;
-    };
-    double v[ONE_ITEMS];
+    OneResult R;
     u64 nz = 0;
 #pragma unroll
-    for (int k = 0; k < ONE_ITEMS; ++k) {
-        const u64 i = (u64)k * ONE_BLOCK + t;
-        v[k] = 0.0;
-        if (k < nk && i < n) v[k] = J.D ? J.D[i] : J.a[i];
-        nz += v[k] != 0.0 ? 1 : 0;
-        if (J.Dz && v[k] != 0.0) J.Dz[i] = 0.0;
-    }
-    const u64 total = block_sum(nz);
-    bool all = J.all() || total <= J.M;
-    const bool none = J.M == 0;
+    for (int k = 0; k < ONE_ITEMS; ++k) nz += v[k] != 0.0 ? 1 : 0;
+    R.total = one_sum(L, nz);
+    R.all = M == UINT64_MAX || R.total <= M;
+    const bool none = M == 0;
     bool use_thr = false;
     u128 KM = ~(u128)0;
-    u64 cmin = ~0ull, thr = ~0ull;
-    if (!all && !none) {
+    u64 thr = ~0ull;
+    R.cmin = ~0ull;
+    if (!R.all && !none) {
         KM = block_kth(
-            S,
+            L.S,
             [&](auto&& f) {
 #pragma unroll
                 for (int k = 0; k < ONE_ITEMS; ++k)
                     if (k < nk && v[k] != 0.0) f(sel_key(rank_of(k), v[k], g));
             },
-            J.M, 0, (u128)0, g);
-        cmin = (u64)(KM >> g.rank_bits);
-        thr = abs_bits(__longlong_as_double((long long)cmin) * (1.0 - 1.0 / 68719476736.0));
-        if (J.band) {
+            M, 0, (u128)0, g);
+        R.cmin = (u64)(KM >> g.rank_bits);
+        thr = abs_bits(__longlong_as_double((long long)R.cmin) * (1.0 - 1.0 / 68719476736.0));
+        if (band) {
             u64 c = 0;
 #pragma unroll
             for (int k = 0; k < ONE_ITEMS; ++k) c += (v[k] != 0.0 && abs_bits(v[k]) >= thr) ? 1 : 0;
-            use_thr = block_sum(c) <= J.M + (u64)SFCI_TIE_SLACK;
+            use_thr = one_sum(L, c) <= M + (u64)SFCI_TIE_SLACK;
         }
     }
     u64 m[ONE_ITEMS];
+    keep = 0;
 #pragma unroll
     for (int k = 0; k < ONE_ITEMS; ++k) {
         bool p = k < nk && v[k] != 0.0 && !none;
-        if (p && !all) p = use_thr ? abs_bits(v[k]) >= thr : sel_key(rank_of(k), v[k], g) >= KM;
+        if (p && !R.all) p = use_thr ? abs_bits(v[k]) >= thr : sel_key(rank_of(k), v[k], g) >= KM;
         m[k] = __ballot(p);
-        if (lane == 0) cpos[k * NW + wave] = (unsigned)__popcll(m[k]);
+        keep |= p ? 1u << k : 0u;
+        if (lane == 0) L.cpos[k * NW + wave] = (unsigned)__popcll(m[k]);
     }
     __syncthreads();
     if (wave == 0) {
         unsigned carry = 0;
         for (int b = 0; b < ONE_ITEMS * NW; b += 64) {
-            const unsigned c = cpos[b + lane];
+            const unsigned c = L.cpos[b + lane];
             unsigned inc = c;
             for (int off = 1; off < 64; off <<= 1) {
                 const unsigned y = __shfl_up(inc, off);
                 if (lane >= off) inc += y;
             }
-            cpos[b + lane] = carry + inc - c;
+            L.cpos[b + lane] = carry + inc - c;
             carry += (unsigned)__shfl((int)inc, 63);
         }
-        if (lane == 0) s_count = carry;
+        if (lane == 0) L.count = carry;
     }
     __syncthreads();
+    R.count = L.count;
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k)
+        at[k] = L.cpos[k * NW + wave] + (unsigned)__popcll(m[k] & ((1ull << lane) - 1ull));
+    return R;
+}
+
+template <class JP>
+__global__ __launch_bounds__(ONE_BLOCK) void k_sel_one(JP jp) {
+    __shared__ OneLds L;
+    const SelJob J = jp(blockIdx.y);
+    const u64 n = J.D ? J.Dn : min(*J.n, J.cap);
+    const int nk = (int)((n + ONE_BLOCK - 1) / ONE_BLOCK);
+    auto rank_of = [&](int k) -> u64 {
+        const u64 i = (u64)k * ONE_BLOCK + threadIdx.x;
+        return J.D ? i : J.r[i];
+    };
+    double v[ONE_ITEMS];
 #pragma unroll
     for (int k = 0; k < ONE_ITEMS; ++k) {
-        if ((m[k] >> lane) & 1u) {
-            const u64 at = cpos[k * NW + wave] + (u64)__popcll(m[k] & ((1ull << lane) - 1ull));
-            J.out_r[at] = rank_of(k);
-            J.out_a[at] = v[k];
+        const u64 i = (u64)k * ONE_BLOCK + threadIdx.x;
+        v[k] = 0.0;
+        if (k < nk && i < n) v[k] = J.D ? J.D[i] : J.a[i];
+        if (J.Dz && v[k] != 0.0) J.Dz[i] = 0.0;
+    }
+    unsigned keep, at[ONE_ITEMS];
+    const OneResult R = one_select(L, v, nk, rank_of, J.M, J.band != 0, J.g, keep, at);
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        if ((keep >> k) & 1u) {
+            J.out_r[at[k]] = rank_of(k);
+            J.out_a[at[k]] = v[k];
         }
     }
-    if (t == 0) {
-        if (J.out_n) *J.out_n = s_count;
-        J.st->total = total;
-        J.st->take_all = all ? 1 : 0;
-        J.st->count_out = s_count;
-        J.st->cmin = cmin;
+    if (threadIdx.x == 0) {
+        if (J.out_n) *J.out_n = R.count;
+        J.st->total = R.total;
+        J.st->take_all = R.all ? 1 : 0;
+        J.st->count_out = R.count;
+        J.st->cmin = R.cmin;
     }
+}
+
+// ---- one step of the iteration on a space of at most SEL_ONE determinants ----
+// (smallh.hip forms y = H w_j in D.)  One workgroup, the accumulator in LDS:
+// the dots T_lj, S_lj of all l (a wavefront each), Eq. 10's two subtractions,
+// the truncation, Eq. 11, and w_{j+1} both as a list and as the dense vector
+// the next y = H w is formed from.
+struct StepLds {
+    OneLds one;
+    double t_jj, t_mj;
+    u64 nz;
+};
+
+// w = the kept entries of u, divided by their norm: list l and the dense copy.
+__device__ __forceinline__ void small_store(const SmallStep& s, StepLds& L, double (&v)[ONE_ITEMS], int nk, int l) {
+    const Geo g = geo_of(s.rank_bits, s.N - 1);
+    unsigned keep, at[ONE_ITEMS];
+    const OneResult R = one_select(
+        L.one, v, nk, [&](int k) -> u64 { return (u64)k * ONE_BLOCK + threadIdx.x; }, s.M, s.band != 0, g, keep, at);
+    double ss = 0.0;
+    u64 nz = 0;
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k)
+        if ((keep >> k) & 1u) {
+            ss += v[k] * v[k];
+            nz += s.nz[(u64)k * ONE_BLOCK + threadIdx.x];
+        }
+    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
+    if ((threadIdx.x & 63) == 0) L.one.dsum[threadIdx.x >> 6] = ss;
+    nz = one_sum(L.one, nz);  // (its barriers also publish dsum)
+    ss = 0.0;
+    for (int w = 0; w < ONE_BLOCK / 64; ++w) ss += L.one.dsum[w];
+    const bool div = ss > 0.0;
+    const double nrm = sqrt(ss);
+    u64* const Wr = s.Wr + (u64)l * s.cap;
+    double* const Wa = s.Wa + (u64)l * s.cap;
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        const u64 i = (u64)k * ONE_BLOCK + threadIdx.x;
+        if (k >= nk || i >= s.N) continue;
+        const bool on = (keep >> k) & 1u;
+        const double a = on ? (div ? v[k] / nrm : v[k]) : 0.0;
+        s.vd[i] = a;
+        if (on) {
+            Wr[at[k]] = i;
+            Wa[at[k]] = a;
+        }
+    }
+    if (threadIdx.x == 0) {
+        s.nnz[l] = R.count;
+        s.hist[l] = R.count;
+        *s.emitted += nz;
+    }
+}
+
+__global__ __launch_bounds__(ONE_BLOCK) void k_small_step(SmallStep s, int j) {
+    extern __shared__ double lds[];
+    __shared__ StepLds L;
+    double* const y = lds;          // N
+    double* const w = lds + s.N;    // N when it fits (s.w_lds), else the global copy
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (u64 i = threadIdx.x; i < s.N; i += ONE_BLOCK) {
+        y[i] = s.D[i];
+        if (s.w_lds) w[i] = s.vd[i];
+    }
+    __syncthreads();
+    for (int l = wave; l <= j; l += ONE_BLOCK / 64) {
+        const u64* r = s.Wr + (u64)l * s.cap;
+        const double* a = s.Wa + (u64)l * s.cap;
+        const u64 n = s.nnz[l];
+        double st = 0.0, sv = 0.0;
+        constexpr int U = 8;
+        for (u64 i0 = 0; i0 < n; i0 += 64 * U) {
+            u64 rr[U];
+            double aa[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const u64 i = i0 + (u64)u * 64 + lane;
+                rr[u] = i < n ? r[i] : 0;
+                aa[u] = i < n ? a[i] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (i0 + (u64)u * 64 + lane >= n) continue;
+                st += aa[u] * y[rr[u]];
+                sv += aa[u] * (s.w_lds ? w[rr[u]] : s.vd[rr[u]]);
+            }
+        }
+        for (int off = 32; off >= 1; off >>= 1) {
+            st += __shfl_xor(st, off);
+            sv += __shfl_xor(sv, off);
+        }
+        if (lane == 0) {
+            s.T[l * s.nL + j] = st;
+            s.T[j * s.nL + l] = st;
+            s.S[l * s.nL + j] = sv;
+            s.S[j * s.nL + l] = sv;
+            if (l == j) L.t_jj = st;
+            if (l == j - 1) L.t_mj = st;
+        }
+    }
+    if (j + 1 == s.nL) return;
+    __syncthreads();
+    for (int b = 0; b < 2; ++b) {
+        // u = (y - T_jj w_j) - T_{j-1,j} w_{j-1}
+        const int l = j - b;
+        if (l < 0) break;
+        const double c = b ? L.t_mj : L.t_jj;
+        const u64 n = s.nnz[l];
+        for (u64 i = threadIdx.x; i < n; i += ONE_BLOCK) {
+            const double prod = c * s.Wa[(u64)l * s.cap + i];
+            const u64 k = s.Wr[(u64)l * s.cap + i];
+            y[k] = y[k] - prod;
+        }
+        __syncthreads();
+    }
+    const int nk = (int)((s.N + ONE_BLOCK - 1) / ONE_BLOCK);
+    double v[ONE_ITEMS];
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        const u64 i = (u64)k * ONE_BLOCK + threadIdx.x;
+        v[k] = (k < nk && i < s.N) ? y[i] : 0.0;
+    }
+    small_store(s, L, v, nk, j + 1);
+}
+
+// Block end: Psi = sum_j x_j w_j into D (final) or, truncated and normalised, w_0.
+__global__ __launch_bounds__(ONE_BLOCK) void k_small_psi(SmallStep s, const double* __restrict__ x, int final) {
+    extern __shared__ double lds[];
+    __shared__ StepLds L;
+    for (u64 i = threadIdx.x; i < s.N; i += ONE_BLOCK) lds[i] = 0.0;
+    __syncthreads();
+    for (int l = 0; l < s.nL; ++l) {
+        const double c = x[l];
+        const u64 n = s.nnz[l];
+        for (u64 i = threadIdx.x; i < n; i += ONE_BLOCK) {
+            const double prod = c * s.Wa[(u64)l * s.cap + i];
+            const u64 k = s.Wr[(u64)l * s.cap + i];
+            lds[k] = lds[k] + prod;
+        }
+        __syncthreads();
+    }
+    const int nk = (int)((s.N + ONE_BLOCK - 1) / ONE_BLOCK);
+    double v[ONE_ITEMS];
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) {
+        const u64 i = (u64)k * ONE_BLOCK + threadIdx.x;
+        const bool in = k < nk && i < s.N;
+        v[k] = in ? lds[i] : 0.0;
+        if (final && in) s.D[i] = v[k];
+    }
+    if (!final) small_store(s, L, v, nk, 0);
 }
 
 unsigned seg_grid(int num_cu, u64 nseg) {
@@ -1155,5 +1336,26 @@ void bstep_select(hipStream_t st, const BInst* d, int n, int out_kind, int j, u6
         hipLaunchKernelGGL(k_sel_write<BatchJobs>, dim3(seg_grid(num_cu, select_chunks(max_ndet)), N), dim3(256), 0,
                            st, jp);
     }
+    SFCI_CHECK_HIP(hipGetLastError());
+}
+
+// Dynamic LDS of the small-space kernels: one array of N doubles, or two where they fit.
+size_t small_step_lds(u64 N, bool two) { return (size_t)(two ? 2 : 1) * N * sizeof(double); }
+
+void small_step_setup(sfci_problem* P) {
+    for (const void* f : {(const void*)k_small_step, (const void*)k_small_psi})
+        SFCI_CHECK_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(SEL_ONE * sizeof(double))));
+    (void)P;
+}
+
+void launch_small_step(sfci_problem* P, const SmallStep& s, int j) {
+    hipLaunchKernelGGL(k_small_step, dim3(1), dim3(ONE_BLOCK), small_step_lds(s.N, s.w_lds != 0), P->stream, s, j);
+    SFCI_CHECK_HIP(hipGetLastError());
+}
+
+void launch_small_psi(sfci_problem* P, const SmallStep& s, const double* x, bool final) {
+    hipLaunchKernelGGL(k_small_psi, dim3(1), dim3(ONE_BLOCK), small_step_lds(s.N, false), P->stream, s, x,
+                       final ? 1 : 0);
     SFCI_CHECK_HIP(hipGetLastError());
 }

@@ -126,6 +126,9 @@ struct sfci_problem {
     DevBuf ws_tup_k, ws_tup_v, ws_tup_k2, ws_tup_v2, ws_seg_v, ws_seg_f, ws_src_cnt, ws_src_off, ws_hist;
     DevBuf ws_list_r, ws_list_a, ws_prod;
     DevBuf ws_cand_r, ws_cand_a;  // top-M of a dense source: its candidates
+    DevBuf sh_idx, sh_val, sh_nz, sh_vd;  // small spaces (smallh.hip): H by rows, terms per column, dense v
+    int sh_state = 0;                     // 0 untried, 1 built, -1 the space is too large
+    hipEvent_t ev[2] = {nullptr, nullptr};  // around a call, created on first use
     int sel_mode = 0;             // what select_prepare left for select_write (select.hip)
     CandSrc sel_src{};
     DevBuf ws_lz[8];
@@ -367,6 +370,39 @@ int select_shift(u64 lcap);      // log2 of a list's entries per segment
 u64 select_segments(u64 lcap);
 void select_prepare_ws(sfci_problem* P, const CandSrc& src, u64 M, u64* count_dev, const SelWs& ws);
 void select_write_ws(sfci_problem* P, const CandSrc& src, u64* out_rank, double* out_amp, const SelWs& ws);
+
+// ---- small spaces (smallh.hip; the step kernels in select.hip) ----
+// Whether H is kept as a table (builds it on first use).
+bool small_h_ready(sfci_problem* P);
+// The input vector of the next launch_small_sigma: n_host entries, or *n_dev.
+// check: flags[0] a rank out of range, flags[1] ranks not strictly ascending
+// (the vector then counts as empty).  nnz_out, hist (may be NULL) receive the
+// length; its terms are added to *emitted.
+void launch_small_load(sfci_problem* P, const u64* r, const double* a, const u64* n_dev, u64 n_host, bool check,
+                       u64* nnz_out, u64* hist, u64* emitted, int* flags);
+// D = H v (every slot written; |y| < eps written as 0).
+void launch_small_sigma(sfci_problem* P, double eps);
+// The rest of an iteration step: the basis and what a step writes.
+struct SmallStep {
+    u64* Wr;
+    double* Wa;
+    u64* nnz;  // of w_l
+    u64 cap;
+    double* D;
+    u64 N;
+    double* vd;    // dense copy of the vector sigma is applied to
+    const u32* nz; // terms per column of H
+    double *T, *S;
+    int nL, band;
+    u64 M;
+    u64* emitted;
+    u64* hist;  // nnz of the block's vectors
+    int rank_bits;
+    int w_lds;  // the dense copy fits in LDS beside the accumulator
+};
+void small_step_setup(sfci_problem* P);
+void launch_small_step(sfci_problem* P, const SmallStep& s, int j);
+void launch_small_psi(sfci_problem* P, const SmallStep& s, const double* x, bool final);
 
 // ---- sort path (sortpath.hip) ----
 // sigma = H v by stable sort + in-order segmented sum; result sorted by rank,
