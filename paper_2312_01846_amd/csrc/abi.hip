@@ -627,7 +627,7 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
             ++sigma_calls;
             launch_small_step(P, s, j);
         }
-        launch_geneig_full(P, nL, T, S, lam, xd, energies_d + b, status);
+        launch_geneig_full(P, nL, T, S, lam, xd, energies_d + b, status, det);
         blocks_run = b + 1;
         const bool last = b + 1 == nblk || halt_after_block(P, o, energies_d, b);
         s.hist = nnz_hist + (size_t)(b + 1) * nL;  // w_0 of the next block
@@ -686,7 +686,7 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
                 launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
             }
         }
-        launch_geneig_full(P, nL, T, S, lam, xd, energies_d + b, status);
+        launch_geneig_full(P, nL, T, S, lam, xd, energies_d + b, status, det);
         for (int j = 0; j < nL; ++j) {
             DVec wj = W(j);
             launch_axpy_scatter(P, P->d_D, wj.r, wj.a, wj.nnz, cap, xd + j, +1.0);

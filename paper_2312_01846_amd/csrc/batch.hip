@@ -522,7 +522,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
         fan([&](int k) {
             Inst& q = I[k];
             sfci_problem* P = q.P;
-            launch_geneig_full(P, nL, q.T, q.S, q.lam, q.x, q.energies, q.status, q.blk);
+            launch_geneig_full(P, nL, q.T, q.S, q.lam, q.x, q.energies, q.status, det, q.blk);
             for (int j = 0; j < nL; ++j) {
                 DVec wj = q.W(j);
                 launch_axpy_scatter(P, P->d_D, wj.r, wj.a, wj.nnz, q.cap, q.x + j, +1.0);

@@ -531,10 +531,96 @@ __device__ void jacobi_dev(int m, double (*A)[GE_MAX], double (*V)[GE_MAX], doub
     wave_sync();
 }
 
+// The same decomposition for fast mode: the rotations of a sweep in rounds of
+// floor(m / 2) disjoint pairs (a round robin), a lane per pair, so that a sweep
+// is m - 1 dependent steps instead of m (m - 1) / 2.  What a step costs is the
+// chain of divisions and square roots of a rotation (~1 000 cycles); 10 x 10:
+// 320 -> 118 us for the two decompositions of a block.  Same stopping rule.
+__device__ void jacobi_rounds(int m, double (*A)[GE_MAX], double (*V)[GE_MAX], double* w,
+                              double (*cs)[2], int (*pq)[2]) {
+    const int lane = threadIdx.x;
+    for (int e = lane; e < m * m; e += 64) V[e / m][e % m] = (e / m == e % m) ? 1.0 : 0.0;
+    const int me = m + (m & 1);  // players, one idle where m is odd
+    wave_sync();
+    for (int sweep = 0; sweep < 64; ++sweep) {
+        double off = 0.0, dg = 0.0;
+        for (int e = lane; e < m * m; e += 64) {
+            const int p = e / m, q = e % m;
+            const double x = A[p][q] * A[p][q];
+            if (p == q) dg += x;
+            else if (p < q) off += x;
+        }
+        for (int o = 32; o >= 1; o >>= 1) {
+            off += __shfl_xor(off, o);
+            dg += __shfl_xor(dg, o);
+        }
+        if (off <= 1e-30 * dg || m < 2) break;
+        for (int round = 0; round < me - 1; ++round) {
+            if (lane < me / 2) {
+                // player me - 1 stays, the others move on by one seat per round
+                int p = lane == 0 ? me - 1 : (round + lane) % (me - 1);
+                int q = lane == 0 ? round : (round + me - 1 - lane) % (me - 1);
+                if (p > q) {
+                    const int x = p;
+                    p = q;
+                    q = x;
+                }
+                double c = 1.0, s = 0.0;
+                if (q < m) {
+                    const double apq = A[p][q];
+                    if (apq != 0.0) {
+                        const double theta = (A[q][q] - A[p][p]) / (2.0 * apq);
+                        double t = 1.0 / (fabs(theta) + sqrt(theta * theta + 1.0));
+                        if (theta < 0.0) t = -t;
+                        c = 1.0 / sqrt(t * t + 1.0);
+                        s = t * c;
+                    }
+                }
+                pq[lane][0] = p;
+                pq[lane][1] = q < m ? q : -1;
+                cs[lane][0] = c;
+                cs[lane][1] = s;
+            }
+            wave_sync();
+            // columns of A and V, then rows of A, by every pair's rotation
+            for (int e = lane; e < (me / 2) * m; e += 64) {
+                const int k = e / m, r = e % m, p = pq[k][0], q = pq[k][1];
+                if (q < 0) continue;
+                const double c = cs[k][0], s = cs[k][1];
+                const double ap = A[r][p], aq = A[r][q], vp = V[r][p], vq = V[r][q];
+                A[r][p] = c * ap - s * aq;
+                A[r][q] = s * ap + c * aq;
+                V[r][p] = c * vp - s * vq;
+                V[r][q] = s * vp + c * vq;
+            }
+            wave_sync();
+            for (int e = lane; e < (me / 2) * m; e += 64) {
+                const int k = e / m, r = e % m, p = pq[k][0], q = pq[k][1];
+                if (q < 0) continue;
+                const double c = cs[k][0], s = cs[k][1];
+                const double ap = A[p][r], aq = A[q][r];
+                A[p][r] = c * ap - s * aq;
+                A[q][r] = s * ap + c * aq;
+            }
+            wave_sync();
+            if (lane < me / 2 && pq[lane][1] >= 0) {
+                // exactly zero in exact arithmetic
+                A[pq[lane][0]][pq[lane][1]] = 0.0;
+                A[pq[lane][1]][pq[lane][0]] = 0.0;
+            }
+            wave_sync();
+        }
+    }
+    if (lane < m) w[lane] = A[lane][lane];
+    wave_sync();
+}
+
 // Canonical orthogonalisation: S = U s U^T, keep s_k > 1e-10 max s,
 // X = U_k s_k^(-1/2), Jacobi on X^T T X, x = X y for the lowest eigenvalue,
 // sign fixed so that the largest |x_i| (lowest i on ties) is positive.
-// One wavefront; every sum keeps the reference's order.
+// One wavefront; every sum keeps the reference's order.  ORDERED: the
+// decompositions too (deterministic mode's bits).
+template <bool ORDERED>
 __device__ __forceinline__ void geneig_body(int m, const double* __restrict__ T, const double* __restrict__ S,
                                             double* lambda, double* x, double* energy_slot, const int* blk,
                                             int* status) {
@@ -542,11 +628,17 @@ __device__ __forceinline__ void geneig_body(int m, const double* __restrict__ T,
     __shared__ double sv[GE_MAX], lam[GE_MAX], xs[GE_MAX];
     __shared__ int keep[GE_MAX];
     __shared__ int s_r, s_best, s_flag;
+    __shared__ double cs[GE_MAX / 2][2];
+    __shared__ int pq[GE_MAX / 2][2];
+    auto jacobi = [&](int k, double* w) {
+        if (ORDERED) jacobi_dev(k, A, U, w, &s_flag);
+        else jacobi_rounds(k, A, U, w, cs, pq);
+    };
     const int i = threadIdx.x;
     if (i < m)
         for (int j = 0; j < m; ++j) A[i][j] = S[i * m + j];
     wave_sync();
-    jacobi_dev(m, A, U, sv, &s_flag);
+    jacobi(m, sv);
     if (i == 0) {
         double smax = 0.0;
         for (int k = 0; k < m; ++k)
@@ -586,7 +678,7 @@ __device__ __forceinline__ void geneig_body(int m, const double* __restrict__ T,
             A[c][i] = v;
         }
     wave_sync();
-    jacobi_dev(r, A, U, lam, &s_flag);  // U now holds the eigenvectors y of X^T T X
+    jacobi(r, lam);  // U now holds the eigenvectors y of X^T T X
     if (i == 0) {
         int best = 0;
         for (int k = 1; k < r; ++k)
@@ -617,10 +709,11 @@ __device__ __forceinline__ void geneig_body(int m, const double* __restrict__ T,
     }
 }
 
+template <bool ORDERED>
 __global__ __launch_bounds__(64) void k_geneig(int m, const double* __restrict__ T, const double* __restrict__ S,
                                                double* lambda, double* x, double* energy_slot, const int* blk,
                                                int* status) {
-    geneig_body(m, T, S, lambda, x, energy_slot, blk, status);
+    geneig_body<ORDERED>(m, T, S, lambda, x, energy_slot, blk, status);
 }
 
 unsigned gsz(u64 cap) {
@@ -745,8 +838,9 @@ void launch_copy_vec(sfci_problem* P, const u64* r, const double* a, const u64* 
 }
 
 void launch_geneig_full(sfci_problem* P, int m, const double* T, const double* S, double* lambda, double* x,
-                        double* energy_slot, int* status, const int* blk) {
-    hipLaunchKernelGGL(k_geneig, dim3(1), dim3(64), 0, P->stream, m, T, S, lambda, x, energy_slot, blk, status);
+                        double* energy_slot, int* status, bool ordered, const int* blk) {
+    hipLaunchKernelGGL(ordered ? k_geneig<true> : k_geneig<false>, dim3(1), dim3(64), 0, P->stream, m, T, S, lambda,
+                       x, energy_slot, blk, status);
     SFCI_CHECK_HIP(hipGetLastError());
 }
 
@@ -913,7 +1007,7 @@ __global__ void k_bfill_zero(const BInst* __restrict__ B) {
 
 __global__ __launch_bounds__(64) void k_bgeneig(const BInst* __restrict__ B, int m) {
     const BInst& b = B[blockIdx.y];
-    geneig_body(m, b.T, b.S, b.lam, b.x, b.energies, b.blk, b.status);
+    geneig_body<false>(m, b.T, b.S, b.lam, b.x, b.energies, b.blk, b.status);
 }
 
 __global__ void k_binc_blk(const BInst* __restrict__ B) {

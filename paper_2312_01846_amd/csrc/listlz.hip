@@ -700,7 +700,7 @@ void lanczos_list(sfci_problem* P, const sfci_lanczos_opts* o, const ListBasis& 
                 select_into(src, j + 1, false);
             }
         }
-        launch_geneig_full(P, nL, T, S, Bs.lam, Bs.xd, Bs.energies_d + b, Bs.status_d);
+        launch_geneig_full(P, nL, T, S, Bs.lam, Bs.xd, Bs.energies_d + b, Bs.status_d, det);
         // Psi = sum_j x_j w_j: stable sort of the scaled concatenation, in-order sums
         u64* offs = ls + 88;
         hipLaunchKernelGGL(k_concat_offsets, dim3(1), dim3(64), 0, P->stream, sc, nL, offs);

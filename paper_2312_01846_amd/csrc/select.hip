@@ -456,87 +456,101 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_sel_hist(JP jp, int L) {
 // LDS of block_kth.
 struct KthLds {
     u32 hist[NBIN];
-    u64 hi[64], lo[64];
+    u64 p[64], q[64];
     u64 wsum[ONE_BLOCK / 64];
-    u64 need, pre_hi, pre_lo, khi, klo;
+    u64 need, pre, kp, kq;
     u32 bin, n;
 };
 
-// The need-th largest key of a workgroup's keys (each(f) calls f for the keys
-// of the calling thread; those that do not start with the digits pre above
-// level L are skipped): digit by digit until at most 64 share them, then by
-// counting.  Every thread gets it.  A workgroup of ONE_BLOCK threads.
+// A key's two halves: the bits of |c| (63) and N_det - 1 - rank.
+struct KeyPair {
+    u64 p, q;
+};
+
+// The need-th largest key of a workgroup's keys (each(f) calls f(p, q) for the
+// keys of the calling thread; those that do not start with the digits pre
+// above level L are skipped): digit by digit, first of the magnitude (levels
+// 0 to 5: 11 bits, the last 8), then of the rank, until at most 64 share them,
+// then by counting.  Every thread gets it.  A workgroup of ONE_BLOCK threads.
+// (64-bit halves: shifts and compares of the 128-bit key took most of the
+// time.)
 template <class Each>
-__device__ __forceinline__ u128 block_kth(KthLds& S, const Each& each, u64 need0, int L, u128 pre0, const Geo& g) {
+__device__ __forceinline__ KeyPair block_kth(KthLds& S, const Each& each, u64 need0, int L, u64 pre0, int rank_bits) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     constexpr int NW = ONE_BLOCK / 64;
+    constexpr int PL = 6;  // levels of the magnitude
     if (t == 0) {
         S.need = need0;
-        S.pre_hi = (u64)(pre0 >> 64);
-        S.pre_lo = (u64)pre0;
+        S.pre = pre0;
         S.n = 0;
     }
+    u64 pfull = 0;  // the magnitude, once every digit of it is fixed
     for (;; ++L) {
         S.hist[t] = 0;
         S.hist[t + ONE_BLOCK] = 0;
         __syncthreads();
-        const u128 pre = ((u128)S.pre_hi << 64) | S.pre_lo;
-        const u64 need = S.need;
-        const int lo = dig_lo(g, L), hi_sh = g.tb - DIG * L;
-        each([&](u128 K) {
-            if (L == 0 || (K >> hi_sh) == pre) atomicAdd(&S.hist[(unsigned)((K >> lo) & (u128)(NBIN - 1))], 1u);
+        const u64 pre = S.pre, need = S.need;
+        const bool mag = L < PL;
+        if (L == PL) pfull = pre;
+        // this level's digit: bits [lo, hi) of its half
+        const int hi = mag ? 63 - DIG * L : rank_bits - DIG * (L - PL);
+        const int lo = max(0, hi - DIG);
+        const unsigned mask = (1u << (hi - lo)) - 1u;
+        const u64 pq = L > PL ? pre : 0;  // digits of the rank fixed so far
+        auto in_prefix = [&](u64 p, u64 q) {
+            return mag ? (L == 0 || (p >> hi) == pre) : (p == pfull && (L == PL || (q >> hi) == pq));
+        };
+        each([&](u64 p, u64 q) {
+            if (in_prefix(p, q)) atomicAdd(&S.hist[(unsigned)((mag ? p : q) >> lo) & mask], 1u);
         });
         __syncthreads();
         // two bins per thread: the entries above each, by a suffix scan
         const u32 h0 = S.hist[2 * t], h1 = S.hist[2 * t + 1];
-        u64 suf = (u64)h0 + h1;
+        u32 suf = h0 + h1;
         for (int off = 1; off < 64; off <<= 1) {
-            const u64 y = (u64)__shfl_down((long long)suf, off);
+            const u32 y = (u32)__shfl_down((int)suf, off);
             if (lane + off < 64) suf += y;
         }
         if (lane == 0) S.wsum[wave] = suf;
         __syncthreads();
         u64 above = suf - h0 - h1;
         for (int w = wave + 1; w < NW; ++w) above += S.wsum[w];
-        const int width = hi_sh - lo;
-        auto picked = [&](int b, u64 hi, u32 h) {
-            const u128 p = (pre << width) | (u128)(unsigned)b;
-            S.pre_hi = (u64)(p >> 64);
-            S.pre_lo = (u64)p;
-            S.need = need - hi;
+        auto picked = [&](unsigned b, u64 over, u32 h) {
+            S.pre = ((L == PL ? 0 : pre) << (hi - lo)) | b;
+            S.need = need - over;
             S.bin = h;
         };
-        if (above < need && above + h1 >= need) picked(2 * t + 1, above, h1);
-        else if (above + h1 < need && above + h1 + h0 >= need) picked(2 * t, above + h1, h0);
+        if (above < need && above + h1 >= need) picked(2u * t + 1, above, h1);
+        else if (above + h1 < need && above + h1 + h0 >= need) picked(2u * t, above + h1, h0);
         __syncthreads();
-        const u128 pre2 = ((u128)S.pre_hi << 64) | S.pre_lo;
-        if (L == g.ndig - 1) return pre2;  // every digit fixed
+        const u64 pre2 = S.pre;
+        if (!mag && lo == 0) return KeyPair{pfull, pre2};  // every digit fixed
         if (S.bin > 64) continue;
-        each([&](u128 K) {
-            if ((K >> lo) == pre2) {
+        each([&](u64 p, u64 q) {
+            if (mag ? (p >> lo) == pre2 : (p == pfull && (q >> lo) == pre2)) {
                 const unsigned at = atomicAdd(&S.n, 1u);
-                S.hi[at] = (u64)(K >> 64);
-                S.lo[at] = (u64)K;
+                S.p[at] = p;
+                S.q[at] = q;
             }
         });
         __syncthreads();
         const unsigned c = S.bin;
         if ((unsigned)t < c) {
             const u64 need2 = S.need;
-            const u128 K = ((u128)S.hi[t] << 64) | S.lo[t];
+            const u64 p = S.p[t], q = S.q[t];
             unsigned more = 0, same = 0;
-            for (unsigned q = 0; q < c; ++q) {
-                const u128 Q = ((u128)S.hi[q] << 64) | S.lo[q];
-                more += Q > K ? 1u : 0u;
-                same += Q == K ? 1u : 0u;
+            for (unsigned x = 0; x < c; ++x) {
+                const u64 P = S.p[x], Q = S.q[x];
+                more += (P > p || (P == p && Q > q)) ? 1u : 0u;
+                same += (P == p && Q == q) ? 1u : 0u;
             }
             if (more < need2 && more + same >= need2) {  // (equal keys write the same)
-                S.khi = (u64)(K >> 64);
-                S.klo = (u64)K;
+                S.kp = p;
+                S.kq = q;
             }
         }
         __syncthreads();
-        return ((u128)S.khi << 64) | S.klo;
+        return KeyPair{S.kp, S.kq};
     }
 }
 
@@ -545,7 +559,7 @@ __device__ __forceinline__ u128 block_kth(KthLds& S, const Each& each, u64 need0
 template <class JP>
 __global__ __launch_bounds__(ONE_BLOCK) void k_sel_small(JP jp) {
     __shared__ KthLds S;
-    __shared__ u64 hi[SEL_SMALL], lo[SEL_SMALL];
+    __shared__ u64 kp[SEL_SMALL], kq[SEL_SMALL];
     const SelJob J = jp(blockIdx.y);
     SelState* st = J.st;
     if (st->done || st->bin > SEL_SMALL) return;
@@ -555,24 +569,25 @@ __global__ __launch_bounds__(ONE_BLOCK) void k_sel_small(JP jp) {
         const u128 K = sel_key(r, c, J.g);
         if ((K >> sh) == pre) {
             const unsigned at = atomicAdd(&st->small_n, 1u);
-            shared_store(&st->small_hi[at], (u64)(K >> 64));
-            shared_store(&st->small_lo[at], (u64)K);
+            shared_store(&st->small_p[at], abs_bits(c));
+            shared_store(&st->small_q[at], J.g.ndet_m1 - r);
         }
     });
     if (!last_workgroup(&st->ticket[SEL_TICKETS - 2], gridDim.x)) return;
     const unsigned n = (unsigned)st->bin;
     for (unsigned t = threadIdx.x; t < n; t += blockDim.x) {
-        hi[t] = shared_load(&st->small_hi[t]);
-        lo[t] = shared_load(&st->small_lo[t]);
+        kp[t] = shared_load(&st->small_p[t]);
+        kq[t] = shared_load(&st->small_q[t]);
     }
     __syncthreads();
-    const u128 K = block_kth(
+    // two digits are fixed: the top 22 bits of the magnitude
+    const KeyPair K = block_kth(
         S,
         [&](auto&& f) {
-            for (unsigned t = threadIdx.x; t < n; t += ONE_BLOCK) f(((u128)hi[t] << 64) | lo[t]);
+            for (unsigned t = threadIdx.x; t < n; t += ONE_BLOCK) f(kp[t], kq[t]);
         },
-        st->need, st->level, pre, J.g);
-    if (threadIdx.x == 0) sel_decide(st, K, J.g);
+        st->need, st->level, (u64)pre, J.g.rank_bits);
+    if (threadIdx.x == 0) sel_decide(st, ((u128)K.p << J.g.rank_bits) | K.q, J.g);
 }
 
 struct SelPred {
@@ -798,7 +813,7 @@ __global__ __launch_bounds__(CBLOCK) void k_dense_write(JP jp) {
 }
 
 // The whole selection of a source of at most SEL_ONE entries by one
-// workgroup, the values in registers: one launch (30 us at 3 136 slots) where
+// workgroup, the values in registers: one launch (20 us at 3 136 slots) where
 // the steps above are 7 and the histogram per digit took 24.
 struct OneLds {
     KthLds S;
@@ -839,7 +854,7 @@ __device__ __forceinline__ OneResult one_select(OneLds& L, const double (&v)[ONE
     R.all = M == UINT64_MAX || R.total <= M;
     const bool none = M == 0;
     bool use_thr = false;
-    u128 KM = ~(u128)0;
+    KeyPair KM{~0ull, ~0ull};
     u64 thr = ~0ull;
     R.cmin = ~0ull;
     if (!R.all && !none) {
@@ -848,10 +863,10 @@ __device__ __forceinline__ OneResult one_select(OneLds& L, const double (&v)[ONE
             [&](auto&& f) {
 #pragma unroll
                 for (int k = 0; k < ONE_ITEMS; ++k)
-                    if (k < nk && v[k] != 0.0) f(sel_key(rank_of(k), v[k], g));
+                    if (k < nk && v[k] != 0.0) f(abs_bits(v[k]), g.ndet_m1 - rank_of(k));
             },
-            M, 0, (u128)0, g);
-        R.cmin = (u64)(KM >> g.rank_bits);
+            M, 0, 0, g.rank_bits);
+        R.cmin = KM.p;
         thr = abs_bits(__longlong_as_double((long long)R.cmin) * (1.0 - 1.0 / 68719476736.0));
         if (band) {
             u64 c = 0;
@@ -865,7 +880,10 @@ __device__ __forceinline__ OneResult one_select(OneLds& L, const double (&v)[ONE
 #pragma unroll
     for (int k = 0; k < ONE_ITEMS; ++k) {
         bool p = k < nk && v[k] != 0.0 && !none;
-        if (p && !R.all) p = use_thr ? abs_bits(v[k]) >= thr : sel_key(rank_of(k), v[k], g) >= KM;
+        if (p && !R.all) {
+            const u64 b = abs_bits(v[k]);
+            p = use_thr ? b >= thr : b > KM.p || (b == KM.p && g.ndet_m1 - rank_of(k) >= KM.q);
+        }
         m[k] = __ballot(p);
         keep |= p ? 1u << k : 0u;
         if (lane == 0) L.cpos[k * NW + wave] = (unsigned)__popcll(m[k]);

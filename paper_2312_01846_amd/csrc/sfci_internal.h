@@ -72,7 +72,7 @@ struct SelState {
     unsigned small_n, pad;
     unsigned ticket[SEL_TICKETS];
     u64 hist[2048];
-    u64 small_hi[SEL_SMALL], small_lo[SEL_SMALL];  // the picked bin's keys
+    u64 small_p[SEL_SMALL], small_q[SEL_SMALL];  // the picked bin's keys: bits of |c|, N_det - 1 - rank
 };
 
 // What a selection reads: the dense accumulator or a list.
@@ -484,7 +484,7 @@ u64 normalise_ws_doubles();
 void launch_scatter_set(sfci_problem* P, double* D, const u64* r, const double* a, const u64* nnz, u64 cap);
 // energy_slot[blk ? *blk : 0] receives lambda (blk: device block index, may be null)
 void launch_geneig_full(sfci_problem* P, int m, const double* T, const double* S, double* lambda, double* x,
-                        double* energy_slot, int* status, const int* blk = nullptr);
+                        double* energy_slot, int* status, bool ordered, const int* blk = nullptr);
 void launch_inc_int(sfci_problem* P, int* p);
 void launch_add_u64(sfci_problem* P, u64* dst, const u64* src);  // *dst += *src
 void launch_div_by_sumsq(sfci_problem* P, const double* a, const u64* nnz, u64 cap, double* out);
