@@ -766,15 +766,26 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
     if (!P || !v || !sbar) return (sfci_status)sfci_set_error(SFCI_E_ARG, "NULL argument");
     if ((v->nnz && (!v->rank || !v->amp)) || (sbar->nnz && (!sbar->rank || !sbar->amp)))
         return (sfci_status)sfci_set_error(SFCI_E_ARG, "NULL input arrays");
-    validate_vec(P, v->rank, v->nnz);
-    validate_vec(P, sbar->rank, sbar->nnz);
-    if (!ensure_dense(P))
+    if (!ensure_dense(P)) {
+        validate_vec(P, v->rank, v->nnz);
+        validate_vec(P, sbar->rank, sbar->nnz);
         return (sfci_status)sfci_set_error(SFCI_E_UNSUPPORTED, "backward needs the dense array (N_det doubles)");
+    }
     const int n = P->n;
     const u64 n2 = (u64)n * n, n4 = n2 * n2;
+    // [0] nnz(v) [1] nnz(sbar) [2] transposed v's count [4], [5] the vectors' flags: both are checked on the
+    // device, where a bad one counts as empty, and the flags are read once the work is queued
     u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, P->stream, scal, (u64)v->nnz);
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, P->stream, scal + 1, (u64)sbar->nnz);
+    launch_fill_u64(scal, 8, 0, P->stream);
+    launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
+    launch_check_vec(P, sbar->rank, sbar->nnz, scal + 1, (int*)&scal[5]);
+    auto finish = [&] {
+        u64 flags[2];
+        SFCI_CHECK_HIP(hipMemcpyAsync(flags, &scal[4], sizeof(flags), hipMemcpyDeviceToHost, P->stream));
+        sync(P);
+        throw_bad_vec((const int*)&flags[0]);
+        throw_bad_vec((const int*)&flags[1]);
+    };
     double* raw = (double*)P->ws_red.get((RAW_PAD + n2 + n4) * sizeof(double));
     SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
     if (!v_bar && v->nnz && sbar->nnz && rowtile_grad_available(P)) {
@@ -794,13 +805,17 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
         J.vt_amp = (double*)P->ws_list_a.get(v->nnz * sizeof(double));
         J.vt_nnz = scal + 2;
         rowtile_gradients(P->stream, 1, &J, P->grad_ws);
-        sync(P);
+        finish();
         return SFCI_OK;
     }
     launch_scatter_set(P, P->d_D, sbar->rank, sbar->amp, scal + 1, std::max<u64>(1, sbar->nnz));
-    launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2);
+    if (v->nnz && sbar->nnz && back_rows_available(P, v->nnz))
+        launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
+                         raw + RAW_PAD + n2);
+    else
+        launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2);
     launch_scatter_zero(P, P->d_D, sbar->rank, scal + 1, std::max<u64>(1, sbar->nnz));
-    sync(P);
+    finish();
     return SFCI_OK;
     SFCI_GUARD_END
 }

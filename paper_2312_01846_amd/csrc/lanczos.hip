@@ -106,37 +106,15 @@ constexpr int OS_EVENTS = 24;                  // singly added terms of a chunk 
 
 __device__ __forceinline__ int os_slot(int i) { return i + (i >> 3); }
 
-// One step of a wavefront scan or reduction: the value CTRL selects from a
-// lower lane, `idle` where there is none (row_shr 1, 2, 4, 8 within rows of
-// 16 lanes, then the last lane of row 0 and 2 to the next, of row 1 to 2 and 3).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double os_dpp(double idle, double x) {
-    const int lo = __builtin_amdgcn_update_dpp(__double2loint(idle), __double2loint(x), CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(idle), __double2hiint(x), CTRL, ROWS, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double os_scan_add(double x) {
-    x += os_dpp<0x111, 0xf>(0.0, x);
-    x += os_dpp<0x112, 0xf>(0.0, x);
-    x += os_dpp<0x114, 0xf>(0.0, x);
-    x += os_dpp<0x118, 0xf>(0.0, x);
-    x += os_dpp<0x142, 0xa>(0.0, x);
-    x += os_dpp<0x143, 0xc>(0.0, x);
-    return x;
-}
 // the wavefront's minimum (of finite values or infinities), in every lane
-__device__ __forceinline__ double os_last(double x) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
-                            __builtin_amdgcn_readlane(__double2loint(x), 63));
-}
 __device__ __forceinline__ double os_min(double x) {
-    x = fmin(x, os_dpp<0x111, 0xf>(x, x));
-    x = fmin(x, os_dpp<0x112, 0xf>(x, x));
-    x = fmin(x, os_dpp<0x114, 0xf>(x, x));
-    x = fmin(x, os_dpp<0x118, 0xf>(x, x));
-    x = fmin(x, os_dpp<0x142, 0xa>(x, x));
-    x = fmin(x, os_dpp<0x143, 0xc>(x, x));
-    return os_last(x);
+    x = fmin(x, wave_dpp<0x111, 0xf>(x, x));
+    x = fmin(x, wave_dpp<0x112, 0xf>(x, x));
+    x = fmin(x, wave_dpp<0x114, 0xf>(x, x));
+    x = fmin(x, wave_dpp<0x118, 0xf>(x, x));
+    x = fmin(x, wave_dpp<0x142, 0xa>(x, x));
+    x = fmin(x, wave_dpp<0x143, 0xc>(x, x));
+    return lane_f64(x, 63);
 }
 
 // s's biased exponent, and whether s is a normal number (then s = S 2^-sh)
@@ -185,7 +163,7 @@ __device__ double os_events(const double* st, double s, int lane) {
         } else if (os_normal(s, sh)) {
             const double x = ldexp(t, sh), r = rint(x);
             const double S = ldexp(s, sh);
-            const double P = os_scan_add(r);
+            const double P = wave_scan_dpp(r);
             const u64 bad = __ballot(!(fabs(x - r) < 0.5 && os_inside(S, P, P)));
             first = bad ? __builtin_ctzll(bad) : 64;
             if (first > 0) {
@@ -254,7 +232,7 @@ __device__ __forceinline__ double os_block_sum(u64 n, const Load& load, const Te
                     lo = fmin(lo, d);
                     hi = fmax(hi, d);
                 }
-                const double inc = os_scan_add(d);
+                const double inc = wave_scan_dpp(d);
                 const double before = inc - d;
                 const double wlo = os_min(before + lo), whi = -os_min(-(before + hi));
                 const bool all_exact = __ballot(!exact) == 0, all_zero = __ballot(!zero) == 0;

@@ -2197,6 +2197,11 @@ RowTileDesc rowtile_prepare(sfci_problem* P, const SigmaLaunch& v, double* D, un
 
 size_t rowtile_desc_bytes() { return sizeof(RTParams); }
 
+RowView rowtile_view(const RowTileDesc& d) {
+    const RTParams& p = *(const RTParams*)d.raw;
+    return RowView{p.rowbeg, p.rowend, p.v_beta, p.v_rb, p.T1, p.K4};
+}
+
 // One launch over n_inst instances whose descriptions (and the exclusive
 // prefix of their item counts, n_inst + 1 values) are already on the device.
 RowTileGeom rowtile_geom(const RowTileDesc* d, int n_inst) {

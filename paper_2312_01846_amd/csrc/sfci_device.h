@@ -161,6 +161,33 @@ __device__ __forceinline__ void wave_sync() {
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
+// Lane l's value, l uniform.
+__device__ __forceinline__ double lane_f64(double x, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
+// One step of a wavefront scan or reduction: the value CTRL selects from a
+// lower lane, `idle` where there is none (row_shr 1, 2, 4, 8 within rows of
+// 16 lanes, then the last lane of row 0 and 2 to the next, of row 1 to 2 and 3).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double wave_dpp(double idle, double x) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(idle), __double2loint(x), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(idle), __double2hiint(x), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+// Inclusive scan and sum (in every lane); all 64 lanes take part.
+__device__ __forceinline__ double wave_scan_dpp(double x) {
+    x += wave_dpp<0x111, 0xf>(0.0, x);
+    x += wave_dpp<0x112, 0xf>(0.0, x);
+    x += wave_dpp<0x114, 0xf>(0.0, x);
+    x += wave_dpp<0x118, 0xf>(0.0, x);
+    x += wave_dpp<0x142, 0xa>(0.0, x);
+    x += wave_dpp<0x143, 0xc>(0.0, x);
+    return x;
+}
+__device__ __forceinline__ double wave_sum_dpp(double x) { return lane_f64(wave_scan_dpp(x), 63); }
+
 // Pair index -> (x, y), 0 <= x < y < k, in lexicographic order.
 __device__ __forceinline__ uint16_t decode_pair(int idx, int k) {
     int x = 0;

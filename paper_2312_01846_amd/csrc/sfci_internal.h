@@ -178,6 +178,11 @@ void launch_unrank(sfci_problem* P, const u64* rank, u64 cnt, u64* a, u64* b, in
 void launch_backward_dense(sfci_problem* P, const SigmaLaunch& v, const double* D, double* vbar, double* dh, double* dg,
                            double* Rh, double* Rg);
 void launch_scatter_zero(sfci_problem* P, double* D, const u64* r, const u64* nnz, u64 cap);
+// The same from the row view of v and the beta-single table (backrows.hip),
+// where they are available; s_rank: the ranks of the cotangent, Rg = Rh + n^2.
+bool back_rows_available(sfci_problem* P, u64 nnz);
+void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
+                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg);
 
 // ---- target-owned dense sigma (rowtile.hip) ----
 bool rowtile_available(sfci_problem* P);  // builds the per-problem tables on first use
@@ -223,6 +228,14 @@ struct RowTileTune {
 // D need not be zero before the launch.
 RowTileDesc rowtile_prepare(sfci_problem* P, const SigmaLaunch& v, double* D, unsigned long long* emitted,
                             double eps = 0.0, bool ab_lists = false, bool full_rows = false);
+// The input view and tables a prepared description points to.
+struct RowView {
+    const u64 *rowbeg, *rowend;   // per alpha row: its entries
+    const u32 *v_beta, *v_rb;     // per entry: beta string, beta rank
+    const u32* T1;                // beta singles per beta rank (rowtile.hip)
+    const double* K4;             // same-spin double elements by orbital pairs
+};
+RowView rowtile_view(const RowTileDesc& d);
 size_t rowtile_desc_bytes();
 // Target alpha rows [lo, hi) of a prepared description only, written into
 // Dp[rank - lo * N_beta] (touched tiles are overwritten, the rest is left
