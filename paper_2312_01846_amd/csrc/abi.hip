@@ -286,7 +286,7 @@ sfci_status sfci_problem_destroy(sfci_problem* P) {
     for (hipEvent_t e : P->ev)
         if (e) (void)hipEventDestroy(e);
     rowtile_release(P);
-    for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd}) b->release();
+    for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd, &P->io_tab}) b->release();
     DevBuf* bufs[] = {&P->ws_sel,   &P->ws_cnt,   &P->ws_scan,  &P->ws_scan2,  &P->ws_scalar, &P->ws_red,
                       &P->ws_tup_k, &P->ws_tup_v, &P->ws_tup_k2, &P->ws_tup_v2, &P->ws_seg_v, &P->ws_seg_f,
                       &P->ws_src_cnt, &P->ws_src_off, &P->ws_hist, &P->ws_list_r, &P->ws_list_a, &P->ws_prod,
@@ -349,7 +349,10 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     if (!(opts->screen_eps >= 0.0) || !(opts->excite_eps >= 0.0))
         return (sfci_status)sfci_set_error(SFCI_E_ARG, "screen_eps and excite_eps must be >= 0");
     const u64 tps = terms_per_source(P->n, P->na, P->nb);
-    bool use_sort = opts->deterministic || opts->dedup == SFCI_DEDUP_SORT;
+    // deterministic: in order into the dense accumulator where that is possible, else by the sort path
+    const bool inorder = opts->deterministic && opts->dedup != SFCI_DEDUP_SORT && inorder_available(P, v->nnz) &&
+                         ensure_dense(P);
+    bool use_sort = !inorder && (opts->deterministic || opts->dedup == SFCI_DEDUP_SORT);
     bool list_tiles = false;  // no N_det array, fast: the tile kernel's slices may serve
     if (!use_sort && !ensure_dense(P)) {
         if (opts->dedup == SFCI_DEDUP_DENSE || opts->dedup == SFCI_DEDUP_DENSE_ATOMIC) {
@@ -367,7 +370,8 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
     // [0] nnz(v) [1] emitted [2] count [3] list count [4] validation flags
     u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));
-    const bool small = !use_sort && opts->dedup == SFCI_DEDUP_AUTO && opts->excite_eps == 0.0 && small_h_ready(P);
+    const bool small = !use_sort && !inorder && opts->dedup == SFCI_DEDUP_AUTO && opts->excite_eps == 0.0 &&
+                       small_h_ready(P);
     launch_fill_u64(scal, 8, 0, P->stream);
     SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
     if (use_sort) {
@@ -404,7 +408,8 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
         launch_small_sigma(P, opts->screen_eps);
     } else {
         launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
-        dense_sigma(P, sl, opts->dedup, (unsigned long long*)&scal[1], opts->screen_eps);
+        if (inorder) launch_sigma_inorder(P, sl, P->d_D, (unsigned long long*)&scal[1], opts->screen_eps);
+        else dense_sigma(P, sl, opts->dedup, (unsigned long long*)&scal[1], opts->screen_eps);
     }
     src.dense = P->d_D;
     // an output that holds whatever may be kept is written without waiting for the count
@@ -541,7 +546,8 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
     u64 lcap = 0;
     u64 *lr = nullptr;
     double* la = nullptr;
-    if (det && !list_mode) {
+    const bool inorder = det && !list_mode && inorder_available(P, cap);
+    if (det && !list_mode && !inorder) {
         lcap = std::min<u64>(P->Ndet, cap * tps);
         lr = (u64*)P->ws_list_r.get(lcap * sizeof(u64));
         la = (double*)P->ws_list_a.get(lcap * sizeof(double));
@@ -648,7 +654,10 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
                                           P->stream));
             SigmaLaunch sl{wj.r, wj.a, wj.nnz, cap};
             tsig.begin(P->stream);
-            if (det) {
+            if (inorder) {
+                launch_sigma_inorder(P, sl, P->d_D, (unsigned long long*)(sc + 32), o->screen_eps);
+                tsig.end(P->stream);
+            } else if (det) {
                 sigma_sorted(P, sl, lcap, lr, la, sc + 33, sc + 32);
                 tsig.end(P->stream);
                 launch_scatter_set(P, P->d_D, lr, la, sc + 33, lcap);

@@ -74,6 +74,7 @@ struct Inst {
     u64* psi_r;
     double* psi_a;
     double* sbar;
+    bool inorder;  // deterministic sigma without a sort
     u64 lcap;
     u64* lr;
     double* la;
@@ -228,7 +229,8 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
         q.psi_r = (u64*)P->ws_lz[5].get(pcap * sizeof(u64));
         q.psi_a = (double*)P->ws_lz[7].get(2 * pcap * sizeof(double));
         q.sbar = q.psi_a + pcap;
-        if (det) {
+        q.inorder = det && inorder_available(P, q.cap);
+        if (det && !q.inorder) {
             q.lcap = std::min<u64>(P->Ndet, q.cap * q.tps);
             q.lr = (u64*)P->ws_list_r.get(q.lcap * sizeof(u64));
             q.la = (double*)P->ws_list_a.get(q.lcap * sizeof(double));
@@ -412,7 +414,9 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             Inst& q = I[k];
             DVec w = q.W(j);
             SigmaLaunch sl{w.r, w.a, w.nnz, w.cap};
-            if (det) {
+            if (q.inorder) {
+                launch_sigma_inorder(q.P, sl, q.P->d_D, (unsigned long long*)(q.sc + 32), o->screen_eps);
+            } else if (det) {
                 sigma_sorted(q.P, sl, q.lcap, q.lr, q.la, q.sc + 33, q.sc + 32);
                 launch_scatter_set(q.P, q.P->d_D, q.lr, q.la, q.sc + 33, q.lcap);
                 if (o->screen_eps > 0.0) launch_screen(q.P, q.P->d_D, q.P->Ndet, o->screen_eps);

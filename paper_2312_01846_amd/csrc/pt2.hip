@@ -199,16 +199,19 @@ unsigned grid_of(u64 n) {
 
 }  // namespace
 
-// H Psi as a rank-sorted list: the sort path (deterministic, or when the
-// N_det array does not fit) or the dense tile kernel compacted in rank order.
+// H Psi as a rank-sorted list: the dense accumulator compacted in rank order
+// (the in-order kernel in deterministic mode, the tile kernel otherwise), or
+// the sort path where those do not apply.
 u64 sigma_full_list(sfci_problem* P, const SigmaLaunch& sl, bool det, u64* emitted, u64** yr, double** ya,
                     u64* cnt_dev) {
-    if (det || !ensure_dense(P)) {
+    const bool inorder = det && inorder_available(P, sl.cap) && ensure_dense(P);
+    if (!inorder && (det || !ensure_dense(P))) {
         const u64 n = sigma_list_full(P, sl, emitted, yr, ya);
         launch_set_u64(P, cnt_dev, n);
         return n;
     }
-    dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)emitted);
+    if (inorder) launch_sigma_inorder(P, sl, P->d_D, (unsigned long long*)emitted, 0.0);
+    else dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)emitted);
     CandSrc src{};
     src.dense = P->d_D;
     select_prepare(P, src, UINT64_MAX, cnt_dev);

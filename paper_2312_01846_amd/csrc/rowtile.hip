@@ -1954,6 +1954,11 @@ const u32* rowtile_T1(sfci_problem* P) {
     return rowtile_available(P) ? rt_state(P)->d_T1 : nullptr;
 }
 
+RowTables rowtile_tables(sfci_problem* P) {
+    const RowTileState* S = rt_state(P);
+    return RowTables{S->d_T1, S->d_TS, S->d_T2r, S->d_T2e, S->d_K, S->d_K4};
+}
+
 bool rowtile_available(sfci_problem* P) {
     // the packed single-excitation table holds a target beta rank in 21 bits
     if (P->n > 32 || P->nb * (P->n - P->nb) > SFCI_MAX_SINGLES || P->Nb >= (1ull << 21)) return false;

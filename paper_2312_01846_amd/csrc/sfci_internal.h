@@ -128,6 +128,8 @@ struct sfci_problem {
     DevBuf ws_cand_r, ws_cand_a;  // top-M of a dense source: its candidates
     DevBuf sh_idx, sh_val, sh_nz, sh_vd;  // small spaces (smallh.hip): H by rows, terms per column, dense v
     int sh_state = 0;                     // 0 untried, 1 built, -1 the space is too large
+    DevBuf io_tab;      // in-order sigma: alpha strings, nonzero (ia|..) slabs
+    int io_state = 0;   // 0 untried, 1 available, -1 not
     hipEvent_t ev[2] = {nullptr, nullptr};  // around a call, created on first use
     int sel_mode = 0;             // what select_prepare left for select_write (select.hip)
     CandSrc sel_src{};
@@ -236,6 +238,19 @@ struct RowView {
     const double* K4;             // same-spin double elements by orbital pairs
 };
 RowView rowtile_view(const RowTileDesc& d);
+// The per-problem tables (rowtile_available(P) must hold; T2 may be NULL).
+struct RowTables {
+    const u32* T1;
+    const double* TS;
+    const u32* T2r;
+    const double *T2e, *K2, *K4;
+};
+RowTables rowtile_tables(sfci_problem* P);
+// Deterministic sigma into D, every row written, without a sort (inorder.hip):
+// where a target row fits in LDS, the alpha strings are at most 65 536 and nnz
+// entries are worth writing N_det sums.
+bool inorder_available(sfci_problem* P, u64 nnz);
+void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, double* D, unsigned long long* emitted, double eps);
 size_t rowtile_desc_bytes();
 // Target alpha rows [lo, hi) of a prepared description only, written into
 // Dp[rank - lo * N_beta] (touched tiles are overwritten, the rest is left
