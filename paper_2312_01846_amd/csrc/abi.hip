@@ -286,7 +286,7 @@ sfci_status sfci_problem_destroy(sfci_problem* P) {
     for (hipEvent_t e : P->ev)
         if (e) (void)hipEventDestroy(e);
     rowtile_release(P);
-    for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd, &P->io_tab}) b->release();
+    for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd, &P->io_tab, &P->ws_os}) b->release();
     DevBuf* bufs[] = {&P->ws_sel,   &P->ws_cnt,   &P->ws_scan,  &P->ws_scan2,  &P->ws_scalar, &P->ws_red,
                       &P->ws_tup_k, &P->ws_tup_v, &P->ws_tup_k2, &P->ws_tup_v2, &P->ws_seg_v, &P->ws_seg_f,
                       &P->ws_src_cnt, &P->ws_src_off, &P->ws_hist, &P->ws_list_r, &P->ws_list_a, &P->ws_prod,

@@ -92,8 +92,7 @@ __global__ __launch_bounds__(RB) void k_dot_final(const double* __restrict__ par
 // (os_events), or term by term where such terms are frequent.
 // Bound by: added one by one, the latency of the chain (~17 cycles a term:
 // 7.34 ms for 1e6 squares); this way the loads and reductions of one compute
-// unit (0.69 ms; truncation of 4e6 entries to 1e6 with its norm 7.94 -> 1.00
-// ms).  Sums that wander about zero leave their binade every few dozen terms
+// unit (0.69 ms); long sums are spread over the chip (launch_ordered).  Sums that wander about zero leave their binade every few dozen terms
 // and gain little.
 enum { OS_SUM = 0, OS_DOT = 1, OS_SUMSQ = 2 };
 constexpr int OS_WAVES = 8;
@@ -191,22 +190,42 @@ struct OsChunk {
     int pad;
 };
 
-// The sum of the n terms term(i, x, y) of the values load(i, x, y) reads, the
-// same in every thread.
+// A lane's OS_K terms and, over the wavefront, its chunk's: 1 / unit = 2^sh.
+__device__ __forceinline__ OsChunk os_chunk(const double (&t)[OS_K], int sh, bool normal) {
+    double d = 0.0, lo = INFINITY, hi = -INFINITY;
+    bool exact = true, zero = true;
+#pragma unroll
+    for (int k = 0; k < OS_K; ++k) {
+        const double v = ldexp(t[k], sh), r = rint(v);
+        exact = exact && fabs(v - r) < 0.5;
+        zero = zero && t[k] == 0.0;
+        d += r;
+        lo = fmin(lo, d);
+        hi = fmax(hi, d);
+    }
+    const double inc = wave_scan_dpp(d);
+    const double before = inc - d;
+    const double wlo = os_min(before + lo), whi = -os_min(-(before + hi));
+    const bool all_exact = __ballot(!exact) == 0, all_zero = __ballot(!zero) == 0;
+    return OsChunk{inc, wlo, whi, all_zero ? 2 : (all_exact && normal ? 1 : 0), 0};  // d in lane 63
+}
+
+// s and, after it, the terms term(x, y), first <= i < n, of the values
+// load(i, x, y) reads, the same in every thread.
 template <class Load, class Term>
-__device__ __forceinline__ double os_block_sum(u64 n, const Load& load, const Term& term) {
+__device__ __forceinline__ double os_block_sum(u64 n, const Load& load, const Term& term, u64 first = 0,
+                                               double s = 0.0) {
     __shared__ double stage[OS_WAVES][OS_PAD];
     __shared__ OsChunk ch[2][OS_WAVES];
     __shared__ double s_next;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double* const st = stage[wave];
-    double s = 0.0;
     double x[OS_K], y[OS_K];
     const u64 mine = (u64)wave * OS_CHUNK + lane;
 #pragma unroll
-    for (int k = 0; k < OS_K; ++k) load(mine + (u64)k * 64, x[k], y[k]);
+    for (int k = 0; k < OS_K; ++k) load(first + mine + (u64)k * 64, x[k], y[k]);
     int par = 0;
-    for (u64 base = 0; base < n; base += OS_STEP) {
+    for (u64 base = first; base < n; base += OS_STEP) {
         // coalesced loads, then each lane's OS_K consecutive terms by way of LDS
 #pragma unroll
         for (int k = 0; k < OS_K; ++k) st[os_slot(k * 64 + lane)] = term(x[k], y[k]);
@@ -221,22 +240,8 @@ __device__ __forceinline__ double os_block_sum(u64 n, const Load& load, const Te
             int sh;
             const bool normal = os_normal(s, sh);
             if (wave >= w0) {
-                double d = 0.0, lo = INFINITY, hi = -INFINITY;
-                bool exact = true, zero = true;
-#pragma unroll
-                for (int k = 0; k < OS_K; ++k) {
-                    const double v = ldexp(t[k], sh), r = rint(v);
-                    exact = exact && fabs(v - r) < 0.5;
-                    zero = zero && t[k] == 0.0;
-                    d += r;
-                    lo = fmin(lo, d);
-                    hi = fmax(hi, d);
-                }
-                const double inc = wave_scan_dpp(d);
-                const double before = inc - d;
-                const double wlo = os_min(before + lo), whi = -os_min(-(before + hi));
-                const bool all_exact = __ballot(!exact) == 0, all_zero = __ballot(!zero) == 0;
-                if (lane == 63) ch[par][wave] = OsChunk{inc, wlo, whi, all_zero ? 2 : (all_exact && normal ? 1 : 0), 0};
+                const OsChunk c = os_chunk(t, sh, normal);
+                if (lane == 63) ch[par][wave] = c;
             }
             __syncthreads();
             double S = normal ? ldexp(s, sh) : 0.0;
@@ -264,21 +269,147 @@ __device__ __forceinline__ double os_block_sum(u64 n, const Load& load, const Te
 }
 
 template <int MODE>
+struct OsTerms {
+    const u64* r;
+    const double *a, *D;
+    u64 n;
+    __device__ __forceinline__ void operator()(u64 i, double& x, double& y) const {
+        x = 0.0;
+        y = 0.0;
+        if (i < n) {
+            x = a[i];
+            if (MODE == OS_DOT) y = D[r[i]];
+        }
+    }
+    static __device__ __forceinline__ double term(double x, double y) {
+        return MODE == OS_SUM ? x : (MODE == OS_SUMSQ ? x * x : x * y);
+    }
+};
+
+template <int MODE>
 __global__ __launch_bounds__(OS_BLOCK) void k_ordered(const u64* __restrict__ r, const double* __restrict__ a,
                                                       const u64* __restrict__ nnz, const double* __restrict__ D,
                                                       double* out1, double* out2) {
     const u64 n = *nnz;
-    const double s = os_block_sum(
-        n,
-        [&](u64 i, double& x, double& y) {
-            x = 0.0;
-            y = 0.0;
-            if (i < n) {
-                x = a[i];
-                if (MODE == OS_DOT) y = D[r[i]];
+    const double s = os_block_sum(n, OsTerms<MODE>{r, a, D, n}, OsTerms<MODE>::term);
+    if (threadIdx.x == 0) {
+        *out1 = s;
+        if (out2) *out2 = s;
+    }
+}
+
+// Long sums over the chip: blocks of span terms (at most OS_BLOCKS of them)
+// are summed in any order, which tells the binade s will be in when a block
+// begins; each block is then reduced as if s were in it, and one workgroup
+// applies the blocks in order, going through the terms only of those that do
+// not fit (another binade, a tie, a prefix that leaves it).  The result does
+// not depend on the guess.  Bound by: the blocks gone through again, ~3 us per
+// 4096 terms (1e6 squares in 0.14 ms, 0.69 by one workgroup; truncation of 4e6
+// entries to 1e6 with its norm 0.91 -> 0.32 ms).
+constexpr int OS_BLOCKS = 256;
+
+struct OsBlock {
+    OsChunk c;
+    int sh, pad;
+};
+
+template <int MODE>
+__global__ __launch_bounds__(OS_BLOCK) void k_os_guess(const u64* __restrict__ r, const double* __restrict__ a,
+                                                       const u64* __restrict__ nnz, const double* __restrict__ D,
+                                                       u64 span, double* __restrict__ guess) {
+    __shared__ double part[OS_WAVES];
+    const u64 n = *nnz, b = (u64)blockIdx.x * span, e = min(n, b + span);
+    const OsTerms<MODE> load{r, a, D, n};
+    double s = 0.0;
+    for (u64 i = b + threadIdx.x; i < e; i += OS_BLOCK) {
+        double x, y;
+        load(i, x, y);
+        s += OsTerms<MODE>::term(x, y);
+    }
+    s = wave_sum_dpp(s);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < OS_WAVES; ++w) s += part[w];
+        guess[blockIdx.x] = s;
+    }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(OS_BLOCK) void k_os_blocks(const u64* __restrict__ r, const double* __restrict__ a,
+                                                        const u64* __restrict__ nnz, const double* __restrict__ D,
+                                                        u64 span, const double* __restrict__ guess,
+                                                        OsBlock* __restrict__ out) {
+    __shared__ double stage[OS_WAVES][OS_PAD], part[OS_WAVES];
+    __shared__ OsChunk ch[OS_WAVES];
+    const u64 n = *nnz, b = (u64)blockIdx.x * span, e = min(n, b + span);
+    if (b >= e) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double g = threadIdx.x < blockIdx.x ? guess[threadIdx.x] : 0.0;
+    g = wave_sum_dpp(g);
+    if (lane == 0) part[wave] = g;
+    __syncthreads();
+    double s = part[0];
+    for (int w = 1; w < OS_WAVES; ++w) s += part[w];
+    int sh;
+    const bool normal = os_normal(s, sh);
+    const OsTerms<MODE> load{r, a, D, e};
+    double* const st = stage[wave];
+    OsChunk all{0.0, INFINITY, -INFINITY, 2, 0};
+    for (u64 base = b; base < e; base += OS_STEP) {
+#pragma unroll
+        for (int k = 0; k < OS_K; ++k) {
+            double x, y;
+            load(base + (u64)wave * OS_CHUNK + lane + (u64)k * 64, x, y);
+            st[os_slot(k * 64 + lane)] = OsTerms<MODE>::term(x, y);
+        }
+        wave_sync();
+        double t[OS_K];
+#pragma unroll
+        for (int k = 0; k < OS_K; ++k) t[k] = st[lane * (OS_K + 1) + k];
+        const OsChunk c = os_chunk(t, sh, normal);
+        __syncthreads();
+        if (lane == 63) ch[wave] = c;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int w = 0; w < OS_WAVES; ++w) {
+                const OsChunk q = ch[w];
+                if (q.ok == 2) continue;
+                all.ok = q.ok == 1 && all.ok != 0 ? 1 : 0;
+                all.lo = fmin(all.lo, all.d + q.lo);
+                all.hi = fmax(all.hi, all.d + q.hi);
+                all.d += q.d;
             }
-        },
-        [](double x, double y) { return MODE == OS_SUM ? x : (MODE == OS_SUMSQ ? x * x : x * y); });
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = OsBlock{all, sh, 0};
+}
+
+template <int MODE>
+__global__ __launch_bounds__(OS_BLOCK) void k_os_apply(const u64* __restrict__ r, const double* __restrict__ a,
+                                                       const u64* __restrict__ nnz, const double* __restrict__ D,
+                                                       u64 span, const OsBlock* __restrict__ blocks, double* out1,
+                                                       double* out2) {
+    __shared__ OsBlock bl[OS_BLOCKS];
+    const u64 n = *nnz;
+    const int nb = (int)((n + span - 1) / span);
+    for (int t = threadIdx.x; t < nb; t += OS_BLOCK) bl[t] = blocks[t];
+    __syncthreads();
+    double s = 0.0;
+    for (int b = 0; b < nb; ++b) {
+        const OsBlock q = bl[b];
+        if (q.c.ok == 2) continue;
+        int sh;
+        if (q.c.ok == 1 && os_normal(s, sh) && sh == q.sh) {
+            const double S = ldexp(s, sh);
+            if (os_inside(S, q.c.lo, q.c.hi)) {
+                s = ldexp(S + q.c.d, -sh);
+                continue;
+            }
+        }
+        __syncthreads();  // the last call's LDS
+        const u64 e = min(n, (u64)(b + 1) * span);
+        s = os_block_sum(e, OsTerms<MODE>{r, a, D, e}, OsTerms<MODE>::term, (u64)b * span, s);
+    }
     if (threadIdx.x == 0) {
         *out1 = s;
         if (out2) *out2 = s;
@@ -703,10 +834,34 @@ unsigned gsz(u64 cap) {
 
 }  // namespace
 
+// In-order sum of up to cap terms.  From OS_LONG on over the chip: 1e6 squares
+// 0.69 ms by one workgroup, 0.14 this way; 1e5 squares with a binade change or
+// tie in most blocks 75 and 71 us, so that shorter sums gain nothing.
+constexpr u64 OS_LONG = 65536;
+
+template <int MODE>
+static void launch_ordered(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
+                           double* out1, double* out2) {
+    if (cap < OS_LONG) {
+        hipLaunchKernelGGL(k_ordered<MODE>, dim3(1), dim3(OS_BLOCK), 0, P->stream, r, a, nnz, D, out1, out2);
+        return;
+    }
+    const u64 steps = (cap + OS_STEP - 1) / OS_STEP, per = (steps + OS_BLOCKS - 1) / OS_BLOCKS;
+    const u64 span = per * OS_STEP;
+    const unsigned nb = (unsigned)((cap + span - 1) / span);
+    double* guess = (double*)P->ws_os.get(OS_BLOCKS * (sizeof(double) + sizeof(OsBlock)));
+    OsBlock* blocks = (OsBlock*)(guess + OS_BLOCKS);
+    hipLaunchKernelGGL(k_os_guess<MODE>, dim3(nb), dim3(OS_BLOCK), 0, P->stream, r, a, nnz, D, span, guess);
+    hipLaunchKernelGGL(k_os_blocks<MODE>, dim3(nb), dim3(OS_BLOCK), 0, P->stream, r, a, nnz, D, span,
+                       (const double*)guess, blocks);
+    hipLaunchKernelGGL(k_os_apply<MODE>, dim3(1), dim3(OS_BLOCK), 0, P->stream, r, a, nnz, D, span,
+                       (const OsBlock*)blocks, out1, out2);
+}
+
 void launch_dot_dense(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, const double* D,
                       double* out1, double* out2, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_DOT>, dim3(1), dim3(OS_BLOCK), 0, P->stream, r, a, nnz, D, out1, out2);
+        launch_ordered<OS_DOT>(P, r, a, nnz, cap, D, out1, out2);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
         unsigned g = std::min<unsigned>(RGRID, gsz(cap));
@@ -718,8 +873,7 @@ void launch_dot_dense(sfci_problem* P, const u64* r, const double* a, const u64*
 
 void launch_sum(sfci_problem* P, const double* x, const u64* nnz, u64 cap, double* out, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_SUM>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, x, nnz,
-                           (const double*)nullptr, out, (double*)nullptr);
+        launch_ordered<OS_SUM>(P, nullptr, x, nnz, cap, nullptr, out, nullptr);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
         unsigned g = std::min<unsigned>(RGRID, gsz(cap));
@@ -731,8 +885,7 @@ void launch_sum(sfci_problem* P, const double* x, const u64* nnz, u64 cap, doubl
 
 void launch_sumsq(sfci_problem* P, const double* a, const u64* nnz, u64 cap, double* out, bool ordered) {
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, a, nnz,
-                           (const double*)nullptr, out, (double*)nullptr);
+        launch_ordered<OS_SUMSQ>(P, nullptr, a, nnz, cap, nullptr, out, nullptr);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
         unsigned g = std::min<unsigned>(RGRID, gsz(cap));
@@ -747,8 +900,7 @@ void launch_dot_sparse(sfci_problem* P, const u64* xr, const double* xa, const u
     if (ordered) {
         double* prod = (double*)P->ws_prod.get(std::max<u64>(1, xcap) * sizeof(double));
         hipLaunchKernelGGL(k_sparse_products, dim3(gsz(xcap)), dim3(RB), 0, P->stream, xr, xa, xn, yr, ya, yn, prod);
-        hipLaunchKernelGGL(k_ordered<OS_SUM>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr,
-                           (const double*)prod, xn, (const double*)nullptr, out1, out2);
+        launch_ordered<OS_SUM>(P, nullptr, prod, xn, xcap, nullptr, out1, out2);
     } else {
         double* part = (double*)P->ws_red.get(RGRID * sizeof(double));
         unsigned g = std::min<unsigned>(RGRID, gsz(xcap));
@@ -798,8 +950,10 @@ void launch_normalise(sfci_problem* P, double* a, const u64* nnz, u64 cap, bool 
     double* part = part_ws ? part_ws : (double*)P->ws_red.get((RGRID + 8) * sizeof(double));
     double* ss = part + RGRID;
     if (ordered) {
-        hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, a, nnz,
-                           (const double*)nullptr, ss, (double*)nullptr);
+        if (part_ws)  // the caller's scratch holds no more
+            hipLaunchKernelGGL(k_ordered<OS_SUMSQ>, dim3(1), dim3(OS_BLOCK), 0, P->stream, (const u64*)nullptr, a, nnz,
+                               (const double*)nullptr, ss, (double*)nullptr);
+        else launch_ordered<OS_SUMSQ>(P, nullptr, a, nnz, cap, nullptr, ss, nullptr);
     } else {
         unsigned g = std::min<unsigned>(RGRID, gsz(cap));
         hipLaunchKernelGGL(k_sumsq_part, dim3(g), dim3(RB), 0, P->stream, a, nnz, part);

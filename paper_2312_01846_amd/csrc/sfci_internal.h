@@ -128,6 +128,7 @@ struct sfci_problem {
     DevBuf ws_cand_r, ws_cand_a;  // top-M of a dense source: its candidates
     DevBuf sh_idx, sh_val, sh_nz, sh_vd;  // small spaces (smallh.hip): H by rows, terms per column, dense v
     int sh_state = 0;                     // 0 untried, 1 built, -1 the space is too large
+    DevBuf ws_os;       // blocks of a long in-order sum
     DevBuf io_tab;      // in-order sigma: alpha strings, nonzero (ia|..) slabs
     int io_state = 0;   // 0 untried, 1 available, -1 not
     hipEvent_t ev[2] = {nullptr, nullptr};  // around a call, created on first use
