@@ -1,8 +1,9 @@
 // The SFCI iteration (Sec. 2.1) without a dense N_det array: every vector is
 // a rank-sorted (rank, amplitude) list and sigma = H w_j comes one alpha-rank
 // range at a time (Sec. 2.2's buckets, restricted to the spin-up string as in
-// Sec. 3) from the sort path, or in fast mode from the tile kernel in row
-// slices when the input is large enough (list_sigma_tiles).  This is what runs
+// Sec. 3) from the sort path, or in fast mode by target rows: all through the
+// tile kernel when the input is large enough (list_sigma_tiles), else only the
+// rows of many terms, the others through hash tables (sigma_row_passes).  This is what runs
 // when 8 N_det bytes do not fit the device (12 electrons in 28 orbitals:
 // 1.14 TB).
 //
@@ -184,10 +185,11 @@ __global__ void k_add_two(u64* __restrict__ Rn, const u64* __restrict__ a, const
 
 // After cutting the candidate list back: its length, and the bound a later
 // entry must beat (the smallest |c| among the K selected).
-__global__ void k_after_cut(const SelState* __restrict__ st, u64* __restrict__ Rn, u64* __restrict__ bound_bits) {
+__global__ void k_after_cut(const SelState* __restrict__ st, u64* __restrict__ Rn, u64* __restrict__ bound_bits,
+                            int ties) {
     if (threadIdx.x == 0) {
         *Rn = st->count_out;
-        if (!st->take_all && st->cmin != ~0ull) *bound_bits = st->cmin;
+        if (!st->take_all && st->cmin != ~0ull) *bound_bits = st->cmin - (ties && st->cmin ? 1 : 0);
     }
 }
 
@@ -315,6 +317,7 @@ struct ListCands {
     u64* Rn;        // device: list length
     u64* bound;     // device: |c| bits a new entry must exceed
     int* overflow;  // device flag
+    bool ties = false;  // entries that equal the bound join too (ranks do not come in order)
 
     u64* Rr() { return (u64*)ws.Rr.p; }
     double* Ra() { return (double*)ws.Ra.p; }
@@ -324,6 +327,7 @@ struct ListCands {
         launch_fill_u64(Rn, 1, 0, P->stream);
         launch_fill_u64(bound, 1, 0, P->stream);
         n_upper = 0;
+        ties = false;
     }
     void ensure(u64 more) {
         const u64 need = n_upper + more + reserve;
@@ -348,7 +352,8 @@ struct ListCands {
         src.lcap = n;
         select_prepare(P, src, K, nullptr);
         select_write(P, src, r2, a2, false);
-        hipLaunchKernelGGL(k_after_cut, dim3(1), dim3(64), 0, P->stream, (const SelState*)P->ws_sel.p, Rn, bound);
+        hipLaunchKernelGGL(k_after_cut, dim3(1), dim3(64), 0, P->stream, (const SelState*)P->ws_sel.p, Rn, bound,
+                           ties ? 1 : 0);
         n_upper = read_dev(P, Rn);
         SFCI_CHECK_HIP(hipMemcpyAsync(Rr(), r2, n_upper * sizeof(u64), hipMemcpyDeviceToDevice, P->stream));
         SFCI_CHECK_HIP(hipMemcpyAsync(Ra(), a2, n_upper * sizeof(double), hipMemcpyDeviceToDevice, P->stream));
@@ -402,6 +407,16 @@ struct ListPassSink : SortPassSink {
     }
 };
 
+// From how many terms a target row goes to the tile kernel, whose items cost
+// the same whatever they receive, rather than to the hash tables, which walk a
+// long row's terms once per part.  An iteration at 28 orbitals, M = 50 000 (24
+// tiles per row): 178 ms with 400 terms per tile, 124 with 800, 123 with 1 600
+// and 3 200, 285 with 6 400.  SFCI_LIST_HEAVY=terms sets it for a row.
+u64 heavy_row_terms(sfci_problem* P) {
+    if (const char* env = getenv("SFCI_LIST_HEAVY")) return (u64)strtoull(env, nullptr, 10);
+    return 1600 * (u64)rowtile_ntiles(P);
+}
+
 // How many of the best entries the running candidate list must keep so that
 // the final selection sees all it needs: M (at least 1), and with the tie
 // band its reach plus one more, which tells whether the band overflows.
@@ -425,9 +440,92 @@ void sort_by_rank(sfci_problem* P, u64* r, double* a, u64 n) {
     }
 }
 
+// The tile kernel's passes whose finished tiles are consumed in the kernel
+// (FusedOut): the T gathers, the marks of supp(w_j) U supp(w_{j-1}), the
+// candidate appends above the running bound.  A pass whose appends overflow the
+// candidate list is run again after the list has grown.
+struct FusedPasses {
+    sfci_problem* P;
+    ListPassSink& sink;
+    u64* emitted;
+    RowTileDesc all;
+    FusedOut h{};
+    FusedOut* d_fo;
+    u64 room;
+
+    FusedPasses(sfci_problem* P_, const SigmaLaunch& v, ListPassSink& sink_, u64* emitted_dev, double eps)
+        : P(P_), sink(sink_), emitted(emitted_dev),
+          all(rowtile_prepare(P_, v, nullptr, (unsigned long long*)emitted_dev, eps, true)) {
+        ListWs& ws = P->list_ws;
+        ListCands& C = *sink.cands;
+        const int nl = sink.nl;
+        u64* rowptr = (u64*)ws.rowptr.get((size_t)std::max(1, nl) * (P->Na + 1) * sizeof(u64));
+        const unsigned gr = (unsigned)std::min<u64>((P->Na + 256) / 256, 16384);
+        for (int l = 0; l < nl; ++l)
+            hipLaunchKernelGGL(k_row_ptrs, dim3(gr), dim3(256), 0, P->stream, sink.Wr + (size_t)l * sink.cap,
+                               sink.nnz + l, P->Na, P->Nb, rowptr + (size_t)l * (P->Na + 1));
+        SFCI_CHECK_HIP(hipGetLastError());
+        h.Wr = sink.Wr;
+        h.rowptr = rowptr;
+        h.Y = sink.Y;
+        h.cap = sink.cap;
+        h.na_rows = P->Na;
+        h.nl = nl;
+        h.mark_from = sink.mark_from;
+        h.collect = sink.collect ? 1 : 0;
+        h.bound = C.bound;
+        h.Rn = C.Rn;
+        h.overflow = C.overflow;
+        h.distinct = sink.distinct;
+        d_fo = (FusedOut*)ws.fo.get(sizeof(FusedOut));
+        room = std::max<u64>(1ull << 24, 4 * std::min<u64>(C.K, 1ull << 26));
+    }
+
+    // Target rows [lo, hi), or rows[lo .. hi) of a device list; through the
+    // tile kernel, or (hash) through the hash tables.
+    void pass(u64 lo, u64 hi, const u32* rows, const SigmaLaunch* hash = nullptr, double eps = 0.0,
+              bool small = false) {
+        ListCands& C = *sink.cands;
+        u32 more = 1;
+        for (u64 extra = 0;;) {
+            if (sink.collect) C.ensure(room + extra);
+            h.Rr = C.Rr();
+            h.Ra = C.Ra();
+            h.Rcap = C.cap();
+            const u64 n_before = C.n_upper;
+            const u64 dist_before = sink.distinct ? read_dev(P, sink.distinct) : 0;
+            const u64 emit_before = emitted ? read_dev(P, emitted) : 0;
+            SFCI_CHECK_HIP(hipMemcpyAsync(d_fo, &h, sizeof(h), hipMemcpyHostToDevice, P->stream));
+            // (both synchronise the stream)
+            if (hash) launch_hash_rows(P, *hash, all, lo, hi, rows, d_fo, (unsigned long long*)emitted, eps, more,
+                                       small);
+            else launch_sigma_rowtile_rows_fused(P, all, lo, hi, d_fo, rows);
+            if (!sink.collect && !hash) return;
+            int ovf = 0;
+            SFCI_CHECK_HIP(hipMemcpyAsync(&ovf, C.overflow, sizeof(int), hipMemcpyDeviceToHost, P->stream));
+            SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+            if (!ovf) break;
+            // run the pass again with room for what it appends
+            const u64 need = (ovf & 1) ? read_dev(P, C.Rn) - n_before : 0;
+            if (ovf & 2) more *= 2;
+            if (more > 1024) throw sfci_error(-5, "list path: a row's part does not fit its table");
+            launch_fill_u64(C.Rn, 1, n_before, P->stream);
+            launch_fill_u64((u64*)C.overflow, 1, 0, P->stream);
+            if (sink.distinct) launch_fill_u64(sink.distinct, 1, dist_before, P->stream);
+            if (emitted) launch_fill_u64(emitted, 1, emit_before, P->stream);
+            extra = std::max(extra, need + need / 4);
+        }
+        if (!sink.collect) return;
+        C.n_upper = read_dev(P, C.Rn);
+        C.maybe_cut();
+    }
+};
+
 }  // namespace
 
 u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps);
+u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps);
+bool list_sigma_rows(sfci_problem* P);
 
 u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank, double* out_amp, u64 out_cap,
                     u64* emitted_dev, u64* distinct_host, bool tiles_ok, double eps) {
@@ -444,6 +542,8 @@ u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank,
     sink.distinct = ls + 4;
     if (tiles_ok && list_sigma_tiles(P, read_dev(P, v.v_nnz)))
         sigma_dense_passes(P, v, sink, emitted_dev, eps);
+    else if (tiles_ok && list_sigma_rows(P))
+        sigma_row_passes(P, v, sink, emitted_dev, eps);
     else
         sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
     check_overflow(P, (const int*)(ls + 3));
@@ -465,12 +565,16 @@ u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank,
 }
 
 // Which passes sigma takes in fast mode.  The tile kernel pays a fixed cost
-// per (target row, tile) item (its neighbour records) plus ~2.2e-11 s per term;
-// the sort path ~4.2e-11 s per term and nothing per item (measured at 28
-// orbitals, M = 1e6 and 1e7: the item cost is ~1.2e-7 s).  The tile kernel is
-// taken once terms exceed ~5 700 per item.  SFCI_LIST_SIGMA=tile|sort forces
-// one kind.
+// per (target row, tile) item (its neighbour records), ~1.2e-7 s at 28 orbitals,
+// plus ~2.2e-11 s per term; all rows go to it once terms exceed ~5 700 per item.
+// SFCI_LIST_SIGMA=tile|sort forces tiles for all rows or the sort path.
 constexpr double kSortTermsPerTileItem = 5700.0;
+
+// Otherwise by rows, unless the sort path is asked for.
+bool list_sigma_rows(sfci_problem* P) {
+    const char* env = getenv("SFCI_LIST_SIGMA");
+    return rowtile_available(P) && !(env && !strcmp(env, "sort"));
+}
 
 bool list_sigma_tiles(sfci_problem* P, u64 nnz) {
     if (!rowtile_available(P)) return false;
@@ -495,60 +599,12 @@ u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink
     ListWs& ws = P->list_ws;
     const char* fenv = getenv("SFCI_LIST_FUSED");
     if (!(fenv && fenv[0] == '0')) {
-        const RowTileDesc all = rowtile_prepare(P, v, nullptr, (unsigned long long*)emitted_dev, eps, true);
-        ListCands& C = *sink.cands;
-        const int nl = sink.nl;
-        u64* rowptr = (u64*)ws.rowptr.get((size_t)std::max(1, nl) * (P->Na + 1) * sizeof(u64));
-        const unsigned gr = (unsigned)std::min<u64>((P->Na + 256) / 256, 16384);
-        for (int l = 0; l < nl; ++l)
-            hipLaunchKernelGGL(k_row_ptrs, dim3(gr), dim3(256), 0, P->stream, sink.Wr + (size_t)l * sink.cap,
-                               sink.nnz + l, P->Na, P->Nb, rowptr + (size_t)l * (P->Na + 1));
-        SFCI_CHECK_HIP(hipGetLastError());
-        FusedOut h{};
-        h.Wr = sink.Wr;
-        h.rowptr = rowptr;
-        h.Y = sink.Y;
-        h.cap = sink.cap;
-        h.na_rows = P->Na;
-        h.nl = nl;
-        h.mark_from = sink.mark_from;
-        h.collect = sink.collect ? 1 : 0;
-        h.bound = C.bound;
-        h.Rn = C.Rn;
-        h.overflow = C.overflow;
-        h.distinct = sink.distinct;
-        FusedOut* d_fo = (FusedOut*)ws.fo.get(sizeof(FusedOut));
-        const u64 room = std::max<u64>(1ull << 24, 4 * std::min<u64>(C.K, 1ull << 26));
-        u64 lo = 0, passes = 0, extra = 0;
-        while (lo < P->Na) {
+        FusedPasses F(P, v, sink, emitted_dev, eps);
+        u64 lo = 0, passes = 0;
+        for (; lo < P->Na; ++passes) {
             const u64 rows = std::max<u64>(1, passes == 0 ? P->Na / 64 : P->Na / 8);
             const u64 hi = std::min<u64>(P->Na, lo + rows);
-            if (sink.collect) C.ensure(room + extra);
-            h.Rr = C.Rr();
-            h.Ra = C.Ra();
-            h.Rcap = C.cap();
-            const u64 n_before = C.n_upper;
-            const u64 dist_before = sink.distinct ? read_dev(P, sink.distinct) : 0;
-            SFCI_CHECK_HIP(hipMemcpyAsync(d_fo, &h, sizeof(h), hipMemcpyHostToDevice, P->stream));
-            launch_sigma_rowtile_rows_fused(P, all, lo, hi, d_fo);  // synchronises the stream
-            if (sink.collect) {
-                int ovf = 0;
-                SFCI_CHECK_HIP(hipMemcpyAsync(&ovf, C.overflow, sizeof(int), hipMemcpyDeviceToHost, P->stream));
-                SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
-                if (ovf) {
-                    // run the pass again with room for what it appends
-                    const u64 need = read_dev(P, C.Rn) - n_before;
-                    launch_fill_u64(C.Rn, 1, n_before, P->stream);
-                    launch_fill_u64((u64*)C.overflow, 1, 0, P->stream);
-                    if (sink.distinct) launch_fill_u64(sink.distinct, 1, dist_before, P->stream);
-                    extra = need + need / 4;
-                    continue;
-                }
-                C.n_upper = read_dev(P, C.Rn);
-                C.maybe_cut();
-            }
-            extra = 0;
-            ++passes;
+            F.pass(lo, hi, nullptr);
             lo = hi;
         }
         return passes;
@@ -587,6 +643,59 @@ u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink
         launch_add_u64(P, out.base_dev, &sc[0]);
         SFCI_CHECK_HIP(hipGetLastError());
         sink.end(lo, hi);
+    }
+    return passes;
+}
+
+// Row passes: heavy rows through the tile kernel, the others through hash
+// tables, each in descending order of their terms (in classes of a quarter
+// power of two) and the first pass small, so that the bound is set before most
+// rows append.
+u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps) {
+    FusedPasses F(P, v, sink, emitted_dev, eps);
+    HashReach reach;
+    if (!hash_rows_reach(P, F.all, &reach)) return sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
+    const auto cls = [](u64 c) {
+        const int b = 63 - __builtin_clzll(c);
+        return b < 2 ? b * 4 : b * 4 + (int)((c >> (b - 2)) & 3);
+    };
+    u64 at[257] = {};
+    for (u64 c : reach.count)
+        if (c) ++at[255 - cls(c)];
+    u64 n = 0;
+    for (int k = 0; k < 257; ++k) {
+        const u64 x = at[k];
+        at[k] = n;
+        n += x;
+    }
+    std::vector<u32> rows(n);
+    std::vector<u64> terms(n);
+    const u64 above = heavy_row_terms(P);
+    u64 nh = 0, heavy_terms = 0;
+    for (u64 r = 0; r < P->Na; ++r)
+        if (const u64 c = reach.count[r]) {
+            const u64 k = at[255 - cls(c)]++;
+            rows[k] = (u32)r;
+            terms[k] = c;
+        }
+    while (nh < n && terms[nh] > above) heavy_terms += terms[nh++];
+    u32* d = (u32*)P->list_ws.heavy.get(std::max<u64>(1, n) * sizeof(u32));
+    SFCI_CHECK_HIP(hipMemcpyAsync(d, rows.data(), n * sizeof(u32), hipMemcpyHostToDevice, P->stream));
+    SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+    // ranks do not come in order: a candidate that equals the bound stays in
+    sink.cands->ties = true;
+    u64 passes = 0;
+    for (u64 lo = 0, step = 32; lo < nh; step *= 16, ++passes) {
+        const u64 hi = std::min<u64>(nh, lo + step);
+        F.pass(lo, hi, d);
+        lo = hi;
+    }
+    u64 ns = nh;  // (classes mix what lies about the limit: the table's parts are by each row's own count)
+    while (ns < n && terms[ns] > hash_rows_small()) ++ns;
+    for (u64 lo = nh, step = std::max<u64>(2048, nh); lo < n; step *= 16, ++passes) {
+        const u64 hi = std::min<u64>(lo < ns ? ns : n, lo + step);
+        F.pass(lo, hi, d, &v, eps, lo >= ns);
+        lo = hi;
     }
     return passes;
 }
@@ -670,6 +779,8 @@ void lanczos_list(sfci_problem* P, const sfci_lanczos_opts* o, const ListBasis& 
             tsig.begin(P->stream);
             if (dense_passes)
                 sigma_dense_passes(P, sl, sink, sc + 32, o->screen_eps);
+            else if (tiles_ok && list_sigma_rows(P))
+                sigma_row_passes(P, sl, sink, sc + 32, o->screen_eps);
             else
                 sigma_sorted_passes(P, sl, sink, sc + 32, tup_cap, o->screen_eps);
             tsig.end(P->stream);

@@ -89,6 +89,7 @@ struct RTParams {
     // of the records.  nullptr = off.
     unsigned long long* phase_ns;
     const FusedOut* fo;  // sigma: finished tiles go here instead of D (nullptr: written to D)
+    const u32* rows;     // the target rows of the items, in their order (nullptr: all, ascending)
 };
 
 // One contributing source row of the current (target row, tile).
@@ -406,8 +407,9 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
         const u64 n_nbr = 1 + (u64)sA + (u64)PA * QA;
         const bool whole_rows = WHOLE || p.ntiles == 1;
         const u64 item = s_item + p.item_base;
-        const u64 rAt = WHOLE ? item : item / (u64)p.ntiles;
-        const int tile = WHOLE ? 0 : (int)(item - rAt * (u64)p.ntiles);
+        const u64 nth = WHOLE ? item : item / (u64)p.ntiles;
+        const int tile = WHOLE ? 0 : (int)(item - nth * (u64)p.ntiles);
+        const u64 rAt = p.rows ? (u64)p.rows[nth] : nth;
         const u64 tlo = whole_rows ? 0 : p.tile_lo[tile], thi = whole_rows ? Nb : p.tile_lo[tile + 1];
         const int tsz = (int)(thi - tlo);
         const u32 At = str_unrank_wave(rAt, na, n, sB);
@@ -2156,6 +2158,7 @@ RowTileDesc rowtile_prepare(sfci_problem* P, const SigmaLaunch& v, double* D, un
     rp.ab_rowchunk = nullptr;
     if (ab_lists) build_ab_lists(P, S, v, rowbeg, rowend, vrb, rp);
     rp.fo = nullptr;
+    rp.rows = nullptr;
     rp.phase_ns = nullptr;
     if (const char* env = getenv("SFCI_RT_PHASES"))
         if (env[0] == '1') {
@@ -2318,10 +2321,12 @@ void launch_sigma_rowtile_rows(sfci_problem* P, const RowTileDesc& all, u64 lo, 
     if (rp.phase_ns && hi == P->Na) report_phases(P, "sigma, all row slices");
 }
 
-void launch_sigma_rowtile_rows_fused(sfci_problem* P, const RowTileDesc& all, u64 lo, u64 hi, const FusedOut* d_fo) {
+void launch_sigma_rowtile_rows_fused(sfci_problem* P, const RowTileDesc& all, u64 lo, u64 hi, const FusedOut* d_fo,
+                                     const u32* rows) {
     RowTileDesc d = all;
     RTParams& rp = *(RTParams*)d.raw;
     rp.fo = d_fo;
+    rp.rows = rows;
     rp.D = nullptr;
     launch_sigma_rowtile_rows(P, d, lo, hi, nullptr);
 }

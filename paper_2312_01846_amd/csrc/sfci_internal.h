@@ -102,10 +102,11 @@ struct RowPassWs {
 
 // Buffers of the list-based iteration and sigma (listlz.hip).
 struct ListWs {
-    DevBuf scal, pr, pa, mark, Rr, Ra, R2r, R2a, yg, taken, psi_r, psi_a, dpass, dcnt, scal2, rowptr, fo;
+    DevBuf scal, pr, pa, mark, Rr, Ra, R2r, R2a, yg, taken, psi_r, psi_a, dpass, dcnt, scal2, rowptr, fo, heavy, hr_cnt, hr_pre, hr_src,
+        hr_list, hr_ctr;
     void release() {
         for (DevBuf* b : {&scal, &pr, &pa, &mark, &Rr, &Ra, &R2r, &R2a, &yg, &taken, &psi_r, &psi_a, &dpass, &dcnt,
-                          &scal2, &rowptr, &fo})
+                          &scal2, &rowptr, &fo, &heavy, &hr_cnt, &hr_pre, &hr_src, &hr_list, &hr_ctr})
             b->release();
     }
 };
@@ -285,7 +286,21 @@ struct FusedOut {
 // Target alpha rows [lo, hi) of a prepared description, each finished tile
 // handed to the FusedOut at d_fo (device) instead of being written.
 // Synchronises the stream.
-void launch_sigma_rowtile_rows_fused(sfci_problem* P, const RowTileDesc& all, u64 lo, u64 hi, const FusedOut* d_fo);
+// Sigma by target rows with an LDS hash table each (hashrows.hip): the terms
+// of every target row and the lists of source rows that reach it (kept in
+// list_ws), then rows[lo .. hi) (device) handed to the FusedOut at d_fo.  A
+// part of a row that did not fit sets *overflow to 2 or 3: to be run again with
+// a larger more.  Both synchronise the stream.
+struct HashReach {
+    std::vector<u64> count;  // terms per target row
+};
+bool hash_rows_reach(sfci_problem* P, const RowTileDesc& all, HashReach* out);  // false: lists too long for the device
+void launch_hash_rows(sfci_problem* P, const SigmaLaunch& sl, const RowTileDesc& all, u64 lo, u64 hi, const u32* rows,
+                      const FusedOut* d_fo, unsigned long long* emitted, double eps, u32 more, bool small);
+u64 hash_rows_small();  // rows of at most so many terms take the small table
+// With rows (device) the target rows are rows[lo .. hi).
+void launch_sigma_rowtile_rows_fused(sfci_problem* P, const RowTileDesc& all, u64 lo, u64 hi, const FusedOut* d_fo,
+                                     const u32* rows = nullptr);
 unsigned rowtile_grid(int num_cu, size_t lds_bytes, u64 total_items, unsigned per_cu_override = 0);
 size_t rowtile_scratch_bytes(unsigned grid, u64 nbr_cap);
 // fill_counter = false: the caller has already zeroed *d_counter on the stream.
