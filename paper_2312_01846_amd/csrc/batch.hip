@@ -390,8 +390,8 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
         d_pre = (u64*)B->prefix.get((size_t)(n + 1) * sizeof(u64));
         d_cnt = (unsigned*)B->counter.get(64);
         // room for the largest grid a tuning candidate may use
-        const unsigned gmax = std::max(rowtile_grid(B->P[0]->num_cu, geom.lds, total_items),
-                                       rowtile_grid(B->P[0]->num_cu, geom.lds, total_items, kTuneMaxPerCu));
+        const unsigned gmax = std::max(rowtile_grid(B->P[0]->num_cu, geom, total_items),
+                                       rowtile_grid(B->P[0]->num_cu, geom, total_items, kTuneMaxPerCu));
         d_scr = B->scratch.get(rowtile_scratch_bytes(gmax, nbr_cap));
         if (upload) {
             std::vector<unsigned char> host((size_t)n * db);
@@ -436,7 +436,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
         for (int k = 0; k < n; ++k)
             SFCI_CHECK_HIP(hipMemcpyAsync(I[k].sc + 40, I[k].sc + 32, sizeof(u64), hipMemcpyDeviceToDevice, st));
         const unsigned auto_per_cu =
-            std::max(1u, rowtile_grid(1, geom.lds, ~0ull));  // workgroups per CU the default grid uses
+            std::max(1u, rowtile_grid(1, geom, ~0ull));  // workgroups per CU the default grid uses
         auto trial = [&](const RowTileTune& t) {
             hipEvent_t a, z;
             SFCI_CHECK_HIP(hipEventCreate(&a));

@@ -28,6 +28,15 @@ namespace {
 
 constexpr int RT_WAVES = 16;
 constexpr int RT_BLOCK = 64 * RT_WAVES;
+// Rows of one tile that leave LDS for two workgroups on a compute unit may take
+// eight wavefronts each: one row's barriers and its write (18 % of the time of
+// 900 138 entries at 20 orbitals, 4 with two) overlap the other's sums.  But a
+// single heavy row takes twice as long, so this serves several instances in one
+// launch (8 at 20 orbitals 177 -> 161 ms, 16 orbitals 20.3 -> 17.3, 12 orbitals
+// 15.7 -> 12.5; 2 at 20 orbitals 17.5 and 17.6) and vectors of at most an entry
+// per row (20 orbitals, 3 000 entries 0.52 -> 0.47 ms; but 30 000 near the
+// aufbau string 0.87 -> 1.03, 900 138 6.19 -> 6.41).
+constexpr int RT_PAIRS8 = 256;  // orbital pairs of such a launch
 constexpr int RT_PH = 10;  // phase-timing bins
 
 struct RTParams {
@@ -205,12 +214,14 @@ enum { RT_SIGMA = 0, RT_GRAD_A = 1, RT_GRAD_B = 2 };
 // One launch serves one or many problem instances: item i belongs to the
 // instance whose [item_prefix[k], item_prefix[k+1]) holds it; a workgroup
 // reloads the instance description when consecutive items change instance.
-template <int MODE, bool TIMED = false, bool WHOLE = false>
+template <int MODE, bool TIMED = false, bool WHOLE = false, int WAVES = RT_WAVES>
 __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs, const u64* __restrict__ item_prefix,
                                              int n_inst, unsigned* __restrict__ counter, void* nbr_scratch,
                                              u64 nbr_cap, unsigned slab_off, unsigned slab_n2, unsigned itab_off,
                                              unsigned b1_chunk, unsigned bb_chunk, unsigned ja_off) {
     constexpr bool GRAD = MODE != RT_SIGMA;
+    constexpr int BLOCK = 64 * WAVES;
+    constexpr int PAIRS = WAVES == RT_WAVES ? SFCI_MAX_PAIRS : RT_PAIRS8;
     extern __shared__ double acc[];
     double* const itab = acc + itab_off;  // sigma: per-item element tables
     // sigma, when it fits (ja_off != 0): per item, (jb|kk) for each occupied
@@ -218,9 +229,9 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
     // j n + b: the alpha part of the identity row's beta-single elements
     double* const ja = acc + ja_off;
     __shared__ BinomLds sB;
-    __shared__ WaveScratch sw[RT_WAVES];
+    __shared__ WaveScratch sw[WAVES];
     __shared__ uint8_t occA[32], virA[32];
-    __shared__ uint16_t pairNA[SFCI_MAX_PAIRS], pairVA[SFCI_MAX_PAIRS], pairNB[SFCI_MAX_PAIRS], pairVB[SFCI_MAX_PAIRS];
+    __shared__ uint16_t pairNA[PAIRS], pairVA[PAIRS], pairNB[PAIRS], pairVB[PAIRS];
     // the item's records: alpha-single source rows at list[0, s_nlist), the
     // others at list[nbr_cap - s_nlist2, nbr_cap) (phase 3 visits only the former)
     __shared__ unsigned s_nbr, s_nlist, s_nlist2, s_next, s_next2, s_touched, s_idb, s_ide;
@@ -238,10 +249,10 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
     __shared__ u32 s_row_idb, s_row_ide;
     __shared__ RTParams p;
     // phase timing (timed build only): per wavefront, RT_PH bins
-    __shared__ unsigned long long s_ph[TIMED ? RT_WAVES : 1][TIMED ? RT_PH : 1];
+    __shared__ unsigned long long s_ph[TIMED ? WAVES : 1][TIMED ? RT_PH : 1];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (TIMED && threadIdx.x < RT_WAVES * RT_PH) s_ph[threadIdx.x / RT_PH][threadIdx.x % RT_PH] = 0;
+    if (TIMED && threadIdx.x < WAVES * RT_PH) s_ph[threadIdx.x / RT_PH][threadIdx.x % RT_PH] = 0;
     u64 t_mark = 0;  // phase timing: the last timestamp of this wavefront
     auto ph_add = [&](bool on, int bin) {
         if (on) {
@@ -276,7 +287,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
     double* const wslab = acc + slab_off + (u32)wave * (slab_n2 + 32);
     double* const wo = wslab + slab_n2;
     if (GRAD)
-        for (u32 t = threadIdx.x; t < (u32)RT_WAVES * (slab_n2 + 32); t += RT_BLOCK) acc[slab_off + t] = 0.0;
+        for (u32 t = threadIdx.x; t < (u32)WAVES * (slab_n2 + 32); t += BLOCK) acc[slab_off + t] = 0.0;
     if (threadIdx.x == 0) {
         s_cur = -1;
         s_left = 0;
@@ -373,21 +384,21 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             my_terms = 0;
             __syncthreads();
             const int words = (int)(sizeof(RTParams) / sizeof(u32));
-            for (int t = threadIdx.x; t < words; t += RT_BLOCK) ((u32*)&p)[t] = ((const u32*)&descs[s_inst])[t];
+            for (int t = threadIdx.x; t < words; t += BLOCK) ((u32*)&p)[t] = ((const u32*)&descs[s_inst])[t];
             __syncthreads();
             const int na_ = p.sp.na, nb_ = p.sp.nb, nva_ = p.sp.n - na_, nvb_ = p.sp.n - nb_;
-            for (int t = threadIdx.x; t < na_ * (na_ - 1) / 2; t += RT_BLOCK) pairNA[t] = decode_pair(t, na_);
-            for (int t = threadIdx.x; t < nva_ * (nva_ - 1) / 2; t += RT_BLOCK) pairVA[t] = decode_pair(t, nva_);
-            for (int t = threadIdx.x; t < nb_ * (nb_ - 1) / 2; t += RT_BLOCK) pairNB[t] = decode_pair(t, nb_);
-            for (int t = threadIdx.x; t < nvb_ * (nvb_ - 1) / 2; t += RT_BLOCK) pairVB[t] = decode_pair(t, nvb_);
+            for (int t = threadIdx.x; t < na_ * (na_ - 1) / 2; t += BLOCK) pairNA[t] = decode_pair(t, na_);
+            for (int t = threadIdx.x; t < nva_ * (nva_ - 1) / 2; t += BLOCK) pairVA[t] = decode_pair(t, nva_);
+            for (int t = threadIdx.x; t < nb_ * (nb_ - 1) / 2; t += BLOCK) pairNB[t] = decode_pair(t, nb_);
+            for (int t = threadIdx.x; t < nvb_ * (nvb_ - 1) / 2; t += BLOCK) pairVB[t] = decode_pair(t, nvb_);
             if (!GRAD) {
                 const int n_ = p.sp.n, n2_ = n_ * n_;
-                for (int t = threadIdx.x; t < n2_; t += RT_BLOCK) {
+                for (int t = threadIdx.x; t < n2_; t += BLOCK) {
                     const int q = t / n_, q2 = t - q * n_;
                     itab[t] = p.K2[t];
                     itab[n2_ + t] = p.I.G(q, q, q2, q2);
                 }
-                for (int t = threadIdx.x; t < n_; t += RT_BLOCK) itab[2 * n2_ + t] = p.I.H(t, t);
+                for (int t = threadIdx.x; t < n_; t += BLOCK) itab[2 * n2_ + t] = p.I.H(t, t);
             }
             if (threadIdx.x == 0) {
                 s_cur = s_inst;
@@ -421,16 +432,16 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
         }
         if (GRAD) {
             const double* src = p.D + (rAt - p.row_base) * Nb + tlo;
-            for (int x = threadIdx.x; x < tsz; x += RT_BLOCK) acc[x] = src[x];
+            for (int x = threadIdx.x; x < tsz; x += BLOCK) acc[x] = src[x];
         } else {
-            for (int x = threadIdx.x; x < tsz; x += RT_BLOCK) acc[x] = 0.0;
+            for (int x = threadIdx.x; x < tsz; x += BLOCK) acc[x] = 0.0;
         }
         __syncthreads();
         ph_add(timing, 8);
         if (!GRAD && ja_off) {
             // read in phase 3, after phase 1's barrier
             const u32 n2 = (u32)n * n;
-            for (u32 t = threadIdx.x; t < (u32)na * n2; t += RT_BLOCK) {
+            for (u32 t = threadIdx.x; t < (u32)na * n2; t += BLOCK) {
                 const u32 qi = t / n2, jb = t - qi * n2;
                 const u32 kq = occA[qi];
                 ja[t] = p.I.g[(jb * (u32)n + kq) * (u32)n + kq];
@@ -448,7 +459,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 s_ide = s_row_ide;
             }
             const unsigned nrow = s_nrow + s_nrow2;
-            for (unsigned b0 = 0; b0 < nrow; b0 += RT_BLOCK) {
+            for (unsigned b0 = 0; b0 < nrow; b0 += BLOCK) {
                 const unsigned t = b0 + threadIdx.x;
                 NbrRec r;
                 r.type = 255;
@@ -589,7 +600,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 s_cache_inst = s_inst;
             }
         }
-        if (!GRAD && threadIdx.x == RT_BLOCK - 1) {
+        if (!GRAD && threadIdx.x == BLOCK - 1) {
             // the alpha h_pp of the diagonal, summed from zero in ascending order
             double x = 0.0;
             for (u32 m = At; m; m &= m - 1u) x += p.I.H(__builtin_ctz(m), __builtin_ctz(m));
@@ -604,7 +615,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             // nothing lands here: D keeps its zeros, or gets them (full_rows)
             if (!GRAD && p.full_rows && !p.fo) {
                 double* dst = p.D + (rAt - p.row_base) * Nb + tlo;
-                for (int x = threadIdx.x; x < tsz; x += RT_BLOCK) dst[x] = 0.0;
+                for (int x = threadIdx.x; x < tsz; x += BLOCK) dst[x] = 0.0;
             }
             continue;
         }
@@ -619,7 +630,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             return r.e1 - r.e0 > (r.type == 1 ? 4u : (r.type == 2 ? p.short_dbl : 32u));
         };
         if (!GRAD) {
-            for (unsigned li = threadIdx.x; li < nlist; li += RT_BLOCK) {
+            for (unsigned li = threadIdx.x; li < nlist; li += BLOCK) {
                 const NbrRec r = rec(li);
                 if (by_wave(r)) continue;
                 // RT_UNROLL entries at a time, their loads in flight together
@@ -776,7 +787,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             // and (identity row) P_pq over entries with p and q occupied.
             const u32 n2 = (u32)n * n;
             auto gi = [&](int a_, int b_, int c_, int d_) { return (((u32)a_ * n + b_) * n + c_) * n + d_; };
-            for (unsigned li = threadIdx.x; li < nlist; li += RT_BLOCK) {
+            for (unsigned li = threadIdx.x; li < nlist; li += BLOCK) {
                 const NbrRec r = rec(li);
                 if (r.type != 2 || r.e1 - r.e0 > 32) continue;
                 double w = 0.0;
@@ -1448,21 +1459,21 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                     if (rb >= tlo && rb < thi) fn(i, (u32)(rb - tlo));
                 }
             };
-            for (int l = wave; l < f.nl; l += RT_WAVES)
+            for (int l = wave; l < f.nl; l += WAVES)
                 scan_basis(l, [&](u64 i, u32 x) { f.Y[(u64)l * f.cap + i] = yval(x); });
             if (f.distinct) {
                 u32 nz = 0;
-                for (int x = threadIdx.x; x < tsz; x += RT_BLOCK) nz += (yval((u32)x) != 0.0) ? 1u : 0u;
+                for (int x = threadIdx.x; x < tsz; x += BLOCK) nz += (yval((u32)x) != 0.0) ? 1u : 0u;
                 for (int off = 32; off >= 1; off >>= 1) nz += (u32)__shfl_xor((int)nz, off);
                 if (lane == 0 && nz) atomicAdd((unsigned long long*)f.distinct, (unsigned long long)nz);
             }
             __syncthreads();
-            for (int l = f.mark_from + wave; l < f.nl; l += RT_WAVES)
+            for (int l = f.mark_from + wave; l < f.nl; l += WAVES)
                 scan_basis(l, [&](u64, u32 x) { acc[x] = 0.0; });
             __syncthreads();
             if (f.collect) {
                 const u64 tb = *f.bound;
-                for (int x0 = 0; x0 < tsz; x0 += RT_BLOCK) {
+                for (int x0 = 0; x0 < tsz; x0 += BLOCK) {
                     const int x = x0 + (int)threadIdx.x;
                     const double v = (x < tsz) ? yval((u32)x) : 0.0;
                     const bool pk = ((u64)__double_as_longlong(v) & 0x7fffffffffffffffull) > tb;
@@ -1486,15 +1497,15 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             double* dst = p.D + (rAt - p.row_base) * Nb + tlo;
             const double eps = p.eps;
             if (eps > 0.0)
-                for (int x = threadIdx.x; x < tsz; x += RT_BLOCK) dst[x] = (fabs(acc[x]) < eps) ? 0.0 : acc[x];
+                for (int x = threadIdx.x; x < tsz; x += BLOCK) dst[x] = (fabs(acc[x]) < eps) ? 0.0 : acc[x];
             else
-                for (int x = threadIdx.x; x < tsz; x += RT_BLOCK) dst[x] = acc[x];
+                for (int x = threadIdx.x; x < tsz; x += BLOCK) dst[x] = acc[x];
         }
         ph_add(timing, 5);
     }
     if (TIMED && !GRAD && s_cur >= 0 && p.phase_ns) {
         __syncthreads();
-        if (threadIdx.x < RT_WAVES * RT_PH && s_ph[threadIdx.x / RT_PH][threadIdx.x % RT_PH])
+        if (threadIdx.x < WAVES * RT_PH && s_ph[threadIdx.x / RT_PH][threadIdx.x % RT_PH])
             atomicAdd(p.phase_ns + (threadIdx.x % RT_PH), s_ph[threadIdx.x / RT_PH][threadIdx.x % RT_PH]);
     }
     if (lane == 0) my_terms += wterms;
@@ -1546,6 +1557,28 @@ __global__ __launch_bounds__(RT_BLOCK) void k_sigma_rowtile_whole_timed(const RT
                                                                         unsigned bb_chunk, unsigned ja_off) {
     rowtile_body<RT_SIGMA, true, true>(descs, item_prefix, n_inst, counter, nbr_scratch, nbr_cap, slab_off, slab_n2,
                                        itab_off, b1_chunk, bb_chunk, ja_off);
+}
+
+// The same with eight wavefronts, two workgroups to a compute unit.
+__global__ __launch_bounds__(RT_BLOCK / 2) void k_sigma_rowtile_whole8(const RTParams* __restrict__ descs,
+                                                                       const u64* __restrict__ item_prefix, int n_inst,
+                                                                       unsigned* __restrict__ counter,
+                                                                       void* nbr_scratch, u64 nbr_cap,
+                                                                       unsigned slab_off, unsigned slab_n2,
+                                                                       unsigned itab_off, unsigned b1_chunk,
+                                                                       unsigned bb_chunk, unsigned ja_off) {
+    rowtile_body<RT_SIGMA, false, true, RT_WAVES / 2>(descs, item_prefix, n_inst, counter, nbr_scratch, nbr_cap,
+                                                      slab_off, slab_n2, itab_off, b1_chunk, bb_chunk, ja_off);
+}
+__global__ __launch_bounds__(RT_BLOCK / 2) void k_sigma_rowtile_whole8_timed(const RTParams* __restrict__ descs,
+                                                                             const u64* __restrict__ item_prefix,
+                                                                             int n_inst, unsigned* __restrict__ counter,
+                                                                             void* nbr_scratch, u64 nbr_cap,
+                                                                             unsigned slab_off, unsigned slab_n2,
+                                                                             unsigned itab_off, unsigned b1_chunk,
+                                                                             unsigned bb_chunk, unsigned ja_off) {
+    rowtile_body<RT_SIGMA, true, true, RT_WAVES / 2>(descs, item_prefix, n_inst, counter, nbr_scratch, nbr_cap,
+                                                     slab_off, slab_n2, itab_off, b1_chunk, bb_chunk, ja_off);
 }
 
 __global__ __launch_bounds__(RT_BLOCK) void k_grad_rowtile_a(const RTParams* __restrict__ descs,
@@ -1889,6 +1922,16 @@ static unsigned rt_itab_doubles(unsigned n2) { return (2 * n2 + 40 + 1) & ~1u; }
 
 // The tile kernels' static LDS, as compiled (the largest of the three), so
 // that static + dynamic LDS never exceeds what a workgroup may hold.
+static size_t rt_static_lds8() {
+    static size_t cached = 0;
+    if (cached == 0) {
+        hipFuncAttributes attr{};
+        SFCI_CHECK_HIP(hipFuncGetAttributes(&attr, (const void*)k_sigma_rowtile_whole8));
+        cached = attr.sharedSizeBytes;
+    }
+    return cached;
+}
+
 static size_t rt_static_lds() {
     static size_t cached = 0;
     if (cached == 0) {
@@ -2032,6 +2075,7 @@ bool rowtile_available(sfci_problem* P) {
     const int dyn_max = maxlds - (int)rt_static_lds();
     for (const void* f : {(const void*)k_sigma_rowtile, (const void*)k_sigma_rowtile_timed,
                           (const void*)k_sigma_rowtile_whole, (const void*)k_sigma_rowtile_whole_timed,
+                          (const void*)k_sigma_rowtile_whole8, (const void*)k_sigma_rowtile_whole8_timed,
                           (const void*)k_grad_rowtile_a, (const void*)k_grad_rowtile_b})
         SFCI_CHECK_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_max));
     SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
@@ -2197,6 +2241,7 @@ RowTileDesc rowtile_prepare(sfci_problem* P, const SigmaLaunch& v, double* D, un
     out.n_items = P->Na * (u64)((S->ntiles + rp.tile_chunk - 1) / rp.tile_chunk);
     out.nbr_cap = 1 + (u64)na * nva + (u64)(na * (na - 1) / 2) * (u64)(nva * (nva - 1) / 2);
     out.lds_bytes = S->lds_bytes;
+    out.cap = v.cap;
     out.n2 = (unsigned)(P->n * P->n);
     out.ja_doubles = (unsigned)(P->na * P->n * P->n);
     out.max_lds = S->maxlds;
@@ -2226,13 +2271,32 @@ RowTileGeom rowtile_geom(const RowTileDesc* d, int n_inst) {
     const unsigned itab_off = (unsigned)(tile / sizeof(double));
     const unsigned slab_off = itab_off + rt_itab_doubles(n2);
     const size_t base = (size_t)slab_off * sizeof(double);
-    RowTileGeom g{base + (size_t)RT_WAVES * 32 * sizeof(double), slab_off, 0u, itab_off, 0u, true};
+    RowTileGeom g{base + (size_t)RT_WAVES * 32 * sizeof(double), slab_off, 0u, itab_off, 0u, true, RT_WAVES};
     for (int k = 0; k < n_inst; ++k) g.whole = g.whole && ((const RTParams*)d[k].raw)->ntiles == 1;
     const size_t with = base + (size_t)RT_WAVES * (n2 + 32) * sizeof(double);
     if (with + rt_static_lds() <= (size_t)maxlds) g.lds = with, g.slab_n2 = n2;
-    // then the identity row's alpha-part table, if it still fits
     unsigned ja = 0;
     for (int k = 0; k < n_inst; ++k) ja = std::max(ja, d[k].ja_doubles);
+    // two workgroups of eight wavefronts where both fit
+    bool half = g.whole && (n_inst > 1 || d[0].cap <= ((const RTParams*)d[0].raw)->sp.Na);
+    for (int k = 0; k < n_inst; ++k) {
+        const SpaceDev& sp = ((const RTParams*)d[k].raw)->sp;
+        for (int m : {sp.na, sp.nb, sp.n - sp.na, sp.n - sp.nb}) half = half && m * (m - 1) / 2 <= RT_PAIRS8;
+    }
+    const size_t room = (size_t)maxlds / 2 - rt_static_lds8();
+    const size_t with8 = base + (size_t)(RT_WAVES / 2) * (n2 + 32) * sizeof(double);
+    if (half && with8 <= room) {
+        g.waves = RT_WAVES / 2;
+        g.lds = with8;
+        g.slab_n2 = n2;
+        const size_t ja_at = (g.lds + 15) & ~(size_t)15;
+        if (ja && ja_at + (size_t)ja * sizeof(double) <= room) {
+            g.ja_off = (unsigned)(ja_at / sizeof(double));
+            g.lds = ja_at + (size_t)ja * sizeof(double);
+        }
+        return g;
+    }
+    // then the identity row's alpha-part table, if it still fits
     const size_t ja_at = (g.lds + 15) & ~(size_t)15;
     if (ja && ja_at + (size_t)ja * sizeof(double) + rt_static_lds() <= (size_t)maxlds) {
         g.ja_off = (unsigned)(ja_at / sizeof(double));
@@ -2245,15 +2309,21 @@ void rowtile_run(hipStream_t stream, int num_cu, const void* d_descs, const u64*
                  unsigned* d_counter, void* scratch, u64 nbr_cap, const RowTileGeom& geom, u64 total_items,
                  bool fill_counter, const RowTileTune& tune, bool timed) {
     if (fill_counter) launch_fill_u64((u64*)d_counter, 1, 0, stream);
-    const unsigned grid = rowtile_grid(num_cu, geom.lds, total_items, tune.per_cu);
-    auto* kern = geom.whole ? (timed ? k_sigma_rowtile_whole_timed : k_sigma_rowtile_whole)
-                            : (timed ? k_sigma_rowtile_timed : k_sigma_rowtile);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(RT_BLOCK), geom.lds, stream,
+    const unsigned grid = rowtile_grid(num_cu, geom, total_items, tune.per_cu);
+    auto* kern = geom.waves != RT_WAVES ? (timed ? k_sigma_rowtile_whole8_timed : k_sigma_rowtile_whole8)
+                 : geom.whole          ? (timed ? k_sigma_rowtile_whole_timed : k_sigma_rowtile_whole)
+                                       : (timed ? k_sigma_rowtile_timed : k_sigma_rowtile);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * geom.waves), geom.lds, stream,
                        (const RTParams*)d_descs,
                        d_prefix, n_inst, d_counter, scratch, nbr_cap, geom.slab_off, geom.slab_n2, geom.itab_off,
                        tune.b1_chunk ? tune.b1_chunk : RT_B1_CHUNK, tune.bb_chunk ? tune.bb_chunk : RT_BB_CHUNK,
                        geom.ja_off);
     SFCI_CHECK_HIP(hipGetLastError());
+}
+
+unsigned rowtile_grid(int num_cu, const RowTileGeom& geom, u64 total_items, unsigned per_cu_override) {
+    return rowtile_grid(num_cu, geom.lds, total_items,
+                        !per_cu_override && geom.waves != RT_WAVES ? 2u : per_cu_override);
 }
 
 unsigned rowtile_grid(int num_cu, size_t lds_bytes, u64 total_items, unsigned per_cu_override) {
@@ -2290,7 +2360,7 @@ void launch_sigma_rowtile(sfci_problem* P, const SigmaLaunch& v, double* D, unsi
     SFCI_CHECK_HIP(hipMemcpyAsync(buf, d.raw, sizeof(RTParams), hipMemcpyHostToDevice, P->stream));
     SFCI_CHECK_HIP(hipMemcpyAsync(buf + sizeof(RTParams), prefix, sizeof(prefix), hipMemcpyHostToDevice, P->stream));
     const RowTileGeom geom = rowtile_geom(&d, 1);
-    const unsigned grid = rowtile_grid(P->num_cu, geom.lds, d.n_items);
+    const unsigned grid = rowtile_grid(P->num_cu, geom, d.n_items);
     void* scratch = P->ws_rt_nbr.get(rowtile_scratch_bytes(grid, d.nbr_cap));
     const bool timed = ((RTParams*)d.raw)->phase_ns != nullptr;
     rowtile_run(P->stream, P->num_cu, buf, (const u64*)(buf + sizeof(RTParams)), 1,
@@ -2311,7 +2381,7 @@ void launch_sigma_rowtile_rows(sfci_problem* P, const RowTileDesc& all, u64 lo, 
     SFCI_CHECK_HIP(hipMemcpyAsync(buf, d.raw, sizeof(RTParams), hipMemcpyHostToDevice, P->stream));
     SFCI_CHECK_HIP(hipMemcpyAsync(buf + sizeof(RTParams), prefix, sizeof(prefix), hipMemcpyHostToDevice, P->stream));
     const RowTileGeom geom = rowtile_geom(&d, 1);
-    const unsigned grid = rowtile_grid(P->num_cu, geom.lds, d.n_items);
+    const unsigned grid = rowtile_grid(P->num_cu, geom, d.n_items);
     void* scratch = P->ws_rt_nbr.get(rowtile_scratch_bytes(grid, d.nbr_cap));
     rowtile_run(P->stream, P->num_cu, buf, (const u64*)(buf + sizeof(RTParams)), 1,
                 (unsigned*)(buf + sizeof(RTParams) + 16), scratch, d.nbr_cap, geom, d.n_items, true, RowTileTune{},

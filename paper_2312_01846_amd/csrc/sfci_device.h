@@ -25,11 +25,11 @@ typedef int64_t i64;
 
 // Binomial table C(a, b), 0 <= a, b <= 32, row-major 33 x 33 (C(a,b) = 0 for b > a).
 struct BinomLds {
-    u64 c[33][33];
+    u32 c[33][33];  // up to C(32, 16) = 601 080 390
 };
 
 __device__ __forceinline__ void load_binom(BinomLds& B, const u64* __restrict__ gtab) {
-    for (int t = threadIdx.x; t < 33 * 33; t += blockDim.x) (&B.c[0][0])[t] = gtab[t];
+    for (int t = threadIdx.x; t < 33 * 33; t += blockDim.x) (&B.c[0][0])[t] = (u32)gtab[t];
 }
 
 // Eq. 12 on a spin string: sum over occupied orbitals p (ascending, t-th

@@ -204,6 +204,7 @@ void launch_sigma_rowtile(sfci_problem* P, const SigmaLaunch& v, double* D, unsi
 struct RowTileDesc {
     alignas(8) unsigned char raw[384];  // kernel-side description of one instance
     u64 n_items, nbr_cap;
+    u64 cap;           // entries of the input at most
     size_t lds_bytes;  // the tile
     unsigned n2;       // n^2 of the instance
     unsigned ja_doubles;  // n_alpha n^2: the identity row's alpha-part table
@@ -218,6 +219,7 @@ struct RowTileGeom {
     unsigned itab_off;  // per-item element tables
     unsigned ja_off;    // the identity row's alpha-part table (0: not staged)
     bool whole = false; // every instance's rows are one tile (the one-tile kernel runs)
+    int waves = 16;     // wavefronts per workgroup (8: two workgroups to a compute unit)
 };
 RowTileGeom rowtile_geom(const RowTileDesc* d, int n_inst);
 // Launch-time work sizes of the sigma tile kernel (0 = the built-in default):
@@ -301,6 +303,7 @@ u64 hash_rows_small();  // rows of at most so many terms take the small table
 // With rows (device) the target rows are rows[lo .. hi).
 void launch_sigma_rowtile_rows_fused(sfci_problem* P, const RowTileDesc& all, u64 lo, u64 hi, const FusedOut* d_fo,
                                      const u32* rows = nullptr);
+unsigned rowtile_grid(int num_cu, const RowTileGeom& geom, u64 total_items, unsigned per_cu_override = 0);
 unsigned rowtile_grid(int num_cu, size_t lds_bytes, u64 total_items, unsigned per_cu_override = 0);
 size_t rowtile_scratch_bytes(unsigned grid, u64 nbr_cap);
 // fill_counter = false: the caller has already zeroed *d_counter on the stream.
