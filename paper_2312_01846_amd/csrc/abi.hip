@@ -340,6 +340,14 @@ sfci_status sfci_unrank(sfci_problem* P, const uint64_t* rank, uint64_t cnt, uin
     SFCI_GUARD_END
 }
 
+// A truncated fast sigma leaves the N_det array out from here on, if M is a
+// small part of it: the array's write and the selection's passes cost ~8.1e-12 s
+// per determinant, consuming the tiles in the kernel ~1.2e-12 s per term.  5 + 5
+// electrons, dense and list, ms: 26 orbitals (4.3e9 determinants) 1 000 entries
+// 35.1 and 2.5, 1e5 44.5 and 17.4, 1e6 82.8 and 69.5; 22 (6.9e8) 5.9 and 2.3,
+// 9.9 and 9.5, 30.0 and 35.7; 20 (2.4e8) 2.1 and 2.0, 5.4 and 6.5, 21.3 and 27.3.
+constexpr u64 SIGMA_LIST_NDET = u64(1) << 29;
+
 sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opts* opts, sfci_svec* out,
                        sfci_sigma_stats* stats) {
     SFCI_GUARD_BEGIN
@@ -354,7 +362,11 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
                          ensure_dense(P);
     bool use_sort = !inorder && (opts->deterministic || opts->dedup == SFCI_DEDUP_SORT);
     bool list_tiles = false;  // no N_det array, fast: the tile kernel's slices may serve
-    if (!use_sort && !ensure_dense(P)) {
+    if (!use_sort && opts->dedup == SFCI_DEDUP_AUTO && P->Ndet >= SIGMA_LIST_NDET && opts->M <= P->Ndet / 1024 &&
+        v->nnz * tps <= 6 * P->Ndet && rowtile_available(P)) {
+        use_sort = true;
+        list_tiles = true;
+    } else if (!use_sort && !ensure_dense(P)) {
         if (opts->dedup == SFCI_DEDUP_DENSE || opts->dedup == SFCI_DEDUP_DENSE_ATOMIC) {
             validate_vec(P, v->rank, v->nnz);
             return (sfci_status)sfci_set_error(SFCI_E_UNSUPPORTED, "dense accumulator does not fit on the device");

@@ -200,7 +200,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_hash_rows(HashRows p) {
     __shared__ BinomLds B;
     __shared__ uint16_t pO[SFCI_MAX_PAIRS], pV[SFCI_MAX_PAIRS];
     __shared__ uint8_t occ[WAVES][32], vir[WAVES][32];
-    __shared__ u32 s_item;
+    __shared__ u32 s_item, s_cand[WAVES];
+    __shared__ unsigned long long s_cand0;
     load_binom(B, p.binom);
     const int n = p.sp.n, na = p.sp.na, nb = p.sp.nb, nvb = n - nb, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const u64 Nb = p.sp.Nb;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_hash_rows(HashRows p) {
     for (int t = threadIdx.x; t < p.PB; t += BLOCK) pO[t] = decode_pair(t, nb);
     for (int t = threadIdx.x; t < p.QB; t += BLOCK) pV[t] = decode_pair(t, nvb);
     const FusedOut f = *p.fo;
-    u64 terms = 0;
+    u64 terms = 0, distinct = 0;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) s_item = atomicAdd(p.counter, 1u);
@@ -405,37 +406,48 @@ __global__ __launch_bounds__(64 * WAVES) void k_hash_rows(HashRows p) {
             };
             for (int l = wave; l < f.nl; l += WAVES)
                 scan_basis(l, [&](u64 i, u32 h) { f.Y[(u64)l * f.cap + i] = yval(h); });
-            if (f.distinct) {
-                u32 nz = 0;
-                for (u32 x = threadIdx.x; x < SLOTS; x += BLOCK) nz += yval(x) != 0.0 ? 1u : 0u;
-                for (int off = 32; off >= 1; off >>= 1) nz += (u32)__shfl_xor((int)nz, off);
-                if (lane == 0 && nz) atomicAdd((unsigned long long*)f.distinct, (unsigned long long)nz);
-            }
+            if (f.distinct)
+                for (u32 x = threadIdx.x; x < SLOTS; x += BLOCK) distinct += yval(x) != 0.0 ? 1u : 0u;
             if (!f.collect) continue;
             __syncthreads();
             for (int l = f.mark_from + wave; l < f.nl; l += WAVES) scan_basis(l, [&](u64, u32 h) { val[h] = 0.0; });
             __syncthreads();
+            // counted first: one addition to the list's length per part
             const u64 tb = *f.bound;
-            for (u32 x0 = 0; x0 < SLOTS; x0 += BLOCK) {
-                const u32 x = x0 + threadIdx.x;
-                const double v = yval(x);
-                const bool pk = ((u64)__double_as_longlong(v) & 0x7fffffffffffffffull) > tb;
+            auto cand = [&](u32 x) {
+                return ((u64)__double_as_longlong(yval(x)) & 0x7fffffffffffffffull) > tb;
+            };
+            u32 mine = 0;
+            for (u32 x = threadIdx.x; x < SLOTS; x += BLOCK) mine += (u32)__popcll(__ballot(cand(x)));
+            if (lane == 0) s_cand[wave] = mine;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                u32 all = 0;
+                for (int w = 0; w < WAVES; ++w) all += s_cand[w];
+                s_cand0 = all ? atomicAdd((unsigned long long*)f.Rn, (unsigned long long)all) : 0ull;
+            }
+            __syncthreads();
+            u64 at0 = s_cand0;
+            for (int w = 0; w < wave; ++w) at0 += s_cand[w];
+            for (u32 x = threadIdx.x; mine && x < SLOTS; x += BLOCK) {
+                const bool pk = cand(x);
                 const u64 m = __ballot(pk);
-                if (m == 0) continue;
-                u64 at0 = 0;
-                if (lane == 0) at0 = atomicAdd((unsigned long long*)f.Rn, (unsigned long long)__popcll(m));
-                at0 = (u64)__shfl((long long)at0, 0);
                 if (pk) {
                     const u64 at = at0 + (u64)__popcll(m & ((1ull << lane) - 1ull));
                     if (at < f.Rcap) {
                         f.Rr[at] = rowbase + key[x];
-                        f.Ra[at] = v;
+                        f.Ra[at] = yval(x);
                     } else {
                         atomicOr(f.overflow, 1);
                     }
                 }
+                at0 += (u64)__popcll(m);
             }
         }
+    }
+    if (f.distinct) {
+        for (int off = 32; off >= 1; off >>= 1) distinct += (u64)__shfl_xor((long long)distinct, off);
+        if (lane == 0 && distinct) atomicAdd((unsigned long long*)f.distinct, (unsigned long long)distinct);
     }
     for (int off = 32; off >= 1; off >>= 1) terms += (u64)__shfl_xor((long long)terms, off);
     if (lane == 0 && terms && p.emitted) atomicAdd(p.emitted, (unsigned long long)terms);

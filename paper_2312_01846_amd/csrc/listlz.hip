@@ -452,6 +452,7 @@ struct FusedPasses {
     FusedOut h{};
     FusedOut* d_fo;
     u64 room;
+    bool rest = false;  // the candidates of all rows behind the first pass fit
 
     FusedPasses(sfci_problem* P_, const SigmaLaunch& v, ListPassSink& sink_, u64* emitted_dev, double eps)
         : P(P_), sink(sink_), emitted(emitted_dev),
@@ -479,6 +480,10 @@ struct FusedPasses {
         h.distinct = sink.distinct;
         d_fo = (FusedOut*)ws.fo.get(sizeof(FusedOut));
         room = std::max<u64>(1ull << 24, 4 * std::min<u64>(C.K, 1ull << 26));
+        size_t freeb = 0, totb = 0;
+        SFCI_CHECK_HIP(hipMemGetInfo(&freeb, &totb));
+        rest = sink.collect && C.K < (1ull << 40) && 80 * C.K * 16 < freeb / 8;
+        if (rest) room = std::max<u64>(room, 80 * C.K);
     }
 
     // Target rows [lo, hi), or rows[lo .. hi) of a device list; through the
@@ -602,7 +607,7 @@ u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink
         FusedPasses F(P, v, sink, emitted_dev, eps);
         u64 lo = 0, passes = 0;
         for (; lo < P->Na; ++passes) {
-            const u64 rows = std::max<u64>(1, passes == 0 ? P->Na / 64 : P->Na / 8);
+            const u64 rows = std::max<u64>(1, passes == 0 ? P->Na / 64 : F.rest ? P->Na : P->Na / 8);
             const u64 hi = std::min<u64>(P->Na, lo + rows);
             F.pass(lo, hi, nullptr);
             lo = hi;

@@ -220,6 +220,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                                              u64 nbr_cap, unsigned slab_off, unsigned slab_n2, unsigned itab_off,
                                              unsigned b1_chunk, unsigned bb_chunk, unsigned ja_off) {
     constexpr bool GRAD = MODE != RT_SIGMA;
+    constexpr bool FUSED = !GRAD && WAVES == RT_WAVES;  // finished tiles may go to a FusedOut
     constexpr int BLOCK = 64 * WAVES;
     constexpr int PAIRS = WAVES == RT_WAVES ? SFCI_MAX_PAIRS : RT_PAIRS8;
     extern __shared__ double acc[];
@@ -248,6 +249,8 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
     __shared__ unsigned s_nrow, s_nrow2;
     __shared__ u32 s_row_idb, s_row_ide;
     __shared__ RTParams p;
+    __shared__ u32 s_cand[WAVES];  // FusedOut: candidates of a tile per wavefront
+    __shared__ unsigned long long s_cand0, s_distinct;
     // phase timing (timed build only): per wavefront, RT_PH bins
     __shared__ unsigned long long s_ph[TIMED ? WAVES : 1][TIMED ? RT_PH : 1];
 
@@ -289,6 +292,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
     if (GRAD)
         for (u32 t = threadIdx.x; t < (u32)WAVES * (slab_n2 + 32); t += BLOCK) acc[slab_off + t] = 0.0;
     if (threadIdx.x == 0) {
+        s_distinct = 0;
         s_cur = -1;
         s_left = 0;
         s_cache_row = ~0ull;
@@ -613,7 +617,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
         auto rec = [&](unsigned li) -> const NbrRec& { return list[li < n1 ? li : nbr_cap - 1 - (li - n1)]; };
         if (nlist == 0 && !s_touched) {
             // nothing lands here: D keeps its zeros, or gets them (full_rows)
-            if (!GRAD && p.full_rows && !p.fo) {
+            if (!GRAD && p.full_rows && !(FUSED && p.fo)) {
                 double* dst = p.D + (rAt - p.row_base) * Nb + tlo;
                 for (int x = threadIdx.x; x < tsz; x += BLOCK) dst[x] = 0.0;
             }
@@ -1440,7 +1444,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
         if (lane == 0) my_terms += wterms;  // the per-wavefront count, folded once per item
         wterms = 0;
         __syncthreads();
-        if (!GRAD && p.fo) {
+        if (FUSED && p.fo) {
             // the list iteration's pass work on the finished tile (FusedOut)
             const FusedOut& f = *p.fo;
             const u64 rowbase = rAt * Nb;
@@ -1463,34 +1467,51 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 scan_basis(l, [&](u64 i, u32 x) { f.Y[(u64)l * f.cap + i] = yval(x); });
             if (f.distinct) {
                 u32 nz = 0;
-                for (int x = threadIdx.x; x < tsz; x += BLOCK) nz += (yval((u32)x) != 0.0) ? 1u : 0u;
-                for (int off = 32; off >= 1; off >>= 1) nz += (u32)__shfl_xor((int)nz, off);
-                if (lane == 0 && nz) atomicAdd((unsigned long long*)f.distinct, (unsigned long long)nz);
+                for (int x0 = 0; x0 < tsz; x0 += BLOCK) {
+                    const int x = x0 + (int)threadIdx.x;
+                    nz += (u32)__popcll(__ballot(x < tsz && yval((u32)x) != 0.0));
+                }
+                if (lane == 0 && nz) atomicAdd(&s_distinct, (unsigned long long)nz);
             }
             __syncthreads();
             for (int l = f.mark_from + wave; l < f.nl; l += WAVES)
                 scan_basis(l, [&](u64, u32 x) { acc[x] = 0.0; });
             __syncthreads();
             if (f.collect) {
+                // counted first: one addition to the list's length per tile (one
+                // per 64 candidates was a queue at that address: 26 of the 87 ms
+                // of 1e6 entries at 26 orbitals)
                 const u64 tb = *f.bound;
-                for (int x0 = 0; x0 < tsz; x0 += BLOCK) {
-                    const int x = x0 + (int)threadIdx.x;
+                auto cand = [&](int x) {
                     const double v = (x < tsz) ? yval((u32)x) : 0.0;
-                    const bool pk = ((u64)__double_as_longlong(v) & 0x7fffffffffffffffull) > tb;
+                    return ((u64)__double_as_longlong(v) & 0x7fffffffffffffffull) > tb;
+                };
+                u32 mine = 0;
+                for (int x0 = 0; x0 < tsz; x0 += BLOCK) mine += (u32)__popcll(__ballot(cand(x0 + (int)threadIdx.x)));
+                if (lane == 0) s_cand[wave] = mine;
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    u32 all = 0;
+                    for (int w = 0; w < WAVES; ++w) all += s_cand[w];
+                    s_cand0 = all ? atomicAdd((unsigned long long*)f.Rn, (unsigned long long)all) : 0ull;
+                }
+                __syncthreads();
+                u64 at0 = s_cand0;
+                for (int w = 0; w < wave; ++w) at0 += s_cand[w];
+                for (int x0 = 0; mine && x0 < tsz; x0 += BLOCK) {
+                    const int x = x0 + (int)threadIdx.x;
+                    const bool pk = cand(x);
                     const u64 m = __ballot(pk);
-                    if (m == 0) continue;
-                    u64 at0 = 0;
-                    if (lane == 0) at0 = atomicAdd((unsigned long long*)f.Rn, (unsigned long long)__popcll(m));
-                    at0 = (u64)__shfl((long long)at0, 0);
                     if (pk) {
                         const u64 at = at0 + (u64)__popcll(m & ((1ull << lane) - 1ull));
                         if (at < f.Rcap) {
                             f.Rr[at] = rowbase + tlo + (u64)x;
-                            f.Ra[at] = v;
+                            f.Ra[at] = yval((u32)x);
                         } else {
                             *f.overflow = 1;
                         }
                     }
+                    at0 += (u64)__popcll(m);
                 }
             }
         } else if (!GRAD && s_touched) {
@@ -1511,6 +1532,10 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
     if (lane == 0) my_terms += wterms;
     for (int off = 32; off >= 1; off >>= 1) my_terms += __shfl_xor(my_terms, off);
     if (lane == 0 && s_cur >= 0 && p.emitted && my_terms) atomicAdd(p.emitted, (unsigned long long)my_terms);
+    if (FUSED) {
+        __syncthreads();
+        if (threadIdx.x == 0 && s_distinct) atomicAdd((unsigned long long*)p.fo->distinct, s_distinct);
+    }
 }
 
 // slab_n2 > 0: every wavefront stages the (ia|jb) slab of its alpha-single
@@ -1922,12 +1947,13 @@ static unsigned rt_itab_doubles(unsigned n2) { return (2 * n2 + 40 + 1) & ~1u; }
 
 // The tile kernels' static LDS, as compiled (the largest of the three), so
 // that static + dynamic LDS never exceeds what a workgroup may hold.
+// (more than 128 registers would leave one such workgroup on a compute unit)
 static size_t rt_static_lds8() {
     static size_t cached = 0;
     if (cached == 0) {
         hipFuncAttributes attr{};
         SFCI_CHECK_HIP(hipFuncGetAttributes(&attr, (const void*)k_sigma_rowtile_whole8));
-        cached = attr.sharedSizeBytes;
+        cached = attr.numRegs <= 128 ? attr.sharedSizeBytes : (size_t)1 << 20;
     }
     return cached;
 }
@@ -2282,8 +2308,9 @@ RowTileGeom rowtile_geom(const RowTileDesc* d, int n_inst) {
     for (int k = 0; k < n_inst; ++k) {
         const SpaceDev& sp = ((const RTParams*)d[k].raw)->sp;
         for (int m : {sp.na, sp.nb, sp.n - sp.na, sp.n - sp.nb}) half = half && m * (m - 1) / 2 <= RT_PAIRS8;
+        half = half && !((const RTParams*)d[k].raw)->fo;
     }
-    const size_t room = (size_t)maxlds / 2 - rt_static_lds8();
+    const size_t room = (size_t)std::max<long long>(0, (long long)maxlds / 2 - (long long)rt_static_lds8());
     const size_t with8 = base + (size_t)(RT_WAVES / 2) * (n2 + 32) * sizeof(double);
     if (half && with8 <= room) {
         g.waves = RT_WAVES / 2;
