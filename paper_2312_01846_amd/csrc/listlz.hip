@@ -452,7 +452,7 @@ struct FusedPasses {
     FusedOut h{};
     FusedOut* d_fo;
     u64 room;
-    bool rest = false;  // the candidates of all rows behind the first pass fit
+    bool rest = false;  // the candidates of all rows behind the first pass fit, or none are wanted
 
     FusedPasses(sfci_problem* P_, const SigmaLaunch& v, ListPassSink& sink_, u64* emitted_dev, double eps)
         : P(P_), sink(sink_), emitted(emitted_dev),
@@ -482,8 +482,8 @@ struct FusedPasses {
         room = std::max<u64>(1ull << 24, 4 * std::min<u64>(C.K, 1ull << 26));
         size_t freeb = 0, totb = 0;
         SFCI_CHECK_HIP(hipMemGetInfo(&freeb, &totb));
-        rest = sink.collect && C.K < (1ull << 40) && 80 * C.K * 16 < freeb / 8;
-        if (rest) room = std::max<u64>(room, 80 * C.K);
+        rest = !sink.collect || (C.K < (1ull << 40) && 80 * C.K * 16 < freeb / 8);
+        if (rest && sink.collect) room = std::max<u64>(room, 80 * C.K);
     }
 
     // Target rows [lo, hi), or rows[lo .. hi) of a device list; through the
@@ -607,7 +607,7 @@ u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink
         FusedPasses F(P, v, sink, emitted_dev, eps);
         u64 lo = 0, passes = 0;
         for (; lo < P->Na; ++passes) {
-            const u64 rows = std::max<u64>(1, passes == 0 ? P->Na / 64 : F.rest ? P->Na : P->Na / 8);
+            const u64 rows = std::max<u64>(1, passes == 0 && sink.collect ? P->Na / 64 : F.rest ? P->Na : P->Na / 8);
             const u64 hi = std::min<u64>(P->Na, lo + rows);
             F.pass(lo, hi, nullptr);
             lo = hi;
@@ -676,28 +676,38 @@ u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, 
     std::vector<u32> rows(n);
     std::vector<u64> terms(n);
     const u64 above = heavy_row_terms(P);
-    u64 nh = 0, heavy_terms = 0;
+    u64 nh = 0;
     for (u64 r = 0; r < P->Na; ++r)
         if (const u64 c = reach.count[r]) {
             const u64 k = at[255 - cls(c)]++;
             rows[k] = (u32)r;
             terms[k] = c;
         }
-    while (nh < n && terms[nh] > above) heavy_terms += terms[nh++];
+    while (nh < n && terms[nh] > above) ++nh;
     u32* d = (u32*)P->list_ws.heavy.get(std::max<u64>(1, n) * sizeof(u32));
     SFCI_CHECK_HIP(hipMemcpyAsync(d, rows.data(), n * sizeof(u32), hipMemcpyHostToDevice, P->stream));
     SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
     // ranks do not come in order: a candidate that equals the bound stays in
     sink.cands->ties = true;
     u64 passes = 0;
-    for (u64 lo = 0, step = 32; lo < nh; step *= 16, ++passes) {
+    u64 ns = nh;  // (classes mix what lies about the limit: the table's parts are by each row's own count)
+    while (ns < n && terms[ns] > hash_rows_small()) ++ns;
+    // The bound comes from a first, small pass: of hash rows where the
+    // candidates above it surely fit, so that the heavy rows' tiles are one
+    // launch (of few heavy rows they were 6.5 ms of idle compute units), else
+    // of the heaviest rows.
+    u64 first = 0;
+    if (F.rest && sink.collect && ns > nh) {
+        first = std::min<u64>(ns - nh, 2048);
+        F.pass(nh, nh + first, d, &v, eps);
+        ++passes;
+    }
+    for (u64 lo = 0, step = first || !sink.collect ? std::max<u64>(1, nh) : 32; lo < nh; step *= 16, ++passes) {
         const u64 hi = std::min<u64>(nh, lo + step);
         F.pass(lo, hi, d);
         lo = hi;
     }
-    u64 ns = nh;  // (classes mix what lies about the limit: the table's parts are by each row's own count)
-    while (ns < n && terms[ns] > hash_rows_small()) ++ns;
-    for (u64 lo = nh, step = std::max<u64>(2048, nh); lo < n; step *= 16, ++passes) {
+    for (u64 lo = nh + first, step = F.rest ? n : std::max<u64>(2048, nh); lo < n; step *= 16, ++passes) {
         const u64 hi = std::min<u64>(lo < ns ? ns : n, lo + step);
         F.pass(lo, hi, d, &v, eps, lo >= ns);
         lo = hi;
