@@ -93,7 +93,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sigma_rowtile_c4batch_traffic.m
 
 
 def measured_traffic():
-    """HBM bytes per k_sigma_rowtile_whole launch from the committed counter summary
+    """HBM bytes per k_sigma_rowtile_whole8 launch from the committed counter summary
     (FETCH_SIZE + WRITE_SIZE, copy-calibrated), or None when the kernel source
     has changed since the counters were taken."""
     import hashlib
@@ -465,7 +465,7 @@ def bench_batch(args, torch, sfci, synth):
             "batched_speedup_vs_plain": plain["speedup"] if plain else None,
             "parallelism": "single GPU",
         },
-        "roofline": tile_roofline(st, alg_bytes, traffic, roof, kernel="k_sigma_rowtile_whole"),
+        "roofline": tile_roofline(st, alg_bytes, traffic, roof, kernel="k_sigma_rowtile_whole8"),
         "cpu_baseline": cpu,
     }
     print(json.dumps(rec))

