@@ -125,11 +125,12 @@ __device__ __forceinline__ int t1_par(u32 t) { return (int)(t >> 31); }
 // Input entries per chunk of the alpha-beta item lists (one wavefront's lanes).
 constexpr unsigned AB_CHUNK = 64;
 
-// An alpha-beta item: target beta rank within its tile (bits 0..13, tiles
-// hold at most 16 384 ranks), j n + b of the beta single (bits 14..23), the
-// entry within its chunk (bits 24..29), beta phase (bit 31, as in T1).
+// An alpha-beta item: target beta rank within its tile (bits 0..14, tiles
+// hold at most RT_TILE_MAX ranks), j n + b of the beta single (bits 15..24), the
+// entry within its chunk (bits 25..30), beta phase (bit 31, as in T1).
+constexpr int RT_TILE_MAX = 32768;
 __device__ __forceinline__ u32 ab_item(u32 rank_in_tile, u32 te, u32 entry) {
-    return rank_in_tile | (((te >> 21) & 1023u) << 14) | (entry << 24) | (te & 0x80000000u);
+    return rank_in_tile | (((te >> 21) & 1023u) << 15) | (entry << 25) | (te & 0x80000000u);
 }
 
 // Entries of the identity row per beta-beta-double and per beta-single work unit.
@@ -1317,9 +1318,9 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                             double e[AB_UNROLL], cc[AB_UNROLL];
 #pragma unroll
                             for (int u = 0; u < AB_UNROLL; ++u) {
-                                const u32 jb = (it[u] >> 14) & 1023u;
+                                const u32 jb = (it[u] >> 15) & 1023u;
                                 e[u] = gs ? slab[jb] : grow[jb];
-                                cc[u] = ampg[kc + ((it[u] >> 24) & 63u)];
+                                cc[u] = ampg[kc + ((it[u] >> 25) & 63u)];
                             }
 #pragma unroll
                             for (int u = 0; u < AB_UNROLL; ++u) {
@@ -1328,7 +1329,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                                 const double t = __hiloint2double(
                                     __double2hiint(pr) ^ (int)((it[u] ^ pa_bit) & 0x80000000u), __double2loint(pr));
                                 const bool keep = act && !xscreened(t, eps_x);
-                                if (keep) atomicAdd(&acc[it[u] & 0x3FFFu], t);
+                                if (keep) atomicAdd(&acc[it[u] & 0x7FFFu], t);
                                 wterms += (u32)__popcll(__ballot(keep && e[u] != 0.0));
                             }
                         }
@@ -2047,7 +2048,7 @@ bool rowtile_available(sfci_problem* P) {
     const size_t reserve = (rt_itab_doubles((unsigned)(P->n * P->n)) + RT_WAVES * 32) * sizeof(double);
     int tile_max = (int)(((size_t)maxlds - static_lds - reserve - 512) / sizeof(double));
     if (tile_max < 1024) return false;
-    tile_max = std::min(tile_max, 16384);
+    tile_max = std::min(tile_max, RT_TILE_MAX);
     if (const char* env = getenv("SFCI_TILE_MAX")) tile_max = std::max(1024, std::min(tile_max, atoi(env)));
     plan_tiles(P, S, tile_max);
     S->lds_bytes = (size_t)S->tile_max * sizeof(double);
@@ -2145,7 +2146,7 @@ static void build_ab_lists(sfci_problem* P, RowTileState* S, const SigmaLaunch& 
     size_t freeb = 0, totb = 0;
     SFCI_CHECK_HIP(hipMemGetInfo(&freeb, &totb));
     const size_t held = P->ws_ab_rc.bytes + P->ws_ab_cr.bytes + P->ws_ab_off.bytes + P->ws_ab_it.bytes;
-    if (need > (freeb + held) / 3 || S->tile_max > 16384) return;
+    if (need > (freeb + held) / 3 || S->tile_max > RT_TILE_MAX) return;
     u64* rowchunk = (u64*)P->ws_ab_rc.get((P->Na + 1) * sizeof(u64));
     u32* chunkrow = (u32*)P->ws_ab_cr.get(chunks_max * sizeof(u32));
     u64* off = (u64*)P->ws_ab_off.get(n_off * sizeof(u64));
