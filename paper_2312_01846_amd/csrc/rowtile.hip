@@ -1466,7 +1466,9 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             };
             for (int l = wave; l < f.nl; l += WAVES)
                 scan_basis(l, [&](u64 i, u32 x) { f.Y[(u64)l * f.cap + i] = yval(x); });
-            if (f.distinct) {
+            // nonzero sums, before supp(w_j) and supp(w_{j-1}) are taken out
+            const bool both = f.collect && f.nl == 0;  // counted with the candidates
+            if (f.distinct && !both) {
                 u32 nz = 0;
                 for (int x0 = 0; x0 < tsz; x0 += BLOCK) {
                     const int x = x0 + (int)threadIdx.x;
@@ -1474,22 +1476,27 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 }
                 if (lane == 0 && nz) atomicAdd(&s_distinct, (unsigned long long)nz);
             }
-            __syncthreads();
-            for (int l = f.mark_from + wave; l < f.nl; l += WAVES)
-                scan_basis(l, [&](u64, u32 x) { acc[x] = 0.0; });
-            __syncthreads();
+            if (f.nl > 0) {
+                __syncthreads();
+                for (int l = f.mark_from + wave; l < f.nl; l += WAVES)
+                    scan_basis(l, [&](u64, u32 x) { acc[x] = 0.0; });
+                __syncthreads();
+            }
             if (f.collect) {
                 // counted first: one addition to the list's length per tile (one
                 // per 64 candidates was a queue at that address: 26 of the 87 ms
                 // of 1e6 entries at 26 orbitals)
                 const u64 tb = *f.bound;
-                auto cand = [&](int x) {
+                auto above = [&](double v) { return ((u64)__double_as_longlong(v) & 0x7fffffffffffffffull) > tb; };
+                u32 mine = 0, nz = 0;
+                for (int x0 = 0; x0 < tsz; x0 += BLOCK) {
+                    const int x = x0 + (int)threadIdx.x;
                     const double v = (x < tsz) ? yval((u32)x) : 0.0;
-                    return ((u64)__double_as_longlong(v) & 0x7fffffffffffffffull) > tb;
-                };
-                u32 mine = 0;
-                for (int x0 = 0; x0 < tsz; x0 += BLOCK) mine += (u32)__popcll(__ballot(cand(x0 + (int)threadIdx.x)));
+                    mine += (u32)__popcll(__ballot(above(v)));
+                    nz += (u32)__popcll(__ballot(v != 0.0));
+                }
                 if (lane == 0) s_cand[wave] = mine;
+                if (lane == 0 && both && f.distinct && nz) atomicAdd(&s_distinct, (unsigned long long)nz);
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     u32 all = 0;
@@ -1501,13 +1508,14 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 for (int w = 0; w < wave; ++w) at0 += s_cand[w];
                 for (int x0 = 0; mine && x0 < tsz; x0 += BLOCK) {
                     const int x = x0 + (int)threadIdx.x;
-                    const bool pk = cand(x);
+                    const double v = (x < tsz) ? yval((u32)x) : 0.0;
+                    const bool pk = above(v);
                     const u64 m = __ballot(pk);
                     if (pk) {
                         const u64 at = at0 + (u64)__popcll(m & ((1ull << lane) - 1ull));
                         if (at < f.Rcap) {
                             f.Rr[at] = rowbase + tlo + (u64)x;
-                            f.Ra[at] = yval((u32)x);
+                            f.Ra[at] = v;
                         } else {
                             *f.overflow = 1;
                         }
