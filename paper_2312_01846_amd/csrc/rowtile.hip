@@ -81,7 +81,7 @@ struct RTParams {
                                  // need not be zero before the launch
     u32 gs_min;                  // sigma, alpha-beta doubles: a source row's (ia|jb) slab is staged in LDS
                                  // when it has more than this many entries (else elements are read globally)
-    u32 pad_gs;
+    u32 split;                   // sigma: entries of an alpha-single record at most (a multiple of 64)
     // Rows of several tiles (sigma): the alpha-beta doubles' items of every
     // input chunk (up to AB_CHUNK consecutive entries of one alpha row), by
     // target tile: the items of (chunk c, tile t) are ab_it[ab_off[c ntiles
@@ -453,6 +453,32 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
             }
         }
 
+        // sigma: an alpha single of more than p.split entries is several records,
+        // for several wavefronts; a tile's direct targets stay with the first
+        // (one-tile rows: with the entries).
+        auto push_parts = [&](NbrRec& r, bool keep) {
+            if (GRAD) {
+                push(r, keep);
+                return;
+            }
+            u32 rest = keep && r.type == 1 && r.rowe - r.rowb > p.split ? r.rowe : 0u;
+            if (rest) {
+                r.rowe = r.rowb + p.split;
+                if (whole_rows) r.e1 = r.rowe;
+            }
+            push(r, keep);
+            while (__ballot(rest != 0u)) {
+                if (rest) {
+                    r.rowb = r.rowe;
+                    r.rowe = min(rest, r.rowb + p.split);
+                    r.e0 = whole_rows ? r.rowb : 0u;
+                    r.e1 = whole_rows ? r.rowe : 0u;
+                }
+                push(r, rest != 0u);
+                if (r.rowe == rest) rest = 0u;
+            }
+        };
+
         // Phase 1: the nonempty source rows, with their entry range in this tile.
         const bool multi = !WHOLE && !GRAD && p.ntiles > 1;
         const bool cached = multi && s_cache_row == rAt && s_cache_inst == s_inst;
@@ -476,7 +502,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                     // an alpha double's few entries here are added at once (no list entry)
                     if (r.type == 2 && (r.e1 <= r.e0 || take_double(r, (u32)tlo, p))) r.type = 255;
                 }
-                push(r, r.type != 255);
+                push_parts(r, r.type != 255);
             }
         }
         for (;;) {
@@ -596,7 +622,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 if (k1) rowlist[s1 + __popcll(m1 & lt)] = rr;
                 if (k2) rowlist[nbr_cap - 1 - (s2 + __popcll(m2 & lt))] = rr;
             }
-            push(r, r.type != 255);
+            push_parts(r, r.type != 255);
         }
         if (multi && !cached) {
             __syncthreads();
@@ -1292,7 +1318,7 @@ __device__ __forceinline__ void rowtile_body(const RTParams* __restrict__ descs,
                 const auto ampg = gl(p.v_amp);
                 const auto grow = gl(p.I.g + ((u32)I_ * n + A_) * (u32)(n * n));
                 const u64 nt = (u64)p.ntiles;
-                const u64 c0 = p.ab_rowchunk[r.rAs];
+                const u64 c0 = p.ab_rowchunk[r.rAs] + (r.rowb - (u32)p.rowbeg[r.rAs]) / AB_CHUNK;
                 const u64 c1 = c0 + (r.rowe - r.rowb + AB_CHUNK - 1) / AB_CHUNK;
                 const u32 pa_bit = (gs ? 0u : (u32)r.par) << 31;
                 const double eps_x = p.eps_x;
@@ -2271,10 +2297,19 @@ RowTileDesc rowtile_prepare(sfci_problem* P, const SigmaLaunch& v, double* D, un
     // sigma per run.  SFCI_GS_MIN overrides.
     rp.gs_min = (S->ntiles == 1) ? 32u : 0u;
     if (const char* env = getenv("SFCI_GS_MIN")) rp.gs_min = (u32)std::max(0, atoi(env));
-    rp.pad_gs = 0;
+    // alpha-single rows in records of at most 256 entries (of several tiles, at
+    // most 8 192 such parts more than rows): one record per row left wavefronts
+    // waiting for the longest.  20 orbitals, ms with 128, 256, 512, 1 024 entries
+    // and whole rows: 900 138 entries 5.87, 5.75, 5.78, 5.93, 6.20; PT2 of 300 007
+    // 2.61, 2.61, 2.68, 2.82, 2.93; batch of 8 161.7, 160.0, 159.5, 159.6, 160.0;
+    // 26 orbitals, 1e6 entries, 64, 128, 256, 512, 1 024 and whole: 54.5, 53.5,
+    // 53.8, 55.5, 57.7, 62.6
+    rp.split = 256;
+    if (S->ntiles > 1) rp.split = (u32)std::max<u64>(256, (v.cap / 8192 + 63) / 64 * 64);
     if (const char* env = getenv("SFCI_SHORT_DOUBLE")) rp.short_dbl = (u32)std::max(0, atoi(env));
     out.n_items = P->Na * (u64)((S->ntiles + rp.tile_chunk - 1) / rp.tile_chunk);
     out.nbr_cap = 1 + (u64)na * nva + (u64)(na * (na - 1) / 2) * (u64)(nva * (nva - 1) / 2);
+    out.nbr_cap += std::min<u64>((u64)na * nva * (P->Nb / rp.split), v.cap / rp.split);  // parts of split rows
     out.lds_bytes = S->lds_bytes;
     out.cap = v.cap;
     out.n2 = (unsigned)(P->n * P->n);
