@@ -830,7 +830,7 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
         return SFCI_OK;
     }
     launch_scatter_set(P, P->d_D, sbar->rank, sbar->amp, scal + 1, std::max<u64>(1, sbar->nnz));
-    if (v->nnz && sbar->nnz && back_rows_available(P, v->nnz))
+    if (v->nnz && sbar->nnz && back_rows_available(P, v->nnz, sbar->nnz))
         launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
                          raw + RAW_PAD + n2);
     else

@@ -426,8 +426,15 @@ __global__ void k_expand_pairs(int n, const double* __restrict__ R4, double* __r
 
 }  // namespace
 
-bool back_rows_available(sfci_problem* P, u64 nnz) {
-    return nnz < (1ull << 31) && P->Na < (1ull << 31) && rowtile_available(P);
+// From a few thousand entries on: below, the walk per source is a few launches
+// less.  us, source walk and rows, v and sbar entries: 8 orbitals, 100 and 100
+// 114 and 164, 1 000 and 1 000 143 and 192; 16 orbitals, 1 000 and 20 000 240
+// and 255, 3 000 and 3 000 249 and 257, 3 000 and 100 000 485 and 292, 10 000
+// and 10 000 548 and 386.  SFCI_BACK_ROWS=0|1 forces one form.
+bool back_rows_available(sfci_problem* P, u64 nnz, u64 nnz_s) {
+    bool pays = nnz >= 4096 || (nnz >= 1024 && nnz_s >= 65536);
+    if (const char* env = getenv("SFCI_BACK_ROWS")) pays = env[0] != '0';
+    return pays && nnz < (1ull << 31) && P->Na < (1ull << 31) && rowtile_available(P);
 }
 
 // sbar must already be scattered into the (otherwise zero) dense array D.

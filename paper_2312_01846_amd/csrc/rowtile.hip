@@ -33,9 +33,10 @@ constexpr int RT_BLOCK = 64 * RT_WAVES;
 // 900 138 entries at 20 orbitals, 4 with two) overlap the other's sums.  But a
 // single heavy row takes twice as long, so this serves several instances in one
 // launch (8 at 20 orbitals 177 -> 161 ms, 16 orbitals 20.3 -> 17.3, 12 orbitals
-// 15.7 -> 12.5; 2 at 20 orbitals 17.5 and 17.6) and vectors of at most an entry
-// per row (20 orbitals, 3 000 entries 0.52 -> 0.47 ms; but 30 000 near the
-// aufbau string 0.87 -> 1.03, 900 138 6.19 -> 6.41).
+// 15.7 -> 12.5; 2 at 20 orbitals 17.5 and 17.6), if there are rows enough or the
+// rows are short (5 of 190 rows, some 500 entries a row: 27.8 -> 34.3), and
+// vectors of at most an entry per row (20 orbitals, 3 000 entries 0.52 -> 0.47
+// ms; but 30 000 near the aufbau string 0.87 -> 1.03, 900 138 6.19 -> 6.41).
 constexpr int RT_PAIRS8 = 256;  // orbital pairs of such a launch
 constexpr int RT_PH = 10;  // phase-timing bins
 
@@ -2348,7 +2349,12 @@ RowTileGeom rowtile_geom(const RowTileDesc* d, int n_inst) {
     unsigned ja = 0;
     for (int k = 0; k < n_inst; ++k) ja = std::max(ja, d[k].ja_doubles);
     // two workgroups of eight wavefronts where both fit
-    bool half = g.whole && (n_inst > 1 || d[0].cap <= ((const RTParams*)d[0].raw)->sp.Na);
+    u64 rows = 0, entries = 0;
+    for (int k = 0; k < n_inst; ++k) {
+        rows += ((const RTParams*)d[k].raw)->sp.Na;
+        entries += d[k].cap;
+    }
+    bool half = g.whole && (n_inst > 1 ? rows >= 4096 || entries <= 128 * rows : entries <= rows);
     for (int k = 0; k < n_inst; ++k) {
         const SpaceDev& sp = ((const RTParams*)d[k].raw)->sp;
         for (int m : {sp.na, sp.nb, sp.n - sp.na, sp.n - sp.nb}) half = half && m * (m - 1) / 2 <= RT_PAIRS8;

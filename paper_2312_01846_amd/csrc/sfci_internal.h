@@ -184,7 +184,7 @@ void launch_backward_dense(sfci_problem* P, const SigmaLaunch& v, const double* 
 void launch_scatter_zero(sfci_problem* P, double* D, const u64* r, const u64* nnz, u64 cap);
 // The same from the row view of v and the beta-single table (backrows.hip),
 // where they are available; s_rank: the ranks of the cotangent, Rg = Rh + n^2.
-bool back_rows_available(sfci_problem* P, u64 nnz);
+bool back_rows_available(sfci_problem* P, u64 nnz, u64 nnz_s);
 void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
                       u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg);
 

@@ -16,12 +16,14 @@ CASES = {"one": (9, 2, 3, 1, 1500, 1.0), "long rows": (11, 1, 5, 3000, 2500, 1.0
          "sparse rows": (12, 4, 4, 2000, 20000, 0.3)}
 
 
+@pytest.mark.parametrize("form", ["1", "0"])
 @pytest.mark.parametrize("name", list(CASES))
-def test_backward_rows_match_oracle(name, monkeypatch):
+def test_backward_rows_match_oracle(name, form, monkeypatch):
     import oracle
 
     from paper_2312_01846_amd import sfci
 
+    monkeypatch.setenv("SFCI_BACK_ROWS", form)  # the rows, and the walk per source that short inputs take
     n, na, nb, nv, ns, rows = CASES[name]
     if name == "tiles":
         monkeypatch.setenv("SFCI_TILE_MAX", "1024")
