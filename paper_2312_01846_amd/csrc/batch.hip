@@ -378,6 +378,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             DVec w = I[k].W(j);
             descs[k] = rowtile_prepare(I[k].P, SigmaLaunch{w.r, w.a, w.nnz, w.cap}, I[k].P->d_D,
                                        (unsigned long long*)(I[k].sc + 32), o->screen_eps, false, batched_rest);
+            if (n > 1) rowtile_many(descs[k]);
         });
         for (int k = 0; k < n; ++k) {
             pre[k + 1] = pre[k] + descs[k].n_items;

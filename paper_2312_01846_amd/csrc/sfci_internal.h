@@ -242,6 +242,7 @@ struct RowView {
     const double* K4;             // same-spin double elements by orbital pairs
 };
 RowView rowtile_view(const RowTileDesc& d);
+void rowtile_many(RowTileDesc& d);  // for a launch of several instances
 // The per-problem tables (rowtile_available(P) must hold; T2 may be NULL).
 struct RowTables {
     const u32* T1;
