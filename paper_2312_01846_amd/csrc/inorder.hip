@@ -670,9 +670,13 @@ bool geometry(sfci_problem* P, Geometry* g) {
 // against 790); above, from a quarter as many terms as determinants: 3 000
 // entries of 4.5e8 determinants (0.07 terms each) 15.0 ms against 10.4, 30 000
 // (0.7) 52 against 63; of 2.4e8 (0.1) 7.5 against 7.0, (1.0) 23 against 41.
+// Few, long rows leave the chip idle behind the longest: entries near the aufbau
+// string, ms, rows and sort: 190 rows of 4 845 slots, 3 000 entries 1.2 and 1.1,
+// 10 000 2.5 and 1.8; 91 rows of 1 001, 3 000 0.65 and 0.88, 10 000 1.24 and 1.12;
+// 1 140 rows, 10 000 2.2 and 2.3, 100 000 8.8 and 14.4.
 bool inorder_available(sfci_problem* P, u64 nnz) {
     Geometry g;
-    if (nnz == 0) return false;
+    if (nnz == 0 || (P->Na < 256 && nnz > 4096 && nnz > 40 * P->Na)) return false;
     if (P->Ndet > (u64(1) << 25) && nnz * terms_per_source(P->n, P->na, P->nb) < P->Ndet / 4) return false;
     if (P->io_state == 0) {
         P->io_state = -1;
