@@ -86,7 +86,8 @@ typedef struct {
 
 /* Deduplication of the intermediate elements (Sec. 2.2 merge step). */
 enum {
-    SFCI_DEDUP_AUTO = 0,         /* dense if 8*N_det bytes fit the device, else sort */
+    SFCI_DEDUP_AUTO = 0,         /* by size: H kept by rows, the N_det array, or (it does not fit, or is
+                                    very large beside M and the input) rank lists */
     SFCI_DEDUP_DENSE = 1,        /* dense N_det array, target-owned tiles accumulated in LDS (order not fixed) */
     SFCI_DEDUP_SORT = 2,         /* stable radix sort + in-order segmented sum (deterministic) */
     SFCI_DEDUP_DENSE_ATOMIC = 3  /* dense N_det array, one FP64 global atomic per term (the first GPU path) */
@@ -95,7 +96,8 @@ enum {
 typedef struct {
     uint64_t M;        /* keep the M largest |sigma_k| (ties: see SFCI_TIE_SLACK); UINT64_MAX = all */
     int32_t dedup;     /* SFCI_DEDUP_* */
-    int32_t deterministic; /* 1: sort dedup and ordered reductions, bit-reproducible */
+    int32_t deterministic; /* 1: sums in ascending source rank (in-order rows or sort) and ordered reductions,
+                              bit-reproducible */
     double screen_eps; /* Sec. 3: merged entries with |sigma_k| < screen_eps are dropped before the
                           truncation (the paper uses 5e-5); 0 = off */
     int32_t tie_band;  /* 1: the truncation extension described at SFCI_TIE_SLACK; 0 = the paper's rule */
@@ -151,12 +153,12 @@ typedef struct {
     uint64_t M;            /* N_d of Sec. 2.1: entries kept per basis vector (at most M + SFCI_TIE_SLACK); UINT64_MAX = all */
     int32_t n_L;           /* basis vectors per block (N_L), 1..32 */
     int32_t n_iter;        /* sigma applications; n_iter / n_L blocks are run */
-    int32_t deterministic; /* 1: sort dedup and ordered reductions */
+    int32_t deterministic; /* 1: sums in ascending source rank and ordered reductions */
     int32_t dedup;         /* SFCI_DEDUP_* (ignored when deterministic) */
     double screen_eps;     /* Sec. 3: entries of H w_j with |c| < eps are dropped before T, Eq. 10
                               and the truncation (the paper uses 5e-5); 0 = off */
     int32_t no_dense;      /* 1: keep every vector as a rank list and never allocate the N_det array
-                              (sort path, alpha-range passes); implied when 8 N_det bytes do not fit */
+                              (passes of target rows); implied when 8 N_det bytes do not fit */
     int32_t autotune;      /* batched fast mode: 1 = choose the tile kernel's work sizes (beta singles and
                               beta-beta doubles per work unit, workgroups per CU) by timing candidates on the
                               last eager sigma step, once per batch; later calls reuse the choice */
@@ -224,9 +226,9 @@ sfci_status sfci_sigma_backward(sfci_problem* prob, const sfci_svec* v, const sf
  *   *e2 = sum over determinants k outside supp(Psi) of (H Psi)_k^2 / (*e0 - H_kk),
  *         divided by <Psi|Psi>;
  *   *n_external (may be NULL) = number of those k with (H Psi)_k != 0.
- * deterministic != 0: H Psi from the sort path and every sum in ascending
- * rank (bit-reproducible); else the dense tile kernel and tree reductions.
- * Needs the full H Psi as a list on the device (distinct entries x 16 B).
+ * deterministic != 0: every sum in ascending rank (bit-reproducible), and the
+ * full H Psi as a list on the device (distinct entries x 16 B); else the dense
+ * tile kernel and tree reductions (the list only where N_det does not fit).
  * Synchronises.  SFCI_E_ARG for an empty or zero-norm Psi. */
 sfci_status sfci_pt2(sfci_problem* prob, const sfci_svec* psi, int32_t deterministic, double* e0, double* e2,
                      uint64_t* n_external);
@@ -239,8 +241,8 @@ sfci_status sfci_pt2(sfci_problem* prob, const sfci_svec* psi, int32_t determini
  *   (an extension, not in the paper), i.e. sfci_sigma_backward with v = Psi
  *   and sbar = Psi / <Psi|Psi>; at an eigenvector these are the energy's
  *   Hellmann-Feynman derivatives.
- * deterministic != 0: H Psi from the sort path and the energy's sums in
- * ascending rank (bit-reproducible); else the dense tile kernel and tree
+ * deterministic != 0: H Psi's and the energy's sums in ascending rank
+ * (bit-reproducible); else the dense tile kernel and tree
  * reductions.  The gradients need the dense array (SFCI_E_UNSUPPORTED when
  * it does not fit).  Synchronises.  SFCI_E_ARG for an empty or zero-norm Psi. */
 sfci_status sfci_energy_gradients(sfci_problem* prob, const sfci_svec* psi, int32_t deterministic, double* energy,

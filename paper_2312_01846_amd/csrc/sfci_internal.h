@@ -585,21 +585,21 @@ struct EventTimer {
 
 // ---- list-based iteration and truncated sigma without an N_det array (listlz.hip) ----
 // sigma = H v in passes of target alpha rows (the sort path's, or with
-// tiles_ok the tile kernel's slices when the per-sigma cost rule picks them);
+// tiles_ok by target rows: tiles for all, or hash tables and tiles);
 // the top-M (tie rule) sorted by rank into out when it fits out_cap.  Returns
 // the selected count; *distinct_host (may be NULL) receives the number of
 // distinct nonzero entries.
 u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank, double* out_amp, u64 out_cap,
                     u64* emitted_dev, u64* distinct_host, bool tiles_ok, double eps = 0.0);
-// Fast mode's per-sigma choice between the tile kernel's slices (true) and
-// the sort path, from the input's size (SFCI_LIST_SIGMA=tile|sort forces one).
+// Fast mode's per-sigma choice of the tile kernel for all rows, from the
+// input's size (SFCI_LIST_SIGMA=tile|sort forces).
 bool list_sigma_tiles(sfci_problem* P, u64 nnz);
 // sigma = H v in full through the sort path's passes, no N_det array: the
 // nonzero entries sorted by rank in list_ws.Rr / Ra; returns their number.
 u64 sigma_list_full(sfci_problem* P, const SigmaLaunch& v, u64* emitted_dev, u64** r, double** a);
-// H v in full as a rank-sorted list (zeros dropped): the sort path when
-// deterministic or when the N_det array does not fit, else the dense tile
-// kernel compacted in rank order (the accumulator is zero again afterwards).
+// H v in full as a rank-sorted list (zeros dropped): the N_det array (in-order
+// rows when deterministic, else the tile kernel) compacted in rank order (it
+// is zero again afterwards), or the sort path where those do not apply.
 // The list lives in the problem's workspace until the next such call;
 // *cnt_dev receives its length, which is also returned.
 u64 sigma_full_list(sfci_problem* P, const SigmaLaunch& sl, bool det, u64* emitted, u64** yr, double** ya,
