@@ -579,13 +579,15 @@ __global__ __launch_bounds__(64 * IO_MAXW) void k_row_inorder(InOrder p) {
 }
 
 // T1x from T1: groups of 64 per beta rank, 1 << shift of them; behind the last
-// single the rank itself, then slots that nothing reads.
+// single, where there are fewer than 64, the rank itself (io_single's OWN form
+// adds the direct element there; the other form adds it apart, and its lanes
+// without a single must not meet a target), then slots that nothing reads.
 __global__ __launch_bounds__(256) void k_io_t1x(u32 Nb, u32 sB, u32 shift, const u32* __restrict__ T1,
                                                 u32* __restrict__ T1x) {
     const u64 all = (u64)Nb << (shift + 6);
     for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < all; t += (u64)gridDim.x * blockDim.x) {
         const u32 r = (u32)(t >> (shift + 6)), s = (u32)t & ((64u << shift) - 1u);
-        u32 v = s == sB ? r : Nb + (s & 63u);
+        u32 v = s == sB && sB < 64u ? r : Nb + (s & 63u);
         if (s < sB) {
             const u32 x = T1[(u64)r * sB + s];
             v = (x & 0x1FFFFFu) | ((x >> 21) & 1023u) << 16 | (x & 0x80000000u);
