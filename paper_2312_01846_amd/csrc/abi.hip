@@ -362,8 +362,8 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
                          ensure_dense(P);
     bool use_sort = !inorder && (opts->deterministic || opts->dedup == SFCI_DEDUP_SORT);
     bool list_tiles = false;  // no N_det array, fast: the tile kernel's slices may serve
-    if (!use_sort && opts->dedup == SFCI_DEDUP_AUTO && P->Ndet >= SIGMA_LIST_NDET && opts->M <= P->Ndet / 1024 &&
-        v->nnz * tps <= 6 * P->Ndet && rowtile_available(P)) {
+    if (!opts->deterministic && !use_sort && opts->dedup == SFCI_DEDUP_AUTO && P->Ndet >= SIGMA_LIST_NDET &&
+        opts->M <= P->Ndet / 1024 && v->nnz * tps <= 6 * P->Ndet && rowtile_available(P)) {
         use_sort = true;
         list_tiles = true;
     } else if (!use_sort && !ensure_dense(P)) {
@@ -394,7 +394,7 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
         u64 distinct = 0;
         const u64 need = sigma_list_topm(P, sl, opts->M, out->rank, out->amp,
                                          (out->rank && out->amp) ? out->capacity : 0, &scal[1], &distinct,
-                                         list_tiles, opts->screen_eps);
+                                         list_tiles && !opts->deterministic, opts->screen_eps);
         SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
         const u64 emitted = read_u64(P, &scal[1]);
         out->nnz = need;
