@@ -555,15 +555,7 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
     launch_fill_u64(sc, nsc, 0, P->stream);
     launch_fill_f64(Td, (size_t)nblk * 2 * nL * nL, 0.0, P->stream);
     SFCI_CHECK_HIP(hipMemsetAsync(status, 0, sizeof(int), P->stream));
-    u64 lcap = 0;
-    u64 *lr = nullptr;
-    double* la = nullptr;
     const bool inorder = det && !list_mode && inorder_available(P, cap);
-    if (det && !list_mode && !inorder) {
-        lcap = std::min<u64>(P->Ndet, cap * tps);
-        lr = (u64*)P->ws_list_r.get(lcap * sizeof(u64));
-        la = (double*)P->ws_list_a.get(lcap * sizeof(double));
-    }
     auto W = [&](int j) { return DVec{Wr + (size_t)j * cap, Wa + (size_t)j * cap, sc + j, cap}; };
     EventTimer tsig;
     tsig.on = (stats != nullptr);
@@ -591,6 +583,16 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
             SFCI_CHECK_HIP(hipMemcpyAsync(hr, yr, ny * sizeof(u64), hipMemcpyDeviceToDevice, P->stream));
             SFCI_CHECK_HIP(hipMemcpyAsync(ha, ya, ny * sizeof(double), hipMemcpyDeviceToDevice, P->stream));
         }
+    }
+    // the sort path's sigma as a list; taken here, as H Psi_i above may have
+    // grown the same workspace (sigma_full_list)
+    u64 lcap = 0;
+    u64 *lr = nullptr;
+    double* la = nullptr;
+    if (det && !list_mode && !inorder) {
+        lcap = std::min<u64>(P->Ndet, cap * tps);
+        lr = (u64*)P->ws_list_r.get(lcap * sizeof(u64));
+        la = (double*)P->ws_list_a.get(lcap * sizeof(double));
     }
     // D <- P D: D -= (<Psi_i|D>/q_i) Psi_i, roots in order
     auto project_dense = [&]() {
