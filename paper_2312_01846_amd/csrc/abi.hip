@@ -90,6 +90,14 @@ __global__ void k_checked_len(u64* nnz, u64 n, const int* flags) {
     if (threadIdx.x == 0) *nnz = (flags[0] || flags[1]) ? 0 : n;
 }
 
+// The lengths of two vectors, both 0 when either is bad.
+__global__ void k_checked_len2(u64* nnz, u64 n0, u64 n1, const int* flags) {
+    if (threadIdx.x != 0) return;
+    const bool bad = flags[0] || flags[1] || flags[2] || flags[3];
+    nnz[0] = bad ? 0 : n0;
+    nnz[1] = bad ? 0 : n1;
+}
+
 __global__ void k_set_u64(u64* p, u64 v) {
     if (threadIdx.x == 0) *p = v;
 }
@@ -797,11 +805,19 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
     const int n = P->n;
     const u64 n2 = (u64)n * n, n4 = n2 * n2;
     // [0] nnz(v) [1] nnz(sbar) [2] transposed v's count [4], [5] the vectors' flags: both are checked on the
-    // device, where a bad one counts as empty, and the flags are read once the work is queued
+    // device, where with a bad one both count as empty and no output is written; the flags are read once the
+    // work is queued
     u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));
+    const int* const bad = (const int*)&scal[4];
     launch_fill_u64(scal, 8, 0, P->stream);
-    launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
-    launch_check_vec(P, sbar->rank, sbar->nnz, scal + 1, (int*)&scal[5]);
+    for (int k = 0; k < 2; ++k) {
+        const sfci_svec* x = k ? sbar : v;
+        if (x->nnz)
+            hipLaunchKernelGGL(k_validate, dim3(g1(x->nnz)), dim3(256), 0, P->stream, x->rank, (u64)x->nnz, P->Ndet,
+                               (int*)&scal[4 + k]);
+    }
+    hipLaunchKernelGGL(k_checked_len2, dim3(1), dim3(64), 0, P->stream, scal, (u64)v->nnz, (u64)sbar->nnz, bad);
+    SFCI_CHECK_HIP(hipGetLastError());
     auto finish = [&] {
         u64 flags[2];
         SFCI_CHECK_HIP(hipMemcpyAsync(flags, &scal[4], sizeof(flags), hipMemcpyDeviceToHost, P->stream));
@@ -827,6 +843,7 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
         J.vt_rank = (u64*)P->ws_list_r.get(v->nnz * sizeof(u64));
         J.vt_amp = (double*)P->ws_list_a.get(v->nnz * sizeof(double));
         J.vt_nnz = scal + 2;
+        J.bad = bad;
         rowtile_gradients(P->stream, 1, &J, P->grad_ws);
         finish();
         return SFCI_OK;
@@ -834,9 +851,9 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
     launch_scatter_set(P, P->d_D, sbar->rank, sbar->amp, scal + 1, std::max<u64>(1, sbar->nnz));
     if (v->nnz && sbar->nnz && back_rows_available(P, v->nnz, sbar->nnz))
         launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
-                         raw + RAW_PAD + n2);
+                         raw + RAW_PAD + n2, bad);
     else
-        launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2);
+        launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2, bad);
     launch_scatter_zero(P, P->d_D, sbar->rank, scal + 1, std::max<u64>(1, sbar->nnz));
     finish();
     return SFCI_OK;

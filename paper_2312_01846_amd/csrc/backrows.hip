@@ -336,6 +336,12 @@ __global__ __launch_bounds__(BW_BLOCK) void k_back_rows(BackRows p) {
     }
 }
 
+// vbar before its partial sums (an empty v writes nothing: see bad).
+__global__ void k_back_zero(double* __restrict__ vbar, const u64* __restrict__ nnz) {
+    const u64 n = *nnz;
+    for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) vbar[i] = 0.0;
+}
+
 // The entries by beta string: how many each has, ...
 __global__ void k_back_count(const u32* __restrict__ vrb, const u64* __restrict__ nnz, u64* __restrict__ cnt) {
     const u64 n = *nnz;
@@ -439,7 +445,7 @@ bool back_rows_available(sfci_problem* P, u64 nnz, u64 nnz_s) {
 
 // sbar must already be scattered into the (otherwise zero) dense array D.
 void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
-                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg) {
+                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg, const int* bad) {
     const int n = P->n, na = P->na, nb = P->nb;
     const u64 n2 = (u64)n * n, n4 = n2 * n2, np2 = (u64)n * (n - 1) / 2;
     hipStream_t st = P->stream;
@@ -459,7 +465,9 @@ void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, co
     u32* used = n_chunk + 2;
     launch_fill_u64(cnt, zero_words, 0, st);
     launch_fill_f64(Rh, n2 + n4, 0.0, st);  // Rh and Rg are adjacent
-    if (vbar) launch_fill_f64(vbar, v.cap, 0.0, st);
+    if (vbar)
+        hipLaunchKernelGGL(k_back_zero, dim3((unsigned)std::max<u64>(1, std::min<u64>((v.cap + 255) / 256, 16384))),
+                           dim3(256), 0, st, vbar, v.v_nnz);
     const unsigned gr = (unsigned)std::min<u64>((P->Na + 255) / 256, 16384);
     hipLaunchKernelGGL(k_back_chunks, dim3(gr), dim3(256), 0, st, SpaceDev{n, na, nb, P->Na, P->Nb}, P->d_binom,
                        rv.rowbeg, rv.rowend, chunk, n_chunk);
@@ -512,6 +520,6 @@ void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, co
     if (np2 > 0)
         hipLaunchKernelGGL(k_expand_pairs, dim3((unsigned)std::min<u64>((np2 * np2 + 255) / 256, 4096)), dim3(256), 0,
                            st, n, (const double*)R4, Rg);
-    launch_symmetrise(P, Rh, Rg, dh, dg);
+    launch_symmetrise(P, Rh, Rg, dh, dg, bad);
     SFCI_CHECK_HIP(hipGetLastError());
 }

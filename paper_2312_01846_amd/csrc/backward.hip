@@ -113,7 +113,8 @@ __global__ __launch_bounds__(SFCI_BLOCK) void k_backward(BackParams p, const dou
 
 // dh = (R + R^T) / 2;  dg = the mean of R over the 8 index permutations of (pq|rs).
 __global__ void k_symmetrise(int n, const double* __restrict__ Rh, const double* __restrict__ Rg,
-                             double* __restrict__ dh, double* __restrict__ dg) {
+                             double* __restrict__ dh, double* __restrict__ dg, const int* __restrict__ bad) {
+    if (bad && (bad[0] || bad[1] || bad[2] || bad[3])) return;
     const int n2 = n * n, n4 = n2 * n2;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n4; t += gridDim.x * blockDim.x) {
         int s = t % n, r = (t / n) % n, q = (t / n2) % n, p = t / (n2 * n);
@@ -146,7 +147,7 @@ unsigned gsz(u64 n) {
 
 // sbar must already be scattered into the (otherwise zero) dense array D.
 void launch_backward_dense(sfci_problem* P, const SigmaLaunch& v, const double* D, double* vbar, double* dh, double* dg,
-                           double* Rh, double* Rg) {
+                           double* Rh, double* Rg, const int* bad) {
     const int n = P->n;
     const u64 n2 = (u64)n * n, n4 = n2 * n2;
     launch_fill_f64(Rh, n2, 0.0, P->stream);
@@ -157,14 +158,14 @@ void launch_backward_dense(sfci_problem* P, const SigmaLaunch& v, const double* 
     u64 maxg = (u64)P->num_cu * 8;
     unsigned grid = (unsigned)(want < 1 ? 1 : (want > maxg ? maxg : want));
     hipLaunchKernelGGL(k_backward, dim3(grid), dim3(SFCI_BLOCK), 0, P->stream, p, D, vbar, Rh, Rg);
-    if (dh || dg) hipLaunchKernelGGL(k_symmetrise, dim3(gsz(n4)), dim3(256), 0, P->stream, n, Rh, Rg, dh, dg);
+    if (dh || dg) hipLaunchKernelGGL(k_symmetrise, dim3(gsz(n4)), dim3(256), 0, P->stream, n, Rh, Rg, dh, dg, bad);
     SFCI_CHECK_HIP(hipGetLastError());
 }
 
-void launch_symmetrise(sfci_problem* P, const double* Rh, const double* Rg, double* dh, double* dg) {
+void launch_symmetrise(sfci_problem* P, const double* Rh, const double* Rg, double* dh, double* dg, const int* bad) {
     const u64 n2 = (u64)P->n * P->n, n4 = n2 * n2;
     if (!dh && !dg) return;
-    hipLaunchKernelGGL(k_symmetrise, dim3(gsz(n4)), dim3(256), 0, P->stream, P->n, Rh, Rg, dh, dg);
+    hipLaunchKernelGGL(k_symmetrise, dim3(gsz(n4)), dim3(256), 0, P->stream, P->n, Rh, Rg, dh, dg, bad);
     SFCI_CHECK_HIP(hipGetLastError());
 }
 

@@ -2641,6 +2641,6 @@ void rowtile_gradients(hipStream_t st, int n_jobs, const GradJob* jobs, RowTileG
         hipLaunchKernelGGL(k_scatter_tr, dim3(g256(J.s_cap)), dim3(256), 0, st, P->d_D, J.s_rank,
                            (const double*)nullptr, J.s_nnz, P->Na, P->Nb);
         SFCI_CHECK_HIP(hipGetLastError());
-        launch_symmetrise(P, J.Rh, J.Rg, J.dh, J.dg);
+        launch_symmetrise(P, J.Rh, J.Rg, J.dh, J.dg, J.bad);
     }
 }

@@ -179,14 +179,17 @@ void launch_rank(sfci_problem* P, const u64* a, const u64* b, u64 cnt, u64* rank
 void launch_unrank(sfci_problem* P, const u64* rank, u64 cnt, u64* a, u64* b, int* bad);
 // Backward of sigma = H v (backward.hip).  The cotangent must already be
 // scattered into the zero dense array D.  Rh (n^2) and Rg (n^4) are scratch.
+// bad (device, may be NULL): four flags; with one set vbar, dh and dg are left
+// as they are (v must then count as empty).
 void launch_backward_dense(sfci_problem* P, const SigmaLaunch& v, const double* D, double* vbar, double* dh, double* dg,
-                           double* Rh, double* Rg);
+                           double* Rh, double* Rg, const int* bad = nullptr);
 void launch_scatter_zero(sfci_problem* P, double* D, const u64* r, const u64* nnz, u64 cap);
 // The same from the row view of v and the beta-single table (backrows.hip),
 // where they are available; s_rank: the ranks of the cotangent, Rg = Rh + n^2.
 bool back_rows_available(sfci_problem* P, u64 nnz, u64 nnz_s);
 void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
-                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg);
+                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg,
+                      const int* bad = nullptr);
 
 // ---- target-owned dense sigma (rowtile.hip) ----
 bool rowtile_available(sfci_problem* P);  // builds the per-problem tables on first use
@@ -333,10 +336,12 @@ struct GradJob {
     // sbar is v scaled by a constant (the energy's gradient): each pair of
     // distinct connected rows is then visited once and counted twice
     bool pair_sym;
+    const int* bad;  // as in launch_backward_dense
 };
 bool rowtile_grad_available(sfci_problem* P);
 void rowtile_gradients(hipStream_t st, int n_jobs, const GradJob* jobs, RowTileGradWs& ws);
-void launch_symmetrise(sfci_problem* P, const double* Rh, const double* Rg, double* dh, double* dg);
+void launch_symmetrise(sfci_problem* P, const double* Rh, const double* Rg, double* dh, double* dg,
+                       const int* bad = nullptr);
 
 // ---- utilities (util.hip) ----
 void launch_fill_f64(double* p, u64 n, double val, hipStream_t s);
