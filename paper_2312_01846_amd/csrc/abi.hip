@@ -849,7 +849,13 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
         return SFCI_OK;
     }
     launch_scatter_set(P, P->d_D, sbar->rank, sbar->amp, scal + 1, std::max<u64>(1, sbar->nnz));
-    if (v->nnz && sbar->nnz && back_rows_available(P, v->nnz, sbar->nnz))
+    // by rows, v_bar collects partial sums while v is read; by sources an entry of v is read before its sum is
+    // written, so that v_bar may stand in v's place
+    const auto over = [&](const void* x) {
+        return v_bar && (const char*)v_bar < (const char*)x + 8 * v->nnz &&
+               (const char*)x < (const char*)(v_bar + v->nnz);
+    };
+    if (v->nnz && sbar->nnz && !over(v->amp) && !over(v->rank) && back_rows_available(P, v->nnz, sbar->nnz))
         launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
                          raw + RAW_PAD + n2, bad);
     else
