@@ -170,7 +170,8 @@ __device__ __forceinline__ double back_neighbours(const BackRows& p, double* sla
 #pragma unroll
         for (int u = 0; u < BW_U; ++u) {
             if (__ballot(sb[u] != 0.0) == 0) continue;
-            const double w = sb[u] * lane_f64(ck, q0 + u);
+            // (no term where the cotangent is zero, whatever the amplitude: an infinite one would leave NaN)
+            const double w = sb[u] != 0.0 ? sb[u] * lane_f64(ck, q0 + u) : 0.0;
             W += w;
             double e = e0;
             if (singles_here) {
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(BW_BLOCK) void k_back_rows(BackRows p) {
             if (!p.row_used[rA]) continue;
             const double sb = lane < cnt ? p.Sd[(u64)rA * Nb + rk] : 0.0;
             if (__ballot(sb != 0.0) == 0) continue;
-            const double w = sb * ck;
+            const double w = sb != 0.0 ? sb * ck : 0.0;
             if (sb != 0.0) {
                 vacc = diag_element(p.I, A, bt) * sb;
                 for (u32 m = bt; m; m &= m - 1u) {
