@@ -11,6 +11,9 @@
 // H is symmetric to the bit (the reversed excitation has the same spectators
 // in the same order of additions), so row k holds what enumerating k as a
 // source gives, in that order, zero elements included (a fixed row length).
+// A product with the whole row also meets the determinants that v does not
+// hold, which adds +-0 for a finite element only: with an element that is not
+// (infinite integrals, an overflow) the table is not used.
 #include <algorithm>
 
 #include "sfci_internal.h"
@@ -25,12 +28,14 @@ struct SinkRow {
     double* val;
     u32 pos;   // wave-uniform
     u32 nonzero;
+    bool odd;      // this lane met an element that is not finite
     __device__ __forceinline__ void operator()(bool ok, u64 tgt, double e, double, const Term&) {
         const u64 m = __ballot(ok);
         if (ok) {
             const u32 at = pos + (u32)__popcll(m & ((1ull << lane_id()) - 1ull));
             idx[at] = (u32)tgt;
             val[at] = e;
+            odd = odd || !(fabs(e) < INFINITY);
         }
         pos += (u32)__popcll(m);
         nonzero += (u32)__popcll(__ballot(ok && e != 0.0));
@@ -47,9 +52,10 @@ __global__ __launch_bounds__(SFCI_BLOCK) void k_small_build(SpaceDev sp, Ints I,
     const int wave = threadIdx.x >> 6;
     const u64 N = sp.Na * sp.Nb;
     for (u64 k = (u64)blockIdx.x * SFCI_WAVES_PER_BLOCK + wave; k < N; k += (u64)gridDim.x * SFCI_WAVES_PER_BLOCK) {
-        SinkRow sink{idx + k * tps, val + k * tps, 0u, 0u};
+        SinkRow sink{idx + k * tps, val + k * tps, 0u, 0u, false};
         enumerate_source<false, SinkRow, true>(sp, I, B, W[wave], k, 1.0, AlphaRange{0, 0}, sink);
         if (lane_id() == 0) nz[k] = sink.nonzero;
+        if (sink.odd) nz[N] = 1u;  // (zero before)
     }
 }
 
@@ -135,13 +141,21 @@ bool small_h_ready(sfci_problem* P) {
     if (N > (u64)SEL_ONE || N * tps * 12 > SMALL_H_BYTES) return false;
     u32* idx = (u32*)P->sh_idx.get(N * tps * sizeof(u32));
     double* val = (double*)P->sh_val.get(N * tps * sizeof(double));
-    u32* nz = (u32*)P->sh_nz.get(N * sizeof(u32));
+    u32* nz = (u32*)P->sh_nz.get((N + 2) * sizeof(u32));  // terms per column, then the flag of an element not finite
+    launch_fill_u64((u64*)(nz + (N & ~u64(1))), 1, 0, P->stream);
     (void)P->sh_vd.get(N * sizeof(double));
     const u64 want = (N + SFCI_WAVES_PER_BLOCK - 1) / SFCI_WAVES_PER_BLOCK;
     hipLaunchKernelGGL(k_small_build, dim3((unsigned)std::min<u64>(want, (u64)P->num_cu * 16)), dim3(SFCI_BLOCK), 0,
                        P->stream, SpaceDev{P->n, P->na, P->nb, P->Na, P->Nb}, Ints{P->d_h, P->d_g, P->n}, P->d_binom,
                        (u32)tps, idx, val, nz);
     SFCI_CHECK_HIP(hipGetLastError());
+    u32 odd = 0;
+    SFCI_CHECK_HIP(hipMemcpyAsync(&odd, nz + N, sizeof(u32), hipMemcpyDeviceToHost, P->stream));
+    SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+    if (odd) {
+        for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd}) b->release();
+        return false;
+    }
     small_step_setup(P);
     P->sh_state = 1;
     return true;
