@@ -931,10 +931,14 @@ __global__ __launch_bounds__(ONE_BLOCK) void k_sel_one(JP jp) {
     }
     unsigned keep, at[ONE_ITEMS];
     const OneResult R = one_select(L, v, nk, rank_of, J.M, J.band != 0, J.g, keep, at);
+    u64 r[ONE_ITEMS];
+#pragma unroll
+    for (int k = 0; k < ONE_ITEMS; ++k) r[k] = ((keep >> k) & 1u) ? rank_of(k) : 0;
+    __syncthreads();  // the output may stand in the list's place
 #pragma unroll
     for (int k = 0; k < ONE_ITEMS; ++k) {
         if ((keep >> k) & 1u) {
-            J.out_r[at[k]] = rank_of(k);
+            J.out_r[at[k]] = r[k];
             J.out_a[at[k]] = v[k];
         }
     }
@@ -1162,9 +1166,12 @@ void list_prepare(sfci_problem* P, const SelJob& J) {
     SFCI_CHECK_HIP(hipGetLastError());
 }
 
+// An output in the list's place is written by one wavefront: an entry never
+// moves up, so in order nothing is overwritten before it is read.
 void list_write(sfci_problem* P, const SelJob& J) {
-    hipLaunchKernelGGL(k_sel_write<OneJob>, dim3(seg_grid(P->num_cu, select_segments(J.cap))), dim3(256), 0,
-                       P->stream, OneJob{J});
+    const bool in_place = J.out_r == J.r || J.out_a == J.a;
+    hipLaunchKernelGGL(k_sel_write<OneJob>, dim3(in_place ? 1 : seg_grid(P->num_cu, select_segments(J.cap))),
+                       dim3(in_place ? 64 : 256), 0, P->stream, OneJob{J});
     SFCI_CHECK_HIP(hipGetLastError());
 }
 
