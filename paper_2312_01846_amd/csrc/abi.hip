@@ -293,6 +293,7 @@ sfci_status sfci_problem_destroy(sfci_problem* P) {
     }
     for (hipEvent_t e : P->ev)
         if (e) (void)hipEventDestroy(e);
+    if (P->io_host) (void)hipHostFree(P->io_host);
     rowtile_release(P);
     for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd, &P->io_tab, &P->ws_os}) b->release();
     DevBuf* bufs[] = {&P->ws_sel,   &P->ws_cnt,   &P->ws_scan,  &P->ws_scan2,  &P->ws_scalar, &P->ws_red,
@@ -365,9 +366,24 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     if (!(opts->screen_eps >= 0.0) || !(opts->excite_eps >= 0.0))
         return (sfci_status)sfci_set_error(SFCI_E_ARG, "screen_eps and excite_eps must be >= 0");
     const u64 tps = terms_per_source(P->n, P->na, P->nb);
-    // deterministic: in order into the dense accumulator where that is possible, else by the sort path
-    const bool inorder = opts->deterministic && opts->dedup != SFCI_DEDUP_SORT && inorder_available(P, v->nnz) &&
-                         ensure_dense(P);
+    CallEvents ev(P);
+    const hipEvent_t e0 = P->ev[0], e1 = P->ev[1];
+    // [0] nnz(v) [1] emitted [2] count [3] list count [4] validation flags
+    u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));
+    SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
+    // deterministic: in order into the dense accumulator where that is possible and the entries suit it (they are
+    // checked on the device first, a bad vector counting as empty), else by the sort path
+    bool inorder = opts->deterministic && opts->dedup != SFCI_DEDUP_SORT && inorder_available(P, v->nnz) &&
+                   ensure_dense(P);
+    RowTileDesc iod;
+    bool timed = false;
+    if (inorder) {
+        SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
+        timed = true;
+        launch_fill_u64(scal, 8, 0, P->stream);
+        launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
+        inorder = inorder_pays(P, sl, &iod);
+    }
     bool use_sort = !inorder && (opts->deterministic || opts->dedup == SFCI_DEDUP_SORT);
     bool list_tiles = false;  // no N_det array, fast: the tile kernel's slices may serve
     if (!opts->deterministic && !use_sort && opts->dedup == SFCI_DEDUP_AUTO && P->Ndet >= SIGMA_LIST_NDET &&
@@ -385,15 +401,10 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     if (use_sort) validate_vec(P, v->rank, v->nnz);
     P->tie_band = opts->tie_band ? 1 : 0;
     P->excite_eps = opts->excite_eps;
-    CallEvents ev(P);
-    const hipEvent_t e0 = P->ev[0], e1 = P->ev[1];
-    SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
-    // [0] nnz(v) [1] emitted [2] count [3] list count [4] validation flags
-    u64* scal = (u64*)P->ws_lz[0].get(8 * sizeof(u64));
+    if (!timed) SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
     const bool small = !use_sort && !inorder && opts->dedup == SFCI_DEDUP_AUTO && opts->excite_eps == 0.0 &&
                        small_h_ready(P);
-    launch_fill_u64(scal, 8, 0, P->stream);
-    SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
+    if (!inorder) launch_fill_u64(scal, 8, 0, P->stream);
     if (use_sort) {
         launch_set_u64(P, scal, v->nnz);
         // alpha-range passes (sort path, or tile-kernel slices in fast mode)
@@ -427,8 +438,8 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
         launch_small_load(P, v->rank, v->amp, nullptr, v->nnz, true, scal, nullptr, &scal[1], (int*)&scal[4]);
         launch_small_sigma(P, opts->screen_eps);
     } else {
-        launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
-        if (inorder) launch_sigma_inorder(P, sl, P->d_D, (unsigned long long*)&scal[1], opts->screen_eps);
+        if (!inorder) launch_check_vec(P, v->rank, v->nnz, scal, (int*)&scal[4]);
+        if (inorder) launch_sigma_inorder(P, sl, iod, P->d_D, (unsigned long long*)&scal[1], opts->screen_eps);
         else dense_sigma(P, sl, opts->dedup, (unsigned long long*)&scal[1], opts->screen_eps);
     }
     src.dense = P->d_D;
@@ -592,16 +603,6 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
             SFCI_CHECK_HIP(hipMemcpyAsync(ha, ya, ny * sizeof(double), hipMemcpyDeviceToDevice, P->stream));
         }
     }
-    // the sort path's sigma as a list; taken here, as H Psi_i above may have
-    // grown the same workspace (sigma_full_list)
-    u64 lcap = 0;
-    u64 *lr = nullptr;
-    double* la = nullptr;
-    if (det && !list_mode && !inorder) {
-        lcap = std::min<u64>(P->Ndet, cap * tps);
-        lr = (u64*)P->ws_list_r.get(lcap * sizeof(u64));
-        la = (double*)P->ws_list_a.get(lcap * sizeof(double));
-    }
     // D <- P D: D -= (<Psi_i|D>/q_i) Psi_i, roots in order
     auto project_dense = [&]() {
         for (int i = 0; i < n_roots; ++i) {
@@ -676,10 +677,15 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
                                           P->stream));
             SigmaLaunch sl{wj.r, wj.a, wj.nnz, cap};
             tsig.begin(P->stream);
-            if (inorder) {
-                launch_sigma_inorder(P, sl, P->d_D, (unsigned long long*)(sc + 32), o->screen_eps);
+            RowTileDesc iod;
+            if (inorder && inorder_pays(P, sl, &iod)) {
+                launch_sigma_inorder(P, sl, iod, P->d_D, (unsigned long long*)(sc + 32), o->screen_eps);
                 tsig.end(P->stream);
             } else if (det) {
+                // the sort path's sigma as a list, in a workspace that H Psi_i above may have grown
+                const u64 lcap = std::min<u64>(P->Ndet, cap * tps);
+                u64* const lr = (u64*)P->ws_list_r.get(lcap * sizeof(u64));
+                double* const la = (double*)P->ws_list_a.get(lcap * sizeof(double));
                 sigma_sorted(P, sl, lcap, lr, la, sc + 33, sc + 32);
                 tsig.end(P->stream);
                 launch_scatter_set(P, P->d_D, lr, la, sc + 33, lcap);

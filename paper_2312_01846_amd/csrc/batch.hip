@@ -230,8 +230,8 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
         q.psi_a = (double*)P->ws_lz[7].get(2 * pcap * sizeof(double));
         q.sbar = q.psi_a + pcap;
         q.inorder = det && inorder_available(P, q.cap);
+        q.lcap = det ? std::min<u64>(P->Ndet, q.cap * q.tps) : 0;
         if (det && !q.inorder) {
-            q.lcap = std::min<u64>(P->Ndet, q.cap * q.tps);
             q.lr = (u64*)P->ws_list_r.get(q.lcap * sizeof(u64));
             q.la = (double*)P->ws_list_a.get(q.lcap * sizeof(double));
         }
@@ -415,9 +415,12 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
             Inst& q = I[k];
             DVec w = q.W(j);
             SigmaLaunch sl{w.r, w.a, w.nnz, w.cap};
-            if (q.inorder) {
-                launch_sigma_inorder(q.P, sl, q.P->d_D, (unsigned long long*)(q.sc + 32), o->screen_eps);
+            RowTileDesc iod;
+            if (q.inorder && inorder_pays(q.P, sl, &iod)) {
+                launch_sigma_inorder(q.P, sl, iod, q.P->d_D, (unsigned long long*)(q.sc + 32), o->screen_eps);
             } else if (det) {
+                q.lr = (u64*)q.P->ws_list_r.get(q.lcap * sizeof(u64));
+                q.la = (double*)q.P->ws_list_a.get(q.lcap * sizeof(double));
                 sigma_sorted(q.P, sl, q.lcap, q.lr, q.la, q.sc + 33, q.sc + 32);
                 launch_scatter_set(q.P, q.P->d_D, q.lr, q.la, q.sc + 33, q.lcap);
                 if (o->screen_eps > 0.0) launch_screen(q.P, q.P->d_D, q.P->Ndet, o->screen_eps);

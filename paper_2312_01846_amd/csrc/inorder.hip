@@ -27,6 +27,9 @@
 // an instruction in ~8 clocks, 230 clocks per alpha-single entry (20 011
 // entries near the aufbau string of 19 orbitals: 1.2 of the call's 1.5 ms).
 #include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <vector>
 
 #include "sfci_internal.h"
 
@@ -624,11 +627,61 @@ __global__ void k_io_slabs(int n, const double* __restrict__ g, const double* __
     if (lane == 0) gnz[ia] = (unsigned char)((o ? 1 : 0) | (d ? 2 : 0));
 }
 
-struct Geometry {
-    u32 words, off_rows, per_wave;
-    int waves, per_cu;
-    size_t lds;
+// us per entry of a target row's own source row, and of an alpha-single source
+// row with and without alpha-beta elements: what the wavefront that owns the
+// target row spends on them (inorder_pays).
+struct IoWeights {
+    float id, single, single0;
 };
+
+// The heaviest target row's time (bits of a float) and the entries' number, to
+// the host words out by the last workgroup.  state: maximum and ticket, zero
+// between launches.
+__global__ __launch_bounds__(256) void k_io_load(SpaceDev sp, const u64* __restrict__ binom,
+                                                 const u32* __restrict__ astr, const u64* __restrict__ beg,
+                                                 const u64* __restrict__ end, const unsigned char* __restrict__ gnz,
+                                                 IoWeights w, const u64* __restrict__ nnz,
+                                                 unsigned* __restrict__ state, u64* __restrict__ out) {
+    __shared__ BinomLds B;
+    __shared__ float s_worst[4];
+    __shared__ uint8_t s_occ[4][32], s_vir[4][32];
+    load_binom(B, binom);
+    __syncthreads();
+    const int n = sp.n, na = sp.na, nva = n - na, sA = na * nva, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint8_t *occ = s_occ[wave], *vir = s_vir[wave];
+    float worst = 0.0f;
+    for (u64 r = (u64)blockIdx.x * 4 + wave; r < sp.Na; r += (u64)gridDim.x * 4) {
+        const u32 A = __builtin_amdgcn_readfirstlane(astr[r]);
+        wave_sync();
+        if (lane < n) {
+            const u32 below = (1u << lane) - 1u;
+            if ((A >> lane) & 1u) occ[__popc(A & below)] = (uint8_t)lane;
+            else vir[lane - __popc(A & below)] = (uint8_t)lane;
+        }
+        wave_sync();
+        float c = lane == 0 ? w.id * (float)(end[r] - beg[r]) : 0.0f;
+        for (int t = lane; t < sA; t += 64) {
+            const int i = vir[t % nva], a = occ[t / nva];  // the source holds i and lacks a
+            const u64 s = str_rank(A ^ (1u << i) ^ (1u << a), B);
+            c += ((gnz[i * n + a] & 1) ? w.single : w.single0) * (float)(end[s] - beg[s]);
+        }
+        for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
+        worst = fmaxf(worst, c);
+    }
+    if (lane == 0) s_worst[wave] = worst;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    worst = fmaxf(fmaxf(s_worst[0], s_worst[1]), fmaxf(s_worst[2], s_worst[3]));
+    __hip_atomic_fetch_max(&state[0], __float_as_uint(worst), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    if (__hip_atomic_fetch_add(&state[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+    out[0] = __hip_atomic_exchange(&state[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    out[1] = *nnz;
+    __hip_atomic_store(&state[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+using Geometry = InOrderGeom;
 
 // log2 of the groups of 64 that hold a beta rank's singles.
 u32 t1x_shift(u32 sB) {
@@ -672,10 +725,9 @@ bool geometry(sfci_problem* P, Geometry* g) {
 // against 790); above, from a quarter as many terms as determinants: 3 000
 // entries of 4.5e8 determinants (0.07 terms each) 15.0 ms against 10.4, 30 000
 // (0.7) 52 against 63; of 2.4e8 (0.1) 7.5 against 7.0, (1.0) 23 against 41.
-// Few, long rows leave the chip idle behind the longest: entries near the aufbau
-// string, ms, rows and sort: 190 rows of 4 845 slots, 3 000 entries 1.2 and 1.1,
-// 10 000 2.5 and 1.8; 91 rows of 1 001, 3 000 0.65 and 0.88, 10 000 1.24 and 1.12;
-// 1 140 rows, 10 000 2.2 and 2.3, 100 000 8.8 and 14.4.
+// Below 256 rows, many entries always make long rows (ms, in order and sort:
+// 190 rows of 4 845 slots, 10 000 entries near the aufbau string 2.5 and 1.8; 91
+// rows of 1 001 1.24 and 1.12); else the entries decide (inorder_pays).
 bool inorder_available(sfci_problem* P, u64 nnz) {
     Geometry g;
     if (nnz == 0 || (P->Na < 256 && nnz > 4096 && nnz > 40 * P->Na)) return false;
@@ -686,9 +738,12 @@ bool inorder_available(sfci_problem* P, u64 nnz) {
         const RowTables t = rowtile_tables(P);
         if (P->nb * (P->nb - 1) > 0 && (P->n - P->nb) * (P->n - P->nb - 1) > 0 && !t.T2r) return false;
         const u32 sB = (u32)(P->nb * (P->n - P->nb)), shift = t1x_shift(sB);
-        const size_t t1x = (size_t)P->Nb << (shift + 6);
-        u32* const tab = (u32*)P->io_tab.get((t1x + P->Na) * sizeof(u32) + 32 * 32 + 8);
+        // [T1x | alpha strings | slab flags, n^2 + 1 bytes | k_io_load's two words]
+        const size_t t1x = (size_t)P->Nb << (shift + 6), io_words = t1x + P->Na + (32 * 32 + 8) / 4;
+        u32* const tab = (u32*)P->io_tab.get((io_words + 2) * sizeof(u32));
         u32* const astr = tab + t1x;
+        SFCI_CHECK_HIP(hipMemsetAsync(tab + io_words, 0, 2 * sizeof(u32), P->stream));
+        P->io_state_words = tab + io_words;
         if (sB)
             hipLaunchKernelGGL(k_io_t1x, dim3((unsigned)std::min<size_t>((t1x + 255) / 256, 4096)), dim3(256), 0,
                                P->stream, (u32)P->Nb, sB, shift, t.T1, tab);
@@ -697,15 +752,75 @@ bool inorder_available(sfci_problem* P, u64 nnz) {
         hipLaunchKernelGGL(k_io_slabs, dim3((unsigned)(P->n * P->n + 1)), dim3(64), 0, P->stream, P->n, P->d_g,
                            t.K4, (unsigned char*)(astr + P->Na));
         SFCI_CHECK_HIP(hipGetLastError());
+        std::vector<unsigned char> f(P->n * P->n + 1);
+        SFCI_CHECK_HIP(hipMemcpyAsync(f.data(), astr + P->Na, f.size(), hipMemcpyDeviceToHost, P->stream));
+        SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+        P->io_ab = false;
+        for (size_t k = 0; k + 1 < f.size(); ++k) P->io_ab = P->io_ab || (f[k] & 1);
+        P->io_pairs = f.back() != 0;
+        P->io_geom = g;
         P->io_state = 1;
     }
     return P->io_state > 0;
 }
 
-void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, double* D, unsigned long long* emitted, double eps) {
-    Geometry g;
-    if (!geometry(P, &g)) throw sfci_error(-8, "in-order sigma: row does not fit");
-    const RowTileDesc d = rowtile_prepare(P, v, D, emitted, eps);
+// A target row is one wavefront's, so a vector whose entries gather in few
+// source rows waits for the longest target row, where the sort path's time
+// depends on the number of terms alone.  The row's time and the sort path's, in
+// us, fitted to 620 calls in 50 spaces (1 to 42 504 alpha rows, 100 to 200 000
+// entries, near the aufbau string and spread out; nine in ten calls near the
+// aufbau string within 25 and 13 %); in order below 0.9 of the sort path's.
+// Without this rule, ms, in order and sort: 18 orbitals, 3 + 5 electrons, 4 000
+// entries near the aufbau string 2.8 and 1.4, 30 000 9.8 and 4.8, but 30 000
+// spread out 1.6 and 5.5; 24, 2 + 4, 10 000 5.4 and 2.4; 16, 1 + 7, 4 000 2.6 and
+// 1.0; 20, 4 + 4, 10 000 2.5 and 3.0.  Over the 620 the choice costs 0.2 % on
+// average against the faster of both, at most 30 %.
+// The row's estimate is a launch and a wait (25 us), left out where no vector of
+// at most v.cap entries can have such a row.
+bool inorder_pays(sfci_problem* P, const SigmaLaunch& v, RowTileDesc* d) {
+    const u64 tps = terms_per_source(P->n, P->na, P->nb);
+    const int sB = P->nb * (P->n - P->nb);
+    const u64 dB = !P->io_pairs ? 0
+                                : (u64)(P->nb * (P->nb - 1) / 2) * (u64)((P->n - P->nb) * (P->n - P->nb - 1) / 2);
+    IoWeights w;
+    const float more = (float)std::max(0, P->na - 4);
+    w.id = dB ? 0.45f + 0.065f * (float)((dB + 63) / 64) + 0.125f * more
+              : 0.42f + 0.08f * more;  // one full row of a Hubbard ring, us: 12 sites, 6 + 6 522, 14, 4 + 4 415, 7 + 7 2 250
+    w.single0 = 0.01f;
+    w.single = sB == 0 ? w.single0 : sB < 64 ? 0.073f : sB == 64 ? 0.12f : 0.36f;
+    // what remains for the row: the rest of the call, and the N_det array that the sort path does not touch
+    const double rest = 198.0 + 7e-6 * (double)std::min<u64>(P->Ndet, u64(1) << 25);
+    const auto limit = [&](u64 nnz) {
+        const double terms = (double)nnz * (double)tps;
+        return 0.9 * (740.0 + 2.78e-5 * terms + 0.0488 * sqrt(terms)) - 2.7e-6 * terms - rest;
+    };
+    const double ws = P->io_ab ? std::max(w.single, w.single0) : w.single0;
+    const auto most = [&](u64 nnz) { return (double)std::min<u64>(nnz, P->Nb) * w.id + (double)nnz * ws; };
+    *d = rowtile_prepare(P, v, nullptr, nullptr);
+    bool sure = true;
+    for (u64 k = 1; sure; k = std::min<u64>(2 * k, v.cap)) {
+        sure = most(k) <= limit(k);
+        if (k >= v.cap) break;
+    }
+    if (sure) return true;
+    if (!P->io_host) SFCI_CHECK_HIP(hipHostMalloc((void**)&P->io_host, 2 * sizeof(u64), hipHostMallocDefault));
+    const RowView rv = rowtile_view(*d);
+    const u32* astr = (const u32*)P->io_tab.p + ((size_t)P->Nb << (t1x_shift((u32)sB) + 6));
+    hipLaunchKernelGGL(k_io_load, dim3((unsigned)std::min<u64>((P->Na + 3) / 4, (u64)P->num_cu * 4)), dim3(256), 0,
+                       P->stream, SpaceDev{P->n, P->na, P->nb, P->Na, P->Nb}, P->d_binom, astr, rv.rowbeg, rv.rowend,
+                       (const unsigned char*)(astr + P->Na), w, v.v_nnz, P->io_state_words, P->io_host);
+    SFCI_CHECK_HIP(hipGetLastError());
+    SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+    const u32 bits = (u32)P->io_host[0];
+    float row;
+    std::memcpy(&row, &bits, sizeof row);
+    return (double)row <= limit(P->io_host[1]);
+}
+
+void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, const RowTileDesc& d, double* D,
+                          unsigned long long* emitted, double eps) {
+    if (P->io_state <= 0) throw sfci_error(-8, "in-order sigma: not available");
+    const Geometry& g = P->io_geom;
     const RowView rv = rowtile_view(d);
     const RowTables t = rowtile_tables(P);
     InOrder p{};

@@ -204,13 +204,14 @@ unsigned grid_of(u64 n) {
 // the sort path where those do not apply.
 u64 sigma_full_list(sfci_problem* P, const SigmaLaunch& sl, bool det, u64* emitted, u64** yr, double** ya,
                     u64* cnt_dev) {
-    const bool inorder = det && inorder_available(P, sl.cap) && ensure_dense(P);
+    RowTileDesc iod;
+    const bool inorder = det && inorder_available(P, sl.cap) && ensure_dense(P) && inorder_pays(P, sl, &iod);
     if (!inorder && (det || !ensure_dense(P))) {
         const u64 n = sigma_list_full(P, sl, emitted, yr, ya);
         launch_set_u64(P, cnt_dev, n);
         return n;
     }
-    if (inorder) launch_sigma_inorder(P, sl, P->d_D, (unsigned long long*)emitted, 0.0);
+    if (inorder) launch_sigma_inorder(P, sl, iod, P->d_D, (unsigned long long*)emitted, 0.0);
     else dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)emitted);
     CandSrc src{};
     src.dense = P->d_D;

@@ -111,6 +111,13 @@ struct ListWs {
     }
 };
 
+// Launch shape of the in-order kernel (inorder.hip).
+struct InOrderGeom {
+    u32 words, off_rows, per_wave;
+    int waves, per_cu;
+    size_t lds;
+};
+
 struct sfci_problem {
     int n, na, nb;
     u64 Na, Nb, Ndet;
@@ -132,6 +139,10 @@ struct sfci_problem {
     DevBuf ws_os;       // blocks of a long in-order sum
     DevBuf io_tab;      // in-order sigma: alpha strings, nonzero (ia|..) slabs
     int io_state = 0;   // 0 untried, 1 available, -1 not
+    InOrderGeom io_geom{};
+    unsigned* io_state_words = nullptr;  // of k_io_load, within io_tab
+    u64* io_host = nullptr;              // its result, pinned
+    bool io_ab = false, io_pairs = false;  // some (ia|jb), i != a, j != b, and some same-spin double are nonzero
     hipEvent_t ev[2] = {nullptr, nullptr};  // around a call, created on first use
     int sel_mode = 0;             // what select_prepare left for select_write (select.hip)
     CandSrc sel_src{};
@@ -256,9 +267,13 @@ struct RowTables {
 RowTables rowtile_tables(sfci_problem* P);
 // Deterministic sigma into D, every row written, without a sort (inorder.hip):
 // where a target row fits in LDS, the alpha strings are at most 65 536 and nnz
-// entries are worth writing N_det sums.
+// entries are worth writing N_det sums; ...
 bool inorder_available(sfci_problem* P, u64 nnz);
-void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, double* D, unsigned long long* emitted, double eps);
+// ... whether it is the faster way for the entries of v (else the sort path);
+// prepares *d for it.  May wait for the stream.
+bool inorder_pays(sfci_problem* P, const SigmaLaunch& v, RowTileDesc* d);
+void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, const RowTileDesc& d, double* D,
+                          unsigned long long* emitted, double eps);
 size_t rowtile_desc_bytes();
 // Target alpha rows [lo, hi) of a prepared description only, written into
 // Dp[rank - lo * N_beta] (touched tiles are overwritten, the rest is left
