@@ -187,6 +187,14 @@ bool ensure_dense(sfci_problem* P) {
     return P->dense_state == 1;
 }
 
+void clear_dense(sfci_problem* P, hipStream_t st) noexcept {
+    if (!P->d_D) return;
+    try {
+        launch_fill_f64(P->d_D, P->Ndet, 0.0, st);
+    } catch (...) {  // (the error that led here is the one reported)
+    }
+}
+
 // Dense-mode sigma into P->d_D: the target-owned tile kernel unless the
 // caller asks for the one-atomic-per-term kernel (or the tiles do not fit), or
 // leaves the choice open and the space is small enough for H as a table.
@@ -434,6 +442,7 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     // the input is checked on the device, a bad vector counts as empty there, and the flags come back with
     // the results
     CandSrc src{};
+    DenseGuard dense(P);
     if (small) {
         launch_small_load(P, v->rank, v->amp, nullptr, v->nnz, true, scal, nullptr, &scal[1], (int*)&scal[4]);
         launch_small_sigma(P, opts->screen_eps);
@@ -454,6 +463,7 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
     SFCI_CHECK_HIP(hipMemcpyAsync(&sst, P->ws_sel.p, offsetof(SelState, ticket), hipMemcpyDeviceToHost, P->stream));
     if (direct) SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
     sync(P);
+    if (((const int*)&hs[4])[0] || ((const int*)&hs[4])[1]) dense.done();  // (sums of nothing: zeros)
     throw_bad_vec((const int*)&hs[4]);
     const u64 need = hs[2];
     sfci_status rc = SFCI_OK;
@@ -469,6 +479,7 @@ sfci_status sfci_sigma(sfci_problem* P, const sfci_svec* v, const sfci_sigma_opt
         SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
         sync(P);
     }
+    dense.done();
     if (stats) {
         float ms = 0.f;
         SFCI_CHECK_HIP(hipEventElapsedTime(&ms, e0, e1));
@@ -578,6 +589,8 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
     auto W = [&](int j) { return DVec{Wr + (size_t)j * cap, Wa + (size_t)j * cap, sc + j, cap}; };
     EventTimer tsig;
     tsig.on = (stats != nullptr);
+    DenseGuard dense(P);
+    if (list_mode) dense.done();
     CallEvents ev(P);
     const hipEvent_t e0 = P->ev[0], e1 = P->ev[1];
     SFCI_CHECK_HIP(hipEventRecord(e0, P->stream));
@@ -766,6 +779,7 @@ sfci_status sfci_lanczos_roots(sfci_problem* P, const sfci_svec* v0, const sfci_
         launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
     }
     }
+    dense.done();
     SFCI_CHECK_HIP(hipEventRecord(e1, P->stream));
     for (int b = 0; b < nblk; ++b) energies[b] = std::numeric_limits<double>::quiet_NaN();
     SFCI_CHECK_HIP(hipMemcpyAsync(energies, energies_d, blocks_run * sizeof(double), hipMemcpyDeviceToHost, P->stream));
@@ -833,6 +847,7 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
     };
     double* raw = (double*)P->ws_red.get((RAW_PAD + n2 + n4) * sizeof(double));
     SigmaLaunch sl{v->rank, v->amp, scal, v->nnz};
+    DenseGuard dense(P);
     if (!v_bar && v->nnz && sbar->nnz && rowtile_grad_available(P)) {
         // integral gradients only: the target-owned tile passes
         GradJob J{};
@@ -851,6 +866,7 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
         J.vt_nnz = scal + 2;
         J.bad = bad;
         rowtile_gradients(P->stream, 1, &J, P->grad_ws);
+        dense.done();
         finish();
         return SFCI_OK;
     }
@@ -867,6 +883,7 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
     else
         launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2, bad);
     launch_scatter_zero(P, P->d_D, sbar->rank, scal + 1, std::max<u64>(1, sbar->nnz));
+    dense.done();
     finish();
     return SFCI_OK;
     SFCI_GUARD_END

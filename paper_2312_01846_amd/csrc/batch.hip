@@ -169,16 +169,21 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
     hipStream_t st = B->own;
     struct Restore {
         sfci_batch* B;
+        bool dirty;  // the N_det arrays hold sums
         ~Restore() {
             hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
             if (hipStreamIsCapturing(B->own, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) {
                 hipGraph_t g = nullptr;  // an error left a capture open: close and drop it
                 if (hipStreamEndCapture(B->own, &g) == hipSuccess && g) (void)hipGraphDestroy(g);
             }
+            if (dirty) {
+                for (auto s : B->aux) (void)hipStreamSynchronize(s);
+                for (auto* P : B->P) clear_dense(P, B->own);
+            }
             (void)hipStreamSynchronize(B->own);
             for (auto* P : B->P) P->stream = B->stream;
         }
-    } restore{B};
+    } restore{B, false};
     for (auto* P : B->P) P->stream = st;
     // Deterministic sigma (sort path) of every instance: an equal share of a
     // quarter of the memory free now for each instance's tuple buffers, so
@@ -628,6 +633,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
     int replayed_blocks = 0;
     SFCI_CHECK_HIP(hipEventRecord(e0, st));
     int sig = 0;
+    restore.dirty = true;
     for (int b = 0; b < nblk; ++b) {
         const bool last = (b + 1 == nblk);
         const bool replay = use_graph && (b >= 1 || graphs_reused);
@@ -744,6 +750,7 @@ sfci_status sfci_batch_lanczos(sfci_batch* B, const sfci_svec* v0s, const uint64
         SFCI_CHECK_HIP(hipMemcpyAsync(&hsc[(size_t)k * 64], I[k].sc, 64 * sizeof(u64), hipMemcpyDeviceToHost, st));
     }
     SFCI_CHECK_HIP(hipStreamSynchronize(st));
+    restore.dirty = false;
     // the step graphs stay for later calls while every buffer they use is alive
     keep_guard.keep = !split_steps && !gstep.empty() && B->gepoch == device_free_epoch();
     if (stats) {

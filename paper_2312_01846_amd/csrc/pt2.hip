@@ -211,6 +211,7 @@ u64 sigma_full_list(sfci_problem* P, const SigmaLaunch& sl, bool det, u64* emitt
         launch_set_u64(P, cnt_dev, n);
         return n;
     }
+    DenseGuard dense(P);
     if (inorder) launch_sigma_inorder(P, sl, iod, P->d_D, (unsigned long long*)emitted, 0.0);
     else dense_sigma(P, sl, SFCI_DEDUP_DENSE, (unsigned long long*)emitted);
     CandSrc src{};
@@ -222,6 +223,7 @@ u64 sigma_full_list(sfci_problem* P, const SigmaLaunch& sl, bool det, u64* emitt
     *yr = (u64*)P->ws_list_r.get(std::max<u64>(1, n) * sizeof(u64));
     *ya = (double*)P->ws_list_a.get(std::max<u64>(1, n) * sizeof(double));
     select_write(P, src, *yr, *ya, true);  // rank order; zeroes the accumulator
+    dense.done();
     return n;
 }
 
@@ -235,6 +237,7 @@ void energy_gradients_at(sfci_problem* P, const sfci_svec* psi, u64* sc, double*
     launch_div_by_sumsq(P, psi->amp, sc, psi->nnz, sbar);
     double* raw = (double*)P->ws_red.get((2048 + n2 + n4) * sizeof(double));
     const SigmaLaunch sl{psi->rank, psi->amp, sc, psi->nnz};
+    DenseGuard dense(P);
     if (rowtile_grad_available(P)) {
         GradJob J{};
         J.P = P;
@@ -257,6 +260,7 @@ void energy_gradients_at(sfci_problem* P, const sfci_svec* psi, u64* sc, double*
         launch_backward_dense(P, sl, P->d_D, nullptr, dh, deri, raw + 2048, raw + 2048 + n2);
         launch_scatter_zero(P, P->d_D, psi->rank, sc, psi->nnz);
     }
+    dense.done();
 }
 
 extern "C" sfci_status sfci_energy_gradients(sfci_problem* P, const sfci_svec* psi, int32_t deterministic,
@@ -277,9 +281,11 @@ extern "C" sfci_status sfci_energy_gradients(sfci_problem* P, const sfci_svec* p
         const SigmaLaunch sl{psi->rank, psi->amp, sc, psi->nnz};
         if (!det && ensure_dense(P)) {
             // H Psi in the accumulator, gathered at supp(Psi)
+            DenseGuard dense(P);
             dense_sigma(P, sl, SFCI_DEDUP_AUTO, (unsigned long long*)(sc + 1));
             launch_dot_dense(P, psi->rank, psi->amp, sc, psi->nnz, P->d_D, sd + 0, nullptr, false);
             launch_fill_f64(P->d_D, P->Ndet, 0.0, P->stream);
+            dense.done();
         } else {
             u64* yr;
             double* ya;
@@ -321,6 +327,7 @@ extern "C" sfci_status sfci_pt2(sfci_problem* P, const sfci_svec* psi, int32_t d
         const SpaceDev sp{P->n, P->na, P->nb, P->Na, P->Nb};
         const Ints I{P->d_h, P->d_g, P->n};
         if (!det && ensure_dense(P)) {
+            DenseGuard dense(P);
             dense_sigma(P, sl, SFCI_DEDUP_AUTO, (unsigned long long*)(sc + 1));
             launch_dot_dense(P, psi->rank, psi->amp, sc, psi->nnz, P->d_D, sd + 0, nullptr, false);
             launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, false);
@@ -333,6 +340,7 @@ extern "C" sfci_status sfci_pt2(sfci_problem* P, const sfci_svec* psi, int32_t d
             hipLaunchKernelGGL(k_pt2_beta, dim3(grid_of(P->Nb)), dim3(PB), 0, P->stream, sp, P->d_binom, bits);
             hipLaunchKernelGGL(k_pt2_rows, dim3(g), dim3(PB), 0, P->stream, sp, I, P->d_binom, P->d_D, bits, sd + 2,
                                part, (unsigned long long*)(sc + 3));
+            dense.done();
             launch_set_u64(P, sc + 2, g);
             launch_sum(P, part, sc + 2, g, sd + 3, false);
         } else {

@@ -567,6 +567,19 @@ void launch_set_u64(sfci_problem* P, u64* p, u64 v);
 void validate_vec(sfci_problem* P, const u64* r, u64 n);  // throws on out-of-range or unsorted ranks
 bool ensure_dense(sfci_problem* P);                       // allocates the zeroed N_det accumulator if it fits
 void dense_sigma(sfci_problem* P, const SigmaLaunch& sl, int dedup, unsigned long long* emitted, double eps = 0.0);
+// Zeroes the N_det array when an error leaves a call while the array holds
+// sums (armed, until done): the next call counts on zeros.
+void clear_dense(sfci_problem* P, hipStream_t st) noexcept;
+struct DenseGuard {
+    sfci_problem* P;
+    bool armed = true;
+    explicit DenseGuard(sfci_problem* P_) : P(P_) {}
+    DenseGuard(const DenseGuard&) = delete;
+    void done() { armed = false; }
+    ~DenseGuard() {
+        if (armed) clear_dense(P, P->stream);
+    }
+};
 // Screening (Sec. 3): D[i] = 0 where 0 < |D[i]| < eps.
 void launch_screen(sfci_problem* P, double* D, u64 n, double eps);
 
