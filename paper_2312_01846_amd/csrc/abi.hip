@@ -877,11 +877,15 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
         return v_bar && (const char*)v_bar < (const char*)x + 8 * v->nnz &&
                (const char*)x < (const char*)(v_bar + v->nnz);
     };
-    if (v->nnz && sbar->nnz && !over(v->amp) && !over(v->rank) && back_rows_available(P, v->nnz, sbar->nnz))
-        launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
-                         raw + RAW_PAD + n2, bad);
-    else
-        launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2, bad);
+    bool rows = v->nnz && sbar->nnz && !over(v->amp) && !over(v->rank) && back_rows_available(P, v->nnz, sbar->nnz);
+    if (rows) try {
+            launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
+                             raw + RAW_PAD + n2, bad);
+        } catch (const sfci_error& e) {
+            if (e.code != SFCI_E_NOMEM) throw;
+            rows = false;  // no room for its lists (taken before it writes an output)
+        }
+    if (!rows) launch_backward_dense(P, sl, P->d_D, v_bar, dh, deri, raw + RAW_PAD, raw + RAW_PAD + n2, bad);
     launch_scatter_zero(P, P->d_D, sbar->rank, scal + 1, std::max<u64>(1, sbar->nnz));
     dense.done();
     finish();

@@ -457,6 +457,7 @@ void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, co
     const u64 max_a = v.cap / 64 + std::min<u64>(P->Na, v.cap) + 1, max_b = v.cap / 64 + std::min<u64>(P->Nb, v.cap) + 1;
     const u64 perm = (3 * v.cap + 1) / 2, zero_words = P->Nb + np2 * np2 + (P->Na + 2) / 2 + 1;
     u64* ws = (u64*)P->ws_prod.get((2 * (max_a + max_b) + perm + zero_words) * sizeof(u64));
+    (void)P->ws_scan.get((P->Nb / 2048 + 1) * sizeof(u64));  // the scan's, before anything is written
     uint4* chunk = (uint4*)ws;
     uint4* chunk_b = chunk + max_a;
     u32* pk = (u32*)(chunk_b + max_b);

@@ -740,7 +740,13 @@ bool inorder_available(sfci_problem* P, u64 nnz) {
         const u32 sB = (u32)(P->nb * (P->n - P->nb)), shift = t1x_shift(sB);
         // [T1x | alpha strings | slab flags, n^2 + 1 bytes | k_io_load's two words]
         const size_t t1x = (size_t)P->Nb << (shift + 6), io_words = t1x + P->Na + (32 * 32 + 8) / 4;
-        u32* const tab = (u32*)P->io_tab.get((io_words + 2) * sizeof(u32));
+        u32* tab;
+        try {
+            tab = (u32*)P->io_tab.get((io_words + 2) * sizeof(u32));
+        } catch (const sfci_error& e) {
+            if (e.code != SFCI_E_NOMEM) throw;
+            return false;  // no room: the sort path serves
+        }
         u32* const astr = tab + t1x;
         SFCI_CHECK_HIP(hipMemsetAsync(tab + io_words, 0, 2 * sizeof(u32), P->stream));
         P->io_state_words = tab + io_words;

@@ -139,11 +139,22 @@ bool small_h_ready(sfci_problem* P) {
     P->sh_state = -1;
     const u64 tps = terms_per_source(P->n, P->na, P->nb), N = P->Ndet;
     if (N > (u64)SEL_ONE || N * tps * 12 > SMALL_H_BYTES) return false;
-    u32* idx = (u32*)P->sh_idx.get(N * tps * sizeof(u32));
-    double* val = (double*)P->sh_val.get(N * tps * sizeof(double));
-    u32* nz = (u32*)P->sh_nz.get((N + 2) * sizeof(u32));  // terms per column, then the flag of an element not finite
+    const auto drop = [&] {
+        for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd}) b->release();
+        return false;
+    };
+    u32 *idx, *nz;
+    double* val;
+    try {
+        idx = (u32*)P->sh_idx.get(N * tps * sizeof(u32));
+        val = (double*)P->sh_val.get(N * tps * sizeof(double));
+        nz = (u32*)P->sh_nz.get((N + 2) * sizeof(u32));  // terms per column, then the flag of an element not finite
+        (void)P->sh_vd.get(N * sizeof(double));
+    } catch (const sfci_error& e) {
+        if (e.code != SFCI_E_NOMEM) throw;
+        return drop();  // no room: the tile kernel serves
+    }
     launch_fill_u64((u64*)(nz + (N & ~u64(1))), 1, 0, P->stream);
-    (void)P->sh_vd.get(N * sizeof(double));
     const u64 want = (N + SFCI_WAVES_PER_BLOCK - 1) / SFCI_WAVES_PER_BLOCK;
     hipLaunchKernelGGL(k_small_build, dim3((unsigned)std::min<u64>(want, (u64)P->num_cu * 16)), dim3(SFCI_BLOCK), 0,
                        P->stream, SpaceDev{P->n, P->na, P->nb, P->Na, P->Nb}, Ints{P->d_h, P->d_g, P->n}, P->d_binom,
@@ -152,10 +163,7 @@ bool small_h_ready(sfci_problem* P) {
     u32 odd = 0;
     SFCI_CHECK_HIP(hipMemcpyAsync(&odd, nz + N, sizeof(u32), hipMemcpyDeviceToHost, P->stream));
     SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
-    if (odd) {
-        for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd}) b->release();
-        return false;
-    }
+    if (odd) return drop();
     small_step_setup(P);
     P->sh_state = 1;
     return true;
