@@ -451,8 +451,13 @@ struct FusedPasses {
     RowTileDesc all;
     FusedOut h{};
     FusedOut* d_fo;
-    u64 room;
-    bool rest = false;  // the candidates of all rows behind the first pass fit, or none are wanted
+    u64 room;           // entries free for a pass to append
+    // The candidates of all rows behind the first pass fit, or none are wanted.
+    // A first pass of a 64th of the rows sets the bound; of a spread-out vector
+    // the others then hold 63 K better ones (measured 63 to 67 K), near the
+    // aufbau string 1 to 26 K: one list of total = 80 K entries serves both.
+    bool rest = false;
+    u64 total = 0;
 
     FusedPasses(sfci_problem* P_, const SigmaLaunch& v, ListPassSink& sink_, u64* emitted_dev, double eps)
         : P(P_), sink(sink_), emitted(emitted_dev),
@@ -480,10 +485,15 @@ struct FusedPasses {
         h.distinct = sink.distinct;
         d_fo = (FusedOut*)ws.fo.get(sizeof(FusedOut));
         room = std::max<u64>(1ull << 24, 4 * std::min<u64>(C.K, 1ull << 26));
+        rest = !sink.collect || (C.K < (1ull << 40) && 80 * C.K * 16 < usable() / 8);
+        if (rest && sink.collect) total = std::max<u64>(room, 80 * C.K);
+    }
+
+    // Device memory that the candidate list may count on: free, or its own.
+    size_t usable() const {
         size_t freeb = 0, totb = 0;
         SFCI_CHECK_HIP(hipMemGetInfo(&freeb, &totb));
-        rest = !sink.collect || (C.K < (1ull << 40) && 80 * C.K * 16 < freeb / 8);
-        if (rest && sink.collect) room = std::max<u64>(room, 80 * C.K);
+        return freeb + P->list_ws.Rr.bytes + P->list_ws.Ra.bytes;
     }
 
     // Target rows [lo, hi), or rows[lo .. hi) of a device list; through the
@@ -493,7 +503,7 @@ struct FusedPasses {
         ListCands& C = *sink.cands;
         u32 more = 1;
         for (u64 extra = 0;;) {
-            if (sink.collect) C.ensure(room + extra);
+            if (sink.collect) C.ensure((total > C.n_upper ? total - C.n_upper : room) + extra);
             h.Rr = C.Rr();
             h.Ra = C.Ra();
             h.Rcap = C.cap();
@@ -510,14 +520,22 @@ struct FusedPasses {
             SFCI_CHECK_HIP(hipMemcpyAsync(&ovf, C.overflow, sizeof(int), hipMemcpyDeviceToHost, P->stream));
             SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
             if (!ovf) break;
-            // run the pass again with room for what it appends
+            // run the pass again with room for what it appends, in eighths if
+            // that is a quarter of the memory (rows in an order in which the
+            // first tell little of the others)
             const u64 need = (ovf & 1) ? read_dev(P, C.Rn) - n_before : 0;
             if (ovf & 2) more *= 2;
             if (more > 1024) throw sfci_error(-5, "list path: a row's part does not fit its table");
+            const bool split = hi - lo >= 8 && (need + need / 4) * 16 > usable() / 4;
             launch_fill_u64(C.Rn, 1, n_before, P->stream);
             launch_fill_u64((u64*)C.overflow, 1, 0, P->stream);
             if (sink.distinct) launch_fill_u64(sink.distinct, 1, dist_before, P->stream);
             if (emitted) launch_fill_u64(emitted, 1, emit_before, P->stream);
+            if (split) {
+                for (u64 k = 0; k < 8; ++k)
+                    pass(lo + (hi - lo) * k / 8, lo + (hi - lo) * (k + 1) / 8, rows, hash, eps, small);
+                return;
+            }
             extra = std::max(extra, need + need / 4);
         }
         if (!sink.collect) return;
