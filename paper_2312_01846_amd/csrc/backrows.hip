@@ -517,7 +517,9 @@ void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, co
     const size_t lds = (size_t)BW_WAVES * std::max<u64>(n2, 64ull * n) * sizeof(double);
     const u64 items = max_a * p.kinds + max_b * p.kinds_b;
     const unsigned grid = (unsigned)std::max<u64>(1, std::min<u64>((items + BW_WAVES - 1) / BW_WAVES, (u64)P->num_cu * 16));
-    SFCI_CHECK_HIP(hipFuncSetAttribute((const void*)k_back_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    // the most any problem asks for: the limit is the function's, not the problem's
+    SFCI_CHECK_HIP(hipFuncSetAttribute((const void*)k_back_rows, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)(BW_WAVES * 64 * 32 * sizeof(double))));
     hipLaunchKernelGGL(k_back_rows, dim3(grid), dim3(BW_BLOCK), lds, st, p);
     if (np2 > 0)
         hipLaunchKernelGGL(k_expand_pairs, dim3((unsigned)std::min<u64>((np2 * np2 + 255) / 256, 4096)), dim3(256), 0,
