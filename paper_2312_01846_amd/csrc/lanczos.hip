@@ -644,9 +644,12 @@ __device__ void jacobi_dev(int m, double (*A)[GE_MAX], double (*V)[GE_MAX], doub
 // floor(m / 2) disjoint pairs (a round robin), a lane per pair, so that a sweep
 // is m - 1 dependent steps instead of m (m - 1) / 2.  What a step costs is the
 // chain of divisions and square roots of a rotation (~1 000 cycles); 10 x 10:
-// 320 -> 118 us for the two decompositions of a block.  Same stopping rule.
+// 320 -> 118 us for the two decompositions of a block.  Same stopping rule, and
+// rotations in the same form, x - s (y + tau x) with tau = s / (1 + c): as
+// c x - s y they rounded the lowest eigenvalue of 10 x 10 blocks to 1.1e-15 on
+// average, this way to 1.9e-16 (one rotation after another 2.2e-16).
 __device__ void jacobi_rounds(int m, double (*A)[GE_MAX], double (*V)[GE_MAX], double* w,
-                              double (*cs)[2], int (*pq)[2]) {
+                              double (*st)[2], int (*pq)[2]) {
     const int lane = threadIdx.x;
     for (int e = lane; e < m * m; e += 64) V[e / m][e % m] = (e / m == e % m) ? 1.0 : 0.0;
     const int me = m + (m & 1);  // players, one idle where m is odd
@@ -665,6 +668,7 @@ __device__ void jacobi_rounds(int m, double (*A)[GE_MAX], double (*V)[GE_MAX], d
         }
         if (off <= 1e-30 * dg || m < 2) break;
         for (int round = 0; round < me - 1; ++round) {
+            double dp = 0.0, dq = 0.0;  // this lane's pair: its diagonal elements after the rotation
             if (lane < me / 2) {
                 // player me - 1 stays, the others move on by one seat per round
                 int p = lane == 0 ? me - 1 : (round + lane) % (me - 1);
@@ -674,48 +678,55 @@ __device__ void jacobi_rounds(int m, double (*A)[GE_MAX], double (*V)[GE_MAX], d
                     p = q;
                     q = x;
                 }
-                double c = 1.0, s = 0.0;
+                double s = 0.0, tau = 0.0;
                 if (q < m) {
                     const double apq = A[p][q];
+                    dp = A[p][p];
+                    dq = A[q][q];
                     if (apq != 0.0) {
-                        const double theta = (A[q][q] - A[p][p]) / (2.0 * apq);
+                        const double theta = (dq - dp) / (2.0 * apq);
                         double t = 1.0 / (fabs(theta) + sqrt(theta * theta + 1.0));
                         if (theta < 0.0) t = -t;
-                        c = 1.0 / sqrt(t * t + 1.0);
+                        const double c = 1.0 / sqrt(t * t + 1.0);
                         s = t * c;
+                        tau = s / (1.0 + c);
+                        dp = dp - t * apq;
+                        dq = dq + t * apq;
                     }
                 }
                 pq[lane][0] = p;
                 pq[lane][1] = q < m ? q : -1;
-                cs[lane][0] = c;
-                cs[lane][1] = s;
+                st[lane][0] = s;
+                st[lane][1] = tau;
             }
             wave_sync();
             // columns of A and V, then rows of A, by every pair's rotation
             for (int e = lane; e < (me / 2) * m; e += 64) {
                 const int k = e / m, r = e % m, p = pq[k][0], q = pq[k][1];
                 if (q < 0) continue;
-                const double c = cs[k][0], s = cs[k][1];
+                const double s = st[k][0], tau = st[k][1];
                 const double ap = A[r][p], aq = A[r][q], vp = V[r][p], vq = V[r][q];
-                A[r][p] = c * ap - s * aq;
-                A[r][q] = s * ap + c * aq;
-                V[r][p] = c * vp - s * vq;
-                V[r][q] = s * vp + c * vq;
+                A[r][p] = ap - s * (aq + tau * ap);
+                A[r][q] = aq + s * (ap - tau * aq);
+                V[r][p] = vp - s * (vq + tau * vp);
+                V[r][q] = vq + s * (vp - tau * vq);
             }
             wave_sync();
             for (int e = lane; e < (me / 2) * m; e += 64) {
                 const int k = e / m, r = e % m, p = pq[k][0], q = pq[k][1];
                 if (q < 0) continue;
-                const double c = cs[k][0], s = cs[k][1];
+                const double s = st[k][0], tau = st[k][1];
                 const double ap = A[p][r], aq = A[q][r];
-                A[p][r] = c * ap - s * aq;
-                A[q][r] = s * ap + c * aq;
+                A[p][r] = ap - s * (aq + tau * ap);
+                A[q][r] = aq + s * (ap - tau * aq);
             }
             wave_sync();
             if (lane < me / 2 && pq[lane][1] >= 0) {
-                // exactly zero in exact arithmetic
-                A[pq[lane][0]][pq[lane][1]] = 0.0;
-                A[pq[lane][1]][pq[lane][0]] = 0.0;
+                const int p = pq[lane][0], q = pq[lane][1];
+                A[p][p] = dp;
+                A[q][q] = dq;
+                A[p][q] = 0.0;
+                A[q][p] = 0.0;
             }
             wave_sync();
         }
@@ -737,11 +748,11 @@ __device__ __forceinline__ void geneig_body(int m, const double* __restrict__ T,
     __shared__ double sv[GE_MAX], lam[GE_MAX], xs[GE_MAX];
     __shared__ int keep[GE_MAX];
     __shared__ int s_r, s_best, s_flag;
-    __shared__ double cs[GE_MAX / 2][2];
+    __shared__ double st[GE_MAX / 2][2];
     __shared__ int pq[GE_MAX / 2][2];
     auto jacobi = [&](int k, double* w) {
         if (ORDERED) jacobi_dev(k, A, U, w, &s_flag);
-        else jacobi_rounds(k, A, U, w, cs, pq);
+        else jacobi_rounds(k, A, U, w, st, pq);
     };
     const int i = threadIdx.x;
     if (i < m)
