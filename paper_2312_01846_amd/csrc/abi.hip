@@ -187,6 +187,24 @@ bool ensure_dense(sfci_problem* P) {
     return P->dense_state == 1;
 }
 
+HostLine host_line(sfci_problem* P) {
+    if (!P->line) {
+        SFCI_CHECK_HIP(hipHostMalloc((void**)&P->line, HostLine::WORDS * sizeof(u64), hipHostMallocCoherent));
+        P->line[HostLine::WORDS - 1] = 0;
+    }
+    return HostLine{P->line, ++P->line_asked};
+}
+
+// Reads the line for a while (some 10 us are usual), then waits for the stream.
+const u64* wait_line(sfci_problem* P, const HostLine& l) {
+    const u64* at = l.p + HostLine::WORDS - 1;
+    for (int k = 0; k < 100000; ++k)
+        if (__atomic_load_n(at, __ATOMIC_ACQUIRE) == l.number) return l.p;
+    sync(P);
+    if (__atomic_load_n(at, __ATOMIC_ACQUIRE) != l.number) throw sfci_error(SFCI_E_DEVICE, "no answer from the device");
+    return l.p;
+}
+
 void clear_dense(sfci_problem* P, hipStream_t st) noexcept {
     if (!P->d_D) return;
     try {
@@ -301,7 +319,7 @@ sfci_status sfci_problem_destroy(sfci_problem* P) {
     }
     for (hipEvent_t e : P->ev)
         if (e) (void)hipEventDestroy(e);
-    if (P->io_host) (void)hipHostFree(P->io_host);
+    if (P->line) (void)hipHostFree(P->line);
     rowtile_release(P);
     for (DevBuf* b : {&P->sh_idx, &P->sh_val, &P->sh_nz, &P->sh_vd, &P->io_tab, &P->ws_os}) b->release();
     DevBuf* bufs[] = {&P->ws_sel,   &P->ws_cnt,   &P->ws_scan,  &P->ws_scan2,  &P->ws_scalar, &P->ws_red,
@@ -879,8 +897,13 @@ sfci_status sfci_sigma_backward(sfci_problem* P, const sfci_svec* v, const sfci_
     };
     bool rows = v->nnz && sbar->nnz && !over(v->amp) && !over(v->rank) && back_rows_available(P, v->nnz, sbar->nnz);
     if (rows) try {
-            launch_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
-                             raw + RAW_PAD + n2, bad);
+            HostLine l;
+            const bool sure = ask_back_rows(P, sl, P->d_D, sbar->rank, scal + 1, &l);
+            const RowTileDesc d = rowtile_prepare(P, sl, nullptr, nullptr);  // (while the answer is on its way)
+            rows = sure || back_rows_answer(P, l);
+            if (rows)
+                launch_back_rows(P, sl, d, P->d_D, sbar->rank, scal + 1, sbar->nnz, v_bar, dh, deri, raw + RAW_PAD,
+                                 raw + RAW_PAD + n2, bad);
         } catch (const sfci_error& e) {
             if (e.code != SFCI_E_NOMEM) throw;
             rows = false;  // no room for its lists (taken before it writes an output)

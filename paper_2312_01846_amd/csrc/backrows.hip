@@ -26,6 +26,7 @@
 // passes (rowtile.hip) stay: they read each row once for all its sources
 // (7.3 ms there).
 #include <algorithm>
+#include <cmath>
 
 #include "sfci_internal.h"
 
@@ -414,6 +415,67 @@ __global__ void k_back_used(const u64* __restrict__ sr, const u64* __restrict__ 
     }
 }
 
+// Rows or walk.  Rows cost their (chunk, kind) items and every entry's share of
+// them (less where the cotangent is in few rows); the walk costs its terms and,
+// ten times as much, those that meet the cotangent.  From BD_BLOCK entries of
+// each vector: how many begin a row, and how many of BD_PAIRS alpha-beta doubles
+// each meet the cotangent.
+constexpr int BD_BLOCK = 1024, BD_PAIRS = 4;
+enum { BD_NNZ = 0, BD_NNZ_S, BD_STARTS, BD_STARTS_S, BD_HITS };
+__global__ __launch_bounds__(BD_BLOCK) void k_back_ask(SpaceDev sp, const u64* __restrict__ binom,
+                                                       const u64* __restrict__ rank, const u64* __restrict__ nnz,
+                                                       const u64* __restrict__ s_rank, const u64* __restrict__ s_nnz,
+                                                       const u32* __restrict__ T1, const double* __restrict__ Sd,
+                                                       HostLine out) {
+    __shared__ BinomLds B;
+    __shared__ u32 s_n[3];
+    if (threadIdx.x < 3) s_n[threadIdx.x] = 0;
+    load_binom(B, binom);
+    __syncthreads();
+    const u64 nv = *nnz, ns = *s_nnz, Nb = sp.Nb;
+    const u32 sA = (u32)(sp.na * (sp.n - sp.na)), sB = (u32)(sp.nb * (sp.n - sp.nb));
+    u32 hits = 0;
+    bool first = false, first_s = false;
+    if (nv) {
+        const u64 k = nv * threadIdx.x / BD_BLOCK, r = rank[k], ra = r / Nb;
+        first = k == 0 || rank[k - 1] / Nb != ra;
+        if (sA && sB) {
+            const u32 A = str_unrank(ra, sp.na, sp.n, B), V = ~A & (sp.n == 32 ? ~0u : (1u << sp.n) - 1u);
+            const u32* t = T1 + (r - ra * Nb) * sB;
+            const u32 nva = (u32)(sp.n - sp.na);
+#pragma unroll
+            for (int u = 0; u < BD_PAIRS; ++u) {
+                const u32 x = (threadIdx.x * BD_PAIRS + (u32)u) * 2654435761u;  // spread over the singles
+                const u32 a = (u32)(((u64)x * sA) >> 32), b = (u32)(((u64)(u32)(x << 11 | x >> 21) * sB) >> 32);
+                u32 o = A, w = V;
+                for (u32 q = a / nva; q; --q) o &= o - 1u;
+                for (u32 q = a % nva; q; --q) w &= w - 1u;
+                const u64 r2 = str_rank(A ^ (o & (0u - o)) ^ (w & (0u - w)), B);
+                if (Sd[r2 * Nb + (t[b] & 0x1FFFFFu)] != 0.0) ++hits;
+            }
+        }
+    }
+    if (ns) {
+        const u64 k = ns * threadIdx.x / BD_BLOCK;
+        first_s = k == 0 || s_rank[k - 1] / Nb != s_rank[k] / Nb;
+    }
+    const u32 f = (u32)__popcll(__ballot(first)), fs = (u32)__popcll(__ballot(first_s));
+    for (int off = 32; off >= 1; off >>= 1) hits += (u32)__shfl_xor((int)hits, off);
+    if (lane_id() == 0) {
+        atomicAdd(&s_n[0], f);
+        atomicAdd(&s_n[1], fs);
+        atomicAdd(&s_n[2], hits);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    out.p[BD_NNZ] = nv;
+    out.p[BD_NNZ_S] = ns;
+    out.p[BD_STARTS] = s_n[0];
+    out.p[BD_STARTS_S] = s_n[1];
+    out.p[BD_HITS] = s_n[2];
+    out.answer();
+}
+
 // Rg += each pair slot's weight on (ia|jb), minus it on (ib|ja), i < j, a < b
 // (every slot meets its own two elements).
 __global__ void k_expand_pairs(int n, const double* __restrict__ R4, double* __restrict__ Rg) {
@@ -433,24 +495,60 @@ __global__ void k_expand_pairs(int n, const double* __restrict__ R4, double* __r
 
 }  // namespace
 
-// From a few thousand entries on: below, the walk per source is a few launches
-// less.  us, source walk and rows, v and sbar entries: 8 orbitals, 100 and 100
-// 114 and 164, 1 000 and 1 000 143 and 192; 16 orbitals, 1 000 and 20 000 240
-// and 255, 3 000 and 3 000 249 and 257, 3 000 and 100 000 485 and 292, 10 000
-// and 10 000 548 and 386.  SFCI_BACK_ROWS=0|1 forces one form.
+// From a few thousand entries on the entries decide (back_rows_answer); below,
+// the walk per source is a few launches less.  us, source walk and rows, v and
+// sbar entries: 8 orbitals, 100 and 100 114 and 164, 1 000 and 1 000 143 and 192;
+// 16 orbitals, 1 000 and 20 000 240 and 255, 3 000 and 3 000 249 and 257, 3 000 and
+// 100 000 485 and 292, 10 000 and 10 000 548 and 386.  SFCI_BACK_ROWS=0|1 forces
+// one form.
 bool back_rows_available(sfci_problem* P, u64 nnz, u64 nnz_s) {
     bool pays = nnz >= 4096 || (nnz >= 1024 && nnz_s >= 65536);
     if (const char* env = getenv("SFCI_BACK_ROWS")) pays = env[0] != '0';
     return pays && nnz < (1ull << 31) && P->Na < (1ull << 31) && rowtile_available(P);
 }
 
+bool ask_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
+                   HostLine* l) {
+    if (getenv("SFCI_BACK_ROWS")) return true;  // (=0 does not come here)
+    *l = host_line(P);
+    hipLaunchKernelGGL(k_back_ask, dim3(1), dim3(BD_BLOCK), 0, P->stream, SpaceDev{P->n, P->na, P->nb, P->Na, P->Nb},
+                       P->d_binom, v.v_rank, v.v_nnz, s_rank, s_nnz, rowtile_T1(P), D, *l);
+    SFCI_CHECK_HIP(hipGetLastError());
+    return false;
+}
+
+// Both forms' times, ms, fitted to 512 calls in 19 spaces (within a third nine
+// times in ten).  By sizes alone 116 of them took longer by rows than the walk
+// did, up to 2.5 times (entries spread out, few to a row): ms, rows and walk, 18
+// orbitals, 9 + 1 electrons, 2e4 and 2e4 entries spread out 1.98 and 0.75, near
+// the aufbau string 0.90 and 1.53; 16, 6 + 2, 5e3 and 5e3 spread out 0.38 and 0.22.
+// Asking costs 15 us.
+bool back_rows_answer(sfci_problem* P, const HostLine& l) {
+    const u64* h = wait_line(P, l);
+    const int n = P->n, na = P->na, nb = P->nb;
+    const double sA = na * (n - na), sB = nb * (n - nb);
+    const double dA = (na * (na - 1) / 2) * ((n - na) * (n - na - 1) / 2), dB = (nb * (nb - 1) / 2) * ((n - nb) * (n - nb - 1) / 2);
+    const double kA = sA + ceil((sA + dA) / 64) + 1, kB = ceil((sB + dB) / 64);
+    const double nv = (double)h[BD_NNZ], ns = (double)h[BD_NNZ_S], Na = (double)P->Na, Nb = (double)P->Nb;
+    const double terms = nv * (double)terms_per_source(n, na, nb);
+    const double met = terms * ((double)h[BD_HITS] / (BD_BLOCK * BD_PAIRS));
+    // chunks by alpha row, by beta string (as of a spread-out vector), rows of the cotangent
+    const double ca = nv * ((double)h[BD_STARTS] / BD_BLOCK) + nv / 64;
+    const double cb = Nb * (1.0 - exp(-nv / Nb)) + nv / 64;
+    const double used = std::min(1.0, ns * ((double)h[BD_STARTS_S] / BD_BLOCK) / Na);
+    const double walk = 0.129 + nv * (2.5e-9 * sA * sB + 4.05e-9 * (dA + dB) + 9.1e-7 * (na + nb)) + 4.6e-8 * met;
+    const double rows = 0.179 + 3.1e-6 * Na + 7.6e-8 * ns + (3.2e-7 + 5.3e-7 * used) * ca * kA + 7.4e-7 * cb * kB +
+                        nv * ((4.1e-8 + 1.08e-7 * used) * kA + 2.3e-7 * kB) + 5.8e-9 * met;
+    return rows < 0.97 * walk;
+}
+
 // sbar must already be scattered into the (otherwise zero) dense array D.
-void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
-                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg, const int* bad) {
+void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const RowTileDesc& d, const double* D, const u64* s_rank,
+                      const u64* s_nnz, u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg,
+                      const int* bad) {
     const int n = P->n, na = P->na, nb = P->nb;
     const u64 n2 = (u64)n * n, n4 = n2 * n2, np2 = (u64)n * (n - 1) / 2;
     hipStream_t st = P->stream;
-    const RowTileDesc d = rowtile_prepare(P, v, nullptr, nullptr);
     const RowView rv = rowtile_view(d);
     // [chunks by row | by beta string | permuted entries | zeroed: entries per beta string, pair slots,
     //  the chunks' numbers, rows of sbar]

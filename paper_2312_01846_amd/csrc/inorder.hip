@@ -634,23 +634,25 @@ struct IoWeights {
     float id, single, single0;
 };
 
-// The heaviest target row's time (bits of a float) and the entries' number, to
-// the host words out by the last workgroup.  state: maximum and ticket, zero
-// between launches.
-__global__ __launch_bounds__(256) void k_io_load(SpaceDev sp, const u64* __restrict__ binom,
-                                                 const u32* __restrict__ astr, const u64* __restrict__ beg,
-                                                 const u64* __restrict__ end, const unsigned char* __restrict__ gnz,
-                                                 IoWeights w, const u64* __restrict__ nnz,
-                                                 unsigned* __restrict__ state, u64* __restrict__ out) {
+// The heaviest target row's time (bits of a float) and the entries' number,
+// answered by the last workgroup.  state: maximum and ticket, zero between
+// launches.  Few, large workgroups: each adds to the queue at state's address.
+constexpr int IO_LOAD_WAVES = 16, IO_LOAD_BLOCK = 64 * IO_LOAD_WAVES;
+__global__ __launch_bounds__(IO_LOAD_BLOCK) void k_io_load(SpaceDev sp, const u64* __restrict__ binom,
+                                                           const u32* __restrict__ astr,
+                                                           const u64* __restrict__ beg, const u64* __restrict__ end,
+                                                           const unsigned char* __restrict__ gnz, IoWeights w,
+                                                           const u64* __restrict__ nnz, unsigned* __restrict__ state,
+                                                           HostLine out) {
     __shared__ BinomLds B;
-    __shared__ float s_worst[4];
-    __shared__ uint8_t s_occ[4][32], s_vir[4][32];
+    __shared__ float s_worst[IO_LOAD_WAVES];
+    __shared__ uint8_t s_occ[IO_LOAD_WAVES][32], s_vir[IO_LOAD_WAVES][32];
     load_binom(B, binom);
     __syncthreads();
     const int n = sp.n, na = sp.na, nva = n - na, sA = na * nva, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint8_t *occ = s_occ[wave], *vir = s_vir[wave];
     float worst = 0.0f;
-    for (u64 r = (u64)blockIdx.x * 4 + wave; r < sp.Na; r += (u64)gridDim.x * 4) {
+    for (u64 r = (u64)blockIdx.x * IO_LOAD_WAVES + wave; r < sp.Na; r += (u64)gridDim.x * IO_LOAD_WAVES) {
         const u32 A = __builtin_amdgcn_readfirstlane(astr[r]);
         wave_sync();
         if (lane < n) {
@@ -671,14 +673,15 @@ __global__ __launch_bounds__(256) void k_io_load(SpaceDev sp, const u64* __restr
     if (lane == 0) s_worst[wave] = worst;
     __syncthreads();
     if (threadIdx.x != 0) return;
-    worst = fmaxf(fmaxf(s_worst[0], s_worst[1]), fmaxf(s_worst[2], s_worst[3]));
+    for (int k = 1; k < IO_LOAD_WAVES; ++k) worst = fmaxf(worst, s_worst[k]);
     __hip_atomic_fetch_max(&state[0], __float_as_uint(worst), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
     if (__hip_atomic_fetch_add(&state[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
-    out[0] = __hip_atomic_exchange(&state[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    out[1] = *nnz;
+    out.p[0] = __hip_atomic_exchange(&state[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    out.p[1] = *nnz;
     __hip_atomic_store(&state[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    out.answer();
 }
 
 using Geometry = InOrderGeom;
@@ -781,7 +784,7 @@ bool inorder_available(sfci_problem* P, u64 nnz) {
 // spread out 1.6 and 5.5; 24, 2 + 4, 10 000 5.4 and 2.4; 16, 1 + 7, 4 000 2.6 and
 // 1.0; 20, 4 + 4, 10 000 2.5 and 3.0.  Over the 620 the choice costs 0.2 % on
 // average against the faster of both, at most 30 %.
-// The row's estimate is a launch and a wait (25 us), left out where no vector of
+// The row's estimate is a launch and a wait (29 us), left out where no vector of
 // at most v.cap entries can have such a row.
 bool inorder_pays(sfci_problem* P, const SigmaLaunch& v, RowTileDesc* d) {
     const u64 tps = terms_per_source(P->n, P->na, P->nb);
@@ -803,24 +806,27 @@ bool inorder_pays(sfci_problem* P, const SigmaLaunch& v, RowTileDesc* d) {
     const double ws = P->io_ab ? std::max(w.single, w.single0) : w.single0;
     const auto most = [&](u64 nnz) { return (double)std::min<u64>(nnz, P->Nb) * w.id + (double)nnz * ws; };
     *d = rowtile_prepare(P, v, nullptr, nullptr);
+    launch_fill_u64((u64*)P->ws_rt_desc.get(64), 1, 0, P->stream);  // the kernel's row counter
     bool sure = true;
     for (u64 k = 1; sure; k = std::min<u64>(2 * k, v.cap)) {
         sure = most(k) <= limit(k);
         if (k >= v.cap) break;
     }
     if (sure) return true;
-    if (!P->io_host) SFCI_CHECK_HIP(hipHostMalloc((void**)&P->io_host, 2 * sizeof(u64), hipHostMallocDefault));
+    const HostLine line = host_line(P);
     const RowView rv = rowtile_view(*d);
     const u32* astr = (const u32*)P->io_tab.p + ((size_t)P->Nb << (t1x_shift((u32)sB) + 6));
-    hipLaunchKernelGGL(k_io_load, dim3((unsigned)std::min<u64>((P->Na + 3) / 4, (u64)P->num_cu * 4)), dim3(256), 0,
+    hipLaunchKernelGGL(k_io_load,
+                       dim3((unsigned)std::min<u64>((P->Na + IO_LOAD_WAVES - 1) / IO_LOAD_WAVES, (u64)P->num_cu / 2)),
+                       dim3(IO_LOAD_BLOCK), 0,
                        P->stream, SpaceDev{P->n, P->na, P->nb, P->Na, P->Nb}, P->d_binom, astr, rv.rowbeg, rv.rowend,
-                       (const unsigned char*)(astr + P->Na), w, v.v_nnz, P->io_state_words, P->io_host);
+                       (const unsigned char*)(astr + P->Na), w, v.v_nnz, P->io_state_words, line);
     SFCI_CHECK_HIP(hipGetLastError());
-    SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
-    const u32 bits = (u32)P->io_host[0];
+    const u64* h = wait_line(P, line);
+    const u32 bits = (u32)h[0];
     float row;
     std::memcpy(&row, &bits, sizeof row);
-    return (double)row <= limit(P->io_host[1]);
+    return (double)row <= limit(h[1]);
 }
 
 void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, const RowTileDesc& d, double* D,
@@ -855,9 +861,7 @@ void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, const RowTileDe
     p.emitted = emitted;
     p.eps = eps;
     p.eps_x = P->excite_eps;
-    unsigned* counter = (unsigned*)P->ws_rt_desc.get(64);
-    launch_fill_u64((u64*)counter, 1, 0, P->stream);
-    p.counter = counter;
+    p.counter = (unsigned*)P->ws_rt_desc.get(64);  // zeroed by inorder_pays
     p.sA = P->na * (P->n - P->na);
     p.sB = P->nb * (P->n - P->nb);
     p.PA = P->na * (P->na - 1) / 2;

@@ -111,6 +111,21 @@ struct ListWs {
     }
 };
 
+// A kernel's answer of up to seven words to the host, by way of coherent pinned
+// memory: the host goes on launching and reads it as soon as it is there.
+struct HostLine {
+    static constexpr int WORDS = 8;  // the last one is the question's number, written after the others
+    u64* p;
+    u64 number;
+#ifdef __HIPCC__
+    __device__ __forceinline__ void answer() const {
+        __hip_atomic_store(p + WORDS - 1, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+#endif
+};
+HostLine host_line(sfci_problem* P);                   // the next question (its memory on first use)
+const u64* wait_line(sfci_problem* P, const HostLine& l);  // the answer
+
 // Launch shape of the in-order kernel (inorder.hip).
 struct InOrderGeom {
     u32 words, off_rows, per_wave;
@@ -141,9 +156,10 @@ struct sfci_problem {
     int io_state = 0;   // 0 untried, 1 available, -1 not
     InOrderGeom io_geom{};
     unsigned* io_state_words = nullptr;  // of k_io_load, within io_tab
-    u64* io_host = nullptr;              // its result, pinned
     bool io_ab = false, io_pairs = false;  // some (ia|jb), i != a, j != b, and some same-spin double are nonzero
     hipEvent_t ev[2] = {nullptr, nullptr};  // around a call, created on first use
+    u64* line = nullptr;    // pinned words that a kernel answers in (HostLine)
+    u64 line_asked = 0;
     int sel_mode = 0;             // what select_prepare left for select_write (select.hip)
     CandSrc sel_src{};
     DevBuf ws_lz[8];
@@ -195,11 +211,17 @@ void launch_unrank(sfci_problem* P, const u64* rank, u64 cnt, u64* a, u64* b, in
 void launch_backward_dense(sfci_problem* P, const SigmaLaunch& v, const double* D, double* vbar, double* dh, double* dg,
                            double* Rh, double* Rg, const int* bad = nullptr);
 void launch_scatter_zero(sfci_problem* P, double* D, const u64* r, const u64* nnz, u64 cap);
+struct RowTileDesc;
 // The same from the row view of v and the beta-single table (backrows.hip),
 // where they are available; s_rank: the ranks of the cotangent, Rg = Rh + n^2.
 bool back_rows_available(sfci_problem* P, u64 nnz, u64 nnz_s);
-void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
-                      u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg,
+// Asks the device whether this is the faster way for the entries (the cotangent
+// already in D); true without asking when SFCI_BACK_ROWS forces it.
+bool ask_back_rows(sfci_problem* P, const SigmaLaunch& v, const double* D, const u64* s_rank, const u64* s_nnz,
+                   HostLine* l);
+bool back_rows_answer(sfci_problem* P, const HostLine& l);
+void launch_back_rows(sfci_problem* P, const SigmaLaunch& v, const RowTileDesc& d, const double* D, const u64* s_rank,
+                      const u64* s_nnz, u64 s_cap, double* vbar, double* dh, double* dg, double* Rh, double* Rg,
                       const int* bad = nullptr);
 
 // ---- target-owned dense sigma (rowtile.hip) ----
@@ -270,7 +292,8 @@ RowTables rowtile_tables(sfci_problem* P);
 // entries are worth writing N_det sums; ...
 bool inorder_available(sfci_problem* P, u64 nnz);
 // ... whether it is the faster way for the entries of v (else the sort path);
-// prepares *d for it.  May wait for the stream.
+// called before each launch_sigma_inorder, which it prepares.  May wait for the
+// device.
 bool inorder_pays(sfci_problem* P, const SigmaLaunch& v, RowTileDesc* d);
 void launch_sigma_inorder(sfci_problem* P, const SigmaLaunch& v, const RowTileDesc& d, double* D,
                           unsigned long long* emitted, double eps);
