@@ -90,19 +90,26 @@ __global__ __launch_bounds__(PB) void k_pt2_beta(SpaceDev sp, const u64* __restr
 }
 
 // The external terms straight from the accumulator, a workgroup per target
-// alpha row, which clears the slots it reads.  H_kk is summed in
-// diag_element's order, so its bits (and E0 - H_kk where the two nearly meet)
-// are the list form's: the alpha parts are formed once per row, the pair terms
-// come from LDS.  Bound by the adds and LDS reads of H_kk; the list form
-// (compaction, a binary search in Psi, two unranks and ~28 gathers of
+// alpha row (or one of segs stretches of it, where rows are few), which clears
+// the slots it reads.  H_kk is summed in diag_element's order, so its bits (and
+// E0 - H_kk where the two nearly meet) are the list form's: the alpha parts are
+// formed once per row, the pair terms come from LDS.  Where most slots hold a
+// sum, a lane takes its own four; else they queue in LDS, so that a short Psi
+// pays for the determinants it reaches (H_kk formed for every slot took 8.7 ms
+// of one entry in 6.9e8 slots at 22 orbitals, the list form 3.9, this 2.7).
+// Bound by the adds and LDS reads of H_kk, or the read of the accumulator; the
+// list form (compaction, a binary search in Psi, two unranks and ~28 gathers of
 // integrals per entry) took 1040 us where this takes 248 us (20 orbitals,
 // 2.0e7 external determinants).
+constexpr int PT_U = 4, PT_Q = 2 * 128;  // slots a lane takes together; queue of a wavefront
 __global__ __launch_bounds__(PB) void k_pt2_rows(SpaceDev sp, Ints I, const u64* __restrict__ binom,
-                                                 double* __restrict__ D, const u32* __restrict__ bits,
+                                                 double* __restrict__ D, const u32* __restrict__ bits, u32 segs,
                                                  const double* __restrict__ e0p, double* __restrict__ part,
                                                  unsigned long long* __restrict__ n_ext) {
     __shared__ BinomLds B;
     __shared__ double K2[32 * 32], J[32 * 32], hd[32], ka[32 * 31 / 2], ea, wsum[PB / 64];
+    __shared__ double qy[PB / 64][PT_Q];
+    __shared__ u32 qb[PB / 64][PT_Q];
     __shared__ uint8_t occ[32];
     load_binom(B, binom);
     const int n = sp.n, na = sp.na;
@@ -114,10 +121,62 @@ __global__ __launch_bounds__(PB) void k_pt2_rows(SpaceDev sp, Ints I, const u64*
     if (threadIdx.x < (unsigned)n) hd[threadIdx.x] = I.H(threadIdx.x, threadIdx.x);
     __syncthreads();
     const double E0 = *e0p;
-    const int lane = threadIdx.x & 63, npair = na * (na - 1) / 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, npair = na * (na - 1) / 2;
+    double* const wy = qy[wave];
+    u32* const wb = qb[wave];
     unsigned long long cnt = 0;
     double sum = 0.0;
-    for (u64 row = blockIdx.x; row < sp.Na; row += gridDim.x) {
+    // H_kk of the current row's determinants with beta strings bt
+    const auto diagonal = [&](const auto& bt, auto& e) {
+        constexpr int U = sizeof(bt) / sizeof(bt[0]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            e[u] = ea;
+            for (u32 m = bt[u]; m; m &= m - 1u) e[u] += hd[__builtin_ctz(m)];
+        }
+        for (int t = 0; t < npair; ++t) {
+            const double k = ka[t];
+#pragma unroll
+            for (int u = 0; u < U; ++u) e[u] += k;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            for (u32 m = bt[u]; m; m &= m - 1u) {
+                const double* Kp = K2 + __builtin_ctz(m) * n;
+                for (u32 m2 = m & (m - 1u); m2; m2 &= m2 - 1u) e[u] += Kp[__builtin_ctz(m2)];
+            }
+        for (int t = 0; t < na; ++t) {
+            const double* Jp = J + occ[t] * n;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                for (u32 m = bt[u]; m; m &= m - 1u) e[u] += Jp[__builtin_ctz(m)];
+        }
+    };
+    // the queue's last up to 128 determinants, two a lane
+    const auto take = [&](int& queued) {
+        const int first = queued > 128 ? queued - 128 : 0;
+        wave_sync();
+        double y[2], e[2];
+        u32 bt[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int q = first + u * 64 + lane;
+            y[u] = q < queued ? wy[q] : 0.0;
+            bt[u] = q < queued ? wb[q] : 0u;
+        }
+        wave_sync();
+        diagonal(bt, e);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (y[u] == 0.0) continue;
+            sum += (y[u] * y[u]) / (E0 - e[u]);
+            ++cnt;
+        }
+        queued = first;
+    };
+    const u64 len = (sp.Nb + segs - 1) / segs;
+    for (u64 item = blockIdx.x; item < sp.Na * segs; item += gridDim.x) {
+        const u64 row = item / segs, x_lo = (item - row * segs) * len, x_hi = min(sp.Nb, x_lo + len);
         const u32 A = str_unrank_wave(row, na, n, B);
         __syncthreads();  // the previous row's tables are no longer read
         if (threadIdx.x < (unsigned)n && ((A >> threadIdx.x) & 1u))
@@ -134,47 +193,48 @@ __global__ __launch_bounds__(PB) void k_pt2_rows(SpaceDev sp, Ints I, const u64*
         }
         __syncthreads();
         double* const Dr = D + row * sp.Nb;
-        constexpr int U = 4;
-        for (u64 x0 = threadIdx.x; x0 < sp.Nb; x0 += (u64)PB * U) {
-            double y[U];
-            u32 bt[U];
+        int queued = 0;
+        for (u64 x0 = x_lo + threadIdx.x; x0 - threadIdx.x < x_hi; x0 += (u64)PB * PT_U) {
+            double y[PT_U];
+            u32 bt[PT_U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < PT_U; ++u) {
                 const u64 x = x0 + (u64)u * PB;
-                y[u] = x < sp.Nb ? Dr[x] : 0.0;
-                bt[u] = x < sp.Nb ? bits[x] : 0u;
+                y[u] = x < x_hi ? Dr[x] : 0.0;
+                bt[u] = x < x_hi ? bits[x] : 0u;
             }
-            double e[U];
+            u64 m[PT_U];
+            int here = 0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                e[u] = ea;
-                for (u32 m = bt[u]; m; m &= m - 1u) e[u] += hd[__builtin_ctz(m)];
+            for (int u = 0; u < PT_U; ++u) {
+                m[u] = __ballot(y[u] != 0.0);
+                here += __popcll(m[u]);
+                if (y[u] != 0.0) Dr[x0 + (u64)u * PB] = 0.0;
             }
-            for (int t = 0; t < npair; ++t) {
-                const double k = ka[t];
+            if (here == 0) continue;
+            if (here > 128) {
+                double e[PT_U];
+                diagonal(bt, e);
 #pragma unroll
-                for (int u = 0; u < U; ++u) e[u] += k;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                for (u32 m = bt[u]; m; m &= m - 1u) {
-                    const double* Kp = K2 + __builtin_ctz(m) * n;
-                    for (u32 m2 = m & (m - 1u); m2; m2 &= m2 - 1u) e[u] += Kp[__builtin_ctz(m2)];
+                for (int u = 0; u < PT_U; ++u) {
+                    if (y[u] == 0.0) continue;
+                    sum += (y[u] * y[u]) / (E0 - e[u]);
+                    ++cnt;
                 }
-            for (int t = 0; t < na; ++t) {
-                const double* Jp = J + occ[t] * n;
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    for (u32 m = bt[u]; m; m &= m - 1u) e[u] += Jp[__builtin_ctz(m)];
+                continue;
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (y[u] == 0.0) continue;
-                Dr[x0 + (u64)u * PB] = 0.0;
-                sum += (y[u] * y[u]) / (E0 - e[u]);
-                ++cnt;
+            for (int u = 0; u < PT_U; ++u) {
+                const int at = queued + __popcll(m[u] & ((1ull << lane) - 1ull));
+                if (y[u] != 0.0) {
+                    wy[at] = y[u];
+                    wb[at] = bt[u];
+                }
+                queued += __popcll(m[u]);
             }
+            if (queued >= 128) take(queued);
         }
+        if (queued) take(queued);
     }
     for (int off = 32; off >= 1; off >>= 1) {
         cnt += __shfl_xor(cnt, off);
@@ -182,7 +242,7 @@ __global__ __launch_bounds__(PB) void k_pt2_rows(SpaceDev sp, Ints I, const u64*
     }
     if (lane == 0) {
         if (cnt) atomicAdd(n_ext, cnt);
-        wsum[threadIdx.x >> 6] = sum;
+        wsum[wave] = sum;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -333,13 +393,15 @@ extern "C" sfci_status sfci_pt2(sfci_problem* P, const sfci_svec* psi, int32_t d
             launch_sumsq(P, psi->amp, sc, psi->nnz, sd + 1, false);
             hipLaunchKernelGGL(k_pt2_e0, dim3(1), dim3(64), 0, P->stream, sd + 0, sd + 1, sd + 2);
             launch_scatter_zero(P, P->d_D, psi->rank, sc, psi->nnz);
-            // a partial sum per workgroup, then the N_beta strings
-            const unsigned g = (unsigned)std::min<u64>(P->Na, (u64)P->num_cu * 8);
+            // a partial sum per workgroup, then the N_beta strings; eight workgroups to a compute unit
+            const u64 most = (u64)P->num_cu * 8;
+            const u32 segs = (u32)std::max<u64>(1, std::min<u64>(most / P->Na, P->Nb / 2048));
+            const unsigned g = (unsigned)std::min<u64>(P->Na * segs, most);
             double* part = (double*)P->ws_prod.get(g * sizeof(double) + P->Nb * sizeof(u32));
             u32* bits = (u32*)(part + g);
             hipLaunchKernelGGL(k_pt2_beta, dim3(grid_of(P->Nb)), dim3(PB), 0, P->stream, sp, P->d_binom, bits);
-            hipLaunchKernelGGL(k_pt2_rows, dim3(g), dim3(PB), 0, P->stream, sp, I, P->d_binom, P->d_D, bits, sd + 2,
-                               part, (unsigned long long*)(sc + 3));
+            hipLaunchKernelGGL(k_pt2_rows, dim3(g), dim3(PB), 0, P->stream, sp, I, P->d_binom, P->d_D, bits, segs,
+                               sd + 2, part, (unsigned long long*)(sc + 3));
             dense.done();
             launch_set_u64(P, sc + 2, g);
             launch_sum(P, part, sc + 2, g, sd + 3, false);
