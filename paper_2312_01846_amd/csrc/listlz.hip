@@ -548,7 +548,7 @@ struct FusedPasses {
 
 u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps);
 u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps);
-bool list_sigma_rows(sfci_problem* P);
+bool list_sigma_rows(sfci_problem* P, u64 nnz);
 
 u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank, double* out_amp, u64 out_cap,
                     u64* emitted_dev, u64* distinct_host, bool tiles_ok, double eps) {
@@ -563,9 +563,10 @@ u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank,
     sink.bounds = ls + 8;
     sink.pcount = ls + 2;
     sink.distinct = ls + 4;
-    if (tiles_ok && list_sigma_tiles(P, read_dev(P, v.v_nnz)))
+    const u64 nnz = tiles_ok ? read_dev(P, v.v_nnz) : 0;
+    if (tiles_ok && list_sigma_tiles(P, nnz))
         sigma_dense_passes(P, v, sink, emitted_dev, eps);
-    else if (tiles_ok && list_sigma_rows(P))
+    else if (tiles_ok && list_sigma_rows(P, nnz))
         sigma_row_passes(P, v, sink, emitted_dev, eps);
     else
         sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
@@ -593,10 +594,24 @@ u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank,
 // SFCI_LIST_SIGMA=tile|sort forces tiles for all rows or the sort path.
 constexpr double kSortTermsPerTileItem = 5700.0;
 
-// Otherwise by rows, unless the sort path is asked for.
-bool list_sigma_rows(sfci_problem* P) {
-    const char* env = getenv("SFCI_LIST_SIGMA");
-    return rowtile_available(P) && !(env && !strcmp(env, "sort"));
+// Otherwise by rows, but for few terms in spaces of few alpha strings, where
+// the passes by rows are bound by their launches and the sort path by nothing
+// else either, with fewer of them.  Five sigmas of an iteration, by rows and
+// by the sort path, ms: 12 orbitals 6 + 6, 1.8e6 terms each, 5.1 and 4.0;
+// 24 orbitals 3 + 3, 5.4e6 terms, 6.0 and 5.1; 20 orbitals 4 + 4 (4 845
+// strings), 5.7e6 terms 6.6 and 6.2, 1.7e7 7.0 and 8.2.  The sort path's cost
+// grows with the strings: 18 orbitals 5 + 5 (8 568), 1.8e5 terms 4.3 and 4.4;
+// 22 orbitals 5 + 5 (26 334), 3e5 terms 5.1 and 6.4.
+// SFCI_LIST_HEAVY, which says what the rows do, asks for them.
+constexpr double kSortTerms = 8.0e6;
+constexpr u64 kSortAlpha = 8192;
+
+bool list_sigma_rows(sfci_problem* P, u64 nnz) {
+    if (!rowtile_available(P)) return false;
+    if (const char* env = getenv("SFCI_LIST_SIGMA"))
+        if (!strcmp(env, "sort")) return false;
+    return getenv("SFCI_LIST_HEAVY") || P->Na > kSortAlpha ||
+           (double)nnz * (double)terms_per_source(P->n, P->na, P->nb) > kSortTerms;
 }
 
 bool list_sigma_tiles(sfci_problem* P, u64 nnz) {
@@ -808,11 +823,12 @@ void lanczos_list(sfci_problem* P, const sfci_lanczos_opts* o, const ListBasis& 
             sink.Y = Y;
             sink.bounds = ls + 8;
             sink.pcount = ls + 2;
-            const bool dense_passes = tiles_ok && list_sigma_tiles(P, read_dev(P, Wn(j)));
+            const u64 wn = tiles_ok ? read_dev(P, Wn(j)) : 0;
+            const bool dense_passes = tiles_ok && list_sigma_tiles(P, wn);
             tsig.begin(P->stream);
             if (dense_passes)
                 sigma_dense_passes(P, sl, sink, sc + 32, o->screen_eps);
-            else if (tiles_ok && list_sigma_rows(P))
+            else if (tiles_ok && list_sigma_rows(P, wn))
                 sigma_row_passes(P, sl, sink, sc + 32, o->screen_eps);
             else
                 sigma_sorted_passes(P, sl, sink, sc + 32, tup_cap, o->screen_eps);
