@@ -457,7 +457,31 @@ unsigned hr_grid(u64 n) { return (unsigned)std::max<u64>(1, std::min<u64>((n + 2
 
 }  // namespace
 
-bool hash_rows_reach(sfci_problem* P, const RowTileDesc& all, HashReach* out) {
+u64 hash_rows_parts(u64 terms) {
+    constexpr u64 part = HR_SLOTS2 / 16 * 11;  // as in k_hash_rows
+    return terms <= HR_SLOTS2 / 4 * 3 ? 1 : (terms + part - 1) / part;
+}
+
+// Where each target row's list starts.
+static void hr_places(sfci_problem* P) {
+    u64* pre = (u64*)P->list_ws.hr_pre.p;
+    hipLaunchKernelGGL(k_hr_pairs, dim3(hr_grid(P->Na)), dim3(256), 0, P->stream, (const u64*)P->list_ws.hr_cnt.p, P->Na,
+                       pre);
+    exclusive_scan_u64(P, pre, pre, P->Na, pre + P->Na);
+}
+
+static void hr_unpack(HashReach* out) {
+    u64 terms = 0, pairs = 0;
+    for (u64& c : out->count) {
+        pairs += c >> HR_PAIR_SHIFT;
+        c &= (1ull << HR_PAIR_SHIFT) - 1ull;
+        terms += c;
+    }
+    out->terms = terms;
+    out->pairs = pairs;
+}
+
+void hash_rows_count(sfci_problem* P, const RowTileDesc& all, bool lists_follow, HashReach* out) {
     const RowView v = rowtile_view(all);
     const u64 Na = P->Na;
     const SpaceDev sp{P->n, P->na, P->nb, Na, P->Nb};
@@ -465,31 +489,45 @@ bool hash_rows_reach(sfci_problem* P, const RowTileDesc& all, HashReach* out) {
     const u64 dB = (u64)(P->nb * (P->nb - 1) / 2) * (u64)((P->n - P->nb) * (P->n - P->nb - 1) / 2);
     ListWs& ws = P->list_ws;
     u64* cnt = (u64*)ws.hr_cnt.get(Na * sizeof(u64));
-    u64* pre = (u64*)ws.hr_pre.get((Na + 1) * sizeof(u64));
+    ws.hr_pre.get((Na + 1) * sizeof(u64));
     u32* src = (u32*)ws.hr_src.get((2 * Na + 2) * sizeof(u32));  // [nonempty rows | cursors | count]
     u32* cursor = src + Na;
     unsigned* n_src = cursor + Na;
     launch_fill_u64(cnt, Na, 0, P->stream);
     SFCI_CHECK_HIP(hipMemsetAsync(cursor, 0, (Na + 1) * sizeof(u32), P->stream));
     hipLaunchKernelGGL(k_hr_nonempty, dim3(hr_grid(Na)), dim3(256), 0, P->stream, v.rowbeg, v.rowend, Na, src, n_src);
-    const unsigned g = (unsigned)P->num_cu * 8;
-    hipLaunchKernelGGL(k_hr_reach<false>, dim3(g), dim3(HR_BLOCK), 0, P->stream, sp, P->d_binom, v.rowbeg, v.rowend,
-                       src, n_src, 1 + sB + dB, 1 + sB, cnt, (const u64*)nullptr, (u32*)nullptr, (u64*)nullptr);
-    hipLaunchKernelGGL(k_hr_pairs, dim3(hr_grid(Na)), dim3(256), 0, P->stream, (const u64*)cnt, Na, pre);
-    exclusive_scan_u64(P, pre, pre, Na, pre + Na);
+    hipLaunchKernelGGL(k_hr_reach<false>, dim3((unsigned)P->num_cu * 8), dim3(HR_BLOCK), 0, P->stream, sp, P->d_binom,
+                       v.rowbeg, v.rowend, src, n_src, 1 + sB + dB, 1 + sB, cnt, (const u64*)nullptr, (u32*)nullptr,
+                       (u64*)nullptr);
+    if (lists_follow) hr_places(P);
+    out->placed = lists_follow;
+    SFCI_CHECK_HIP(hipGetLastError());
     out->count.resize(Na);
-    u64 pairs = 0;
     SFCI_CHECK_HIP(hipMemcpyAsync(out->count.data(), cnt, Na * sizeof(u64), hipMemcpyDeviceToHost, P->stream));
-    SFCI_CHECK_HIP(hipMemcpyAsync(&pairs, pre + Na, sizeof(u64), hipMemcpyDeviceToHost, P->stream));
+    if (lists_follow)
+        SFCI_CHECK_HIP(hipMemcpyAsync(&out->pairs, (const u64*)ws.hr_pre.p + Na, sizeof(u64), hipMemcpyDeviceToHost,
+                                      P->stream));
     SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
+    if (!lists_follow) hr_unpack(out);
+}
+
+bool hash_rows_lists(sfci_problem* P, const RowTileDesc& all, HashReach* reach) {
+    const RowView v = rowtile_view(all);
+    const u64 Na = P->Na;
+    const SpaceDev sp{P->n, P->na, P->nb, Na, P->Nb};
+    ListWs& ws = P->list_ws;
     size_t freeb = 0, totb = 0;
     SFCI_CHECK_HIP(hipMemGetInfo(&freeb, &totb));
-    if (pairs * sizeof(u64) > (freeb + ws.hr_list.bytes) / 4) return false;
-    u64* list = (u64*)ws.hr_list.get(std::max<u64>(1, pairs) * sizeof(u64));
-    hipLaunchKernelGGL(k_hr_reach<true>, dim3(g), dim3(HR_BLOCK), 0, P->stream, sp, P->d_binom, v.rowbeg, v.rowend,
-                       src, n_src, 0, 0, (u64*)nullptr, (const u64*)pre, cursor, list);
+    if (reach->pairs * sizeof(u64) > (freeb + ws.hr_list.bytes) / 4) return false;
+    u64* list = (u64*)ws.hr_list.get(std::max<u64>(1, reach->pairs) * sizeof(u64));
+    u32* src = (u32*)ws.hr_src.p;
+    u32* cursor = src + Na;
+    if (!reach->placed) hr_places(P);
+    hipLaunchKernelGGL(k_hr_reach<true>, dim3((unsigned)P->num_cu * 8), dim3(HR_BLOCK), 0, P->stream, sp, P->d_binom,
+                       v.rowbeg, v.rowend, src, (const unsigned*)(cursor + Na), 0, 0, (u64*)nullptr,
+                       (const u64*)ws.hr_pre.p, cursor, list);
     SFCI_CHECK_HIP(hipGetLastError());
-    for (u64& c : out->count) c &= (1ull << HR_PAIR_SHIFT) - 1ull;
+    if (reach->placed) hr_unpack(reach);
     return true;
 }
 

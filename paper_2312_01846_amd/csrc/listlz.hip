@@ -548,7 +548,7 @@ struct FusedPasses {
 
 u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps);
 u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps);
-bool list_sigma_rows(sfci_problem* P, u64 nnz);
+bool list_sigma_rows(sfci_problem* P, u64 nnz, bool collect);
 
 u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank, double* out_amp, u64 out_cap,
                     u64* emitted_dev, u64* distinct_host, bool tiles_ok, double eps) {
@@ -566,7 +566,7 @@ u64 sigma_list_topm(sfci_problem* P, const SigmaLaunch& v, u64 M, u64* out_rank,
     const u64 nnz = tiles_ok ? read_dev(P, v.v_nnz) : 0;
     if (tiles_ok && list_sigma_tiles(P, nnz))
         sigma_dense_passes(P, v, sink, emitted_dev, eps);
-    else if (tiles_ok && list_sigma_rows(P, nnz))
+    else if (tiles_ok && list_sigma_rows(P, nnz, true))
         sigma_row_passes(P, v, sink, emitted_dev, eps);
     else
         sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
@@ -601,17 +601,56 @@ constexpr double kSortTermsPerTileItem = 5700.0;
 // 24 orbitals 3 + 3, 5.4e6 terms, 6.0 and 5.1; 20 orbitals 4 + 4 (4 845
 // strings), 5.7e6 terms 6.6 and 6.2, 1.7e7 7.0 and 8.2.  The sort path's cost
 // grows with the strings: 18 orbitals 5 + 5 (8 568), 1.8e5 terms 4.3 and 4.4;
-// 22 orbitals 5 + 5 (26 334), 3e5 terms 5.1 and 6.4.
+// 22 orbitals 5 + 5 (26 334), 3e5 terms 5.1 and 6.4.  Of long rows it hands on
+// more candidates: one truncated sigma of 24 orbitals 3 + 8 (735 471 beta
+// strings), 1.2e6 and 6.1e6 terms, 1.29 and 1.25, 1.76 and 2.45 ms.  Where the
+// terms do not settle it the rows they reach do (row_passes_pay).
 // SFCI_LIST_HEAVY, which says what the rows do, asks for them.
 constexpr double kSortTerms = 8.0e6;
+constexpr double kSortTermsLong = 1.5e6;  // candidates wanted of rows of more than kSortBeta
 constexpr u64 kSortAlpha = 8192;
+constexpr u64 kSortBeta = 1ull << 18;
 
-bool list_sigma_rows(sfci_problem* P, u64 nnz) {
+bool list_sigma_rows(sfci_problem* P, u64 nnz, bool collect) {
     if (!rowtile_available(P)) return false;
     if (const char* env = getenv("SFCI_LIST_SIGMA"))
         if (!strcmp(env, "sort")) return false;
     return getenv("SFCI_LIST_HEAVY") || P->Na > kSortAlpha ||
-           (double)nnz * (double)terms_per_source(P->n, P->na, P->nb) > kSortTerms;
+           (double)nnz * (double)terms_per_source(P->n, P->na, P->nb) >
+               (collect && P->Nb > kSortBeta ? kSortTermsLong : kSortTerms);
+}
+
+// Whether the rows, of which the first nh go to the tile kernel, pay: terms
+// that gather in few long rows leave hash tables that one workgroup fills part
+// by part, each part a walk over all the row's terms, and tiles that receive
+// little, while the sort path spreads any terms evenly.  The estimates (us)
+// are least-squares fits to 390 sigmas of 19 spaces of 12 to 32 orbitals, near
+// the aufbau determinant and spread out, whose times they meet within a factor
+// of two.  The sort path is taken where it is estimated at 0.7 of the rows; of
+// those sigmas the rows alone took up to 21 times the better way's time
+// (24 orbitals 3 + 8, 300 entries: 7.5 ms and 0.6), this choice up to 2.1 (one
+// sigma, the next 1.4).
+bool row_passes_pay(sfci_problem* P, const std::vector<u64>& terms, u64 nh, const HashReach& reach, bool collect) {
+    if (getenv("SFCI_LIST_HEAVY")) return true;
+    const double all = (double)reach.terms, np = (double)reach.pairs;
+    double heavy = 0;  // terms of the heavy rows
+    for (u64 i = 0; i < nh; ++i) heavy += (double)terms[i];
+    double walk = all - heavy, longest = 0;  // visits of the tables' rows, of one row
+    for (u64 i = nh; i < terms.size(); ++i) {
+        const u64 parts = hash_rows_parts(terms[i]);
+        longest = std::max(longest, (double)terms[i] * (double)parts);
+        walk += (double)terms[i] * (double)(parts - 1);
+        if (terms[i] <= hash_rows_small()) break;  // (descending by classes of a quarter power of two)
+    }
+    const double items = (double)nh * (double)rowtile_ntiles(P);
+    double sort = 240 + 0.031 * (double)P->Na + 3.6e-5 * all + 3e-4 * np;
+    double rows = 280 + 1e-3 * (double)P->Na + 0.02 * (double)terms.size() + 1.1e-5 * walk + 1.1e-2 * longest +
+                  0.085 * items + 2e-4 * np;
+    if (collect) {
+        sort += 100 + 6e-6 * all + 1e-3 * np;
+        rows += 150 + 0.01 * (double)terms.size() + 5e-6 * walk + 0.017 * items + 1e-5 * heavy;
+    }
+    return 0.7 * rows < sort;
 }
 
 bool list_sigma_tiles(sfci_problem* P, u64 nnz) {
@@ -692,7 +731,11 @@ u64 sigma_dense_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink
 u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, u64* emitted_dev, double eps) {
     FusedPasses F(P, v, sink, emitted_dev, eps);
     HashReach reach;
-    if (!hash_rows_reach(P, F.all, &reach)) return sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
+    // of many strings the lists are made while the host sorts the rows, of few
+    // ones, where the sort path may come out ahead, only when it does not
+    const bool ahead = P->Na > kSortAlpha;
+    hash_rows_count(P, F.all, ahead, &reach);
+    if (ahead && !hash_rows_lists(P, F.all, &reach)) return sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
     const auto cls = [](u64 c) {
         const int b = 63 - __builtin_clzll(c);
         return b < 2 ? b * 4 : b * 4 + (int)((c >> (b - 2)) & 3);
@@ -717,6 +760,8 @@ u64 sigma_row_passes(sfci_problem* P, const SigmaLaunch& v, ListPassSink& sink, 
             terms[k] = c;
         }
     while (nh < n && terms[nh] > above) ++nh;
+    if (!row_passes_pay(P, terms, nh, reach, sink.collect) || (!ahead && !hash_rows_lists(P, F.all, &reach)))
+        return sigma_sorted_passes(P, v, sink, emitted_dev, 0, eps);
     u32* d = (u32*)P->list_ws.heavy.get(std::max<u64>(1, n) * sizeof(u32));
     SFCI_CHECK_HIP(hipMemcpyAsync(d, rows.data(), n * sizeof(u32), hipMemcpyHostToDevice, P->stream));
     SFCI_CHECK_HIP(hipStreamSynchronize(P->stream));
@@ -828,7 +873,7 @@ void lanczos_list(sfci_problem* P, const sfci_lanczos_opts* o, const ListBasis& 
             tsig.begin(P->stream);
             if (dense_passes)
                 sigma_dense_passes(P, sl, sink, sc + 32, o->screen_eps);
-            else if (tiles_ok && list_sigma_rows(P, wn))
+            else if (tiles_ok && list_sigma_rows(P, wn, sink.collect))
                 sigma_row_passes(P, sl, sink, sc + 32, o->screen_eps);
             else
                 sigma_sorted_passes(P, sl, sink, sc + 32, tup_cap, o->screen_eps);

@@ -334,11 +334,17 @@ struct FusedOut {
 // of every target row and the lists of source rows that reach it (kept in
 // list_ws), then rows[lo .. hi) (device) handed to the FusedOut at d_fo.  A
 // part of a row that did not fit sets *overflow to 2 or 3: to be run again with
-// a larger more.  Both synchronise the stream.
+// a larger more.  The counts and the rows synchronise the stream.
 struct HashReach {
-    std::vector<u64> count;  // terms per target row
+    std::vector<u64> count;    // terms per target row
+    u64 terms = 0, pairs = 0;  // of all rows; pairs of a target row and a source row
+    bool placed = false;
 };
-bool hash_rows_reach(sfci_problem* P, const RowTileDesc& all, HashReach* out);  // false: lists too long for the device
+// lists_follow: the lists are made next in any case, and the counts are the
+// host's only after that.
+void hash_rows_count(sfci_problem* P, const RowTileDesc& all, bool lists_follow, HashReach* out);
+bool hash_rows_lists(sfci_problem* P, const RowTileDesc& all, HashReach* reach);  // false: too long for the device
+u64 hash_rows_parts(u64 terms);  // in how many parts a row of so many terms is taken
 void launch_hash_rows(sfci_problem* P, const SigmaLaunch& sl, const RowTileDesc& all, u64 lo, u64 hi, const u32* rows,
                       const FusedOut* d_fo, unsigned long long* emitted, double eps, u32 more, bool small);
 u64 hash_rows_small();  // rows of at most so many terms take the small table
