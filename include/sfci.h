@@ -96,8 +96,9 @@ enum {
 typedef struct {
     uint64_t M;        /* keep the M largest |sigma_k| (ties: see SFCI_TIE_SLACK); UINT64_MAX = all */
     int32_t dedup;     /* SFCI_DEDUP_* */
-    int32_t deterministic; /* 1: sums in ascending source rank (in-order rows or sort) and ordered reductions,
-                              bit-reproducible */
+    int32_t deterministic; /* 1: sums in ascending source rank (in-order rows or sort, by the entries: either way
+                              the same bits) and ordered reductions, bit-reproducible.  The in-order rows use the
+                              N_det array, which stays with the problem */
     double screen_eps; /* Sec. 3: merged entries with |sigma_k| < screen_eps are dropped before the
                           truncation (the paper uses 5e-5); 0 = off */
     int32_t tie_band;  /* 1: the truncation extension described at SFCI_TIE_SLACK; 0 = the paper's rule */
@@ -214,7 +215,8 @@ sfci_status sfci_lanczos_roots(sfci_problem* prob, const sfci_svec* v0, const sf
  *   deri = the 8-fold symmetrisation of Gamma/2, with
  *          Gamma_pqrs = sum_ki sbar_k v_i <k| sum_st a+_ps a+_rt a_st a_qs |i>  (device n^4, may be NULL),
  * i.e. the gradients of sbar^T H v along symmetric perturbations of h and eri.
- * Outputs are overwritten.  Asynchronous. */
+ * Outputs are overwritten; a bad vector (SFCI_E_DUP, SFCI_E_RANGE) leaves them as they were.  v_bar may
+ * take the place of an input's amplitudes.  Synchronises. */
 sfci_status sfci_sigma_backward(sfci_problem* prob, const sfci_svec* v, const sfci_svec* sbar, double* v_bar,
                                 double* dh, double* deri);
 

@@ -13,7 +13,9 @@
 //      table surely holds is taken in parts, by a second hash of the target;
 //   3. the finished table is consumed in place (FusedOut): the T gathers, the
 //      marks, the candidates above the bound.
-// Rows of very many terms go to the tile kernel (heavy_row_terms).
+// Rows of very many terms go to the tile kernel (heavy_row_terms); few terms,
+// and such as gather in few long rows, to the sort path (list_sigma_rows,
+// row_passes_pay).
 //
 // Bound by: the walk over a row's terms, once per part, and the table's LDS
 // accesses (key, then an add).  28 orbitals, 50 000 entries, 1.2e9 terms: a
@@ -57,7 +59,8 @@ struct HashRows {
     u32 more;           // parts are taken this many times finer (a part that did not fit)
 };
 
-__device__ __forceinline__ u32 hr_mix(u32 x) {  // a bijection whose bits all depend on all of x's
+// MurmurHash3's 32-bit finaliser (A. Appleby, public domain): a bijection whose bits all depend on all of x's.
+__device__ __forceinline__ u32 hr_mix(u32 x) {
     x ^= x >> 16;
     x *= 0x85ebca6bu;
     x ^= x >> 13;

@@ -92,8 +92,9 @@ __global__ __launch_bounds__(RB) void k_dot_final(const double* __restrict__ par
 // (os_events), or term by term where such terms are frequent.
 // Bound by: added one by one, the latency of the chain (~17 cycles a term:
 // 7.34 ms for 1e6 squares); this way the loads and reductions of one compute
-// unit (0.69 ms); long sums are spread over the chip (launch_ordered).  Sums that wander about zero leave their binade every few dozen terms
-// and gain little.
+// unit (0.69 ms); long sums are spread over the chip (launch_ordered).  Sums
+// that wander about zero leave their binade every few dozen terms and gain
+// little.
 enum { OS_SUM = 0, OS_DOT = 1, OS_SUMSQ = 2 };
 constexpr int OS_WAVES = 8;
 constexpr int OS_BLOCK = 64 * OS_WAVES;
@@ -559,16 +560,6 @@ __global__ void k_div_norm(double* __restrict__ a, const u64* __restrict__ nnz, 
     for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) a[i] = a[i] / nrm;
 }
 
-__global__ void k_copy_vec(const u64* __restrict__ r, const double* __restrict__ a, const u64* __restrict__ nnz,
-                           u64* __restrict__ r2, double* __restrict__ a2, u64* __restrict__ nnz2) {
-    const u64 n = *nnz;
-    for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) {
-        r2[i] = r[i];
-        a2[i] = a[i];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *nnz2 = n;
-}
-
 // ---- generalized eigenproblem, one wavefront (m <= 32) ----
 #define GE_MAX 32
 
@@ -971,12 +962,6 @@ void launch_normalise(sfci_problem* P, double* a, const u64* nnz, u64 cap, bool 
         hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(RB), 0, P->stream, part, (int)g, ss, (double*)nullptr);
     }
     hipLaunchKernelGGL(k_div_norm, dim3(gsz(cap)), dim3(256), 0, P->stream, a, nnz, ss);
-    SFCI_CHECK_HIP(hipGetLastError());
-}
-
-void launch_copy_vec(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, u64* r2, double* a2,
-                     u64* nnz2) {
-    hipLaunchKernelGGL(k_copy_vec, dim3(gsz(cap)), dim3(256), 0, P->stream, r, a, nnz, r2, a2, nnz2);
     SFCI_CHECK_HIP(hipGetLastError());
 }
 

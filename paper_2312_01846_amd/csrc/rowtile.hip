@@ -1981,9 +1981,9 @@ u64 binom_u64(int a, int b) {
 
 static unsigned rt_itab_doubles(unsigned n2) { return (2 * n2 + 40 + 1) & ~1u; }
 
-// The tile kernels' static LDS, as compiled (the largest of the three), so
-// that static + dynamic LDS never exceeds what a workgroup may hold.
-// (more than 128 registers would leave one such workgroup on a compute unit)
+// The eight-wavefront kernel's static LDS, or more than there is where it was
+// compiled to over 128 registers, which would leave one such workgroup on a
+// compute unit.
 static size_t rt_static_lds8() {
     static size_t cached = 0;
     if (cached == 0) {
@@ -1994,6 +1994,8 @@ static size_t rt_static_lds8() {
     return cached;
 }
 
+// The other tile kernels' static LDS, as compiled (the largest of them), so
+// that static + dynamic LDS never exceeds what a workgroup may hold.
 static size_t rt_static_lds() {
     static size_t cached = 0;
     if (cached == 0) {

@@ -327,9 +327,6 @@ struct FusedOut {
     int* overflow;
     u64* distinct;      // may be NULL
 };
-// Target alpha rows [lo, hi) of a prepared description, each finished tile
-// handed to the FusedOut at d_fo (device) instead of being written.
-// Synchronises the stream.
 // Sigma by target rows with an LDS hash table each (hashrows.hip): the terms
 // of every target row and the lists of source rows that reach it (kept in
 // list_ws), then rows[lo .. hi) (device) handed to the FusedOut at d_fo.  A
@@ -348,7 +345,9 @@ u64 hash_rows_parts(u64 terms);  // in how many parts a row of so many terms is 
 void launch_hash_rows(sfci_problem* P, const SigmaLaunch& sl, const RowTileDesc& all, u64 lo, u64 hi, const u32* rows,
                       const FusedOut* d_fo, unsigned long long* emitted, double eps, u32 more, bool small);
 u64 hash_rows_small();  // rows of at most so many terms take the small table
-// With rows (device) the target rows are rows[lo .. hi).
+// Target alpha rows [lo, hi) of a prepared description, or rows[lo .. hi) of a
+// device list, each finished tile handed to the FusedOut at d_fo (device)
+// instead of being written.  Synchronises the stream.
 void launch_sigma_rowtile_rows_fused(sfci_problem* P, const RowTileDesc& all, u64 lo, u64 hi, const FusedOut* d_fo,
                                      const u32* rows = nullptr);
 unsigned rowtile_grid(int num_cu, const RowTileGeom& geom, u64 total_items, unsigned per_cu_override = 0);
@@ -585,8 +584,6 @@ void launch_geneig_full(sfci_problem* P, int m, const double* T, const double* S
 void launch_inc_int(sfci_problem* P, int* p);
 void launch_add_u64(sfci_problem* P, u64* dst, const u64* src);  // *dst += *src
 void launch_div_by_sumsq(sfci_problem* P, const double* a, const u64* nnz, u64 cap, double* out);
-void launch_copy_vec(sfci_problem* P, const u64* r, const double* a, const u64* nnz, u64 cap, u64* r2, double* a2,
-                     u64* nnz2);
 
 int sfci_set_error(int code, const std::string& msg);
 
