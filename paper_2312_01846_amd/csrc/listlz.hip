@@ -629,7 +629,7 @@ bool list_sigma_rows(sfci_problem* P, u64 nnz, bool collect) {
 // of two.  The sort path is taken where it is estimated at 0.7 of the rows; of
 // those sigmas the rows alone took up to 21 times the better way's time
 // (24 orbitals 3 + 8, 300 entries: 7.5 ms and 0.6), this choice up to 2.1 (one
-// sigma, the next 1.4).
+// sigma, the next 1.5).
 bool row_passes_pay(sfci_problem* P, const std::vector<u64>& terms, u64 nh, const HashReach& reach, bool collect) {
     if (getenv("SFCI_LIST_HEAVY")) return true;
     const double all = (double)reach.terms, np = (double)reach.pairs;
